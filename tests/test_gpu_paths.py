@@ -1,0 +1,45 @@
+"""Kernel paths chosen by size, at the sizes where the choice or the kernel's
+tiles end, against the oracle (whole numbers: exact equality)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2509_17837_amd import _lib as X
+from paper_2509_17837_amd import decoder as D
+from tests._parity import Problem, compare_decode, gpu_plan, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no ROCm GPU visible")
+    X.lib()
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("layout,d,n,offset", [
+    (0, 3, 1, 0), (0, 3, 17, 1), (0, 11, 15, 3), (0, 31, 16, 0), (1, 31, 33, 2), (1, 9, 65, 1),
+    (0, 5, 65535, 0), (0, 5, 65536 + 7, 1), (1, 3, 65536 + 63, 0), (1, 15, 65536, 3)])
+def test_syndrome_tiles(layout, d, n, offset):
+    """Tiles of 16 and of 64 configurations, with whole and ragged last tiles,
+    from buffers of every byte alignment; bits above a code are ignored."""
+    print(f"[paths] syndrome layout={layout} d={d} n={n} offset={offset}", flush=True)
+    olat = O.Lattice(layout, d)
+    rng = np.random.default_rng(100 * d + n)
+    cfg = rng.integers(0, 256, (n, olat.nq), dtype=np.uint8)
+    plan = gpu_plan(Problem(layout, d, 0.1, 10.0, 0, 1, 0))
+    buf = torch.zeros(n * olat.nq + offset, dtype=torch.uint8, device="cuda")
+    buf[offset:] = to_dev(cfg.reshape(-1))
+    got = D.syndrome(plan, buf[offset:].reshape(n, olat.nq)).cpu().numpy()
+    fq, fm = olat.fq, olat.fm
+    pad = np.concatenate([cfg & 3, np.zeros((n, 1), np.uint8)], axis=1)
+    want = np.zeros((n, olat.nstab), np.uint8)
+    for s in range(4):
+        c = pad[:, np.where(fq[:, s] < 0, olat.nq, fq[:, s])]
+        want ^= np.where(fm[:, s] == 2, c & 1, np.where(fm[:, s] == 1, c >> 1, 0)).astype(np.uint8)
+    for i in {0, n // 2, n - 1}:
+        assert np.array_equal(want[i], olat.syndrome(cfg[i] & 3))
+    assert np.array_equal(got, want)
