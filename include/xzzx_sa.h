@@ -190,10 +190,14 @@ int xzzx_plan_set_lanes(xzzx_plan *plan, int lanes_per_chain);
  *     specialisation (rows in LDS, schedule read from the plan): rotated
  *     d <= 29, and planar d <= 15, whose lattice turned by 45 degrees has the
  *     same 2 x 2 generator blocks (rows of 2d + 1 columns);
- *   XZZX_KERNEL_BYTES: byte-per-qubit states, lanes_per_chain lanes per chain;
+ *   XZZX_KERNEL_BYTES: byte-per-qubit states, lanes_per_chain lanes per chain
+ *     (from 4 lanes, where a lane gets at most eight generators of a class, the
+ *     form whose energy lookups take half the LDS round trips);
  *   XZZX_KERNEL_AUTO (the default): ROWS where it applies, else on rotated
  *     lattices ROWS_GENERIC where it applies, else BYTES (on planar lattices
- *     BYTES measured faster than ROWS_GENERIC at d = 9).
+ *     BYTES measured faster than ROWS_GENERIC at d = 9); groups too small to
+ *     give the device one chain per lane run on BYTES with as many lanes as a
+ *     colour class has generators (at most 64).
  * EINVAL for ROWS or ROWS_GENERIC on a lattice they do not cover.
  * xzzx_plan_info reports ROWS only where the specialised variant runs. */
 enum { XZZX_KERNEL_AUTO = 0, XZZX_KERNEL_ROWS = 1, XZZX_KERNEL_BYTES = 2, XZZX_KERNEL_ROWS_GENERIC = 3,
@@ -301,7 +305,9 @@ typedef struct {
     uint8_t *d_chain_final;      /* [n_syn][4 n_rep][n_qubits] final states (optional) */
 } xzzx_group;
 
-/* Device workspace needed by xzzx_decode / xzzx_anneal for these groups. */
+/* Device workspace needed by xzzx_decode / xzzx_anneal for these groups.  A
+ * small call is accepted with less (what the packed-row kernels need) and then
+ * runs one chain per lane. */
 int xzzx_decode_workspace(const xzzx_group *groups, int n_groups, size_t *bytes);
 
 /* Full decoder (Alg. 7) for every group: greedy init, annealing of all

@@ -174,7 +174,7 @@ struct GroupArgs {
     int cp_every;                 // sweeps between checkpoints (0 = none)
     uint32_t *min_snap;           // each chain's state at its first E_min: random-site kernel, packed
                                   // words [word][n_chains]; planar kernel specialised to d, its rows
-                                  // [n_chains][planar_state_words(d)]
+                                  // [n_chains][planar_state_words(d)]; grid core [n_chains][grid_words]
 };
 
 struct AnnealArgs {
@@ -1577,6 +1577,11 @@ AnnealKernel ladder_rows_kernel(int d, bool plain);
 AnnealKernel ladder_rows_kernel_large(int d, bool plain);   // d = 17 .. 31 (NULL otherwise)
 AnnealKernel ladder_planar_kernel(int d, bool plain);
 int ladder_rows_state_words(int d);
+// grid core (one chain over `lanes` lanes, `mv` moves per lane and class) and
+// its recovery gather
+AnnealKernel grid_kernel(int lanes, int mv);
+void launch_grid_recovery(const uint32_t *snap, int words, const int32_t *best_chain, int n_rep, int nq, int64_t n_syn,
+                          const PlanDev *pl, uint8_t *recovery, hipStream_t stream);
 typedef void (*ServeKernel)(const ServeTask *, uint32_t, uint32_t);
 
 // The specialised kernels live in several translation units (compiled in

@@ -1,0 +1,83 @@
+// Annealing kernels of the grid core (one chain over several lanes) and the
+// recovery gather from the states it keeps.
+#include "xzzx_grid.h"
+
+namespace xzzx {
+
+// Task loop: persistent wavefronts on the atomic task queue, or one task per
+// workgroup where the launch has no counter (the plain form).
+template <int LOGG, int MV>
+__global__ __launch_bounds__(kWave) void k_anneal_grid(AnnealArgs A)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    const PlanDev *loaded = nullptr;
+    for (int iter = 0;; ++iter) {
+        uint32_t task = 0;
+        if (!A.counter) {
+            if (iter > 0) break;
+            task = blockIdx.x;
+        } else {
+            if (threadIdx.x == 0) task = atomicAdd(A.counter, 1u);
+            task = __builtin_amdgcn_readfirstlane(__shfl(task, 0, kWave));
+        }
+        if (task >= A.n_tasks) break;
+        int gi = 0;
+        while (gi + 1 < A.n_groups && (int64_t)task >= A.g[gi + 1].task_begin) ++gi;
+        const GroupArgs &G = A.g[gi];
+        const int64_t unit0 = ((int64_t)task - G.task_begin) << (6 - LOGG);
+        if (G.plan != loaded) {
+            wave_lds_fence();
+            load_grid_tables(G.plan, smem);
+            loaded = G.plan;
+        }
+        const ChainJob J = batch_job(G, unit0 + (threadIdx.x >> LOGG), false);
+        grid_core<LOGG, MV>(G.plan, J, 0, G.plan->n_sweeps, A.seed_lo, A.seed_hi, smem, G.min_snap);
+    }
+}
+
+template <int LOGG>
+static AnnealKernel pick(int mv)
+{
+    switch (mv) {
+    case 1: return k_anneal_grid<LOGG, 1>;
+    case 2: return k_anneal_grid<LOGG, 2>;
+    case 4: return k_anneal_grid<LOGG, 4>;
+    case 8: return k_anneal_grid<LOGG, 8>;
+    default: return nullptr;
+    }
+}
+
+AnnealKernel grid_kernel(int lanes, int mv)
+{
+    switch (lanes) {
+    case 4: return pick<2>(mv);
+    case 8: return pick<3>(mv);
+    case 16: return pick<4>(mv);
+    case 32: return pick<5>(mv);
+    case 64: return pick<6>(mv);
+    default: return nullptr;
+    }
+}
+
+// Each syndrome's recovery is its best chain's grid at that chain's first
+// E_min (code << 3 per cell); one thread per (syndrome, qubit).
+__global__ void k_grid_recovery(const uint8_t *__restrict__ snap, int bytes, const int32_t *__restrict__ best_chain,
+                                int n_rep, int nq, int64_t n_syn, const PlanDev *__restrict__ pl,
+                                uint8_t *__restrict__ recovery)
+{
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= n_syn * nq) return;
+    const int64_t s = idx / nq;
+    const int q = (int)(idx - s * nq);
+    const int64_t ci = s * 4 * n_rep + best_chain[s];
+    recovery[idx] = snap[ci * bytes + pl->grid_cell[q]] >> 3;
+}
+
+void launch_grid_recovery(const uint32_t *snap, int words, const int32_t *best_chain, int n_rep, int nq, int64_t n_syn,
+                          const PlanDev *pl, uint8_t *recovery, hipStream_t stream)
+{
+    hipLaunchKernelGGL(k_grid_recovery, dim3((unsigned)((n_syn * nq + 255) / 256)), dim3(256), 0, stream,
+                       reinterpret_cast<const uint8_t *>(snap), 4 * words, best_chain, n_rep, nq, n_syn, pl, recovery);
+}
+
+}  // namespace xzzx

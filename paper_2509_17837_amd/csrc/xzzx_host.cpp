@@ -239,6 +239,22 @@ size_t Plan::lds_bytes_site() const
     return (off + 15) & ~size_t(15);
 }
 
+// Grid core: the entries and a spare one, then the chains' grids.
+size_t Plan::lds_bytes_grid(int lanes_per_chain) const
+{
+    return ((8 * ((size_t)hdev.grid_slots + 1) + 15) & ~size_t(15)) +
+           4 * (size_t)hdev.grid_words * (kWave / lanes_per_chain);
+}
+
+// A lane takes one or two generators of a Philox block, one block, or two.
+int Plan::grid_moves(int lanes_per_chain) const
+{
+    const int nblk = (lat.per_class + 3) / 4;
+    for (int mv = 1; mv <= 8; mv *= 2)
+        if (4 * nblk <= mv * lanes_per_chain) return mv;
+    return 0;
+}
+
 size_t Plan::lds_bytes_anneal(int lanes_per_chain) const
 {
     const int C = kWave / lanes_per_chain;
@@ -430,6 +446,112 @@ static int build_graphs(const Lattice &L, const int32_t wg[2], Graph G[2])
     return XZZX_OK;
 }
 
+// Tables of the grid core.
+struct GridTables {
+    int words = 0, pitch = 0, slots = 0, rising = 0;
+    std::vector<uint2> move;        // [4][mpad + 1]
+    std::vector<uint32_t> entry;
+    std::vector<uint16_t> cell;
+};
+
+// The lattice as a grid of bytes in which every generator is a 2 x 2 block:
+// rotated, qubit (x, y) in row y + 1 and column x + 1 of rows of d + 1 bytes
+// (the column left of a row is the one right of the row before; both, and
+// rows -1 and d, hold no qubit); planar, the lattice turned by 45 degrees,
+// row (x - y - 1)/2 + d - 1 and column (x + y - 1)/2 - 1 of rows of 2d bytes.
+// Scratch cells after the last row are for idle moves.  Cells that hold no
+// qubit are 0 and stay 0: their flip bits are.  The blocks of classes 0 and 2
+// start at even bytes, those of 1 and 3 at odd ones.
+//
+// The energy tables: a move's entry is at its shape's table plus the block's
+// pattern b0 + 4 b1 + 16 b2 + 64 b3 (top left, top right, bottom left, bottom
+// right; absent cells 0).  A shape without all four cells uses a few of the
+// 256 patterns, so each shape's table starts at the first slot where its
+// patterns fall between the others' -- 256 entries and a few, not 256 a
+// shape.  Returns false where a table does not fit the core's registers.
+static bool build_grid(const Lattice &L, const std::vector<int32_t> &dE, const std::vector<uint8_t> &lut,
+                       const std::vector<int> &shape_of_face, const std::vector<int> &shapes, int kneg, GridTables &T)
+{
+    const bool rot = L.layout == XZZX_ROTATED;
+    const int d = L.d, rows = rot ? d + 2 : 2 * d - 1;
+    T.pitch = rot ? d + 1 : 2 * d;
+    const int scratch = rows * T.pitch + 2;
+    T.words = (scratch + T.pitch + 2 + 3) / 4;
+    T.words |= 1;   // odd: the chains' grids start in different banks
+    // cell (row, column) of each slot in its block
+    static const int dr[4] = {0, 0, 1, 1}, dc[4] = {0, 1, 0, 1};
+    auto corner = [&](int f) {
+        const int x = L.fcx[f], y = L.fcy[f];
+        return rot ? (y + 1) * T.pitch + x + 1 : ((x - y) / 2 + d - 2) * T.pitch + (x + y) / 2 - 2;
+    };
+    T.cell.assign(L.nq, 0xFFFF);
+    for (int f = 0; f < L.nstab; ++f)
+        for (int s = 0; s < 4; ++s) {
+            const int q = L.fq[4 * f + s];
+            if (q < 0) continue;
+            const int at = corner(f) + dr[s] * T.pitch + dc[s];
+            if (at < 0 || at >= scratch || (T.cell[q] != 0xFFFF && T.cell[q] != at)) return false;
+            T.cell[q] = (uint16_t)at;
+        }
+    std::vector<int> owner(4 * T.words, -1);
+    for (int q = 0; q < L.nq; ++q) {
+        if (T.cell[q] == 0xFFFF || owner[T.cell[q]] >= 0) return false;
+        owner[T.cell[q]] = q;
+    }
+    // an absent slot's cell holds no qubit
+    for (int f = 0; f < L.nstab; ++f)
+        for (int s = 0; s < 4; ++s) {
+            const int at = corner(f) + dr[s] * T.pitch + dc[s];
+            if (at < 0 || at >= 4 * T.words || owner[at] != L.fq[4 * f + s]) return false;
+        }
+    // the shapes' tables
+    std::vector<int> rank_at(1, -1), base(shapes.size(), 0);
+    for (size_t t = 0; t < shapes.size(); ++t) {
+        std::vector<std::pair<int, int>> use;   // block pattern, rank
+        for (int pat = 0; pat < 256; ++pat) {
+            int blk = 0;
+            bool in = true;
+            for (int s = 0; s < 4; ++s) {
+                const int code = (pat >> (2 * s)) & 3;
+                if (!(shapes[t] >> s & 1)) { in = in && code == 0; continue; }
+                blk |= code << (2 * (2 * dr[s] + dc[s]));
+            }
+            if (in) use.push_back({blk, lut[256 * t + pat]});
+        }
+        for (;; ++base[t]) {
+            bool fits = true;
+            for (const auto &u : use)
+                if (base[t] + u.first < (int)rank_at.size() && rank_at[base[t] + u.first] >= 0) { fits = false; break; }
+            if (fits) break;
+        }
+        for (const auto &u : use) {
+            if (base[t] + u.first >= (int)rank_at.size()) rank_at.resize(base[t] + u.first + 1, -1);
+            rank_at[base[t] + u.first] = u.second;
+        }
+    }
+    T.slots = (int)rank_at.size();
+    for (int pass = 0; pass < 2; ++pass) {   // dE > 0 first
+        for (int i = 0; i < T.slots; ++i)
+            if (rank_at[i] >= 0 && (rank_at[i] >= kneg) == (pass == 0))
+                T.entry.push_back((uint32_t)i | ((uint32_t)rank_at[i] << 16));
+        if (pass == 0) T.rising = (int)T.entry.size();
+    }
+    if (T.rising > kGridMaxRising || 8 * T.slots >= 65536) return false;
+    const int mpad = 4 * ((L.per_class + 3) / 4);
+    const uint2 idle = make_uint2((uint32_t)scratch | ((uint32_t)(8 * base.back()) << 16), 0u);   // null shape
+    T.move.assign(4 * (mpad + 1), idle);
+    for (int k = 0; k < 4; ++k)
+        for (int m = 0; m < L.per_class; ++m) {
+            const int f = L.by_class[k * L.per_class + m];
+            uint32_t flip = 0;
+            for (int s = 0; s < 4; ++s)
+                if (L.fq[4 * f + s] >= 0) flip |= ((uint32_t)kSlotPauli[s] << 3) << (8 * (2 * dr[s] + dc[s]));
+            if ((corner(f) & 1) != (k & 1)) return false;
+            T.move[k * (mpad + 1) + m] = make_uint2((uint32_t)corner(f) | ((uint32_t)(8 * base[shape_of_face[f]]) << 16), flip);
+        }
+    return true;
+}
+
 static inline Desc pack_desc(const Lattice &L, int f, int shape)
 {
     uint32_t q[4];
@@ -588,6 +710,10 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
     for (int k = 0; k < 4; ++k)
         for (int m = 0; m < L.per_class; ++m) desc[k * L.per_class + m] = fdesc[L.by_class[k * L.per_class + m]];
 
+    GridTables grid;
+    P.grid_ok = build_grid(L, all, lut, shape_of_face, shapes, P.kneg, grid) ? 1 : 0;
+    if (!P.grid_ok) grid = GridTables();
+
     Graph G[2];
     int rc = build_graphs(L, wg, G);
     if (rc) return rc;
@@ -605,6 +731,9 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
     const size_t o_lx = take(L.nq);
     const size_t o_lz = take(L.nq);
     const size_t o_qpos = take(qpos.size() * 4);
+    const size_t o_gmove = take(grid.move.size() * sizeof(uint2));
+    const size_t o_gentry = take(grid.entry.size() * 4);
+    const size_t o_gcell = take(grid.cell.size() * 2);
     size_t o_cf[2], o_dint[2], o_db[2], o_adj[2];
     for (int g = 0; g < 2; ++g) {
         o_cf[g] = take(G[g].n * 4);
@@ -626,6 +755,9 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
     put(o_lx, L.lx.data(), L.nq);
     put(o_lz, L.lz.data(), L.nq);
     put(o_qpos, qpos.data(), qpos.size() * 4);
+    put(o_gmove, grid.move.data(), grid.move.size() * sizeof(uint2));
+    put(o_gentry, grid.entry.data(), grid.entry.size() * 4);
+    put(o_gcell, grid.cell.data(), grid.cell.size() * 2);
     for (int g = 0; g < 2; ++g) {
         put(o_cf[g], G[g].col_face.data(), G[g].n * 4);
         put(o_dint[g], G[g].dint.data(), (size_t)G[g].n * G[g].n * 4);
@@ -664,6 +796,14 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
     h.lx = base + o_lx;
     h.lz = base + o_lz;
     h.qpos = reinterpret_cast<const uint32_t *>(base + o_qpos);
+    h.grid_words = grid.words;
+    h.grid_pitch = grid.pitch;
+    h.grid_slots = grid.slots;
+    h.grid_entries = (int)grid.entry.size();
+    h.grid_rising = grid.rising;
+    h.grid_move = reinterpret_cast<const uint2 *>(base + o_gmove);
+    h.grid_entry = reinterpret_cast<const uint32_t *>(base + o_gentry);
+    h.grid_cell = reinterpret_cast<const uint16_t *>(base + o_gcell);
     for (int g = 0; g < 2; ++g) {
         h.ncol[g] = G[g].n;
         h.col_face[g] = reinterpret_cast<const int32_t *>(base + o_cf[g]);
@@ -955,6 +1095,7 @@ int xzzx_plan_set_kernel(xzzx_plan *plan, int kernel)
         set_error("unknown kernel");
         return XZZX_EINVAL;
     }
+    plan->P.grid_auto = kernel == XZZX_KERNEL_AUTO;
     return XZZX_OK;
 }
 
@@ -999,6 +1140,7 @@ int xzzx_plan_set_lanes(xzzx_plan *plan, int lanes_per_chain)
     if (plan->P.lds_bytes_anneal(g) > 65536) { set_error("chains per wavefront do not fit in LDS"); return XZZX_ERANGE; }
     plan->P.lanes = g;
     plan->P.hdev.lanes = g;
+    plan->P.grid_auto = lanes_per_chain == 0;
     plan->P.use_rows = (lanes_per_chain == 0 && rows_by_default(plan->P)) ? 1 : 0;
     if (hipMemcpy(&plan->P.ddev->lanes, &g, sizeof(int), hipMemcpyHostToDevice) != hipSuccess) {
         set_error("plan update failed");

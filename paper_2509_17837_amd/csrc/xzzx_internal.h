@@ -19,6 +19,7 @@ constexpr int kMaxD = 31;
 constexpr int kMaxGroups = 16;   // syndrome groups per persistent launch
 constexpr int kMaxRanks = 255;   // distinct move energies per plan (u8 rank)
 constexpr int kMaxTypes = 16;    // generator shapes (subset of the four slots)
+constexpr int kGridMaxRising = 256;   // grid core: table entries with dE > 0
 
 // Generator descriptor, 8 bytes: the four slot qubits (X_left, Z_up, Z_down,
 // X_right), an absent slot pointing at the per-chain scratch byte n_q, and the
@@ -223,6 +224,16 @@ struct PlanDev {
     const int32_t *dE;             // [nranks] ascending
     const uint32_t *thr;           // [n_sweeps][nranks]
     const uint8_t *lx, *lz;        // [nq]
+    // grid core: one byte per cell, a move's block = two adjacent bytes of two
+    // rows (grid_pitch bytes apart)
+    int grid_words;                // 32-bit words of a chain's grid, scratch cells included
+    int grid_pitch;                // bytes per row
+    int grid_slots;                // LDS entries (dE, threshold) of the shapes' tables
+    int grid_entries, grid_rising; // entries in use; the first grid_rising of them have dE > 0
+    const uint2 *grid_move;        // [4][4 nblk + 1] block | entry table << 16, flip mask; the last and the
+                                   // ranks past the class are idle moves
+    const uint32_t *grid_entry;    // [grid_entries] LDS entry | rank << 16
+    const uint16_t *grid_cell;     // [nq] byte of each qubit
     // greedy matching, per decoding-graph colour g
     int ncol[2];
     const int32_t *col_face[2];    // node -> face id (ascending)
@@ -248,6 +259,8 @@ struct Plan {
     int order = 0;                 // XZZX_ORDER_COLOUR or XZZX_ORDER_RANDOM_SITE
     int planar_ok = 0;             // the planar kernel specialised to d applies
     int planar_d = 0;              // d while that kernel is in use, else 0
+    int grid_ok = 0;               // the grid core applies (its tables are in place)
+    int grid_auto = 1;             // no kernel or lane count was asked for: small launches may use the grid core
     int ladder_k = 0;              // replica exchange: levels per ladder (0 = off)
     double ladder_lo = 0, ladder_hi = 0;
     void *ladder_mem = nullptr;    // device tables of the ladder (thresholds per level, exchange powers)
@@ -259,6 +272,8 @@ struct Plan {
     PlanDev hdev{};                // host copy with device pointers
     PlanDev *ddev = nullptr;       // device copy of hdev (inside dmem)
     size_t lds_bytes_anneal(int lanes) const;
+    size_t lds_bytes_grid(int lanes) const;
+    int grid_moves(int lanes) const;   // moves per lane and class of the grid core (0: too many)
     size_t lds_bytes_rows() const;
     size_t lds_bytes_site() const;
 };

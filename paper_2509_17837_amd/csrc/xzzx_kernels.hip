@@ -851,7 +851,8 @@ struct GroupWs {
     uint8_t *refs, *qraw, *qcls;
     int32_t *emin, *stop, *efin, *best_chain;
     uint32_t *cp_rows;     // checkpoints of groups on the specialised packed-row kernel
-    uint32_t *min_snap;    // random-site and planar specialised groups: each chain's state at its first E_min
+    uint32_t *min_snap;    // random-site, planar specialised, ladder and grid groups: each chain's state at its first E_min
+    int grid;              // lanes per chain on the grid core (0: another kernel)
 };
 
 // Replica exchange on the packed-row kernels specialised to d: the distance
@@ -913,7 +914,67 @@ static int checkpoints_of(const xzzx_group &g)
     return (g.plan->P.n_sweeps - 1) / checkpoint_interval(g.plan->P);
 }
 
-static size_t group_ws_bytes(const xzzx_group &g, bool decode)
+static int device_cus()
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
+    return cus;
+}
+
+// Lanes per chain of each group on the grid core, 0 where another kernel runs
+// it.  A plan whose lanes were chosen (the byte-state kernel with L lanes per
+// chain) takes the grid core with those lanes; it has the same use and half
+// the LDS round trips a phase.  A plan left to the default takes it, with
+// the least power of two of lanes that holds a colour class (64 at most),
+//   - where no packed-row kernel applies (planar d > 15): at 64 lanes it ran
+//     2048 syndromes of 64 chains in 9.5 against 14.4 ms (d = 21, 60 sweeps);
+//   - where the call is too small for one chain per lane: up to
+//     kGridChainsPerCu chains per CU, when less than two in five SIMDs would
+//     get a wavefront of 64 chains, each of which takes the whole latency of
+//     a sweep on one lane (7.3 us at d = 11, 0.61 us on 32 or 64 lanes).
+//     Rotated d = 11, 500 sweeps: 64 chains 3.62 -> 0.31 ms, 16384 3.69 ->
+//     1.23, 32768 3.7 -> 2.3, 65536 3.87 -> 4.5 (the packed-row kernel is
+//     the better one from there); the lines of the other lattices cross
+//     between 28000 (planar d = 5) and 65000 chains.  The groups of a call
+//     share the device, so the smallest ones take it while all of them
+//     together stay below the line.
+constexpr int64_t kGridChainsPerCu = 96;
+
+static int grid_lanes(const Plan &P)
+{
+    int lanes = 4;
+    while (lanes < kWave && lanes < P.lat.per_class) lanes *= 2;
+    return P.grid_moves(lanes) ? lanes : 0;
+}
+
+static std::vector<int> grid_routes(const xzzx_group *groups, int n_groups)
+{
+    std::vector<int> lanes(n_groups, 0);
+    std::vector<std::pair<int64_t, int>> small;   // chains, group
+    for (int i = 0; i < n_groups; ++i) {
+        const xzzx_group &g = groups[i];
+        const Plan &P = g.plan->P;
+        if (!P.grid_ok || P.order != XZZX_ORDER_COLOUR || P.ladder_k || g.n_syn <= 0 || g.n_rep <= 0) continue;
+        if (!P.use_rows) {
+            const int l = P.grid_auto ? grid_lanes(P) : P.lanes;
+            if (l >= 4 && P.grid_moves(l)) lanes[i] = l;
+        } else if (P.grid_auto) {
+            small.push_back({g.n_syn * 4 * (int64_t)g.n_rep, i});
+        }
+    }
+    std::sort(small.begin(), small.end());
+    int64_t left = kGridChainsPerCu * device_cus();
+    for (const auto &[chains, i] : small) {
+        if (chains > left) break;
+        left -= chains;
+        lanes[i] = grid_lanes(groups[i].plan->P);
+    }
+    return lanes;
+}
+
+// Bytes of a group's buffers; grid: on the grid core (lanes per chain).
+static size_t group_ws_bytes(const xzzx_group &g, bool decode, int grid)
 {
     const Plan &P = g.plan->P;
     const size_t nq = P.lat.nq, ns = (size_t)g.n_syn, R = (size_t)g.n_rep, nc = 4 * R * ns;
@@ -925,17 +986,34 @@ static size_t group_ws_bytes(const xzzx_group &g, bool decode)
     if (!g.d_chain_stop) b += align256(nc * 4);
     if (!g.d_chain_e) b += align256(nc * 4);
     if (!g.d_best_chain) b += align256(ns * 4);
+    if (grid) return b + align256((size_t)P.hdev.grid_words * nc * 4);
     b += align256((size_t)checkpoints_of(g) * P.lat.d * P.static_words * nc * 4);
     b += align256((size_t)min_snap_words(g) * nc * 4);
     return b;
 }
 
-static GroupWs carve_group(const xzzx_group &g, bool decode, uint8_t *&p)
+// Workspace of a call: what its kernels use at best (`full`), and what it is
+// accepted with (`least`): the grid core's states may take more than the
+// other kernels' checkpoints, and a call whose workspace is short of them
+// runs on those kernels instead.
+static void ws_bytes(const xzzx_group *groups, int n_groups, bool decode, const std::vector<int> &grid, size_t *full,
+                     size_t *least)
+{
+    *full = *least = 256;
+    for (int i = 0; i < n_groups; ++i) {
+        const size_t other = group_ws_bytes(groups[i], decode, 0);
+        *least += other;
+        *full += grid[i] ? std::max(other, group_ws_bytes(groups[i], decode, grid[i])) : other;
+    }
+}
+
+static GroupWs carve_group(const xzzx_group &g, bool decode, int grid, uint8_t *&p)
 {
     const Plan &P = g.plan->P;
     const size_t nq = P.lat.nq, ns = (size_t)g.n_syn, R = (size_t)g.n_rep, nc = 4 * R * ns;
     GroupWs w{};
     auto take = [&](size_t bytes) { uint8_t *r = p; p += align256(bytes); return r; };
+    w.grid = grid;
     w.refs = g.d_refs ? g.d_refs : (decode ? take(ns * R * nq) : nullptr);
     w.qraw = take(ns * R);
     w.qcls = g.d_qcls ? g.d_qcls : take(ns * R);
@@ -943,9 +1021,10 @@ static GroupWs carve_group(const xzzx_group &g, bool decode, uint8_t *&p)
     w.stop = g.d_chain_stop ? g.d_chain_stop : reinterpret_cast<int32_t *>(take(nc * 4));
     w.efin = g.d_chain_e ? g.d_chain_e : reinterpret_cast<int32_t *>(take(nc * 4));
     w.best_chain = g.d_best_chain ? g.d_best_chain : reinterpret_cast<int32_t *>(take(ns * 4));
-    const int ncp = checkpoints_of(g);
-    w.cp_rows = ncp ? reinterpret_cast<uint32_t *>(take((size_t)ncp * P.lat.d * P.static_words * nc * 4)) : nullptr;
-    w.min_snap = min_snap_words(g) ? reinterpret_cast<uint32_t *>(take((size_t)min_snap_words(g) * nc * 4)) : nullptr;
+    const size_t ncp = grid ? 0 : (size_t)checkpoints_of(g);
+    const size_t snap = grid ? (size_t)P.hdev.grid_words : (size_t)min_snap_words(g);
+    w.cp_rows = ncp ? reinterpret_cast<uint32_t *>(take(ncp * P.lat.d * P.static_words * nc * 4)) : nullptr;
+    w.min_snap = snap ? reinterpret_cast<uint32_t *>(take(snap * nc * 4)) : nullptr;
     return w;
 }
 
@@ -969,14 +1048,6 @@ static int validate_groups(const xzzx_group *groups, int n_groups, bool decode)
         if ((int64_t)g.n_syn * 4 * g.n_rep >= ((int64_t)1 << 31)) { set_error("too many chains in one group"); return XZZX_ERANGE; }
     }
     return XZZX_OK;
-}
-
-static int device_cus()
-{
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 256;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-    return cus;
 }
 
 static int anneal_grid(const void *kernel, size_t lds_bytes, uint32_t n_tasks, unsigned *grid)
@@ -1006,7 +1077,7 @@ enum class AnnealMode { Persistent, Replay, Plain };
 static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::vector<int> &sel, bool rows, int lanes,
                       AnnealMode mode, uint64_t seed, int64_t unit_offset, int64_t units_override,
                       uint32_t *d_counter, hipStream_t stream, int static_d = 0, bool site = false,
-                      int planar_d = 0, bool ladder = false)
+                      int planar_d = 0, bool ladder = false, int grid_mv = 0)
 {
     const bool replay = mode == AnnealMode::Replay;
     AnnealArgs A{};
@@ -1048,7 +1119,7 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
         G.cp_rows = cp ? ws[i].cp_rows : nullptr;
         G.cp_every = cp ? checkpoint_interval(P) : 0;
         G.n_chains = g.n_syn * 4 * g.n_rep;
-        G.min_snap = (site || planar_d || ladder) ? ws[i].min_snap : nullptr;
+        G.min_snap = (site || planar_d || ladder || grid_mv) ? ws[i].min_snap : nullptr;
         G.unit_offset = unit_offset;
         const int64_t units = units_of(i);
         G.n_units = units;
@@ -1058,6 +1129,7 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
         lds = std::max(lds, (ladder && (static_d || planar_d))
                                 ? 16 * (size_t)P.ladder_k * P.nranks()
                             : (static_d || planar_d) ? (size_t)0
+                            : grid_mv ? P.lds_bytes_grid(lanes)
                             : ladder ? P.lds_bytes_ladder()
                             : site   ? P.lds_bytes_site()
                             : rows   ? P.lds_bytes_rows()
@@ -1069,7 +1141,10 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
     A.n_tasks = (uint32_t)tasks;
     if (lds > 65536) { set_error("LDS demand above 64 KiB"); return XZZX_ERANGE; }
     if (mode == AnnealMode::Plain) {
-        if (ladder && static_d)
+        A.counter = nullptr;
+        if (grid_mv)
+            hipLaunchKernelGGL(grid_kernel(lanes, grid_mv), dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
+        else if (ladder && static_d)
             hipLaunchKernelGGL(ladder_rows_kernel(static_d, true), dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
         else if (ladder && planar_d)
             hipLaunchKernelGGL(ladder_planar_kernel(planar_d, true), dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
@@ -1087,7 +1162,8 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
             hipLaunchKernelGGL(bytes_kernel(2, lg), dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
         return check_hip(hipGetLastError(), "plain anneal launch");
     }
-    const AnnealKernel kern = (ladder && static_d) ? ladder_rows_kernel(static_d, false)
+    const AnnealKernel kern = grid_mv ? grid_kernel(lanes, grid_mv)
+                              : (ladder && static_d) ? ladder_rows_kernel(static_d, false)
                               : (ladder && planar_d) ? ladder_planar_kernel(planar_d, false)
                               : ladder     ? ladder_kernel(false)
                               : site     ? k_anneal_site
@@ -1206,13 +1282,10 @@ static int fork_join(hipStream_t stream, int n, F launch, bool serial = false)
 // launch; byte-state groups are launched per lanes-per-chain value.  The
 // replay re-runs one chain per syndrome with the byte-state kernel, spreading
 // a chain over more lanes when that is needed to give every CU several
-// wavefronts.  Each launch has its own queue counter: d_counters[0] packed
-// rows, [1..7] byte states by lanes per chain, [16..30] the kernels
-// specialised to d = 3, 5, ..., 31, [40] random-site chains, [41..47] the
-// planar kernels specialised to d = 3, 5, ..., 15, [48] ladders on the generic
-// kernel, [49..55] and [31..38] ladders on the rotated kernels specialised to
-// d = 3, ..., 15 and d = 17, ..., 31, [56..62] on the planar ones
-// (d = 3, ..., 15); a replay (with its own d_counters base) uses [0] and [2].
+// wavefronts.  Each launch has its own queue counter: launch i of an annealing
+// stage d_counters[i]; a replay (with its own d_counters base) uses [0] and
+// [2].
+constexpr int kReplayCounters = 16;   // words before the replay's counters
 static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_groups, AnnealMode mode,
                          uint64_t seed, int64_t unit_offset, int64_t units_override, uint32_t *d_counters,
                          hipStream_t stream, bool serial = false)
@@ -1224,6 +1297,7 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
     std::vector<int> site_sel;    // random-site plans: one chain (replay: syndrome) per lane
     std::vector<int> planar_sel[kPlanarStaticMaxD + 1];   // planar kernels specialised to d
     std::vector<int> gather_sel;  // replay: recoveries gathered from the states kept at E_min
+    std::vector<int> grid_sel[5][4];   // grid core, by lanes per chain (4..64) and moves per lane (1, 2, 4, 8)
     std::vector<int> ladder_sel;  // replica exchange: one chain per lane
     std::vector<int> ladder_rows_sel[kLadderRowsMaxD + 1];      // ... on the rotated kernels specialised to d
     std::vector<int> ladder_planar_sel[kPlanarStaticMaxD + 1];  // ... on the planar kernels specialised to d
@@ -1231,7 +1305,11 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
     for (int i = 0; i < n_groups; ++i) {
         if (groups[i].n_syn <= 0) continue;
         const Plan &P = groups[i].plan->P;
-        if (P.order == XZZX_ORDER_RANDOM_SITE || P.ladder_k ||
+        if (ws[i].grid && mode != AnnealMode::Replay) {
+            grid_sel[log2_int(ws[i].grid) - 2][log2_int(P.grid_moves(ws[i].grid))].push_back(i);
+            continue;
+        }
+        if (ws[i].grid || P.order == XZZX_ORDER_RANDOM_SITE || P.ladder_k ||
             (mode == AnnealMode::Replay && min_snap_words(groups[i]))) {
             if (mode == AnnealMode::Replay) gather_sel.push_back(i);
             else if (ladder_rows_d(groups[i])) ladder_rows_sel[ladder_rows_d(groups[i])].push_back(i);
@@ -1270,7 +1348,10 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
             const int64_t n = g.n_syn * (int64_t)P.lat.nq, nc = g.n_syn * 4 * (int64_t)g.n_rep;
             if ((n + 255) / 256 * 256 > kMaxLaunchItems) { set_error("too many recovery bytes in one group"); return XZZX_ERANGE; }
             const dim3 grid((unsigned)((n + 255) / 256));
-            if (const int ld = ladder_rows_d(g))
+            if (ws[i].grid)
+                launch_grid_recovery(ws[i].min_snap, P.hdev.grid_words, ws[i].best_chain, g.n_rep, P.lat.nq, g.n_syn,
+                                     P.ddev, g.d_recovery, stream);
+            else if (const int ld = ladder_rows_d(g))
                 hipLaunchKernelGGL(k_static_recovery, grid, dim3(256), 0, stream, ws[i].min_snap,
                                    (int)min_snap_words(g), ws[i].best_chain, g.n_rep, ld, g.n_syn,
                                    2 * (ld + 1) <= 32 ? 1 : 2, g.d_recovery);
@@ -1291,45 +1372,42 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
         const std::vector<int> *sel;
         bool rows;
         int lanes;
-        uint32_t *counter;
         int static_d;
         bool site;
         int planar_d;
         bool ladder;
+        int grid_mv;
     };
     std::vector<Set> sets;
-    if (!rows_sel.empty()) sets.push_back({&rows_sel, true, 1, d_counters, 0, false, 0, false});
-    if (!site_sel.empty()) sets.push_back({&site_sel, false, 1, d_counters + 40, 0, true, 0, false});
-    if (!ladder_sel.empty()) sets.push_back({&ladder_sel, false, 1, d_counters + 48, 0, false, 0, true});
+    if (!rows_sel.empty()) sets.push_back({&rows_sel, true, 1, 0, false, 0, false, 0});
+    if (!site_sel.empty()) sets.push_back({&site_sel, false, 1, 0, true, 0, false, 0});
+    if (!ladder_sel.empty()) sets.push_back({&ladder_sel, false, 1, 0, false, 0, true, 0});
     for (int d = 3; d <= kPlanarStaticMaxD; d += 2)
-        if (!planar_sel[d].empty())
-            sets.push_back({&planar_sel[d], true, 1, d_counters + 41 + (d - 3) / 2, 0, false, d, false});
+        if (!planar_sel[d].empty()) sets.push_back({&planar_sel[d], true, 1, 0, false, d, false, 0});
     for (int d = 3; d <= kLadderRowsMaxD; d += 2)
-        if (!ladder_rows_sel[d].empty())
-            sets.push_back({&ladder_rows_sel[d], true, 1, d_counters + (d <= 15 ? 49 + (d - 3) / 2 : 31 + (d - 17) / 2),
-                            d, false, 0, true});
+        if (!ladder_rows_sel[d].empty()) sets.push_back({&ladder_rows_sel[d], true, 1, d, false, 0, true, 0});
     for (int d = 3; d <= kPlanarStaticMaxD; d += 2)
-        if (!ladder_planar_sel[d].empty())
-            sets.push_back({&ladder_planar_sel[d], true, 1, d_counters + 56 + (d - 3) / 2, 0, false, d, true});
+        if (!ladder_planar_sel[d].empty()) sets.push_back({&ladder_planar_sel[d], true, 1, 0, false, d, true, 0});
     for (int d = kStaticMinD; d <= kStaticMaxD; d += 2)
-        if (!static_sel[d].empty())
-            sets.push_back({&static_sel[d], true, 1, d_counters + 16 + (d - kStaticMinD) / 2, d, false, 0, false});
+        if (!static_sel[d].empty()) sets.push_back({&static_sel[d], true, 1, d, false, 0, false, 0});
     for (int l = 0; l < 7; ++l)
-        if (!bytes_sel[l].empty())
-            sets.push_back({&bytes_sel[l], false, 1 << l, d_counters + 1 + l, 0, false, 0, false});
+        if (!bytes_sel[l].empty()) sets.push_back({&bytes_sel[l], false, 1 << l, 0, false, 0, false, 0});
+    for (int l = 0; l < 5; ++l)
+        for (int m = 0; m < 4; ++m)
+            if (!grid_sel[l][m].empty()) sets.push_back({&grid_sel[l][m], false, 4 << l, 0, false, 0, false, 1 << m});
+    // each set holds at least one group, so at most kMaxGroups of them
+    static_assert(kMaxGroups <= kReplayCounters, "queue counters of the sets");
+    auto one = [&](int i, hipStream_t s) {
+        const Set &S = sets[i];
+        return launch_set(groups, ws, *S.sel, S.rows, S.lanes, mode, seed, unit_offset, units_override, d_counters + i,
+                          s, S.static_d, S.site, S.planar_d, S.ladder, S.grid_mv);
+    };
     if (sets.size() <= 1 || mode == AnnealMode::Plain) {
         int rc = XZZX_OK;
-        for (const Set &S : sets)
-            if (!rc)
-                rc = launch_set(groups, ws, *S.sel, S.rows, S.lanes, mode, seed, unit_offset, units_override, S.counter,
-                                stream, S.static_d, S.site, S.planar_d, S.ladder);
+        for (int i = 0; i < (int)sets.size() && !rc; ++i) rc = one(i, stream);
         return rc;
     }
-    return fork_join(stream, (int)sets.size(), [&](int i, hipStream_t s) {
-        const Set &S = sets[i];
-        return launch_set(groups, ws, *S.sel, S.rows, S.lanes, mode, seed, unit_offset, units_override, S.counter, s,
-                          S.static_d, S.site, S.planar_d, S.ladder);
-    }, serial);
+    return fork_join(stream, (int)sets.size(), one, serial);
 }
 
 static int launch_reduce(const xzzx_group &g, const GroupWs &w, hipStream_t stream)
@@ -1409,14 +1487,16 @@ static int run_decode(const xzzx_group *groups, int n_groups, uint64_t greedy_se
         set_error("unknown greedy mode");
         return XZZX_EINVAL;
     }
-    size_t need = 256;
-    for (int i = 0; i < n_groups; ++i) need += group_ws_bytes(groups[i], decode);
-    if (!d_workspace || workspace_bytes < need) { set_error("workspace too small"); return XZZX_ENOMEM; }
+    std::vector<int> grid = grid_routes(groups, n_groups);
+    size_t full = 0, least = 0;
+    ws_bytes(groups, n_groups, decode, grid, &full, &least);
+    if (!d_workspace || workspace_bytes < least) { set_error("workspace too small"); return XZZX_ENOMEM; }
+    if (workspace_bytes < full) std::fill(grid.begin(), grid.end(), 0);
     uint8_t *p = static_cast<uint8_t *>(d_workspace);
     uint32_t *counter = reinterpret_cast<uint32_t *>(p);
     p += 256;
     std::vector<GroupWs> ws(n_groups);
-    for (int i = 0; i < n_groups; ++i) ws[i] = carve_group(groups[i], decode, p);
+    for (int i = 0; i < n_groups; ++i) ws[i] = carve_group(groups[i], decode, grid[i], p);
     const int stage_bits = XZZX_FLAG_STAGE_GREEDY | XZZX_FLAG_STAGE_ANNEAL | XZZX_FLAG_STAGE_FINISH;
     const int stages = (flags & stage_bits) ? (flags & stage_bits) : stage_bits;
     // the groups' greedy launches run concurrently (one group's launch alone
@@ -1459,8 +1539,8 @@ static int run_decode(const xzzx_group *groups, int n_groups, uint64_t greedy_se
         rc = launch_reduce(groups[i], ws[i], stream);
         if (rc) return rc;
     }
-    return launch_anneal(groups, ws.data(), n_groups, AnnealMode::Replay, anneal_seed, 0, -1, counter + 8, stream,
-                         serial);
+    return launch_anneal(groups, ws.data(), n_groups, AnnealMode::Replay, anneal_seed, 0, -1, counter + kReplayCounters,
+                         stream, serial);
 }
 
 
@@ -1581,12 +1661,10 @@ int xzzx_greedy_init(const xzzx_plan *plan, const uint8_t *d_syn, const uint32_t
 int xzzx_decode_workspace(const xzzx_group *groups, int n_groups, size_t *bytes)
 {
     if (!groups || !bytes || n_groups < 1 || n_groups > kMaxGroups) { set_error("bad arguments"); return XZZX_EINVAL; }
-    size_t need = 256;
-    for (int i = 0; i < n_groups; ++i) {
+    for (int i = 0; i < n_groups; ++i)
         if (!groups[i].plan) { set_error("group without plan"); return XZZX_EINVAL; }
-        need += group_ws_bytes(groups[i], true);
-    }
-    *bytes = need;
+    size_t least = 0;
+    ws_bytes(groups, n_groups, true, grid_routes(groups, n_groups), bytes, &least);
     return XZZX_OK;
 }
 
@@ -1637,9 +1715,10 @@ extern "C" {
 int xzzx_decode_noalloc(const xzzx_group *groups, int n_groups, uint64_t greedy_seed, uint64_t anneal_seed,
                         int greedy_mode, int flags, void *stream)
 {
-    size_t need = 0;
-    int rc = xzzx_decode_workspace(groups, n_groups, &need);
+    size_t full = 0, need = 0;
+    int rc = xzzx_decode_workspace(groups, n_groups, &full);
     if (rc) return rc;
+    ws_bytes(groups, n_groups, true, std::vector<int>(n_groups, 0), &full, &need);
     if (need > (size_t)XZZX_NOALLOC_SCRATCH_BYTES) {
         set_error("workspace of these groups exceeds XZZX_NOALLOC_SCRATCH_BYTES");
         return XZZX_ERANGE;

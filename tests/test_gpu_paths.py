@@ -43,3 +43,26 @@ def test_syndrome_tiles(layout, d, n, offset):
     for i in {0, n // 2, n - 1}:
         assert np.array_equal(want[i], olat.syndrome(cfg[i] & 3))
     assert np.array_equal(got, want)
+
+
+# every (lanes, moves per lane) of the grid core: one, two, four and eight
+# moves, classes that fill the lanes and classes that leave some idle
+GRID_CASES = [
+    (0, 3, 4), (0, 3, 64), (0, 5, 4), (0, 5, 8), (0, 7, 4), (0, 7, 8), (0, 7, 16), (0, 9, 8), (0, 9, 16),
+    (0, 9, 32), (0, 11, 4), (0, 11, 8), (0, 11, 16), (0, 11, 32), (0, 11, 64), (0, 13, 16), (0, 13, 32), (0, 13, 64),
+    (0, 15, 8), (0, 15, 16), (0, 15, 32), (0, 15, 64), (0, 17, 32), (0, 17, 64), (0, 21, 16), (0, 21, 32), (0, 21, 64),
+    (0, 25, 64), (0, 29, 32), (0, 31, 32), (0, 31, 64), (1, 3, 4), (1, 5, 16), (1, 7, 8), (1, 7, 32), (1, 9, 16),
+    (1, 9, 64), (1, 13, 32), (1, 15, 64), (1, 17, 64), (1, 21, 64), (1, 23, 64), (1, 25, 64), (1, 31, 64)]
+
+
+@pytest.mark.parametrize("layout,d,lanes", GRID_CASES)
+def test_grid_core(layout, d, lanes):
+    """Chains over several lanes: every chain, its final state, and the
+    recoveries taken from the states kept at E_min."""
+    print(f"[paths] grid layout={layout} d={d} lanes={lanes}", flush=True)
+    prob = Problem(layout, d, 0.15, 5.0, 3, 3, 25 if d < 20 else 9, seed=40 + d, conv=layout)
+    plan = gpu_plan(prob, lanes=lanes)
+    out = D.decode(plan, to_dev(prob.syn), to_dev(prob.uid.view(np.int32)), prob.n_rep, prob.greedy_seed,
+                   prob.anneal_seed, want_chains=True, want_final=True)
+    torch.cuda.synchronize()
+    compare_decode(prob, out, prob.oracle_decode())
