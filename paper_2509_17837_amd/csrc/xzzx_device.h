@@ -124,7 +124,8 @@ struct ChainJob {
 // Serving keeps, per chain, two buffers of byte states and two of packed
 // rows (the specialised kernel's layout), and one entry naming the state a
 // replay of the chain's E_min phase starts from: -1 for the references at
-// sweep 0, else (sweep << 2) | (packed << 1) | b.  Kept states go to buffer
+// sweep 0, kKeptExact for the state at E_min itself (which the grid core
+// keeps, in a buffer of its own), else (sweep << 2) | (packed << 1) | b.  Kept states go to buffer
 // kept_scratch(entry) -- the one the entry does not name -- of either kind:
 // the start state of a sweep range (bytes, by k_serve_stash), and inside a
 // range the state every kServeCheckpointEvery sweeps (bytes from the
@@ -1454,9 +1455,6 @@ __device__ __forceinline__ ChainJob serve_job(const ServeTask &T, int slot, bool
     j.cp_stride = 0;
     j.cp_words = 0;
     j.t0 = 0;
-    // start states kept at sweep-range boundaries: buffer b of chain c at
-    // cp + (b nc + c) nq; cpm[c] = (sweep << 1) | b of the one a replay of
-    // the chain's E_min phase starts from, -1 for the references at sweep 0
     j.cp_meta = nullptr;
     j.cp_base = nullptr;
     j.cp_bstride = 0;
@@ -1507,8 +1505,17 @@ __device__ __forceinline__ void serve_kernel_body(const ServeTask *tasks, uint32
         if (T.row_words == 1) rows_core<1>(pl, J, T.t_begin, T.t_end, seed_lo, seed_hi, smem);
         else rows_core<2>(pl, J, T.t_begin, T.t_end, seed_lo, seed_hi, smem);
     } else {
-        load_plan_tables(pl, smem);
         const int lg = T.log_lanes;
+        if constexpr (REPLAY) {
+            // a state kept at E_min itself is the recovery
+            const int64_t c = *T.best;
+            if (T.cpm && T.cpm[c] == kKeptExact) {
+                const uint8_t *g = reinterpret_cast<const uint8_t *>(T.gs + c * pl->grid_words);
+                for (int q = threadIdx.x; q < pl->nq; q += kWave) T.snap[q] = g[pl->grid_cell[q]] >> 3;
+                return;
+            }
+        }
+        load_plan_tables(pl, smem);
         const ChainJob J = serve_job(T, threadIdx.x >> lg, REPLAY);
         const int tb = REPLAY ? J.t0 : T.t_begin;
         const int te = REPLAY ? pl->n_sweeps : T.t_end;
@@ -1583,6 +1590,7 @@ AnnealKernel grid_kernel(int lanes, int mv);
 void launch_grid_recovery(const uint32_t *snap, int words, const int32_t *best_chain, int n_rep, int nq, int64_t n_syn,
                           const PlanDev *pl, uint8_t *recovery, hipStream_t stream);
 typedef void (*ServeKernel)(const ServeTask *, uint32_t, uint32_t);
+ServeKernel serve_grid_kernel(int mv);
 
 // The specialised kernels live in several translation units (compiled in
 // parallel): the annealing kernels by distance (each part returns its kernels

@@ -430,6 +430,8 @@ __device__ __forceinline__ void grid_core(const PlanDev *pl, const ChainJob &J, 
             J.emin[J.ci] = Emin;
             J.stop[J.ci] = stop;
             J.efin[J.ci] = E;
+            // serving: the kept state is this range's if E_min is
+            if (J.cp_meta && (!J.resume || stop > 4 * t_begin)) J.cp_meta[J.ci] = kKeptExact;
         }
         if (J.states) {
             uint8_t *dst = J.states + (size_t)J.ci * nq;

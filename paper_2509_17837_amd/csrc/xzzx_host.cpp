@@ -476,8 +476,7 @@ static bool build_grid(const Lattice &L, const std::vector<int32_t> &dE, const s
     const int d = L.d, rows = rot ? d + 2 : 2 * d - 1;
     T.pitch = rot ? d + 1 : 2 * d;
     const int scratch = rows * T.pitch + 2;
-    T.words = (scratch + T.pitch + 2 + 3) / 4;
-    T.words |= 1;   // odd: the chains' grids start in different banks
+    T.words = grid_words_of(L.layout, d);
     // cell (row, column) of each slot in its block
     static const int dr[4] = {0, 0, 1, 1}, dc[4] = {0, 1, 0, 1};
     auto corner = [&](int f) {

@@ -20,6 +20,7 @@ constexpr int kMaxGroups = 16;   // syndrome groups per persistent launch
 constexpr int kMaxRanks = 255;   // distinct move energies per plan (u8 rank)
 constexpr int kMaxTypes = 16;    // generator shapes (subset of the four slots)
 constexpr int kGridMaxRising = 256;   // grid core: table entries with dE > 0
+constexpr int64_t kGridChainsPerCu = 96;   // chains per CU up to which the grid core is the faster form (grid_routes)
 
 // Generator descriptor, 8 bytes: the four slot qubits (X_left, Z_up, Z_down,
 // X_right), an absent slot pointing at the per-chain scratch byte n_q, and the
@@ -298,7 +299,11 @@ struct ServeTask {
     uint32_t *cpk;           // kept packed rows [2][4 n_rep][cpk_words]
     int32_t *cpm;            // per chain: entry naming the replay start (see kept_entry)
     int32_t cpk_words;       // words per chain of a packed-rows buffer
+    int32_t grid_mv;         // grid core: moves per lane and class (0: another core)
+    uint32_t *gs;            // grid core: each chain's state at its E_min [4 n_rep][grid_words]
 };
+// entry of a chain whose state at E_min itself is kept (in gs)
+constexpr int32_t kKeptExact = -2;
 
 // Serving-loop finish entry: per-coset reduction of one finished request,
 // and where its result and recovery are gathered for the copy to the host.
@@ -314,7 +319,7 @@ struct ServeFinish {
 
 // One launch of a serving slice: tasks of one kernel family.
 //   kind 0: packed-row kernel; 1: byte-state kernel; 2: packed-row kernel
-//   specialised to distance d.
+//   specialised to distance d; 3: grid core with d moves per lane.
 // One launch of a serving slice; the launches of a slice cover consecutive
 // ranges of one device task array, starting at launches[0].tasks.
 struct ServeLaunch {
@@ -338,6 +343,12 @@ int serve_finish(const ServeFinish *d_fin, const ServeTask *d_replay, int n, siz
 // ---- host helpers (xzzx_host.cpp) ----
 void set_error(const std::string &msg);
 int build_lattice(int layout, int d, Lattice &L);
+// 32-bit words of a chain's grid (grid core)
+inline int grid_words_of(int layout, int d)
+{
+    const int rows = layout == XZZX_ROTATED ? d + 2 : 2 * d - 1, pitch = layout == XZZX_ROTATED ? d + 1 : 2 * d;
+    return ((rows + 1) * pitch + 2 + 2 + 3) / 4 | 1;   // two scratch rows' starts; odd, so that grids start in different banks
+}
 int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const double *beta,
                int n_sweeps, Plan &P);
 uint32_t accept_threshold(double beta, int64_t dE);

@@ -636,7 +636,7 @@ __global__ __launch_bounds__(kWave) void k_serve_replay(const ServeTask *tasks, 
 __global__ __launch_bounds__(256) void k_serve_stash(const ServeTask *tasks)
 {
     const ServeTask &T = tasks[blockIdx.x];
-    if (T.t_begin == 0 || !T.cpm) return;
+    if (T.t_begin == 0 || !T.cpm || T.grid_mv) return;   // the grid core keeps the state at E_min itself
     const int nq = T.plan->nq;
     const int64_t nc = 4 * (int64_t)T.n_rep;
     const int64_t total = (int64_t)T.nchains * nq;
@@ -939,8 +939,6 @@ static int device_cus()
 //     between 28000 (planar d = 5) and 65000 chains.  The groups of a call
 //     share the device, so the smallest ones take it while all of them
 //     together stay below the line.
-constexpr int64_t kGridChainsPerCu = 96;
-
 static int grid_lanes(const Plan &P)
 {
     int lanes = 4;
@@ -1577,7 +1575,9 @@ int serve_slice(const ServeLaunch *launches, int n_launches, uint64_t seed, hipS
     // the launches' tasks are consecutive: stash the start states of them all
     int n_tasks = 0;
     for (int i = 0; i < n_launches; ++i) n_tasks += launches[i].n;
-    if (n_tasks > 0) {
+    bool stash = false;
+    for (int i = 0; i < n_launches; ++i) stash |= launches[i].n > 0 && launches[i].kind != 3;
+    if (stash) {
         hipLaunchKernelGGL(k_serve_stash, dim3((unsigned)n_tasks), dim3(256), 0, stream, launches[0].tasks);
         const int rc = check_hip(hipGetLastError(), "serving stash launch");
         if (rc) return rc;
@@ -1589,6 +1589,8 @@ int serve_slice(const ServeLaunch *launches, int n_launches, uint64_t seed, hipS
             hipLaunchKernelGGL(k_serve_rows, dim3((unsigned)L.n), dim3(kWave), L.lds, s, L.tasks, lo, hi);
         } else if (L.kind == 1) {
             hipLaunchKernelGGL(k_serve_bytes, dim3((unsigned)L.n), dim3(kWave), L.lds, s, L.tasks, lo, hi);
+        } else if (L.kind == 3) {
+            hipLaunchKernelGGL(serve_grid_kernel(L.d), dim3((unsigned)L.n), dim3(kWave), L.lds, s, L.tasks, lo, hi);
         } else {
             const ServeKernel k = static_serve_kernel(L.d);
             if (!k) { set_error("no specialised serving kernel for this distance"); return XZZX_EINVAL; }

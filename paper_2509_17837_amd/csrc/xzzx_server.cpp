@@ -75,6 +75,7 @@ struct xzzx_server {
     // device slot pool
     uint8_t *d_pool = nullptr;
     size_t slot_bytes = 0, off_refs = 0, off_states = 0, off_e3 = 0, off_qraw = 0, off_res = 0, off_rec = 0;
+    size_t off_gs = 0;   // states at E_min the grid core keeps [4R][words of the largest grid]
     size_t off_cp = 0, off_cpk = 0, off_cpm = 0;   // kept states: bytes [2][4R][nq], packed rows [2][4R][cpk_words], entries [4R]
     int cpk_words = 0;
     // staging (device + pinned host)
@@ -134,18 +135,24 @@ constexpr int64_t kSliceGrowth = 64;
 // kernel gives each lane of a chain whole blocks
 int class_blocks(const Plan &P)
 {
-    return (std::max(1, P.lat.nstab / 4) + 3) / 4;
+    return (std::max(1, P.lat.per_class) + 3) / 4;
 }
 
-// lanes per chain for a request when the slice offers g: where g lanes can
-// take every generator of a colour class, the least power of two that gives
-// each lane one generator (the byte-state kernel's one-move-per-lane form);
-// else the least power of two that gives every lane at most one block,
-// capped at g (more lanes would sit idle)
+// lanes per chain for a request when the slice offers g: on the grid core the
+// least power of two on which a lane has no more generators of a class than
+// on g; else (lattices without it, or g < 4) the byte-state kernel's: one
+// generator per lane where g lanes can take a class, else at most one block
+bool on_grid(const Plan &P, int g) { return g >= 4 && P.grid_ok && P.grid_moves(g) > 0; }
+
 int lanes_for(const Plan &P, int g)
 {
-    const int M = std::max(1, P.lat.per_class);
     int c = 1;
+    if (on_grid(P, g)) {
+        c = 4;
+        while (P.grid_moves(c) != P.grid_moves(g)) c *= 2;
+        return c;
+    }
+    const int M = std::max(1, P.lat.per_class);
     if (M <= g && g >= 4) {
         while (c < M) c *= 2;
         return std::max(c, 4);
@@ -156,16 +163,20 @@ int lanes_for(const Plan &P, int g)
 }
 
 // sequential work of one sweep of one chain: attempts on the packed-row
-// kernels (g = 1); on the byte-state kernel, in units of half a block per
-// lane: one generator per lane measured about half the phase latency of one
-// block per lane (0.43-0.47 and 0.92 us at 64 lanes), and each further block
-// per lane adds about one block's latency
+// kernels (g = 1); else in units of 0.3 us: the grid core's sweep takes 0.61,
+// 0.95, 1.8-2.2 and 3.6-4.7 us with one, two, four and eight moves per lane;
+// the byte-state kernel's 0.43 us a phase with one generator per lane, 0.92
+// with a block per lane, and about that much more for each further block
 int64_t sweep_cost(const Plan &P, int g)
 {
     if (g == 1) return P.lat.nstab;
     const int gr = lanes_for(P, g);
-    if (std::max(1, P.lat.per_class) <= gr && gr >= 4) return 1;
-    return 2 * ((class_blocks(P) + gr - 1) / gr);
+    if (on_grid(P, g)) {
+        const int mv = P.grid_moves(gr);
+        return mv == 1 ? 2 : mv == 2 ? 3 : mv == 4 ? 6 : 13;
+    }
+    if (std::max(1, P.lat.per_class) <= gr && gr >= 4) return 6;
+    return 12 * ((class_blocks(P) + gr - 1) / gr);
 }
 
 size_t request_lds(const Plan &P, int n_rep)
@@ -267,8 +278,8 @@ int xzzx_server::slice()
     // longest first, so the slice's long tasks start early and short ones
     // fill the device around them
     using CostTask = std::pair<int64_t, ServeTask>;
-    std::vector<CostTask> rows_t, bytes_t, static_t[kStaticMaxD + 1];
-    size_t lds_rows = 0, lds_bytes = 0;
+    std::vector<CostTask> rows_t, bytes_t, static_t[kStaticMaxD + 1], grid_t[9];
+    size_t lds_rows = 0, lds_bytes = 0, lds_grid[9] = {};
     std::vector<int> finished;
     // lanes per chain for this slice: at light load every chain spreads over
     // up to max_lanes_per_chain lanes of the byte-state kernel (lower latency
@@ -276,15 +287,22 @@ int xzzx_server::slice()
     // fits the wave and LDS budgets, down to each plan's own kernel choice.
     // Every choice gives the same chain trajectories, so it may change from
     // one slice to the next.
+    // Where the default wave budget leaves the choice open, that switch is made
+    // at once from kGridChainsPerCu chains per CU, where one chain per lane is
+    // the faster form (fewer lanes on the grid core are not: 65536 chains at
+    // d = 11, 500 sweeps, take 4.5 ms on 32 lanes, 5.9 on 4 and 3.9 on 1).
     int G = 1;
-    for (int g = cfg.max_lanes_per_chain; g > 1; g >>= 1) {
+    int64_t chains = 0;
+    for (int s : resident) chains += 4 * (int64_t)slots[s].n_rep;
+    const bool full = !cfg.max_waves && chains > kGridChainsPerCu * (wave_budget / 32);
+    for (int g = full ? 1 : cfg.max_lanes_per_chain; g > 1; g >>= 1) {
         int64_t waves = 0;
         size_t lds_max = 0;
         for (int s : resident) {
             const Slot &sl = slots[s];
             const int gr = lanes_for(*sl.plan, g);
             waves += (4 * sl.n_rep * gr + kWave - 1) / kWave;
-            lds_max = std::max(lds_max, sl.plan->lds_bytes_anneal(gr));
+            lds_max = std::max(lds_max, on_grid(*sl.plan, g) ? sl.plan->lds_bytes_grid(gr) : sl.plan->lds_bytes_anneal(gr));
         }
         if (waves <= wave_budget && (size_t)waves * lds_max <= lds_budget) { G = g; break; }
     }
@@ -312,7 +330,8 @@ int xzzx_server::slice()
             const bool rows = G == 1 && P.use_rows;
             const int gr = G > 1 ? lanes_for(P, G) : (P.use_rows ? 1 : P.lanes);
             const int C = kWave / gr;
-            const size_t lds = rows ? P.lds_bytes_rows() : P.lds_bytes_anneal(gr);
+            const int mv = G > 1 && on_grid(P, G) ? P.grid_moves(gr) : 0;
+            const size_t lds = rows ? P.lds_bytes_rows() : mv ? P.lds_bytes_grid(gr) : P.lds_bytes_anneal(gr);
             const int nc = 4 * sl.n_rep;
             uint8_t *base = slot_ptr(s);
             for (int c0 = 0; c0 < nc; c0 += C) {
@@ -337,9 +356,12 @@ int xzzx_server::slice()
                 while ((1 << lg) < gr) ++lg;
                 T.log_lanes = rows ? 0 : lg;
                 T.row_words = rows ? P.row_words : 0;
+                T.grid_mv = mv;
+                T.gs = reinterpret_cast<uint32_t *>(base + off_gs);
                 const int64_t cost = (int64_t)(t1 - t0) * sweep_cost(P, G);
                 if (rows && P.static_d) static_t[serve_class_max(P.static_d)].emplace_back(cost, T);
                 else if (rows) { rows_t.emplace_back(cost, T); lds_rows = std::max(lds_rows, lds); }
+                else if (mv) { grid_t[mv].emplace_back(cost, T); lds_grid[mv] = std::max(lds_grid[mv], lds); }
                 else { bytes_t.emplace_back(cost, T); lds_bytes = std::max(lds_bytes, lds); }
             }
             sl.t = t1;
@@ -365,6 +387,8 @@ int xzzx_server::slice()
     };
     add(rows_t, 0, 0, lds_rows);
     add(bytes_t, 1, 0, lds_bytes);
+    static constexpr int kMoves[] = {8, 4, 2, 1};
+    for (int mv : kMoves) add(grid_t[mv], 3, mv, lds_grid[mv]);
     static constexpr int kClasses[] = {31, 29, 25, 21, 15, 9};
     for (int c : kClasses) add(static_t[c], 2, c, 0);
     if (nt > max_tasks) { set_error("serving task buffer overflow"); return XZZX_ERANGE; }
@@ -372,6 +396,8 @@ int xzzx_server::slice()
         size_t at = 0;
         for (const auto *v : {&rows_t, &bytes_t})
             for (const CostTask &ct : *v) h_tasks[at++] = ct.second;
+        for (int mv : kMoves)
+            for (const CostTask &ct : grid_t[mv]) h_tasks[at++] = ct.second;
         for (int c : kClasses)
             for (const CostTask &ct : static_t[c]) h_tasks[at++] = ct.second;
         rc = check(hipMemcpyAsync(d_stage + st_tasks, h_tasks, nt * sizeof(ServeTask), hipMemcpyHostToDevice, stream),
@@ -415,6 +441,7 @@ int xzzx_server::slice()
             T.cpk = reinterpret_cast<uint32_t *>(base + off_cpk);
             T.cpk_words = cpk_words;
             T.cpm = reinterpret_cast<int32_t *>(base + off_cpm);
+            T.gs = reinterpret_cast<uint32_t *>(base + off_gs);
             T.uid = sl.uid;
             T.n_rep = sl.n_rep;
             T.chain0 = 0;
@@ -544,7 +571,13 @@ int xzzx_server_create(const xzzx_server_cfg *cfg, xzzx_server **out)
     S->cpk_words = dmax * ((2 * (dmax + 1) + 31) / 32);
     S->off_cpk = S->off_cp + align256(2 * 4 * R * nq);
     S->off_cpm = S->off_cpk + align256(2 * 4 * R * (size_t)S->cpk_words * 4);
-    S->slot_bytes = S->off_cpm + align256(4 * R * 4);
+    S->off_gs = S->off_cpm + align256(4 * R * 4);
+    size_t gw = 0;   // the largest grid of a lattice within max_qubits
+    for (int d = 3; d <= kMaxD; d += 2) {
+        if ((size_t)(d * d) <= nq) gw = std::max(gw, (size_t)grid_words_of(XZZX_ROTATED, d));
+        if ((size_t)(d * d + (d - 1) * (d - 1)) <= nq) gw = std::max(gw, (size_t)grid_words_of(XZZX_PLANAR, d));
+    }
+    S->slot_bytes = S->off_gs + align256(4 * R * gw * 4);
     const size_t ns = (size_t)cfg->max_slots;
     S->max_tasks = ns * 4 * R;
     S->st_syn = 0;
