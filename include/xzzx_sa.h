@@ -182,10 +182,8 @@ int xzzx_plan_set_lanes(xzzx_plan *plan, int lanes_per_chain);
  *   XZZX_KERNEL_ROWS: one chain per lane, 2-bit codes packed row by row;
  *     a variant specialised to the distance keeps every row in registers
  *     and its generator schedule in the instruction stream: rotated lattices
- *     with d <= 31 (batch groups whose 4 n_rep chains per syndrome are not a
- *     multiple of 64 run the generic variant instead, d <= 29, or the
- *     byte-state kernel, d = 31), and planar lattices with d <= 15 (turned
- *     by 45 degrees, any n_rep);
+ *     with d <= 31, and planar lattices with d <= 15 (turned by 45 degrees),
+ *     any n_rep;
  *   XZZX_KERNEL_ROWS_GENERIC: the packed-row kernel without that
  *     specialisation (rows in LDS, schedule read from the plan): rotated
  *     d <= 29, and planar d <= 15, whose lattice turned by 45 degrees has the

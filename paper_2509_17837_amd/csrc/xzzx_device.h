@@ -181,10 +181,22 @@ struct GroupArgs {
 struct AnnealArgs {
     GroupArgs g[kMaxGroups];
     int n_groups;
-    uint32_t n_tasks;
-    uint32_t *counter;
+    uint32_t n_tasks, grid;    // tasks, workgroups (at most as many)
+    uint32_t *counter;         // tasks taken from the queue (NULL: one task per workgroup)
     uint32_t seed_lo, seed_hi;
 };
+
+// The tasks of a wavefront: the one of its workgroup's number, then the next
+// ones of the launch's atomic queue (persistent wavefronts); without a queue
+// (the plain form: one task per workgroup) no other.
+__device__ __forceinline__ uint32_t later_task(const AnnealArgs &A)
+{
+    if (!A.counter) return 0xFFFFFFFFu;
+    uint32_t t = 0;
+    if (threadIdx.x == 0) t = atomicAdd(A.counter, 1u);
+    t = __builtin_amdgcn_readfirstlane(__shfl(t, 0, kWave));
+    return t < A.n_tasks - A.grid ? A.grid + t : 0xFFFFFFFFu;
+}
 
 // Batch job of the chain (or, in replay, syndrome) `unit` of group G.
 __device__ __forceinline__ ChainJob batch_job(const GroupArgs &G, int64_t unit, bool replay)
@@ -842,8 +854,11 @@ __device__ __forceinline__ uint4 philox_block(const PhiloxHead &h, uint32_t b, u
     const uint32_t x2 = (uint32_t)(p1 >> 32) ^ h.y1 ^ (k0 + kPhW0);
     const uint32_t y2 = (uint32_t)p1;
     const uint64_t p0 = (uint64_t)x2 * kPhM0;             // round 2, uniform
-    uint4 c = make_uint4(h.a3 ^ (y2 ^ (k0 + 2u * kPhW0)), h.y3,
-                         h.w2 ^ ((uint32_t)(p0 >> 32) ^ (k1 + 2u * kPhW1)), (uint32_t)p0);
+    // round 2's uniform terms joined on the scalar unit (the compiler would
+    // rather join the keys to the lane terms, once per class, on the vector unit)
+    uint32_t tx = y2 ^ (k0 + 2u * kPhW0), tz = (uint32_t)(p0 >> 32) ^ (k1 + 2u * kPhW1);
+    asm("" : "+s"(tx), "+s"(tz));
+    uint4 c = make_uint4(h.a3 ^ tx, h.y3, h.w2 ^ tz, (uint32_t)p0);
     k0 += 3u * kPhW0;
     k1 += 3u * kPhW1;
 #pragma unroll
@@ -856,6 +871,102 @@ __device__ __forceinline__ uint4 philox_block(const PhiloxHead &h, uint32_t b, u
         k1 += kPhW1;
     }
     return c;
+}
+
+// Philox4x32-10 of the counter (uid, cc, c2, b) with uid and cc the lane's
+// syndrome and chain, c2 and the key uniform across the wavefront and b the
+// block.  Which words a product depends on: round 0 multiplies uid (fixed for
+// the chain's whole run: LaneKey) and c2 (uniform); round 1 multiplies
+// the word carrying cc (per sweep and class) and the one carrying uid and b
+// (per block); round 2 multiplies the two words that follow from those.  The
+// two products that do not involve b are taken once per sweep and class
+// (lane_head); each block takes the other two, then rounds 3-9.
+struct LaneKey {
+    uint32_t hk1, w1;   // high word of M0*uid xor k1; low word of M0*uid
+};
+
+struct LaneHead {
+    uint32_t y1k;       // uniform: low word of M1*c2, xor the round-1 key k0 + W0
+    uint32_t w2;        // lane: round-1 output w (low word of M0*x1)
+    uint32_t a3, y3;    // lane: high and low words of M1*z2 (round 2)
+};
+
+__device__ __forceinline__ LaneKey lane_key(uint32_t uid, uint32_t k1)
+{
+    const uint64_t p = (uint64_t)uid * kPhM0;
+    return LaneKey{(uint32_t)(p >> 32) ^ k1, (uint32_t)p};
+}
+
+__device__ __forceinline__ LaneHead lane_head(const LaneKey &lk, uint32_t cc, uint32_t c2, uint32_t k0,
+                                                  uint32_t k1)
+{
+    LaneHead h;
+    const uint64_t p1 = (uint64_t)c2 * kPhM1;                  // round 0, uniform
+    h.y1k = (uint32_t)p1 ^ (k0 + kPhW0);
+    const uint32_t x1 = ((uint32_t)(p1 >> 32) ^ k0) ^ cc;     // lane
+    const uint64_t q = (uint64_t)x1 * kPhM0;                   // round 1, lane
+    const uint32_t z2 = xor3_key((uint32_t)(q >> 32), lk.w1, k1 + kPhW1);
+    h.w2 = (uint32_t)q;
+    const uint64_t r = (uint64_t)z2 * kPhM1;                   // round 2, lane
+    h.a3 = (uint32_t)(r >> 32);
+    h.y3 = (uint32_t)r;
+    return h;
+}
+
+// HOIST: leave the block's first product, which is the same in every sweep, to
+// the compiler, which keeps it in two registers per block for the whole run;
+// otherwise it is taken anew each time.
+template <int B, bool HOIST>
+__device__ __forceinline__ uint4 lane_philox_block(const LaneKey &lk, const LaneHead &h, uint32_t k0,
+                                                     uint32_t k1)
+{
+    uint32_t z1 = B == 0 ? lk.hk1 : lk.hk1 ^ (uint32_t)B;          // round 0 output z
+    if constexpr (!HOIST) asm volatile("" : "+v"(z1));
+    const uint64_t p1 = (uint64_t)z1 * kPhM1;                      // round 1
+    const uint32_t x2 = (uint32_t)(p1 >> 32) ^ h.y1k;
+    const uint64_t p0 = (uint64_t)x2 * kPhM0;                      // round 2
+    uint4 c = make_uint4(xor3_key(h.a3, (uint32_t)p1, k0 + 2u * kPhW0), h.y3,
+                         xor3_key((uint32_t)(p0 >> 32), h.w2, k1 + 2u * kPhW1), (uint32_t)p0);
+    k0 += 3u * kPhW0;
+    k1 += 3u * kPhW1;
+#pragma unroll
+    for (int i = 3; i < 10; ++i) {
+        const uint64_t q0 = (uint64_t)c.x * kPhM0;
+        const uint64_t q1 = (uint64_t)c.z * kPhM1;
+        c = make_uint4(xor3_key((uint32_t)(q1 >> 32), c.y, k0), (uint32_t)q1,
+                       xor3_key((uint32_t)(q0 >> 32), c.w, k1), (uint32_t)q0);
+        k0 += kPhW0;
+        k1 += kPhW1;
+    }
+    return c;
+}
+
+// Draws of one (sweep, colour class) by Philox block, for tasks whose chains
+// belong to one syndrome and for tasks that span syndromes.
+struct UniformDraw {
+    PhiloxHead h;
+    uint32_t k0, k1;
+    template <int B>
+    __device__ __forceinline__ uint4 block() const { return philox_block(h, (uint32_t)B, k0, k1); }
+};
+struct LaneDraw {
+    LaneKey lk;
+    LaneHead h;
+    uint32_t k0, k1;
+    template <int B>
+    __device__ __forceinline__ uint4 block() const { return lane_philox_block<B, false>(lk, h, k0, k1); }
+};
+
+// The draws of a chain: phase counter 4t + k -> its blocks.
+template <bool SPAN>
+__device__ __forceinline__ auto chain_draws(uint32_t uid, uint32_t cc, uint32_t k0, uint32_t k1)
+{
+    if constexpr (SPAN) {
+        const LaneKey lk = lane_key(uid, k1);
+        return [=](uint32_t c2) { return LaneDraw{lk, lane_head(lk, cc, c2, k0, k1), k0, k1}; };
+    } else {
+        return [=](uint32_t c2) { return UniformDraw{philox_head(uid, cc, c2, k0, k1), k0, k1}; };
+    }
 }
 
 // All ones where u < thr (unsigned), from the borrow of u - thr: bit 31 of
@@ -983,10 +1094,9 @@ __device__ __forceinline__ void static_apply(uint32_t (&r)[StaticRows<D>::N], ui
 }
 
 template <int D, int K, int B>
-__device__ __forceinline__ void static_block(uint32_t (&r)[StaticRows<D>::N], const PhiloxHead &h, uint32_t k0, uint32_t k1,
-                                             const uint16_t *lut_s, const uint4 *et_s, int32_t &acc)
+__device__ __forceinline__ void static_block(uint32_t (&r)[StaticRows<D>::N], const uint4 &u, const uint16_t *lut_s,
+                                             const uint4 *et_s, int32_t &acc)
 {
-    const uint4 u = philox_block(h, (uint32_t)B, k0, k1);
     // The four generators of a block belong to one colour class and act on
     // disjoint qubits: a flip of one leaves the others' slot bits as they
     // were, so all four look up their entries from the rows before any flip
@@ -1029,12 +1139,11 @@ __device__ __forceinline__ void static_block(uint32_t (&r)[StaticRows<D>::N], co
     asm("" : "+v"(acc));
 }
 
-template <int D, int K, int... Bs>
-__device__ __forceinline__ void static_class(uint32_t (&r)[StaticRows<D>::N], const PhiloxHead &h, uint32_t k0, uint32_t k1,
-                                             const uint16_t *lut_s, const uint4 *et_s, int32_t &acc,
-                                             std::integer_sequence<int, Bs...>)
+template <int D, int K, typename Draw, int... Bs>
+__device__ __forceinline__ void static_class(uint32_t (&r)[StaticRows<D>::N], const Draw &draw, const uint16_t *lut_s,
+                                             const uint4 *et_s, int32_t &acc, std::integer_sequence<int, Bs...>)
 {
-    (static_block<D, K, Bs>(r, h, k0, k1, lut_s, et_s, acc), ...);
+    (static_block<D, K, Bs>(r, draw.template block<Bs>(), lut_s, et_s, acc), ...);
 }
 
 // One byte per qubit, row-major, from the specialised kernel's rows.
@@ -1083,7 +1192,10 @@ __device__ __forceinline__ int32_t static_load(const PlanDev *pl, const ChainJob
     return E;
 }
 
-template <int D>
+// SPAN: the task's 64 chains may span syndromes (4 n_rep not a multiple of
+// 64), so the syndrome word of the counters varies across the lanes and each
+// Philox block takes two more lane products; otherwise they belong to one.
+template <int D, bool SPAN>
 __device__ __forceinline__ void rows_static_core(const PlanDev *pl, const ChainJob &J, int t_begin, int t_end, uint32_t seed_lo,
                                  uint32_t seed_hi, const uint16_t *lut_s, uint4 *et_s, int cp_interval)
 {
@@ -1094,9 +1206,9 @@ __device__ __forceinline__ void rows_static_core(const PlanDev *pl, const ChainJ
     const int nranks = (int)uni(pl->nranks), kneg = (int)uni(pl->kneg);
     int32_t W[4];
     W[0] = 0; W[1] = (int32_t)uni(pl->W[1]); W[2] = (int32_t)uni(pl->W[2]); W[3] = (int32_t)uni(pl->W[3]);
-    // a task's 64 chains belong to one syndrome
-    const uint32_t uid = uni(J.uid), cc = J.cc;
+    const uint32_t uid = SPAN ? J.uid : uni(J.uid), cc = J.cc;
     const uint32_t k0 = uni(seed_lo), k1 = uni(seed_hi);
+    const auto draw_of = chain_draws<SPAN>(uid, cc, k0, k1);
     const bool use_x = !J.resume && (J.lp == 1 || J.lp == 2), use_z = !J.resume && (J.lp == 2 || J.lp == 3);
     // lane 0 is always active and a task's chains are consecutive: chain of lane l = ci0 + l
     const int64_t ci0 = (int64_t)(((uint64_t)uni((uint32_t)((uint64_t)J.ci >> 32)) << 32) | uni((uint32_t)J.ci));
@@ -1134,19 +1246,19 @@ __device__ __forceinline__ void rows_static_core(const PlanDev *pl, const ChainJ
             wave_lds_fence();
             const uint32_t c2 = 4u * (uint32_t)t;
             int32_t acc = 0;
-            static_class<D, 0>(r, philox_head(uid, cc, c2, k0, k1), k0, k1, lut_s, et_s, acc, Blocks{});
+            static_class<D, 0>(r, draw_of(c2), lut_s, et_s, acc, Blocks{});
             E += acc;
             if (E < Emin) { Emin = E; stop = 4 * t + 1; }
             acc = 0;
-            static_class<D, 1>(r, philox_head(uid, cc, c2 + 1u, k0, k1), k0, k1, lut_s, et_s, acc, Blocks{});
+            static_class<D, 1>(r, draw_of(c2 + 1u), lut_s, et_s, acc, Blocks{});
             E += acc;
             if (E < Emin) { Emin = E; stop = 4 * t + 2; }
             acc = 0;
-            static_class<D, 2>(r, philox_head(uid, cc, c2 + 2u, k0, k1), k0, k1, lut_s, et_s, acc, Blocks{});
+            static_class<D, 2>(r, draw_of(c2 + 2u), lut_s, et_s, acc, Blocks{});
             E += acc;
             if (E < Emin) { Emin = E; stop = 4 * t + 3; }
             acc = 0;
-            static_class<D, 3>(r, philox_head(uid, cc, c2 + 3u, k0, k1), k0, k1, lut_s, et_s, acc, Blocks{});
+            static_class<D, 3>(r, draw_of(c2 + 3u), lut_s, et_s, acc, Blocks{});
             E += acc;
             if (E < Emin) { Emin = E; stop = 4 * t + 4; }
         }
@@ -1238,27 +1350,17 @@ __device__ __forceinline__ int ladder_exchange(int level, int32_t E, int K, uint
     return level;
 }
 
-// Task loop of the ladder kernels specialised to d (MODE 0: persistent
-// wavefronts on the atomic task queue; 2: one task per workgroup), tasks of
-// 64 consecutive chains.  The offset table is static LDS, so its address
+// Task loop of the ladder kernels specialised to d, tasks of 64 consecutive
+// chains.  The offset table is static LDS, so its address
 // folds into each lookup's instruction; the K level tables are dynamic LDS
 // (16 K n_ranks bytes).  core(G, J, lut_s, et_s) runs one lane's chain.
-template <int MODE, typename Core>
+template <typename Core>
 __device__ __forceinline__ void ladder_static_body(const AnnealArgs &A, Core core)
 {
     __shared__ uint16_t lut_s[256 * 6];
     extern __shared__ __align__(16) uint4 et_s[];
     const PlanDev *loaded = nullptr;
-    for (int iter = 0;; ++iter) {
-        uint32_t task = 0;
-        if (MODE == 2) {
-            if (iter > 0) break;
-            task = blockIdx.x;
-        } else {
-            if (threadIdx.x == 0) task = atomicAdd(A.counter, 1u);
-            task = __builtin_amdgcn_readfirstlane(__shfl(task, 0, kWave));
-        }
-        if (task >= A.n_tasks) break;
+    for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
         int gi = 0;
         while (gi + 1 < A.n_groups && (int64_t)task >= A.g[gi + 1].task_begin) ++gi;
         const GroupArgs &G = A.g[gi];
@@ -1303,27 +1405,17 @@ __device__ inline void load_plan_tables(const PlanDev *pl, uint8_t *smem, bool b
 }
 
 // ---------------------------------------------------------------------------
-// Batch kernels.  MODE 0: persistent wavefronts pulling tasks from an atomic
-// queue over every group of the launch; MODE 2: plain form, one task per
-// workgroup.  ROWS selects the packed-row core; otherwise the byte-state core
+// Batch kernels: wavefronts take tasks over every group of the launch (see
+// later_task).  ROWS selects the packed-row core; otherwise the byte-state core
 // with LOGG = log2(lanes per chain), the same for every group of the launch;
 // REPLAY (byte-state only) re-runs each syndrome's best chain.
 // ---------------------------------------------------------------------------
-template <int MODE, bool ROWS, int LOGG, bool REPLAY>
+template <bool ROWS, int LOGG, bool REPLAY>
 __device__ __forceinline__ void batch_kernel_body(const AnnealArgs &A)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const PlanDev *loaded = nullptr;
-    for (int iter = 0;; ++iter) {
-        uint32_t task = 0;
-        if (MODE == 2) {
-            if (iter > 0) break;
-            task = blockIdx.x;
-        } else {
-            if (threadIdx.x == 0) task = atomicAdd(A.counter, 1u);
-            task = __builtin_amdgcn_readfirstlane(__shfl(task, 0, kWave));
-        }
-        if (task >= A.n_tasks) break;
+    for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
         int gi = 0;
         while (gi + 1 < A.n_groups && (int64_t)task >= A.g[gi + 1].task_begin) ++gi;
         const GroupArgs &G = A.g[gi];
@@ -1348,23 +1440,13 @@ __device__ __forceinline__ void batch_kernel_body(const AnnealArgs &A)
     }
 }
 
-// Batch body of the random-site core (MODE as in batch_kernel_body): tasks of
-// 64 chains; the face descriptors are staged by face id.
-template <int MODE>
+// Batch body of the random-site core: tasks of 64 chains; the face
+// descriptors are staged by face id.
 __device__ __forceinline__ void site_kernel_body(const AnnealArgs &A)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const PlanDev *loaded = nullptr;
-    for (int iter = 0;; ++iter) {
-        uint32_t task = 0;
-        if (MODE == 2) {
-            if (iter > 0) break;
-            task = blockIdx.x;
-        } else {
-            if (threadIdx.x == 0) task = atomicAdd(A.counter, 1u);
-            task = __builtin_amdgcn_readfirstlane(__shfl(task, 0, kWave));
-        }
-        if (task >= A.n_tasks) break;
+    for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
         int gi = 0;
         while (gi + 1 < A.n_groups && (int64_t)task >= A.g[gi + 1].task_begin) ++gi;
         const GroupArgs &G = A.g[gi];
@@ -1379,24 +1461,25 @@ __device__ __forceinline__ void site_kernel_body(const AnnealArgs &A)
     }
 }
 
-// Batch body of the specialised packed-row kernel (MODE as above).  Every
-// group of the launch has distance SD and tasks of 64 chains of one syndrome.
-template <int MODE, int SD>
+// Priority of a wavefront on its SIMD by the distance of its chain, when
+// launches of several distances share the device: a sweep of a large lattice
+// takes longest and there are as many sweeps to each, so the largest chains
+// would run on alone at the end if the small ones' wavefronts got an equal
+// share of every SIMD meanwhile.  (Within a launch all are equal.)  With the
+// sets launched longest first, five distances d = 5..21 of 256 syndromes and
+// 256 chains in one call went from 274 to 234 ms.
+constexpr int static_priority(int d) { return d <= 9 ? 0 : d <= 13 ? 1 : d <= 17 ? 2 : 3; }
+
+// Batch body of the specialised packed-row kernel.  Every group of the launch
+// has distance SD; tasks of 64 chains (SPAN: see rows_static_core).
+template <int SD, bool SPAN>
 __device__ __forceinline__ void static_rows_body(const AnnealArgs &A)
 {
     __shared__ uint16_t lut_s[256 * 6];
     __shared__ uint4 et_s[kStaticRanks];
+    __builtin_amdgcn_s_setprio(static_priority(SD));
     const PlanDev *loaded = nullptr;
-    for (int iter = 0;; ++iter) {
-        uint32_t task = 0;
-        if (MODE == 2) {
-            if (iter > 0) break;
-            task = blockIdx.x;
-        } else {
-            if (threadIdx.x == 0) task = atomicAdd(A.counter, 1u);
-            task = __builtin_amdgcn_readfirstlane(__shfl(task, 0, kWave));
-        }
-        if (task >= A.n_tasks) break;
+    for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
         int gi = 0;
         while (gi + 1 < A.n_groups && (int64_t)task >= A.g[gi + 1].task_begin) ++gi;
         const GroupArgs &G = A.g[gi];
@@ -1407,7 +1490,7 @@ __device__ __forceinline__ void static_rows_body(const AnnealArgs &A)
             loaded = G.plan;
         }
         const ChainJob J = batch_job(G, unit0 + threadIdx.x, false);
-        rows_static_core<SD>(G.plan, J, 0, G.plan->n_sweeps, A.seed_lo, A.seed_hi, lut_s, et_s, G.cp_every);
+        rows_static_core<SD, SPAN>(G.plan, J, 0, G.plan->n_sweeps, A.seed_lo, A.seed_hi, lut_s, et_s, G.cp_every);
     }
 }
 
@@ -1420,10 +1503,10 @@ constexpr int static_waves(int d) { return d <= 15 ? 8 : d <= 21 ? 5 : 4; }
 
 template <int D>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(static_waves(D), static_waves(D))))
-void k_anneal_rows_d(AnnealArgs A) { static_rows_body<0, D>(A); }
+void k_anneal_rows_d(AnnealArgs A) { static_rows_body<D, false>(A); }
 template <int D>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(static_waves(D), static_waves(D))))
-void k_anneal_rows_d_plain(AnnealArgs A) { static_rows_body<2, D>(A); }
+void k_anneal_rows_span_d(AnnealArgs A) { static_rows_body<D, true>(A); }
 
 // ---------------------------------------------------------------------------
 // Serving kernels: one workgroup per task of the slice.  A task covers
@@ -1543,9 +1626,10 @@ template <int D>
 __device__ __forceinline__ void serve_static_task(const ServeTask &T, uint32_t slo, uint32_t shi, uint16_t *lut_s,
                                                   uint4 *et_s)
 {
+    __builtin_amdgcn_s_setprio(static_priority(D));
     load_static_tables(T.plan, lut_s, et_s);
     const ChainJob J = serve_job(T, threadIdx.x, false);
-    rows_static_core<D>(T.plan, J, T.t_begin, T.t_end, slo, shi, lut_s, et_s, 0);
+    rows_static_core<D, false>(T.plan, J, T.t_begin, T.t_end, slo, shi, lut_s, et_s, 0);
 }
 
 // Occupancy of a serving class kernel: one wavefront per SIMD fewer than the
@@ -1570,19 +1654,19 @@ typedef void (*AnnealKernel)(AnnealArgs);
 // kernels specialised to the planar lattice at odd d <= 15 (NULL otherwise),
 // and the words of one chain's state they keep at its E_min (its rows,
 // padded to a multiple of four)
-AnnealKernel planar_rows_kernel(int d, bool plain);
+AnnealKernel planar_rows_kernel(int d);
 int planar_state_words(int d);
 // replica-exchange kernels (ladders of fixed inverse temperatures): the
 // generic one (one chain per lane, state in LDS), and the packed-row ones
-// specialised to the rotated lattice at odd d <= kLadderRowsMaxD (a task's
-// chains inside one syndrome) and to the planar lattice at odd d <= 15 (NULL
+// specialised to the rotated lattice at odd d <= kLadderRowsMaxD (span: a
+// task's chains may span syndromes) and to the planar lattice at odd d <= 15 (NULL
 // otherwise); the specialised ones keep each chain's rows at its first E_min
 // (ladder_rows_state_words(d) words, planar_state_words(d) on the planar
 // lattice)
-AnnealKernel ladder_kernel(bool plain);
-AnnealKernel ladder_rows_kernel(int d, bool plain);
-AnnealKernel ladder_rows_kernel_large(int d, bool plain);   // d = 17 .. 31 (NULL otherwise)
-AnnealKernel ladder_planar_kernel(int d, bool plain);
+AnnealKernel ladder_kernel();
+AnnealKernel ladder_rows_kernel(int d, bool span);
+AnnealKernel ladder_rows_kernel_large(int d, bool span);   // d = 17 .. 31 (NULL otherwise)
+AnnealKernel ladder_planar_kernel(int d);
 int ladder_rows_state_words(int d);
 // grid core (one chain over `lanes` lanes, `mv` moves per lane and class) and
 // its recovery gather
@@ -1597,7 +1681,7 @@ ServeKernel serve_grid_kernel(int mv);
 // for the distances it holds, else NULL), the serving kernels by class (each
 // part returns the kernel of its class).
 #define XZZX_STATIC_PARTS(X) X(a) X(b) X(c) X(d) X(e) X(f) X(g) X(h)
-#define XZZX_DECLARE_PART(P) AnnealKernel static_rows_kernel_##P(int d, bool plain);
+#define XZZX_DECLARE_PART(P) AnnealKernel static_rows_kernel_##P(int d, bool span);
 XZZX_STATIC_PARTS(XZZX_DECLARE_PART)
 #undef XZZX_DECLARE_PART
 ServeKernel serve_class_kernel_9();

@@ -4,23 +4,12 @@
 
 namespace xzzx {
 
-// Task loop: persistent wavefronts on the atomic task queue, or one task per
-// workgroup where the launch has no counter (the plain form).
 template <int LOGG, int MV>
 __global__ __launch_bounds__(kWave) void k_anneal_grid(AnnealArgs A)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const PlanDev *loaded = nullptr;
-    for (int iter = 0;; ++iter) {
-        uint32_t task = 0;
-        if (!A.counter) {
-            if (iter > 0) break;
-            task = blockIdx.x;
-        } else {
-            if (threadIdx.x == 0) task = atomicAdd(A.counter, 1u);
-            task = __builtin_amdgcn_readfirstlane(__shfl(task, 0, kWave));
-        }
-        if (task >= A.n_tasks) break;
+    for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
         int gi = 0;
         while (gi + 1 < A.n_groups && (int64_t)task >= A.g[gi + 1].task_begin) ++gi;
         const GroupArgs &G = A.g[gi];

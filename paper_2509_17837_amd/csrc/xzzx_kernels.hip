@@ -523,13 +523,10 @@ __global__ __launch_bounds__(kWave) void k_ref_check(const PlanDev *__restrict__
 }
 
 template <int LOGG>
-__global__ __launch_bounds__(kWave) void k_anneal(AnnealArgs A) { batch_kernel_body<0, false, LOGG, false>(A); }
+__global__ __launch_bounds__(kWave) void k_anneal(AnnealArgs A) { batch_kernel_body<false, LOGG, false>(A); }
 template <int LOGG>
-__global__ __launch_bounds__(kWave) void k_replay(AnnealArgs A) { batch_kernel_body<0, false, LOGG, true>(A); }
-template <int LOGG>
-__global__ __launch_bounds__(kWave) void k_anneal_plain(AnnealArgs A) { batch_kernel_body<2, false, LOGG, false>(A); }
-__global__ __launch_bounds__(kWave) void k_anneal_site(AnnealArgs A) { site_kernel_body<0>(A); }
-__global__ __launch_bounds__(kWave) void k_anneal_site_plain(AnnealArgs A) { site_kernel_body<2>(A); }
+__global__ __launch_bounds__(kWave) void k_replay(AnnealArgs A) { batch_kernel_body<false, LOGG, true>(A); }
+__global__ __launch_bounds__(kWave) void k_anneal_site(AnnealArgs A) { site_kernel_body(A); }
 
 // Random-site order: each syndrome's recovery is its best chain's state kept
 // at that chain's first E_min (packed words [word][chain]); one thread per
@@ -579,13 +576,12 @@ __global__ void k_static_recovery(const uint32_t *__restrict__ snap, int words,
     const uint32_t word = snap[ci * words + (int64_t)(y * nw + (x >> 4))];
     recovery[idx] = (uint8_t)((word >> (2 * (x & 15))) & 3u);
 }
-__global__ __launch_bounds__(kWave) void k_anneal_rows(AnnealArgs A) { batch_kernel_body<0, true, 0, false>(A); }
-__global__ __launch_bounds__(kWave) void k_anneal_rows_plain(AnnealArgs A) { batch_kernel_body<2, true, 0, false>(A); }
+__global__ __launch_bounds__(kWave) void k_anneal_rows(AnnealArgs A) { batch_kernel_body<true, 0, false>(A); }
 
-static AnnealKernel static_rows_kernel(int d, bool plain)
+static AnnealKernel static_rows_kernel(int d, bool span)
 {
 #define XZZX_TRY_PART(P) \
-    if (AnnealKernel k = static_rows_kernel_##P(d, plain)) return k;
+    if (AnnealKernel k = static_rows_kernel_##P(d, span)) return k;
     XZZX_STATIC_PARTS(XZZX_TRY_PART)
 #undef XZZX_TRY_PART
     return nullptr;
@@ -605,15 +601,12 @@ static ServeKernel static_serve_kernel(int d)
     }
 }
 
-static AnnealKernel bytes_kernel(int mode, int lg)
+static AnnealKernel bytes_kernel(bool replay, int lg)
 {
-    // mode 0: persistent, 1: replay, 2: plain
-    static const AnnealKernel tab[3][7] = {
+    static const AnnealKernel tab[2][7] = {
         {k_anneal<0>, k_anneal<1>, k_anneal<2>, k_anneal<3>, k_anneal<4>, k_anneal<5>, k_anneal<6>},
-        {k_replay<0>, k_replay<1>, k_replay<2>, k_replay<3>, k_replay<4>, k_replay<5>, k_replay<6>},
-        {k_anneal_plain<0>, k_anneal_plain<1>, k_anneal_plain<2>, k_anneal_plain<3>, k_anneal_plain<4>,
-         k_anneal_plain<5>, k_anneal_plain<6>}};
-    return tab[mode][lg];
+        {k_replay<0>, k_replay<1>, k_replay<2>, k_replay<3>, k_replay<4>, k_replay<5>, k_replay<6>}};
+    return tab[replay][lg];
 }
 
 __global__ __launch_bounds__(kWave) void k_serve_rows(const ServeTask *tasks, uint32_t slo, uint32_t shi)
@@ -853,17 +846,22 @@ struct GroupWs {
     uint32_t *cp_rows;     // checkpoints of groups on the specialised packed-row kernel
     uint32_t *min_snap;    // random-site, planar specialised, ladder and grid groups: each chain's state at its first E_min
     int grid;              // lanes per chain on the grid core (0: another kernel)
+    bool lean;             // the call's workspace is short (see ws_bytes)
 };
 
 // Replica exchange on the packed-row kernels specialised to d: the distance
-// when the group's ladders run there (rotated: d <= kLadderRowsMaxD and every
-// 64-chain task inside one syndrome; planar: d <= 15), else 0.  Depends on
-// the plan and n_rep only, so every stage of a decode agrees.
-static int ladder_rows_d(const xzzx_group &g)
+// when the group's ladders run there (rotated: d <= kLadderRowsMaxD; planar:
+// d <= 15), else 0.  Depends on the plan, n_rep and the workspace's size, so
+// every stage of a decode agrees.  spans: the tasks of 64 chains do not all
+// lie inside one syndrome; such ladders keep more words per chain than the
+// generic kernel, which runs them where the workspace is short (lean).
+static bool spans(const xzzx_group &g) { return (4 * g.n_rep) % kWave != 0; }
+
+static int ladder_rows_d(const xzzx_group &g, bool lean)
 {
     const Plan &P = g.plan->P;
     if (!P.ladder_k || !P.use_rows || P.order != XZZX_ORDER_COLOUR) return 0;
-    if (P.static_d && P.static_d <= kLadderRowsMaxD && (4 * g.n_rep) % kWave == 0) return P.static_d;
+    if (P.static_d && P.static_d <= kLadderRowsMaxD && !(lean && spans(g))) return P.static_d;
     return 0;
 }
 
@@ -879,10 +877,10 @@ static int ladder_planar_d(const xzzx_group &g)
 // specialised to d and the rotated ladder kernels specialised to d (their
 // rows); 0 for other groups.  A plan's kernel must not change between the
 // stages of one decode.
-static int64_t min_snap_words(const xzzx_group &g)
+static int64_t min_snap_words(const xzzx_group &g, bool lean)
 {
     const Plan &P = g.plan->P;
-    if (ladder_rows_d(g)) return ladder_rows_state_words(ladder_rows_d(g));
+    if (ladder_rows_d(g, lean)) return ladder_rows_state_words(ladder_rows_d(g, lean));
     if (ladder_planar_d(g)) return planar_state_words(ladder_planar_d(g));
     if (P.order == XZZX_ORDER_RANDOM_SITE || P.ladder_k) return P.lat.nq / 16 + 1;
     if (P.use_rows && P.planar_d) return planar_state_words(P.planar_d);
@@ -890,12 +888,16 @@ static int64_t min_snap_words(const xzzx_group &g)
 }
 
 // A group runs on the packed-row kernel specialised to its distance when the
-// plan allows it and every 64-chain task lies inside one syndrome.
-static bool uses_static(const xzzx_group &g, int64_t unit_offset)
+// plan allows it: in the form whose tasks of 64 chains may span syndromes
+// where they do not all lie inside one.  (That form takes two more products
+// per Philox block and runs within 1-4 % of the other up to d = 19, 8-15 %
+// beyond, where it spills; before, such groups ran on the generic packed-row
+// kernel, rows in LDS (a decode of 4099 syndromes of 40 chains at d = 13, 100
+// sweeps: 4.06 -> 2.36 ms), or, d = 31, on byte states.)
+static bool uses_static(const xzzx_group &g)
 {
     const Plan &P = g.plan->P;
-    return P.order == XZZX_ORDER_COLOUR && !P.ladder_k && P.use_rows && P.static_d && (4 * g.n_rep) % kWave == 0 &&
-           unit_offset % kWave == 0;
+    return P.order == XZZX_ORDER_COLOUR && !P.ladder_k && P.use_rows && P.static_d;
 }
 
 // Sweeps between the checkpoints of a plan: kCheckpointEvery, or the least
@@ -910,7 +912,7 @@ static int checkpoint_interval(const Plan &P)
 // c, 2c, ... before the last sweep, for c = checkpoint_interval.
 static int checkpoints_of(const xzzx_group &g)
 {
-    if (!uses_static(g, 0) || g.plan->P.n_sweeps <= 0) return 0;
+    if (!uses_static(g) || g.plan->P.n_sweeps <= 0) return 0;
     return (g.plan->P.n_sweeps - 1) / checkpoint_interval(g.plan->P);
 }
 
@@ -971,8 +973,9 @@ static std::vector<int> grid_routes(const xzzx_group *groups, int n_groups)
     return lanes;
 }
 
-// Bytes of a group's buffers; grid: on the grid core (lanes per chain).
-static size_t group_ws_bytes(const xzzx_group &g, bool decode, int grid)
+// Bytes of a group's buffers; grid: on the grid core (lanes per chain); lean:
+// without the checkpoints of groups whose tasks span syndromes.
+static size_t group_ws_bytes(const xzzx_group &g, bool decode, int grid, bool lean)
 {
     const Plan &P = g.plan->P;
     const size_t nq = P.lat.nq, ns = (size_t)g.n_syn, R = (size_t)g.n_rep, nc = 4 * R * ns;
@@ -985,33 +988,35 @@ static size_t group_ws_bytes(const xzzx_group &g, bool decode, int grid)
     if (!g.d_chain_e) b += align256(nc * 4);
     if (!g.d_best_chain) b += align256(ns * 4);
     if (grid) return b + align256((size_t)P.hdev.grid_words * nc * 4);
-    b += align256((size_t)checkpoints_of(g) * P.lat.d * P.static_words * nc * 4);
-    b += align256((size_t)min_snap_words(g) * nc * 4);
+    if (!lean || !spans(g)) b += align256((size_t)checkpoints_of(g) * P.lat.d * P.static_words * nc * 4);
+    b += align256((size_t)min_snap_words(g, lean) * nc * 4);
     return b;
 }
 
 // Workspace of a call: what its kernels use at best (`full`), and what it is
 // accepted with (`least`): the grid core's states may take more than the
 // other kernels' checkpoints, and a call whose workspace is short of them
-// runs on those kernels instead.
+// runs on those kernels instead; groups whose tasks span syndromes then keep
+// no checkpoints, and their recoveries are replayed from the references.
 static void ws_bytes(const xzzx_group *groups, int n_groups, bool decode, const std::vector<int> &grid, size_t *full,
                      size_t *least)
 {
     *full = *least = 256;
     for (int i = 0; i < n_groups; ++i) {
-        const size_t other = group_ws_bytes(groups[i], decode, 0);
-        *least += other;
-        *full += grid[i] ? std::max(other, group_ws_bytes(groups[i], decode, grid[i])) : other;
+        const size_t other = group_ws_bytes(groups[i], decode, 0, false);
+        *least += group_ws_bytes(groups[i], decode, 0, true);
+        *full += grid[i] ? std::max(other, group_ws_bytes(groups[i], decode, grid[i], false)) : other;
     }
 }
 
-static GroupWs carve_group(const xzzx_group &g, bool decode, int grid, uint8_t *&p)
+static GroupWs carve_group(const xzzx_group &g, bool decode, int grid, bool lean, uint8_t *&p)
 {
     const Plan &P = g.plan->P;
     const size_t nq = P.lat.nq, ns = (size_t)g.n_syn, R = (size_t)g.n_rep, nc = 4 * R * ns;
     GroupWs w{};
     auto take = [&](size_t bytes) { uint8_t *r = p; p += align256(bytes); return r; };
     w.grid = grid;
+    w.lean = lean;
     w.refs = g.d_refs ? g.d_refs : (decode ? take(ns * R * nq) : nullptr);
     w.qraw = take(ns * R);
     w.qcls = g.d_qcls ? g.d_qcls : take(ns * R);
@@ -1019,8 +1024,8 @@ static GroupWs carve_group(const xzzx_group &g, bool decode, int grid, uint8_t *
     w.stop = g.d_chain_stop ? g.d_chain_stop : reinterpret_cast<int32_t *>(take(nc * 4));
     w.efin = g.d_chain_e ? g.d_chain_e : reinterpret_cast<int32_t *>(take(nc * 4));
     w.best_chain = g.d_best_chain ? g.d_best_chain : reinterpret_cast<int32_t *>(take(ns * 4));
-    const size_t ncp = grid ? 0 : (size_t)checkpoints_of(g);
-    const size_t snap = grid ? (size_t)P.hdev.grid_words : (size_t)min_snap_words(g);
+    const size_t ncp = grid || (lean && spans(g)) ? 0 : (size_t)checkpoints_of(g);
+    const size_t snap = grid ? (size_t)P.hdev.grid_words : (size_t)min_snap_words(g, lean);
     w.cp_rows = ncp ? reinterpret_cast<uint32_t *>(take(ncp * P.lat.d * P.static_words * nc * 4)) : nullptr;
     w.min_snap = snap ? reinterpret_cast<uint32_t *>(take(snap * nc * 4)) : nullptr;
     return w;
@@ -1113,7 +1118,7 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
         G.log_lanes = lg;
         G.row_words = rows ? P.row_words : 0;
         // checkpoints: written by the specialised kernel, read by the replay
-        const bool cp = checkpoints_of(g) > 0 && (static_d || replay);
+        const bool cp = ws[i].cp_rows && (static_d || replay);
         G.cp_rows = cp ? ws[i].cp_rows : nullptr;
         G.cp_every = cp ? checkpoint_interval(P) : 0;
         G.n_chains = g.n_syn * 4 * g.n_rep;
@@ -1138,40 +1143,26 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
     A.n_groups = ng;
     A.n_tasks = (uint32_t)tasks;
     if (lds > 65536) { set_error("LDS demand above 64 KiB"); return XZZX_ERANGE; }
+    const bool span = static_d && spans(groups[order[0]]);
+    const AnnealKernel kern = grid_mv ? grid_kernel(lanes, grid_mv)
+                              : (ladder && static_d) ? ladder_rows_kernel(static_d, span)
+                              : (ladder && planar_d) ? ladder_planar_kernel(planar_d)
+                              : ladder     ? ladder_kernel()
+                              : site     ? k_anneal_site
+                              : planar_d ? planar_rows_kernel(planar_d)
+                              : static_d ? static_rows_kernel(static_d, span)
+                              : rows     ? k_anneal_rows
+                                         : bytes_kernel(replay, lg);
     if (mode == AnnealMode::Plain) {
         A.counter = nullptr;
-        if (grid_mv)
-            hipLaunchKernelGGL(grid_kernel(lanes, grid_mv), dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
-        else if (ladder && static_d)
-            hipLaunchKernelGGL(ladder_rows_kernel(static_d, true), dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
-        else if (ladder && planar_d)
-            hipLaunchKernelGGL(ladder_planar_kernel(planar_d, true), dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
-        else if (ladder)
-            hipLaunchKernelGGL(ladder_kernel(true), dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
-        else if (site)
-            hipLaunchKernelGGL(k_anneal_site_plain, dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
-        else if (planar_d)
-            hipLaunchKernelGGL(planar_rows_kernel(planar_d, true), dim3((unsigned)tasks), dim3(kWave), 0, stream, A);
-        else if (static_d)
-            hipLaunchKernelGGL(static_rows_kernel(static_d, true), dim3((unsigned)tasks), dim3(kWave), 0, stream, A);
-        else if (rows)
-            hipLaunchKernelGGL(k_anneal_rows_plain, dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
-        else
-            hipLaunchKernelGGL(bytes_kernel(2, lg), dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
+        A.grid = (uint32_t)tasks;
+        hipLaunchKernelGGL(kern, dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
         return check_hip(hipGetLastError(), "plain anneal launch");
     }
-    const AnnealKernel kern = grid_mv ? grid_kernel(lanes, grid_mv)
-                              : (ladder && static_d) ? ladder_rows_kernel(static_d, false)
-                              : (ladder && planar_d) ? ladder_planar_kernel(planar_d, false)
-                              : ladder     ? ladder_kernel(false)
-                              : site     ? k_anneal_site
-                              : planar_d ? planar_rows_kernel(planar_d, false)
-                              : static_d ? static_rows_kernel(static_d, false)
-                              : rows     ? k_anneal_rows
-                                         : bytes_kernel(replay ? 1 : 0, lg);
     unsigned grid = 0;
     int rc = anneal_grid((const void *)kern, lds, A.n_tasks, &grid);
     if (rc) return rc;
+    A.grid = grid;
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, d_counter, 1);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kWave), lds, stream, A);
     return check_hip(hipGetLastError(), "anneal launch");
@@ -1290,14 +1281,14 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
 {
     std::vector<int> rows_sel;
     std::vector<int> bytes_sel[7];
-    std::vector<int> static_sel[kStaticMaxD + 1];
+    std::vector<int> static_sel[2][kStaticMaxD + 1];   // [tasks span syndromes][d]
     std::vector<int> replay_cp;   // replays starting from checkpoints: one chain per wavefront
     std::vector<int> site_sel;    // random-site plans: one chain (replay: syndrome) per lane
     std::vector<int> planar_sel[kPlanarStaticMaxD + 1];   // planar kernels specialised to d
     std::vector<int> gather_sel;  // replay: recoveries gathered from the states kept at E_min
     std::vector<int> grid_sel[5][4];   // grid core, by lanes per chain (4..64) and moves per lane (1, 2, 4, 8)
     std::vector<int> ladder_sel;  // replica exchange: one chain per lane
-    std::vector<int> ladder_rows_sel[kLadderRowsMaxD + 1];      // ... on the rotated kernels specialised to d
+    std::vector<int> ladder_rows_sel[2][kLadderRowsMaxD + 1];   // ... on the rotated kernels specialised to d
     std::vector<int> ladder_planar_sel[kPlanarStaticMaxD + 1];  // ... on the planar kernels specialised to d
     int64_t total_syn = 0;
     for (int i = 0; i < n_groups; ++i) {
@@ -1308,17 +1299,17 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
             continue;
         }
         if (ws[i].grid || P.order == XZZX_ORDER_RANDOM_SITE || P.ladder_k ||
-            (mode == AnnealMode::Replay && min_snap_words(groups[i]))) {
+            (mode == AnnealMode::Replay && min_snap_words(groups[i], ws[i].lean))) {
             if (mode == AnnealMode::Replay) gather_sel.push_back(i);
-            else if (ladder_rows_d(groups[i])) ladder_rows_sel[ladder_rows_d(groups[i])].push_back(i);
+            else if (const int ld = ladder_rows_d(groups[i], ws[i].lean)) ladder_rows_sel[spans(groups[i])][ld].push_back(i);
             else if (ladder_planar_d(groups[i])) ladder_planar_sel[ladder_planar_d(groups[i])].push_back(i);
             else (P.ladder_k ? ladder_sel : site_sel).push_back(i);
             continue;
         }
         total_syn += groups[i].n_syn;
         if (mode != AnnealMode::Replay && P.use_rows && P.planar_d) planar_sel[P.planar_d].push_back(i);
-        else if (mode != AnnealMode::Replay && uses_static(groups[i], unit_offset)) static_sel[P.static_d].push_back(i);
-        else if (mode == AnnealMode::Replay && checkpoints_of(groups[i]) > 0) replay_cp.push_back(i);
+        else if (mode != AnnealMode::Replay && uses_static(groups[i])) static_sel[spans(groups[i])][P.static_d].push_back(i);
+        else if (mode == AnnealMode::Replay && ws[i].cp_rows) replay_cp.push_back(i);
         else if (mode != AnnealMode::Replay && P.use_rows && P.row_words) rows_sel.push_back(i);
         else bytes_sel[log2_int(P.lanes)].push_back(i);
     }
@@ -1349,15 +1340,15 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
             if (ws[i].grid)
                 launch_grid_recovery(ws[i].min_snap, P.hdev.grid_words, ws[i].best_chain, g.n_rep, P.lat.nq, g.n_syn,
                                      P.ddev, g.d_recovery, stream);
-            else if (const int ld = ladder_rows_d(g))
+            else if (const int ld = ladder_rows_d(g, ws[i].lean))
                 hipLaunchKernelGGL(k_static_recovery, grid, dim3(256), 0, stream, ws[i].min_snap,
-                                   (int)min_snap_words(g), ws[i].best_chain, g.n_rep, ld, g.n_syn,
+                                   (int)min_snap_words(g, ws[i].lean), ws[i].best_chain, g.n_rep, ld, g.n_syn,
                                    2 * (ld + 1) <= 32 ? 1 : 2, g.d_recovery);
             else if (P.order == XZZX_ORDER_RANDOM_SITE || (P.ladder_k && !ladder_planar_d(g)))
                 hipLaunchKernelGGL(k_site_recovery, grid, dim3(256), 0, stream, ws[i].min_snap, nc, ws[i].best_chain,
                                    g.n_rep, P.lat.nq, g.n_syn, g.d_recovery);
             else
-                hipLaunchKernelGGL(k_rows_recovery, grid, dim3(256), 0, stream, ws[i].min_snap, (int)min_snap_words(g),
+                hipLaunchKernelGGL(k_rows_recovery, grid, dim3(256), 0, stream, ws[i].min_snap, (int)min_snap_words(g, ws[i].lean),
                                    ws[i].best_chain, g.n_rep, P.lat.nq, g.n_syn, P.ddev, P.row_words, g.d_recovery);
             rc = check_hip(hipGetLastError(), "recovery gather launch");
         }
@@ -1382,17 +1373,28 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
     if (!ladder_sel.empty()) sets.push_back({&ladder_sel, false, 1, 0, false, 0, true, 0});
     for (int d = 3; d <= kPlanarStaticMaxD; d += 2)
         if (!planar_sel[d].empty()) sets.push_back({&planar_sel[d], true, 1, 0, false, d, false, 0});
-    for (int d = 3; d <= kLadderRowsMaxD; d += 2)
-        if (!ladder_rows_sel[d].empty()) sets.push_back({&ladder_rows_sel[d], true, 1, d, false, 0, true, 0});
+    for (auto &sel : ladder_rows_sel)
+        for (int d = 3; d <= kLadderRowsMaxD; d += 2)
+            if (!sel[d].empty()) sets.push_back({&sel[d], true, 1, d, false, 0, true, 0});
     for (int d = 3; d <= kPlanarStaticMaxD; d += 2)
         if (!ladder_planar_sel[d].empty()) sets.push_back({&ladder_planar_sel[d], true, 1, 0, false, d, true, 0});
-    for (int d = kStaticMinD; d <= kStaticMaxD; d += 2)
-        if (!static_sel[d].empty()) sets.push_back({&static_sel[d], true, 1, d, false, 0, false, 0});
+    for (auto &sel : static_sel)
+        for (int d = kStaticMinD; d <= kStaticMaxD; d += 2)
+            if (!sel[d].empty()) sets.push_back({&sel[d], true, 1, d, false, 0, false, 0});
     for (int l = 0; l < 7; ++l)
         if (!bytes_sel[l].empty()) sets.push_back({&bytes_sel[l], false, 1 << l, 0, false, 0, false, 0});
     for (int l = 0; l < 5; ++l)
         for (int m = 0; m < 4; ++m)
             if (!grid_sel[l][m].empty()) sets.push_back({&grid_sel[l][m], false, 4 << l, 0, false, 0, false, 1 << m});
+    // the sets whose tasks take longest first: with more sets than queues the
+    // last ones start when earlier ones have ended, and the longest tasks
+    // must not be among them
+    auto task_work = [&](const Set &S) {
+        double w = 0;
+        for (int i : *S.sel) w = std::max(w, (double)groups[i].plan->P.n_sweeps * groups[i].plan->P.lat.nstab / S.lanes);
+        return w;
+    };
+    std::stable_sort(sets.begin(), sets.end(), [&](const Set &a, const Set &b) { return task_work(a) > task_work(b); });
     // each set holds at least one group, so at most kMaxGroups of them
     static_assert(kMaxGroups <= kReplayCounters, "queue counters of the sets");
     auto one = [&](int i, hipStream_t s) {
@@ -1489,12 +1491,13 @@ static int run_decode(const xzzx_group *groups, int n_groups, uint64_t greedy_se
     size_t full = 0, least = 0;
     ws_bytes(groups, n_groups, decode, grid, &full, &least);
     if (!d_workspace || workspace_bytes < least) { set_error("workspace too small"); return XZZX_ENOMEM; }
-    if (workspace_bytes < full) std::fill(grid.begin(), grid.end(), 0);
+    const bool lean = workspace_bytes < full;
+    if (lean) std::fill(grid.begin(), grid.end(), 0);
     uint8_t *p = static_cast<uint8_t *>(d_workspace);
     uint32_t *counter = reinterpret_cast<uint32_t *>(p);
     p += 256;
     std::vector<GroupWs> ws(n_groups);
-    for (int i = 0; i < n_groups; ++i) ws[i] = carve_group(groups[i], decode, grid[i], p);
+    for (int i = 0; i < n_groups; ++i) ws[i] = carve_group(groups[i], decode, grid[i], lean, p);
     const int stage_bits = XZZX_FLAG_STAGE_GREEDY | XZZX_FLAG_STAGE_ANNEAL | XZZX_FLAG_STAGE_FINISH;
     const int stages = (flags & stage_bits) ? (flags & stage_bits) : stage_bits;
     // the groups' greedy launches run concurrently (one group's launch alone
@@ -1502,6 +1505,10 @@ static int run_decode(const xzzx_group *groups, int n_groups, uint64_t greedy_se
     std::vector<int> gsel;
     for (int i = 0; i < n_groups; ++i)
         if (decode && groups[i].n_syn > 0 && (stages & XZZX_FLAG_STAGE_GREEDY)) gsel.push_back(i);
+    // (largest lattices first, as the annealing sets)
+    std::stable_sort(gsel.begin(), gsel.end(), [&](int a, int b) {
+        return groups[a].plan->P.lat.nstab > groups[b].plan->P.lat.nstab;
+    });
     rc = fork_join(stream, (int)gsel.size(), [&](int k, hipStream_t s) {
         const int i = gsel[k];
         const xzzx_group &g = groups[i];

@@ -152,23 +152,12 @@ __device__ inline void ladder_core(const PlanDev *pl, const ChainJob &J, uint32_
     wave_lds_fence();
 }
 
-// MODE 0: persistent wavefronts on the atomic task queue; 2: one task per
-// workgroup.  Tasks of 64 consecutive chains of a group.
-template <int MODE>
+// Task loop (see later_task).  Tasks of 64 consecutive chains of a group.
 __device__ __forceinline__ void ladder_body(const AnnealArgs &A)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const PlanDev *loaded = nullptr;
-    for (int iter = 0;; ++iter) {
-        uint32_t task = 0;
-        if (MODE == 2) {
-            if (iter > 0) break;
-            task = blockIdx.x;
-        } else {
-            if (threadIdx.x == 0) task = atomicAdd(A.counter, 1u);
-            task = __builtin_amdgcn_readfirstlane(__shfl(task, 0, kWave));
-        }
-        if (task >= A.n_tasks) break;
+    for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
         int gi = 0;
         while (gi + 1 < A.n_groups && (int64_t)task >= A.g[gi + 1].task_begin) ++gi;
         const GroupArgs &G = A.g[gi];
@@ -192,9 +181,8 @@ __device__ __forceinline__ void ladder_body(const AnnealArgs &A)
     }
 }
 
-__global__ __launch_bounds__(kWave) void k_anneal_ladder(AnnealArgs A) { ladder_body<0>(A); }
-__global__ __launch_bounds__(kWave) void k_anneal_ladder_plain(AnnealArgs A) { ladder_body<2>(A); }
+__global__ __launch_bounds__(kWave) void k_anneal_ladder(AnnealArgs A) { ladder_body(A); }
 
-AnnealKernel ladder_kernel(bool plain) { return plain ? k_anneal_ladder_plain : k_anneal_ladder; }
+AnnealKernel ladder_kernel() { return k_anneal_ladder; }
 
 }  // namespace xzzx

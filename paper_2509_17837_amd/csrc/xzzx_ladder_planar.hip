@@ -22,7 +22,7 @@ __device__ __forceinline__ void ladder_planar_core(const PlanDev *pl, const Chai
     W[0] = 0; W[1] = (int32_t)uni(pl->W[1]); W[2] = (int32_t)uni(pl->W[2]); W[3] = (int32_t)uni(pl->W[3]);
     const uint32_t uid = J.uid, cc = J.cc;
     const uint32_t k0 = uni(seed_lo), k1 = uni(seed_hi);
-    const PlanarLaneKey lk = planar_lane_key(uid, k1);
+    const LaneKey lk = lane_key(uid, k1);
     // ladder position: replica r = bK + j starts at level j; coset P
     const uint32_t rep = cc >> 2, P = cc & 3u;
     const uint32_t ladder_id = 4u * (rep / (uint32_t)K) + P;
@@ -63,31 +63,28 @@ __device__ __forceinline__ void ladder_planar_core(const PlanDev *pl, const Chai
     }
 }
 
-template <int MODE, int D>
+template <int D>
 __device__ __forceinline__ void ladder_planar_body(const AnnealArgs &A)
 {
-    ladder_static_body<MODE>(A, [&](const GroupArgs &G, const ChainJob &J, const uint16_t *lut_s, const uint4 *et_s) {
+    ladder_static_body(A, [&](const GroupArgs &G, const ChainJob &J, const uint16_t *lut_s, const uint4 *et_s) {
         ladder_planar_core<D>(G.plan, J, A.seed_lo, A.seed_hi, lut_s, et_s, G.min_snap);
     });
 }
 
 template <int D>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(planar_waves(D), planar_waves(D))))
-void k_anneal_ladder_planar_d(AnnealArgs A) { ladder_planar_body<0, D>(A); }
-template <int D>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(planar_waves(D), planar_waves(D))))
-void k_anneal_ladder_planar_d_plain(AnnealArgs A) { ladder_planar_body<2, D>(A); }
+void k_anneal_ladder_planar_d(AnnealArgs A) { ladder_planar_body<D>(A); }
 
-AnnealKernel ladder_planar_kernel(int d, bool plain)
+AnnealKernel ladder_planar_kernel(int d)
 {
     switch (d) {
-    case 3: return plain ? k_anneal_ladder_planar_d_plain<3> : k_anneal_ladder_planar_d<3>;
-    case 5: return plain ? k_anneal_ladder_planar_d_plain<5> : k_anneal_ladder_planar_d<5>;
-    case 7: return plain ? k_anneal_ladder_planar_d_plain<7> : k_anneal_ladder_planar_d<7>;
-    case 9: return plain ? k_anneal_ladder_planar_d_plain<9> : k_anneal_ladder_planar_d<9>;
-    case 11: return plain ? k_anneal_ladder_planar_d_plain<11> : k_anneal_ladder_planar_d<11>;
-    case 13: return plain ? k_anneal_ladder_planar_d_plain<13> : k_anneal_ladder_planar_d<13>;
-    case 15: return plain ? k_anneal_ladder_planar_d_plain<15> : k_anneal_ladder_planar_d<15>;
+    case 3: return k_anneal_ladder_planar_d<3>;
+    case 5: return k_anneal_ladder_planar_d<5>;
+    case 7: return k_anneal_ladder_planar_d<7>;
+    case 9: return k_anneal_ladder_planar_d<9>;
+    case 11: return k_anneal_ladder_planar_d<11>;
+    case 13: return k_anneal_ladder_planar_d<13>;
+    case 15: return k_anneal_ladder_planar_d<15>;
     default: return nullptr;
     }
 }

@@ -8,9 +8,9 @@
 // its rows at its first E_min for the recovery.  Chains, draws and exchanges
 // are those of the generic ladder kernel, bit for bit.
 //
-// A task's 64 chains lie inside one syndrome (4 n_rep is a multiple of 64),
-// so the Philox counter's uid is uniform and the split form of the
-// annealing kernel applies.  The kernels are instantiated over several
+// SPAN as in the annealing kernel: a task's 64 chains may span syndromes.
+// Either way a ladder's chains lie in one task (a block of 4K lanes, K a
+// divisor of 16), in one syndrome.  The kernels are instantiated over several
 // translation units (xzzx_ladder_rows*.hip), which build in parallel.
 #pragma once
 
@@ -21,7 +21,7 @@ namespace xzzx {
 
 // snap: each chain's rows at its first E_min, chain-major (word i of chain
 // ci at snap[ci * ladder_rows_state_words(D) + i])
-template <int D>
+template <int D, bool SPAN>
 __device__ __forceinline__ void ladder_rows_core(const PlanDev *pl, const ChainJob &J, uint32_t seed_lo,
                                                  uint32_t seed_hi, const uint16_t *lut_s, const uint4 *et_s,
                                                  uint32_t *snap)
@@ -32,8 +32,9 @@ __device__ __forceinline__ void ladder_rows_core(const PlanDev *pl, const ChainJ
     const int nranks = (int)uni(pl->nranks), n_sweeps = (int)uni(pl->n_sweeps), K = (int)uni(pl->ladder_k);
     int32_t W[4];
     W[0] = 0; W[1] = (int32_t)uni(pl->W[1]); W[2] = (int32_t)uni(pl->W[2]); W[3] = (int32_t)uni(pl->W[3]);
-    const uint32_t uid = uni(J.uid), cc = J.cc;
+    const uint32_t uid = SPAN ? J.uid : uni(J.uid), cc = J.cc;
     const uint32_t k0 = uni(seed_lo), k1 = uni(seed_hi);
+    const auto draw_of = chain_draws<SPAN>(uid, cc, k0, k1);
     // ladder position: replica r = bK + j starts at level j; coset P
     const uint32_t rep = cc >> 2, P = cc & 3u;
     const uint32_t ladder_id = 4u * (rep / (uint32_t)K) + P;
@@ -49,19 +50,19 @@ __device__ __forceinline__ void ladder_rows_core(const PlanDev *pl, const ChainJ
         const uint4 *et_l = et_s + level * nranks;
         const uint32_t c2 = 4u * (uint32_t)t;
         int32_t acc = 0;
-        static_class<D, 0>(r, philox_head(uid, cc, c2, k0, k1), k0, k1, lut_s, et_l, acc, Blocks{});
+        static_class<D, 0>(r, draw_of(c2), lut_s, et_l, acc, Blocks{});
         E += acc;
         if (E < Emin) { Emin = E; stop = 4 * t + 1; if (keep) store_rows(keep, r); }
         acc = 0;
-        static_class<D, 1>(r, philox_head(uid, cc, c2 + 1u, k0, k1), k0, k1, lut_s, et_l, acc, Blocks{});
+        static_class<D, 1>(r, draw_of(c2 + 1u), lut_s, et_l, acc, Blocks{});
         E += acc;
         if (E < Emin) { Emin = E; stop = 4 * t + 2; if (keep) store_rows(keep, r); }
         acc = 0;
-        static_class<D, 2>(r, philox_head(uid, cc, c2 + 2u, k0, k1), k0, k1, lut_s, et_l, acc, Blocks{});
+        static_class<D, 2>(r, draw_of(c2 + 2u), lut_s, et_l, acc, Blocks{});
         E += acc;
         if (E < Emin) { Emin = E; stop = 4 * t + 3; if (keep) store_rows(keep, r); }
         acc = 0;
-        static_class<D, 3>(r, philox_head(uid, cc, c2 + 3u, k0, k1), k0, k1, lut_s, et_l, acc, Blocks{});
+        static_class<D, 3>(r, draw_of(c2 + 3u), lut_s, et_l, acc, Blocks{});
         E += acc;
         if (E < Emin) { Emin = E; stop = 4 * t + 4; if (keep) store_rows(keep, r); }
         if (K > 1) level = ladder_exchange(level, E, K, P, uid, ladder_id, t, k0, k1, pl->ladder_pow);
@@ -74,19 +75,19 @@ __device__ __forceinline__ void ladder_rows_core(const PlanDev *pl, const ChainJ
     }
 }
 
-template <int MODE, int D>
+template <int D, bool SPAN>
 __device__ __forceinline__ void ladder_rows_body(const AnnealArgs &A)
 {
-    ladder_static_body<MODE>(A, [&](const GroupArgs &G, const ChainJob &J, const uint16_t *lut_s, const uint4 *et_s) {
-        ladder_rows_core<D>(G.plan, J, A.seed_lo, A.seed_hi, lut_s, et_s, G.min_snap);
+    ladder_static_body(A, [&](const GroupArgs &G, const ChainJob &J, const uint16_t *lut_s, const uint4 *et_s) {
+        ladder_rows_core<D, SPAN>(G.plan, J, A.seed_lo, A.seed_hi, lut_s, et_s, G.min_snap);
     });
 }
 
 template <int D>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(static_waves(D), static_waves(D))))
-void k_anneal_ladder_rows_d(AnnealArgs A) { ladder_rows_body<0, D>(A); }
+void k_anneal_ladder_rows_d(AnnealArgs A) { ladder_rows_body<D, false>(A); }
 template <int D>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(static_waves(D), static_waves(D))))
-void k_anneal_ladder_rows_d_plain(AnnealArgs A) { ladder_rows_body<2, D>(A); }
+void k_anneal_ladder_rows_span_d(AnnealArgs A) { ladder_rows_body<D, true>(A); }
 
 }  // namespace xzzx

@@ -4,13 +4,13 @@
 
 namespace xzzx {
 
-AnnealKernel ladder_rows_kernel_c(int d, bool plain)
+AnnealKernel ladder_rows_kernel_c(int d, bool span)
 {
     switch (d) {
-    case 25: return plain ? k_anneal_ladder_rows_d_plain<25> : k_anneal_ladder_rows_d<25>;
-    case 27: return plain ? k_anneal_ladder_rows_d_plain<27> : k_anneal_ladder_rows_d<27>;
-    case 29: return plain ? k_anneal_ladder_rows_d_plain<29> : k_anneal_ladder_rows_d<29>;
-    case 31: return plain ? k_anneal_ladder_rows_d_plain<31> : k_anneal_ladder_rows_d<31>;
+    case 25: return span ? k_anneal_ladder_rows_span_d<25> : k_anneal_ladder_rows_d<25>;
+    case 27: return span ? k_anneal_ladder_rows_span_d<27> : k_anneal_ladder_rows_d<27>;
+    case 29: return span ? k_anneal_ladder_rows_span_d<29> : k_anneal_ladder_rows_d<29>;
+    case 31: return span ? k_anneal_ladder_rows_span_d<31> : k_anneal_ladder_rows_d<31>;
     default: return nullptr;
     }
 }

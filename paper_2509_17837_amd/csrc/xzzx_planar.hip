@@ -20,7 +20,7 @@ __device__ __forceinline__ void planar_static_core(const PlanDev *pl, const Chai
     W[0] = 0; W[1] = (int32_t)uni(pl->W[1]); W[2] = (int32_t)uni(pl->W[2]); W[3] = (int32_t)uni(pl->W[3]);
     const uint32_t uid = J.uid, cc = J.cc;
     const uint32_t k0 = uni(seed_lo), k1 = uni(seed_hi);
-    const PlanarLaneKey lk = planar_lane_key(uid, k1);
+    const LaneKey lk = lane_key(uid, k1);
     const bool use_x = J.lp == 1 || J.lp == 2, use_z = J.lp == 2 || J.lp == 3;
 
     uint32_t r[PR::N];
@@ -61,24 +61,14 @@ __device__ __forceinline__ void planar_static_core(const PlanDev *pl, const Chai
     }
 }
 
-// MODE 0: persistent wavefronts on the atomic task queue; 2: one task per
-// workgroup.  Tasks of 64 consecutive chains of a group.
-template <int MODE, int D>
+// Tasks of 64 consecutive chains of a group.
+template <int D>
 __device__ __forceinline__ void planar_rows_body(const AnnealArgs &A)
 {
     __shared__ uint16_t lut_s[256 * 6];
     __shared__ uint4 et_s[kStaticRanks];
     const PlanDev *loaded = nullptr;
-    for (int iter = 0;; ++iter) {
-        uint32_t task = 0;
-        if (MODE == 2) {
-            if (iter > 0) break;
-            task = blockIdx.x;
-        } else {
-            if (threadIdx.x == 0) task = atomicAdd(A.counter, 1u);
-            task = __builtin_amdgcn_readfirstlane(__shfl(task, 0, kWave));
-        }
-        if (task >= A.n_tasks) break;
+    for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
         int gi = 0;
         while (gi + 1 < A.n_groups && (int64_t)task >= A.g[gi + 1].task_begin) ++gi;
         const GroupArgs &G = A.g[gi];
@@ -95,26 +85,23 @@ __device__ __forceinline__ void planar_rows_body(const AnnealArgs &A)
 
 template <int D>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(planar_waves(D), planar_waves(D))))
-void k_anneal_planar_d(AnnealArgs A) { planar_rows_body<0, D>(A); }
-template <int D>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(planar_waves(D), planar_waves(D))))
-void k_anneal_planar_d_plain(AnnealArgs A) { planar_rows_body<2, D>(A); }
+void k_anneal_planar_d(AnnealArgs A) { planar_rows_body<D>(A); }
 
 int planar_state_words(int d)
 {
     return ((2 * d - 1) * (2 * (2 * d + 1) <= 32 ? 1 : 2) + 3) / 4 * 4;
 }
 
-AnnealKernel planar_rows_kernel(int d, bool plain)
+AnnealKernel planar_rows_kernel(int d)
 {
     switch (d) {
-    case 3: return plain ? k_anneal_planar_d_plain<3> : k_anneal_planar_d<3>;
-    case 5: return plain ? k_anneal_planar_d_plain<5> : k_anneal_planar_d<5>;
-    case 7: return plain ? k_anneal_planar_d_plain<7> : k_anneal_planar_d<7>;
-    case 9: return plain ? k_anneal_planar_d_plain<9> : k_anneal_planar_d<9>;
-    case 11: return plain ? k_anneal_planar_d_plain<11> : k_anneal_planar_d<11>;
-    case 13: return plain ? k_anneal_planar_d_plain<13> : k_anneal_planar_d<13>;
-    case 15: return plain ? k_anneal_planar_d_plain<15> : k_anneal_planar_d<15>;
+    case 3: return k_anneal_planar_d<3>;
+    case 5: return k_anneal_planar_d<5>;
+    case 7: return k_anneal_planar_d<7>;
+    case 9: return k_anneal_planar_d<9>;
+    case 11: return k_anneal_planar_d<11>;
+    case 13: return k_anneal_planar_d<13>;
+    case 15: return k_anneal_planar_d<15>;
     default: return nullptr;
     }
 }

@@ -5,11 +5,11 @@
 
 namespace xzzx {
 
-AnnealKernel static_rows_kernel_b(int d, bool plain)
+AnnealKernel static_rows_kernel_b(int d, bool span)
 {
     switch (d) {
-    case 15: return plain ? k_anneal_rows_d_plain<15> : k_anneal_rows_d<15>;
-    case 17: return plain ? k_anneal_rows_d_plain<17> : k_anneal_rows_d<17>;
+    case 15: return span ? k_anneal_rows_span_d<15> : k_anneal_rows_d<15>;
+    case 17: return span ? k_anneal_rows_span_d<17> : k_anneal_rows_d<17>;
     default: return nullptr;
     }
 }

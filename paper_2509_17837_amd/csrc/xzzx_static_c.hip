@@ -5,11 +5,11 @@
 
 namespace xzzx {
 
-AnnealKernel static_rows_kernel_c(int d, bool plain)
+AnnealKernel static_rows_kernel_c(int d, bool span)
 {
     switch (d) {
-    case 19: return plain ? k_anneal_rows_d_plain<19> : k_anneal_rows_d<19>;
-    case 21: return plain ? k_anneal_rows_d_plain<21> : k_anneal_rows_d<21>;
+    case 19: return span ? k_anneal_rows_span_d<19> : k_anneal_rows_d<19>;
+    case 21: return span ? k_anneal_rows_span_d<21> : k_anneal_rows_d<21>;
     default: return nullptr;
     }
 }

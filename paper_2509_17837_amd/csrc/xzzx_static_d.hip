@@ -5,10 +5,10 @@
 
 namespace xzzx {
 
-AnnealKernel static_rows_kernel_d(int d, bool plain)
+AnnealKernel static_rows_kernel_d(int d, bool span)
 {
     switch (d) {
-    case 23: return plain ? k_anneal_rows_d_plain<23> : k_anneal_rows_d<23>;
+    case 23: return span ? k_anneal_rows_span_d<23> : k_anneal_rows_d<23>;
     default: return nullptr;
     }
 }

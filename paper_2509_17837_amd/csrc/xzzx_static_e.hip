@@ -5,10 +5,10 @@
 
 namespace xzzx {
 
-AnnealKernel static_rows_kernel_e(int d, bool plain)
+AnnealKernel static_rows_kernel_e(int d, bool span)
 {
     switch (d) {
-    case 25: return plain ? k_anneal_rows_d_plain<25> : k_anneal_rows_d<25>;
+    case 25: return span ? k_anneal_rows_span_d<25> : k_anneal_rows_d<25>;
     default: return nullptr;
     }
 }

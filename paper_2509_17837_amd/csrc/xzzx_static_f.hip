@@ -5,10 +5,10 @@
 
 namespace xzzx {
 
-AnnealKernel static_rows_kernel_f(int d, bool plain)
+AnnealKernel static_rows_kernel_f(int d, bool span)
 {
     switch (d) {
-    case 27: return plain ? k_anneal_rows_d_plain<27> : k_anneal_rows_d<27>;
+    case 27: return span ? k_anneal_rows_span_d<27> : k_anneal_rows_d<27>;
     default: return nullptr;
     }
 }

@@ -5,10 +5,10 @@
 
 namespace xzzx {
 
-AnnealKernel static_rows_kernel_g(int d, bool plain)
+AnnealKernel static_rows_kernel_g(int d, bool span)
 {
     switch (d) {
-    case 29: return plain ? k_anneal_rows_d_plain<29> : k_anneal_rows_d<29>;
+    case 29: return span ? k_anneal_rows_span_d<29> : k_anneal_rows_d<29>;
     default: return nullptr;
     }
 }

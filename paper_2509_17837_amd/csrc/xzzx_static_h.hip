@@ -5,10 +5,10 @@
 
 namespace xzzx {
 
-AnnealKernel static_rows_kernel_h(int d, bool plain)
+AnnealKernel static_rows_kernel_h(int d, bool span)
 {
     switch (d) {
-    case 31: return plain ? k_anneal_rows_d_plain<31> : k_anneal_rows_d<31>;
+    case 31: return span ? k_anneal_rows_span_d<31> : k_anneal_rows_d<31>;
     default: return nullptr;
     }
 }

@@ -66,3 +66,49 @@ def test_grid_core(layout, d, lanes):
                    prob.anneal_seed, want_chains=True, want_final=True)
     torch.cuda.synchronize()
     compare_decode(prob, out, prob.oracle_decode())
+
+
+@pytest.mark.parametrize("d", range(3, 32, 2))
+def test_tasks_spanning_syndromes(d):
+    """The packed-row kernels specialised to d where 4 n_rep is no multiple of
+    64: tasks of 64 chains span syndromes (12 chains each, the last task
+    ragged).  Annealing with checkpoints and with a workspace too short for
+    them, in the plain form, and ladders (24 chains each)."""
+    print(f"[paths] spanning tasks d={d}", flush=True)
+    prob = Problem(0, d, 0.15, 10.0, 11, 3, 70, seed=60 + d)
+    plan = gpu_plan(prob)
+    plan.set_kernel(X.KERNEL_ROWS)
+    ref = prob.oracle_decode()
+    syn, uid = to_dev(prob.syn), to_dev(prob.uid.view(np.int32))
+    for flags, short in ((0, 0), (0, 1), (X.FLAG_PLAIN, 0)):
+        g, out = D.make_group(plan, prob.n_rep, uid, syn=syn, want_chains=True, want_final=True)
+        ws = D.workspace([g])
+        D.decode_groups([g], prob.greedy_seed, prob.anneal_seed, flags=flags, ws=ws[:ws.numel() - short])
+        torch.cuda.synchronize()
+        compare_decode(prob, out, ref)
+    prob = Problem(0, d, 0.15, 10.0, 5, 6, 12, seed=90 + d)
+    plan = gpu_plan(prob)
+    plan.set_ladder(2, 0.5, 4.0)
+    ref = prob.oracle_decode(order=O.ORDER_LADDER, ladder=(2, 0.5, 4.0))
+    syn, uid = to_dev(prob.syn), to_dev(prob.uid.view(np.int32))
+    for short in (0, 1):
+        g, out = D.make_group(plan, prob.n_rep, uid, syn=syn, want_chains=True, want_final=True)
+        ws = D.workspace([g])
+        D.decode_groups([g], prob.greedy_seed, prob.anneal_seed, ws=ws[:ws.numel() - short])
+        torch.cuda.synchronize()
+        compare_decode(prob, out, ref)
+
+
+def test_short_workspace_leaves_the_grid_core():
+    """A small call whose workspace holds no grid states runs one chain per
+    lane: the same results."""
+    prob = Problem(0, 11, 0.15, 10.0, 3, 16, 20, seed=77)
+    plan = gpu_plan(prob)
+    ref = prob.oracle_decode()
+    syn, uid = to_dev(prob.syn), to_dev(prob.uid.view(np.int32))
+    for short in (0, 1):
+        g, out = D.make_group(plan, prob.n_rep, uid, syn=syn, want_chains=True)
+        ws = D.workspace([g])
+        D.decode_groups([g], prob.greedy_seed, prob.anneal_seed, ws=ws[:ws.numel() - short])
+        torch.cuda.synchronize()
+        compare_decode(prob, out, ref)
