@@ -796,17 +796,53 @@ __device__ inline void rows_core(const PlanDev *pl, const ChainJob &J, int t_beg
 // class) is a compile-time table, so the sweep is straight-line code: no
 // descriptor loads, no row loads or stores, no per-move scalar work, and the
 // null generators that pad a class to whole Philox blocks cost nothing.  The
-// move-energy lookup maps (shape, pattern) to the byte offset of a 16-byte
-// (dE, threshold, always-accept mask) entry in static LDS; the four generators
+// move-energy lookup maps (shape, pattern) to the byte offset of an 8-byte
+// entry (see move_entry) in static LDS; the four generators
 // of a Philox block are disjoint, so their patterns are read before any flips.
 // ---------------------------------------------------------------------------
-__device__ inline void load_static_tables(const PlanDev *pl, uint16_t *lut_s, uint4 *et_s)
+// Energy-table entry of a move in the specialised kernels, eight bytes (a
+// ds_read_b64: 2.8 cycles of the CU's LDS, 4.6 at random entries of this
+// table, where the twelve-byte entry before took a ds_read_b96 of 9.7 and
+// 20): x is the threshold (0 where the move always accepts, dE <= 0), y holds
+// dE modulo 2^31 and, in bit 31, the threshold's top bit (1 where the move
+// always accepts).  Energies are sums of weights, in [0, 2^31) (the plan
+// checks it), so they are exact modulo 2^31.
+__device__ __forceinline__ uint2 move_entry(int32_t de, uint32_t thr)
+{
+    const uint32_t e = (uint32_t)de & 0x7FFFFFFFu;
+    return de <= 0 ? make_uint2(0u, e | 0x80000000u) : make_uint2(thr, e | (thr & 0x80000000u));
+}
+
+// Acceptance mask of a move, all ones iff u < thr or it always accepts: the
+// borrow of u - thr is bit 31 of (~u & thr) | (~(u ^ thr) & (u - thr)) (one
+// v_bitop3, truth table 0x8E), which reads thr itself only in bit 31, so the
+// entry's second word does; spread by a shift.  Always: thr = 0 with the bit
+// set gives ~u | u.  Three fast instructions (see the rates below); a compare
+// and a borrow from an always-accept word were two slow ones that shared one
+// condition register.
+__device__ __forceinline__ uint32_t accept_mask(uint32_t u, const uint2 &e)
+{
+    return (uint32_t)((int32_t)__builtin_amdgcn_bitop3_b32(u, e.y, u - e.x, 0x8E) >> 31);
+}
+
+// E plus the accepted moves' words y.
+__device__ __forceinline__ int32_t add_energy(int32_t E, int32_t acc) { return (E + acc) & 0x7FFFFFFF; }
+
+// The thresholds of a sweep in the entries with dE > 0 (ranks kneg and up).
+__device__ __forceinline__ void set_thresholds(uint2 *et_s, const uint32_t *thr, int kneg, int nranks)
+{
+    for (int i = kneg + (int)threadIdx.x; i < nranks; i += kWave) {
+        const uint32_t v = thr[i];
+        et_s[i] = make_uint2(v, (et_s[i].y & 0x7FFFFFFFu) | (v & 0x80000000u));
+    }
+}
+
+__device__ inline void load_static_tables(const PlanDev *pl, uint16_t *lut_s, uint2 *et_s)
 {
     const int lane = threadIdx.x;
-    for (int i = lane; i < 256 * 6; i += kWave) lut_s[i] = (uint16_t)(16u * pl->lut[i]);
+    for (int i = lane; i < 256 * 6; i += kWave) lut_s[i] = (uint16_t)(8u * pl->lut[i]);
     for (int i = lane; i < pl->nranks; i += kWave) {
-        const int32_t de = pl->dE[i];
-        et_s[i] = make_uint4((uint32_t)de, 0u, de <= 0 ? 0xFFFFFFFFu : 0u, 0u);
+        et_s[i] = move_entry(pl->dE[i], 0u);
     }
     wave_lds_fence();
 }
@@ -969,22 +1005,27 @@ __device__ __forceinline__ auto chain_draws(uint32_t uid, uint32_t cc, uint32_t 
     }
 }
 
-// All ones where u < thr (unsigned), from the borrow of u - thr: bit 31 of
-// (~u & thr) | (~(u ^ thr) & (u - thr)), one v_bitop3 (truth table 0x8E).
-__device__ __forceinline__ uint32_t lt_mask(uint32_t u, uint32_t thr)
-{
-    return (uint32_t)((int32_t)__builtin_amdgcn_bitop3_b32(u, thr, u - thr, 0x8E) >> 31);
-}
+// Instruction rates that shape the specialised kernels (cycles per wave64
+// instruction and SIMD, eight wavefronts): 2.0-2.3 for xor, and, add, sub,
+// bitop3, right shifts and moves; 4.0-4.2 for everything else used here --
+// left shifts, and_or, add3, alignbit, compares, borrows, the products.  So a
+// move takes two fast instructions rather than one slow one where it can.
 
-// Acceptance mask of a move of the specialised kernels: all ones iff
-// u < thr or the move always accepts (dE <= 0: always = all ones, and its
-// table threshold is 0, so the borrow of u - thr is 0).  Two instructions:
-// the borrow of u - thr goes through the carry into always - 0 - borrow.
+// Acceptance mask in two instructions through the condition register: all ones
+// iff u < thr or always = all ones (thr must then be 0).
 __device__ __forceinline__ uint32_t accept_sel(uint32_t u, uint32_t thr, uint32_t always)
 {
     unsigned int borrow, unused;
     (void)__builtin_subc(u, thr, 0u, &borrow);
     return __builtin_subc(always, 0u, borrow, &unused);
+}
+
+// Table index of a block pattern, twice (byte offset of 16-bit entries): the
+// upper row's nibble at bits 1-4, the lower row's at bits 5-8, joined by a
+// v_bitop3 ((lower & mask) | upper, truth table 0xEA; a v_and_or is slow).
+__device__ __forceinline__ uint32_t join_pattern(uint32_t upper, uint32_t lower)
+{
+    return __builtin_amdgcn_bitop3_b32(lower, 0x1E0u, upper, 0xEA);
 }
 
 // Rows of the specialised kernel: the d lattice rows only, qubit x of a row
@@ -1013,28 +1054,31 @@ __device__ __forceinline__ uint32_t row_bits(const uint32_t *w)
     }
 }
 
-// A 32-bit constant materialised in a scalar register where it is used.
-// Large lattices use dozens of distinct flip masks; left to itself the
-// compiler hoists them all out of the sweep loop and spills the surplus.
-template <uint32_t C>
-__device__ __forceinline__ uint32_t sreg_const()
+// A zero in a scalar register whose value the compiler does not know.  Large
+// lattices use dozens of distinct flip masks; left to itself the compiler
+// hoists them all out of the sweep loop and spills the surplus.  A mask or-ed
+// with a zero of its own Philox block is made where it is used, by one scalar
+// instruction.  (A mask moved by inline asm each time cost a wait state after
+// most of them: 719 of 25334 instructions a sweep at d = 31.)
+__device__ __forceinline__ uint32_t opaque_zero()
 {
-    uint32_t v;
-    asm volatile("s_mov_b32 %0, %1" : "=s"(v) : "i"(C));
-    return v;
+    uint32_t z;
+    asm volatile("s_mov_b32 %0, 0" : "=s"(z));
+    return z;
 }
 
 // w ^= (MASK << BO) & sel over the words of one row (MASK: 4 bits; for
-// BO = -2 the bits of the missing column drop out)
+// BO = -2 the bits of the missing column drop out); zero: see opaque_zero
+// (rows of two words)
 template <int NW, int BO, uint32_t MASK>
-__device__ __forceinline__ void row_flip_static(uint32_t *w, uint32_t sel)
+__device__ __forceinline__ void row_flip_static(uint32_t *w, uint32_t sel, uint32_t zero)
 {
     constexpr uint64_t m = BO >= 0 ? (uint64_t)MASK << BO : (uint64_t)(MASK >> -BO);
     if constexpr (NW == 1) {
         w[0] = xor_and(w[0], (uint32_t)m, sel);
     } else {
-        if constexpr ((uint32_t)m != 0u) w[0] = xor_and(w[0], sreg_const<(uint32_t)m>(), sel);
-        if constexpr ((uint32_t)(m >> 32) != 0u) w[1] = xor_and(w[1], sreg_const<(uint32_t)(m >> 32)>(), sel);
+        if constexpr ((uint32_t)m != 0u) w[0] = xor_and(w[0], (uint32_t)m | zero, sel);
+        if constexpr ((uint32_t)(m >> 32) != 0u) w[1] = xor_and(w[1], (uint32_t)(m >> 32) | zero, sel);
     }
 }
 
@@ -1051,85 +1095,59 @@ struct StaticGen {
 
 // The move's energy-table entry, looked up from its 8-bit slot pattern.
 template <int D, int K, int B, int W>
-__device__ __forceinline__ uint4 static_lookup(const uint32_t (&r)[StaticRows<D>::N], const uint16_t *lut_s,
-                                               const uint4 *et_s)
+__device__ __forceinline__ uint2 static_lookup(const uint32_t (&r)[StaticRows<D>::N], const uint16_t *lut_s,
+                                               const uint2 *et_s)
 {
     using G = StaticGen<D, K, B, W>;
     constexpr int NW = StaticRows<D>::NW;
     if constexpr (!G::real) {
-        return make_uint4(0u, 0u, 0u, 0u);
+        return make_uint2(0u, 0u);
     } else {
         const uint32_t *ra = r + (G::has_a ? G::ya : 0) * NW, *rb = r + (G::has_b ? G::ya + 1 : 0) * NW;
-        uint32_t pat2 = 0;
-        if constexpr (G::has_a) pat2 |= row_bits<NW, G::BO, 1>(ra) & 0x1Eu;
-        if constexpr (G::has_b) pat2 |= row_bits<NW, G::BO, 5>(rb) & 0x1E0u;
+        uint32_t pat2;
+        if constexpr (!G::has_b) pat2 = row_bits<NW, G::BO, 1>(ra) & 0x1Eu;
+        else if constexpr (!G::has_a) pat2 = row_bits<NW, G::BO, 5>(rb) & 0x1E0u;
+        else pat2 = join_pattern(row_bits<NW, G::BO, 1>(ra) & 0x1Eu, row_bits<NW, G::BO, 5>(rb));
         const uint32_t off = *reinterpret_cast<const uint16_t *>(reinterpret_cast<const uint8_t *>(lut_s) +
                                                                  512u * G::g.shp + pat2);
-        return *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(et_s) + off);
+        return *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint8_t *>(et_s) + off);
     }
 }
 
 // Acceptance of the move with draw u and entry e, its flips and energy.
 template <int D, int K, int B, int W>
-__device__ __forceinline__ void static_apply(uint32_t (&r)[StaticRows<D>::N], uint32_t u, const uint4 &e, int32_t &acc)
+__device__ __forceinline__ void static_apply(uint32_t (&r)[StaticRows<D>::N], uint32_t u, const uint2 &e, int32_t &acc,
+                                             uint32_t zero)
 {
     using G = StaticGen<D, K, B, W>;
     constexpr int NW = StaticRows<D>::NW;
     if constexpr (G::real) {
         uint32_t *ra = r + (G::has_a ? G::ya : 0) * NW, *rb = r + (G::has_b ? G::ya + 1 : 0) * NW;
-        // all ones on accepting lanes: u < threshold, or dE <= 0 (mask all
-        // ones).  Up to d = 15 (eight wavefronts per SIMD) two instructions
-        // through the carry, the table giving those ranks threshold 0; the
-        // larger lattices, at four or five wavefronts, keep the
-        // sign-extension form: the carry form's compare and borrow share one
-        // condition register, which serialises the moves of a block, and
-        // d = 31 ran 21 % slower with it
-        uint32_t sel;
-        if constexpr (D <= 15) sel = accept_sel(u, e.y, e.z);
-        else sel = lt_mask(u, e.y) | e.z;
-        if constexpr (G::has_a) row_flip_static<NW, G::BO, 6u>(ra, sel);   // X_left | Z_up
-        if constexpr (G::has_b) row_flip_static<NW, G::BO, 9u>(rb, sel);   // Z_down | X_right
-        acc += (int32_t)(e.x & sel);
+        const uint32_t sel = accept_mask(u, e);
+        if constexpr (G::has_a) row_flip_static<NW, G::BO, 6u>(ra, sel, zero);   // X_left | Z_up
+        if constexpr (G::has_b) row_flip_static<NW, G::BO, 9u>(rb, sel, zero);   // Z_down | X_right
+        acc += (int32_t)(e.y & sel);
     }
 }
 
 template <int D, int K, int B>
 __device__ __forceinline__ void static_block(uint32_t (&r)[StaticRows<D>::N], const uint4 &u, const uint16_t *lut_s,
-                                             const uint4 *et_s, int32_t &acc)
+                                             const uint2 *et_s, int32_t &acc)
 {
     // The four generators of a block belong to one colour class and act on
     // disjoint qubits: a flip of one leaves the others' slot bits as they
     // were, so all four look up their entries from the rows before any flip
     // and their LDS reads overlap (looked up one after another, each move's
     // pattern waited for the previous move's flips of the same row words).
-    // Moves looked up together per group (measured per distance): four, but
-    // one at a time at d = 15, where four entries in flight spill (and pairs
-    // measured slower).
-    constexpr int OV = D == 15 ? 1 : 4;
-    if constexpr (OV == 1) {
-        static_apply<D, K, B, 0>(r, u.x, static_lookup<D, K, B, 0>(r, lut_s, et_s), acc);
-        static_apply<D, K, B, 1>(r, u.y, static_lookup<D, K, B, 1>(r, lut_s, et_s), acc);
-        static_apply<D, K, B, 2>(r, u.z, static_lookup<D, K, B, 2>(r, lut_s, et_s), acc);
-        static_apply<D, K, B, 3>(r, u.w, static_lookup<D, K, B, 3>(r, lut_s, et_s), acc);
-    } else if constexpr (OV == 2) {
-        const uint4 e0 = static_lookup<D, K, B, 0>(r, lut_s, et_s);
-        const uint4 e1 = static_lookup<D, K, B, 1>(r, lut_s, et_s);
-        static_apply<D, K, B, 0>(r, u.x, e0, acc);
-        static_apply<D, K, B, 1>(r, u.y, e1, acc);
-        const uint4 e2 = static_lookup<D, K, B, 2>(r, lut_s, et_s);
-        const uint4 e3 = static_lookup<D, K, B, 3>(r, lut_s, et_s);
-        static_apply<D, K, B, 2>(r, u.z, e2, acc);
-        static_apply<D, K, B, 3>(r, u.w, e3, acc);
-    } else {
-        const uint4 e0 = static_lookup<D, K, B, 0>(r, lut_s, et_s);
-        const uint4 e1 = static_lookup<D, K, B, 1>(r, lut_s, et_s);
-        const uint4 e2 = static_lookup<D, K, B, 2>(r, lut_s, et_s);
-        const uint4 e3 = static_lookup<D, K, B, 3>(r, lut_s, et_s);
-        static_apply<D, K, B, 0>(r, u.x, e0, acc);
-        static_apply<D, K, B, 1>(r, u.y, e1, acc);
-        static_apply<D, K, B, 2>(r, u.z, e2, acc);
-        static_apply<D, K, B, 3>(r, u.w, e3, acc);
-    }
+    const uint2 e0 = static_lookup<D, K, B, 0>(r, lut_s, et_s);
+    const uint2 e1 = static_lookup<D, K, B, 1>(r, lut_s, et_s);
+    const uint2 e2 = static_lookup<D, K, B, 2>(r, lut_s, et_s);
+    const uint2 e3 = static_lookup<D, K, B, 3>(r, lut_s, et_s);
+    const uint32_t zero = StaticRows<D>::NW == 1 ? 0u : opaque_zero();
+    static_apply<D, K, B, 0>(r, u.x, e0, acc, zero);
+    static_apply<D, K, B, 1>(r, u.y, e1, acc, zero);
+    static_apply<D, K, B, 2>(r, u.z, e2, acc, zero);
+    static_apply<D, K, B, 3>(r, u.w, e3, acc, zero);
     // the energy change is summed block by block: left free, the compiler
     // reassociates the whole class's sum into a tree at the end of the class
     // and keeps every move's term live in a register until then.  The asm is
@@ -1141,7 +1159,7 @@ __device__ __forceinline__ void static_block(uint32_t (&r)[StaticRows<D>::N], co
 
 template <int D, int K, typename Draw, int... Bs>
 __device__ __forceinline__ void static_class(uint32_t (&r)[StaticRows<D>::N], const Draw &draw, const uint16_t *lut_s,
-                                             const uint4 *et_s, int32_t &acc, std::integer_sequence<int, Bs...>)
+                                             const uint2 *et_s, int32_t &acc, std::integer_sequence<int, Bs...>)
 {
     (static_block<D, K, Bs>(r, draw.template block<Bs>(), lut_s, et_s, acc), ...);
 }
@@ -1197,7 +1215,7 @@ __device__ __forceinline__ int32_t static_load(const PlanDev *pl, const ChainJob
 // Philox block takes two more lane products; otherwise they belong to one.
 template <int D, bool SPAN>
 __device__ __forceinline__ void rows_static_core(const PlanDev *pl, const ChainJob &J, int t_begin, int t_end, uint32_t seed_lo,
-                                 uint32_t seed_hi, const uint16_t *lut_s, uint4 *et_s, int cp_interval)
+                                 uint32_t seed_hi, const uint16_t *lut_s, uint2 *et_s, int cp_interval)
 {
     constexpr int NW = StaticRows<D>::NW;
     constexpr int NB = RotSchedule<D>::MP / 4;
@@ -1236,30 +1254,24 @@ __device__ __forceinline__ void rows_static_core(const PlanDev *pl, const ChainJ
         if (keep) t_stop = min(t_end, t_begin + ((t - t_begin) / kServeCheckpointEvery + 1) * kServeCheckpointEvery);
         for (; t < t_stop; ++t) {
             wave_lds_fence();
-            // this sweep's thresholds (0 for the ranks with dE <= 0 where the
-            // acceptance goes through the carry: see static_apply)
-            if constexpr (D <= 15) {
-                for (int i = lane; i < nranks; i += kWave) et_s[i].y = i < kneg ? 0u : pl->thr[(size_t)t * nranks + i];
-            } else {
-                for (int i = lane; i < nranks; i += kWave) et_s[i].y = pl->thr[(size_t)t * nranks + i];
-            }
+            set_thresholds(et_s, pl->thr + (size_t)t * nranks, kneg, nranks);
             wave_lds_fence();
             const uint32_t c2 = 4u * (uint32_t)t;
             int32_t acc = 0;
             static_class<D, 0>(r, draw_of(c2), lut_s, et_s, acc, Blocks{});
-            E += acc;
+            E = add_energy(E, acc);
             if (E < Emin) { Emin = E; stop = 4 * t + 1; }
             acc = 0;
             static_class<D, 1>(r, draw_of(c2 + 1u), lut_s, et_s, acc, Blocks{});
-            E += acc;
+            E = add_energy(E, acc);
             if (E < Emin) { Emin = E; stop = 4 * t + 2; }
             acc = 0;
             static_class<D, 2>(r, draw_of(c2 + 2u), lut_s, et_s, acc, Blocks{});
-            E += acc;
+            E = add_energy(E, acc);
             if (E < Emin) { Emin = E; stop = 4 * t + 3; }
             acc = 0;
             static_class<D, 3>(r, draw_of(c2 + 3u), lut_s, et_s, acc, Blocks{});
-            E += acc;
+            E = add_energy(E, acc);
             if (E < Emin) { Emin = E; stop = 4 * t + 4; }
         }
         if (cp_every && t < t_end && J.active) {
@@ -1304,18 +1316,16 @@ __device__ __forceinline__ uint32_t swap_threshold(const uint64_t *R, uint32_t n
 }
 
 // Tables of the ladder kernels specialised to d: the (shape, pattern) ->
-// entry offset table of the annealing kernels, and one 16-byte entry
-// (dE, threshold, always-accept mask) per (level, rank), the levels' tables
-// one after another; ranks with dE <= 0 take threshold 0 (see accept_sel).
-__device__ inline void load_ladder_tables(const PlanDev *pl, uint16_t *lut_s, uint4 *et_s)
+// entry offset table of the annealing kernels, and one 8-byte entry
+// (see move_entry) per (level, rank), the levels' tables one after another.
+__device__ inline void load_ladder_tables(const PlanDev *pl, uint16_t *lut_s, uint2 *et_s)
 {
     const int lane = threadIdx.x;
-    const int nranks = pl->nranks, kneg = pl->kneg, K = pl->ladder_k;
-    for (int i = lane; i < 256 * 6; i += kWave) lut_s[i] = (uint16_t)(16u * pl->lut[i]);
+    const int nranks = pl->nranks, K = pl->ladder_k;
+    for (int i = lane; i < 256 * 6; i += kWave) lut_s[i] = (uint16_t)(8u * pl->lut[i]);
     for (int i = lane; i < K * nranks; i += kWave) {
         const int rk = i % nranks;
-        const int32_t de = pl->dE[rk];
-        et_s[i] = make_uint4((uint32_t)de, rk < kneg ? 0u : pl->ladder_thr[i], de <= 0 ? 0xFFFFFFFFu : 0u, 0u);
+        et_s[i] = move_entry(pl->dE[rk], pl->ladder_thr[i]);
     }
     wave_lds_fence();
 }
@@ -1353,12 +1363,12 @@ __device__ __forceinline__ int ladder_exchange(int level, int32_t E, int K, uint
 // Task loop of the ladder kernels specialised to d, tasks of 64 consecutive
 // chains.  The offset table is static LDS, so its address
 // folds into each lookup's instruction; the K level tables are dynamic LDS
-// (16 K n_ranks bytes).  core(G, J, lut_s, et_s) runs one lane's chain.
+// (8 K n_ranks bytes).  core(G, J, lut_s, et_s) runs one lane's chain.
 template <typename Core>
 __device__ __forceinline__ void ladder_static_body(const AnnealArgs &A, Core core)
 {
     __shared__ uint16_t lut_s[256 * 6];
-    extern __shared__ __align__(16) uint4 et_s[];
+    extern __shared__ __align__(16) uint2 et_s[];
     const PlanDev *loaded = nullptr;
     for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
         int gi = 0;
@@ -1476,7 +1486,7 @@ template <int SD, bool SPAN>
 __device__ __forceinline__ void static_rows_body(const AnnealArgs &A)
 {
     __shared__ uint16_t lut_s[256 * 6];
-    __shared__ uint4 et_s[kStaticRanks];
+    __shared__ uint2 et_s[kStaticRanks];
     __builtin_amdgcn_s_setprio(static_priority(SD));
     const PlanDev *loaded = nullptr;
     for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
@@ -1504,8 +1514,12 @@ constexpr int static_waves(int d) { return d <= 15 ? 8 : d <= 21 ? 5 : 4; }
 template <int D>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(static_waves(D), static_waves(D))))
 void k_anneal_rows_d(AnnealArgs A) { static_rows_body<D, false>(A); }
+// (tasks that span syndromes: a few registers more, so one wavefront fewer
+// where the rows take two words: 2.00 -> 2.30, 2.06 -> 2.23 and 1.61 -> 1.80 x
+// 10^12 attempts/s at d = 17, 21, 31, most of it from the spills avoided)
+constexpr int span_waves(int d) { return d <= 15 ? 8 : d <= 21 ? 4 : 3; }
 template <int D>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(static_waves(D), static_waves(D))))
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(span_waves(D), span_waves(D))))
 void k_anneal_rows_span_d(AnnealArgs A) { static_rows_body<D, true>(A); }
 
 // ---------------------------------------------------------------------------
@@ -1624,7 +1638,7 @@ __device__ __forceinline__ void serve_kernel_body(const ServeTask *tasks, uint32
 
 template <int D>
 __device__ __forceinline__ void serve_static_task(const ServeTask &T, uint32_t slo, uint32_t shi, uint16_t *lut_s,
-                                                  uint4 *et_s)
+                                                  uint2 *et_s)
 {
     __builtin_amdgcn_s_setprio(static_priority(D));
     load_static_tables(T.plan, lut_s, et_s);
@@ -1644,7 +1658,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(serve_cla
 void k_serve_rows_class(const ServeTask *tasks, uint32_t slo, uint32_t shi)
 {
     __shared__ uint16_t lut_s[256 * 6];
-    __shared__ uint4 et_s[kStaticRanks];
+    __shared__ uint2 et_s[kStaticRanks];
     const ServeTask &T = tasks[blockIdx.x];
     const int d = (int)uni(T.plan->d);
     ((d == Ds ? serve_static_task<Ds>(T, slo, shi, lut_s, et_s) : (void)0), ...);

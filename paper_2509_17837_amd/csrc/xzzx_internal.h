@@ -166,8 +166,8 @@ bool planar_schedule_matches(int d, const std::vector<uint32_t> &rowface, int mp
 constexpr int kStaticMinD = 3, kStaticMaxD = 31;
 constexpr int kStaticRanks = 128;
 // static LDS of a specialised kernel's workgroup: the u16 (shape, pattern)
-// lookup of six shapes and the 16-byte move-energy entries
-constexpr size_t kStaticLdsBytes = 2 * 256 * 6 + 16 * kStaticRanks;
+// lookup of six shapes and the 8-byte move-energy entries
+constexpr size_t kStaticLdsBytes = 2 * 256 * 6 + 8 * kStaticRanks;
 // Rotated distances whose replica-exchange ladders run on a packed-row
 // kernel specialised to d (every distance with such an annealing kernel).
 constexpr int kLadderRowsMaxD = 31;

@@ -890,10 +890,10 @@ static int64_t min_snap_words(const xzzx_group &g, bool lean)
 // A group runs on the packed-row kernel specialised to its distance when the
 // plan allows it: in the form whose tasks of 64 chains may span syndromes
 // where they do not all lie inside one.  (That form takes two more products
-// per Philox block and runs within 1-4 % of the other up to d = 19, 8-15 %
-// beyond, where it spills; before, such groups ran on the generic packed-row
+// per Philox block: 2.17 against 2.31 x 10^12 attempts/s at d = 11, 1.80
+// against 1.93 at d = 31; before, such groups ran on the generic packed-row
 // kernel, rows in LDS (a decode of 4099 syndromes of 40 chains at d = 13, 100
-// sweeps: 4.06 -> 2.36 ms), or, d = 31, on byte states.)
+// sweeps: 4.03 -> 2.29 ms), or, d = 31, on byte states.)
 static bool uses_static(const xzzx_group &g)
 {
     const Plan &P = g.plan->P;
@@ -1130,7 +1130,7 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
         const int C = kWave / lanes;
         tasks += (uint64_t)((units + C - 1) / C);
         lds = std::max(lds, (ladder && (static_d || planar_d))
-                                ? 16 * (size_t)P.ladder_k * P.nranks()
+                                ? 8 * (size_t)P.ladder_k * P.nranks()
                             : (static_d || planar_d) ? (size_t)0
                             : grid_mv ? P.lds_bytes_grid(lanes)
                             : ladder ? P.lds_bytes_ladder()

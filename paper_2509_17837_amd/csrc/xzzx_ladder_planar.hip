@@ -13,7 +13,7 @@ namespace xzzx {
 // ci at snap[ci * planar_state_words(D) + i])
 template <int D>
 __device__ __forceinline__ void ladder_planar_core(const PlanDev *pl, const ChainJob &J, uint32_t seed_lo,
-                                                   uint32_t seed_hi, const uint16_t *lut_s, const uint4 *et_s,
+                                                   uint32_t seed_hi, const uint16_t *lut_s, const uint2 *et_s,
                                                    uint32_t *snap)
 {
     using PR = PlanarRows<D>;
@@ -35,23 +35,23 @@ __device__ __forceinline__ void ladder_planar_core(const PlanDev *pl, const Chai
     uint4 *keep = (snap && J.active) ? reinterpret_cast<uint4 *>(snap + J.ci * NP) : nullptr;
     if (keep) store_rows(keep, r);
     for (int t = 0; t < n_sweeps; ++t) {
-        const uint4 *et_l = et_s + level * nranks;
+        const uint2 *et_l = et_s + level * nranks;
         const uint32_t c2 = 4u * (uint32_t)t;
         int32_t acc = 0;
-        planar_class<D, 0, planar_ladder_pipelined(D)>(r, lk, cc, c2, k0, k1, lut_s, et_l, acc);
-        E += acc;
+        planar_class<D, 0>(r, lk, cc, c2, k0, k1, lut_s, et_l, acc);
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 1; if (keep) store_rows(keep, r); }
         acc = 0;
-        planar_class<D, 1, planar_ladder_pipelined(D)>(r, lk, cc, c2 + 1u, k0, k1, lut_s, et_l, acc);
-        E += acc;
+        planar_class<D, 1>(r, lk, cc, c2 + 1u, k0, k1, lut_s, et_l, acc);
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 2; if (keep) store_rows(keep, r); }
         acc = 0;
-        planar_class<D, 2, planar_ladder_pipelined(D)>(r, lk, cc, c2 + 2u, k0, k1, lut_s, et_l, acc);
-        E += acc;
+        planar_class<D, 2>(r, lk, cc, c2 + 2u, k0, k1, lut_s, et_l, acc);
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 3; if (keep) store_rows(keep, r); }
         acc = 0;
-        planar_class<D, 3, planar_ladder_pipelined(D)>(r, lk, cc, c2 + 3u, k0, k1, lut_s, et_l, acc);
-        E += acc;
+        planar_class<D, 3>(r, lk, cc, c2 + 3u, k0, k1, lut_s, et_l, acc);
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 4; if (keep) store_rows(keep, r); }
         if (K > 1) level = ladder_exchange(level, E, K, P, uid, ladder_id, t, k0, k1, pl->ladder_pow);
     }
@@ -66,7 +66,7 @@ __device__ __forceinline__ void ladder_planar_core(const PlanDev *pl, const Chai
 template <int D>
 __device__ __forceinline__ void ladder_planar_body(const AnnealArgs &A)
 {
-    ladder_static_body(A, [&](const GroupArgs &G, const ChainJob &J, const uint16_t *lut_s, const uint4 *et_s) {
+    ladder_static_body(A, [&](const GroupArgs &G, const ChainJob &J, const uint16_t *lut_s, const uint2 *et_s) {
         ladder_planar_core<D>(G.plan, J, A.seed_lo, A.seed_hi, lut_s, et_s, G.min_snap);
     });
 }

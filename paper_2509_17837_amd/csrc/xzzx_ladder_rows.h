@@ -23,7 +23,7 @@ namespace xzzx {
 // ci at snap[ci * ladder_rows_state_words(D) + i])
 template <int D, bool SPAN>
 __device__ __forceinline__ void ladder_rows_core(const PlanDev *pl, const ChainJob &J, uint32_t seed_lo,
-                                                 uint32_t seed_hi, const uint16_t *lut_s, const uint4 *et_s,
+                                                 uint32_t seed_hi, const uint16_t *lut_s, const uint2 *et_s,
                                                  uint32_t *snap)
 {
     constexpr int N = StaticRows<D>::N;
@@ -47,23 +47,23 @@ __device__ __forceinline__ void ladder_rows_core(const PlanDev *pl, const ChainJ
     uint4 *keep = (snap && J.active) ? reinterpret_cast<uint4 *>(snap + J.ci * NP) : nullptr;
     if (keep) store_rows(keep, r);
     for (int t = 0; t < n_sweeps; ++t) {
-        const uint4 *et_l = et_s + level * nranks;
+        const uint2 *et_l = et_s + level * nranks;
         const uint32_t c2 = 4u * (uint32_t)t;
         int32_t acc = 0;
         static_class<D, 0>(r, draw_of(c2), lut_s, et_l, acc, Blocks{});
-        E += acc;
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 1; if (keep) store_rows(keep, r); }
         acc = 0;
         static_class<D, 1>(r, draw_of(c2 + 1u), lut_s, et_l, acc, Blocks{});
-        E += acc;
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 2; if (keep) store_rows(keep, r); }
         acc = 0;
         static_class<D, 2>(r, draw_of(c2 + 2u), lut_s, et_l, acc, Blocks{});
-        E += acc;
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 3; if (keep) store_rows(keep, r); }
         acc = 0;
         static_class<D, 3>(r, draw_of(c2 + 3u), lut_s, et_l, acc, Blocks{});
-        E += acc;
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 4; if (keep) store_rows(keep, r); }
         if (K > 1) level = ladder_exchange(level, E, K, P, uid, ladder_id, t, k0, k1, pl->ladder_pow);
     }
@@ -78,7 +78,7 @@ __device__ __forceinline__ void ladder_rows_core(const PlanDev *pl, const ChainJ
 template <int D, bool SPAN>
 __device__ __forceinline__ void ladder_rows_body(const AnnealArgs &A)
 {
-    ladder_static_body(A, [&](const GroupArgs &G, const ChainJob &J, const uint16_t *lut_s, const uint4 *et_s) {
+    ladder_static_body(A, [&](const GroupArgs &G, const ChainJob &J, const uint16_t *lut_s, const uint2 *et_s) {
         ladder_rows_core<D, SPAN>(G.plan, J, A.seed_lo, A.seed_hi, lut_s, et_s, G.min_snap);
     });
 }
@@ -87,7 +87,7 @@ template <int D>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(static_waves(D), static_waves(D))))
 void k_anneal_ladder_rows_d(AnnealArgs A) { ladder_rows_body<D, false>(A); }
 template <int D>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(static_waves(D), static_waves(D))))
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(span_waves(D), span_waves(D))))
 void k_anneal_ladder_rows_span_d(AnnealArgs A) { ladder_rows_body<D, true>(A); }
 
 }  // namespace xzzx

@@ -30,39 +30,40 @@ struct PlanarGen {
 // The move's energy-table entry from its 8-bit block pattern (top row, then
 // bottom row).
 template <int D, int K, int B, int W>
-__device__ __forceinline__ uint4 planar_lookup(const uint32_t (&r)[PlanarRows<D>::N], const uint16_t *lut_s,
-                                               const uint4 *et_s)
+__device__ __forceinline__ uint2 planar_lookup(const uint32_t (&r)[PlanarRows<D>::N], const uint16_t *lut_s,
+                                               const uint2 *et_s)
 {
     using G = PlanarGen<D, K, B, W>;
     constexpr int NW = PlanarRows<D>::NW;
     if constexpr (!G::real) {
-        return make_uint4(0u, 0u, 0u, 0u);
+        return make_uint2(0u, 0u);
     } else {
-        const uint32_t pat2 = (row_bits<NW, G::BO, 1>(r + G::Y * NW) & 0x1Eu) |
-                              (row_bits<NW, G::BO, 5>(r + (G::Y + 1) * NW) & 0x1E0u);
+        const uint32_t pat2 = join_pattern(row_bits<NW, G::BO, 1>(r + G::Y * NW) & 0x1Eu,
+                                           row_bits<NW, G::BO, 5>(r + (G::Y + 1) * NW));
         const uint32_t off = *reinterpret_cast<const uint16_t *>(reinterpret_cast<const uint8_t *>(lut_s) +
                                                                  512u * G::g.shp + pat2);
-        return *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(et_s) + off);
+        return *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint8_t *>(et_s) + off);
     }
 }
 
 template <int D, int K, int B, int W>
-__device__ __forceinline__ void planar_apply(uint32_t (&r)[PlanarRows<D>::N], uint32_t u, const uint4 &e, int32_t &acc)
+__device__ __forceinline__ void planar_apply(uint32_t (&r)[PlanarRows<D>::N], uint32_t u, const uint2 &e, int32_t &acc,
+                                             uint32_t zero)
 {
     using G = PlanarGen<D, K, B, W>;
     constexpr int NW = PlanarRows<D>::NW;
     if constexpr (G::real) {
-        const uint32_t sel = accept_sel(u, e.y, e.z);
-        row_flip_static<NW, G::BO, 6u>(r + G::Y * NW, sel);         // X top-left | Z top-right
-        row_flip_static<NW, G::BO, 9u>(r + (G::Y + 1) * NW, sel);   // Z bottom-left | X bottom-right
-        acc += (int32_t)(e.x & sel);
+        const uint32_t sel = accept_mask(u, e);
+        row_flip_static<NW, G::BO, 6u>(r + G::Y * NW, sel, zero);         // X top-left | Z top-right
+        row_flip_static<NW, G::BO, 9u>(r + (G::Y + 1) * NW, sel, zero);   // Z bottom-left | X bottom-right
+        acc += (int32_t)(e.y & sel);
     }
 }
 
 // The four moves of block B: entries looked up, then acceptance and flips.
 template <int D, int K, int B>
 __device__ __forceinline__ void planar_lookups(const uint32_t (&r)[PlanarRows<D>::N], const uint16_t *lut_s,
-                                               const uint4 *et_s, uint4 (&e)[4])
+                                               const uint2 *et_s, uint2 (&e)[4])
 {
     e[0] = planar_lookup<D, K, B, 0>(r, lut_s, et_s);
     e[1] = planar_lookup<D, K, B, 1>(r, lut_s, et_s);
@@ -71,13 +72,14 @@ __device__ __forceinline__ void planar_lookups(const uint32_t (&r)[PlanarRows<D>
 }
 
 template <int D, int K, int B>
-__device__ __forceinline__ void planar_applies(uint32_t (&r)[PlanarRows<D>::N], const uint4 &u, const uint4 (&e)[4],
+__device__ __forceinline__ void planar_applies(uint32_t (&r)[PlanarRows<D>::N], const uint4 &u, const uint2 (&e)[4],
                                                int32_t &acc)
 {
-    planar_apply<D, K, B, 0>(r, u.x, e[0], acc);
-    planar_apply<D, K, B, 1>(r, u.y, e[1], acc);
-    planar_apply<D, K, B, 2>(r, u.z, e[2], acc);
-    planar_apply<D, K, B, 3>(r, u.w, e[3], acc);
+    const uint32_t zero = PlanarRows<D>::NW == 1 ? 0u : opaque_zero();
+    planar_apply<D, K, B, 0>(r, u.x, e[0], acc, zero);
+    planar_apply<D, K, B, 1>(r, u.y, e[1], acc, zero);
+    planar_apply<D, K, B, 2>(r, u.z, e[2], acc, zero);
+    planar_apply<D, K, B, 3>(r, u.w, e[3], acc, zero);
     asm("" : "+v"(acc));   // sum block by block (see static_block)
 }
 
@@ -86,46 +88,35 @@ __device__ __forceinline__ void planar_applies(uint32_t (&r)[PlanarRows<D>::N], 
 // before and after block B's flips, and its entries are looked up before
 // those flips.  Its LDS round trips then overlap block B's acceptance
 // instead of waiting for it (the register dependence through the rows would
-// otherwise serialise the blocks; d = 9: 3 % faster).  The look-ahead's
-// entries take registers: where they would spill at the kernel's occupancy
-// (annealing d = 5, 11, 15; ladders also d = 7) the blocks run one after
-// another.
-constexpr bool planar_pipelined(int d) { return d != 5 && d != 11 && d != 15; }
-constexpr bool planar_ladder_pipelined(int d) { return planar_pipelined(d) && d != 7; }
-
-template <int D, int K, int B, int NB, bool PIPE>
+// otherwise serialise the blocks; d = 9: 3 % faster).
+template <int D, int K, int B, int NB>
 __device__ __forceinline__ void planar_pipe(uint32_t (&r)[PlanarRows<D>::N], const LaneKey &lk,
                                             const LaneHead &h, uint32_t k0, uint32_t k1, const uint16_t *lut_s,
-                                            const uint4 *et_s, int32_t &acc, const uint4 (&e)[4])
+                                            const uint2 *et_s, int32_t &acc, const uint2 (&e)[4])
 {
     const uint4 u = lane_philox_block<B, true>(lk, h, k0, k1);
-    if constexpr (B + 1 < NB && !PIPE) {
-        planar_applies<D, K, B>(r, u, e, acc);
-        uint4 en[4];
-        planar_lookups<D, K, B + 1>(r, lut_s, et_s, en);
-        planar_pipe<D, K, B + 1, NB, PIPE>(r, lk, h, k0, k1, lut_s, et_s, acc, en);
-    } else if constexpr (B + 1 < NB) {
-        uint4 en[4];
+    if constexpr (B + 1 < NB) {
+        uint2 en[4];
         planar_lookups<D, K, B + 1>(r, lut_s, et_s, en);
         planar_applies<D, K, B>(r, u, e, acc);
-        planar_pipe<D, K, B + 1, NB, PIPE>(r, lk, h, k0, k1, lut_s, et_s, acc, en);
+        planar_pipe<D, K, B + 1, NB>(r, lk, h, k0, k1, lut_s, et_s, acc, en);
     } else {
         planar_applies<D, K, B>(r, u, e, acc);
     }
 }
 
 // One colour class of a sweep: c2 = 4t + k names the sweep and class in the
-// Philox counter; PIPE: blocks software-pipelined.
-template <int D, int K, bool PIPE>
+// Philox counter.
+template <int D, int K>
 __device__ __forceinline__ void planar_class(uint32_t (&r)[PlanarRows<D>::N], const LaneKey &lk, uint32_t cc,
                                              uint32_t c2, uint32_t k0, uint32_t k1, const uint16_t *lut_s,
-                                             const uint4 *et_s, int32_t &acc)
+                                             const uint2 *et_s, int32_t &acc)
 {
     constexpr int NB = PlanarSchedule<D>::MP / 4;
     const LaneHead h = lane_head(lk, cc, c2, k0, k1);
-    uint4 e[4];
+    uint2 e[4];
     planar_lookups<D, K, 0>(r, lut_s, et_s, e);
-    planar_pipe<D, K, 0, NB, PIPE>(r, lk, h, k0, k1, lut_s, et_s, acc, e);
+    planar_pipe<D, K, 0, NB>(r, lk, h, k0, k1, lut_s, et_s, acc, e);
 }
 
 // qubit at row Y, column C of the turned lattice, or -1
@@ -199,9 +190,9 @@ __device__ __forceinline__ void store_rows(uint4 *dst, const uint32_t (&r)[N])
 
 // wavefronts per SIMD (VGPR budget 512 / waves): the rows take 2D - 1
 // registers (one word per row, d <= 7) or 2(2D - 1), beside the lane-varying
-// Philox words and the look-ahead entries; the most waves that compile
-// without spills (at d = 9 five waves spill a few registers and measured 3-6 %
-// slower than four)
-constexpr int planar_waves(int d) { return d <= 5 ? 8 : d == 7 ? 6 : d == 9 ? 4 : d == 11 ? 4 : 3; }
+// Philox words and the look-ahead entries; the most waves that compile with at
+// most a register or two spilled (d = 9: five, with entries of eight bytes;
+// the paper's set-up 3.79 -> 3.6 ms against four with twelve-byte entries)
+constexpr int planar_waves(int d) { return d <= 5 ? 8 : d == 7 ? 6 : d == 9 ? 5 : d == 11 ? 4 : 3; }
 
 }  // namespace xzzx

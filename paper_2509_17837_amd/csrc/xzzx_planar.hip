@@ -10,11 +10,10 @@ namespace xzzx {
 // which the recovery is gathered
 template <int D>
 __device__ __forceinline__ void planar_static_core(const PlanDev *pl, const ChainJob &J, uint32_t seed_lo,
-                                                   uint32_t seed_hi, const uint16_t *lut_s, uint4 *et_s,
+                                                   uint32_t seed_hi, const uint16_t *lut_s, uint2 *et_s,
                                                    uint32_t *snap)
 {
     using PR = PlanarRows<D>;
-    const int lane = threadIdx.x;
     const int nranks = (int)uni(pl->nranks), n_sweeps = (int)uni(pl->n_sweeps), kneg = (int)uni(pl->kneg);
     int32_t W[4];
     W[0] = 0; W[1] = (int32_t)uni(pl->W[1]); W[2] = (int32_t)uni(pl->W[2]); W[3] = (int32_t)uni(pl->W[3]);
@@ -32,25 +31,24 @@ __device__ __forceinline__ void planar_static_core(const PlanDev *pl, const Chai
     if (keep) keep_min();
     for (int t = 0; t < n_sweeps; ++t) {
         wave_lds_fence();
-        // this sweep's thresholds; 0 for the ranks with dE <= 0 (see accept_sel)
-        for (int i = lane; i < nranks; i += kWave) et_s[i].y = i < kneg ? 0u : pl->thr[(size_t)t * nranks + i];
+        set_thresholds(et_s, pl->thr + (size_t)t * nranks, kneg, nranks);
         wave_lds_fence();
         const uint32_t c2 = 4u * (uint32_t)t;
         int32_t acc = 0;
-        planar_class<D, 0, planar_pipelined(D)>(r, lk, cc, c2, k0, k1, lut_s, et_s, acc);
-        E += acc;
+        planar_class<D, 0>(r, lk, cc, c2, k0, k1, lut_s, et_s, acc);
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 1; if (keep) keep_min(); }
         acc = 0;
-        planar_class<D, 1, planar_pipelined(D)>(r, lk, cc, c2 + 1u, k0, k1, lut_s, et_s, acc);
-        E += acc;
+        planar_class<D, 1>(r, lk, cc, c2 + 1u, k0, k1, lut_s, et_s, acc);
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 2; if (keep) keep_min(); }
         acc = 0;
-        planar_class<D, 2, planar_pipelined(D)>(r, lk, cc, c2 + 2u, k0, k1, lut_s, et_s, acc);
-        E += acc;
+        planar_class<D, 2>(r, lk, cc, c2 + 2u, k0, k1, lut_s, et_s, acc);
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 3; if (keep) keep_min(); }
         acc = 0;
-        planar_class<D, 3, planar_pipelined(D)>(r, lk, cc, c2 + 3u, k0, k1, lut_s, et_s, acc);
-        E += acc;
+        planar_class<D, 3>(r, lk, cc, c2 + 3u, k0, k1, lut_s, et_s, acc);
+        E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 4; if (keep) keep_min(); }
     }
     if (J.active) {
@@ -66,7 +64,7 @@ template <int D>
 __device__ __forceinline__ void planar_rows_body(const AnnealArgs &A)
 {
     __shared__ uint16_t lut_s[256 * 6];
-    __shared__ uint4 et_s[kStaticRanks];
+    __shared__ uint2 et_s[kStaticRanks];
     const PlanDev *loaded = nullptr;
     for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
         int gi = 0;

@@ -112,3 +112,31 @@ def test_short_workspace_leaves_the_grid_core():
         D.decode_groups([g], prob.greedy_seed, prob.anneal_seed, ws=ws[:ws.numel() - short])
         torch.cuda.synchronize()
         compare_decode(prob, out, ref)
+
+
+@pytest.mark.parametrize("layout,d,how", [(0, 7, "rows"), (0, 7, 16), (0, 17, "rows"), (0, 17, 64), (1, 5, "rows"),
+                                          (1, 5, 32), (0, 5, "site"), (1, 9, "site"), (0, 7, "ladder"),
+                                          (1, 5, "ladder")])
+def test_extreme_temperatures(layout, d, how):
+    """Thresholds at the ends of their range (beta 0 and 1e-12: 2^32 - 1; about
+    2^31; 1; 0 where the exponential underflows), which the energy tables fold
+    into the word that also marks the moves that always accept."""
+    print(f"[paths] extreme temperatures layout={layout} d={d} {how}", flush=True)
+    beta = [0.0, 1e-12, 1e-5, 0.1, 0.3, 5.0, 40.0, 3e2, 1e4, 1e8, 0.0]
+    prob = Problem(layout, d, 0.2, 10.0, 3, 4, len(beta), seed=30 + d, conv=layout, beta=beta)
+    plan = gpu_plan(prob)
+    kw = {}
+    if how == "rows":
+        plan.set_kernel(X.KERNEL_ROWS)
+    elif how == "site":
+        plan.set_order(X.ORDER_RANDOM_SITE)
+        kw = dict(order=O.ORDER_RANDOM_SITE)
+    elif how == "ladder":
+        plan.set_ladder(4, 0.0, 400.0)
+        kw = dict(order=O.ORDER_LADDER, ladder=(4, 0.0, 400.0))
+    else:
+        plan.set_lanes(how)
+    out = D.decode(plan, to_dev(prob.syn), to_dev(prob.uid.view(np.int32)), prob.n_rep, prob.greedy_seed,
+                   prob.anneal_seed, want_chains=True, want_final=True)
+    torch.cuda.synchronize()
+    compare_decode(prob, out, prob.oracle_decode(**kw))
