@@ -469,127 +469,6 @@ __device__ inline void bytes_core(const PlanDev *pl, const ChainJob &J, int t_be
 }
 
 // ---------------------------------------------------------------------------
-// Random-site core (Algs. 2-3 as printed): every step picks one generator
-// uniformly at random, so the steps of a chain are sequential and the
-// parallelism is across chains: one chain per lane, 64 per wavefront.  The
-// state of chain c is packed 2 bits per qubit, qubit q at bits 2 (q mod 16)
-// of word q div 16, and word w of chain c at LDS word 64 w + c: whatever
-// qubits the lanes pick, one instruction's accesses fall in distinct banks.
-// Position nq is scratch for absent generator slots.  Step m of sweep t uses
-// Philox(uid, chain, 2^31 + t, m div 2): words 2 (m mod 2) and 2 (m mod 2) + 1
-// are the site draw (site = floor(u N_stab / 2^32), face-id order) and the
-// acceptance draw.  E_min is tracked after every step; stop = t N_stab + m + 1
-// (0 = the start), and the state at the first E_min is kept in `snap` (word w
-// of chain ci at snap[w * snap_stride + ci]) for the recovery.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ int site_words(int nq) { return nq / 16 + 1; }
-
-__device__ inline void site_core(const PlanDev *pl, const ChainJob &J, uint32_t seed_lo, uint32_t seed_hi,
-                                 uint8_t *smem, uint32_t *snap, int64_t snap_stride)
-{
-    const int c = threadIdx.x;
-    const int nq = pl->nq, nstab = pl->nstab, nranks = pl->nranks, n_sweeps = pl->n_sweeps;
-    const uint32_t kneg = (uint32_t)pl->kneg;
-    int32_t W[4];
-    W[0] = pl->W[0]; W[1] = pl->W[1]; W[2] = pl->W[2]; W[3] = pl->W[3];
-    const LdsLayout lo = lds_layout(pl->M, pl->ntypes, nranks);
-    const uint2 *desc_s = reinterpret_cast<const uint2 *>(smem + lo.desc);   // by face id
-    const uint8_t *lut_s = smem + lo.lut;
-    int2 *et_s = reinterpret_cast<int2 *>(smem + lo.et);
-    uint32_t *st = reinterpret_cast<uint32_t *>(smem + lo.state);
-    const int nw = site_words(nq);
-    const uint32_t uid = J.uid, cc = J.cc;
-
-    const bool use_x = (J.lp == 1 || J.lp == 2), use_z = (J.lp == 2 || J.lp == 3);
-    int32_t E = 0;
-    for (int w = 0; w < nw; ++w) {
-        uint32_t word = 0;
-        for (int i = 0; i < 16; ++i) {
-            const int q = 16 * w + i;
-            if (q >= nq) break;
-            uint32_t v = J.active ? (J.src[q] & 3u) : 0u;
-            if (use_x) v ^= pl->lx[q];
-            if (use_z) v ^= pl->lz[q];
-            word |= v << (2 * i);
-            E += weight_of(W, v);
-        }
-        st[w * kWave + c] = word;
-    }
-    int32_t Emin = E, stop = 0;
-    wave_lds_fence();
-
-    auto save_state = [&](uint8_t *dst) {
-        for (int q = 0; q < nq; ++q) dst[q] = (uint8_t)((st[(q >> 4) * kWave + c] >> (2 * (q & 15))) & 3u);
-    };
-    auto keep_min = [&]() {
-        for (int w = 0; w < nw; ++w) snap[(int64_t)w * snap_stride + J.ci] = st[w * kWave + c];
-    };
-    const bool keep = snap != nullptr && J.active;
-    if (keep) keep_min();
-
-    constexpr int kThrPerLane = (kMaxRanks + kWave - 1) / kWave;
-    uint32_t thr_next[kThrPerLane];
-    auto fetch_thr = [&](int t) {
-#pragma unroll
-        for (int j = 0; j < kThrPerLane; ++j) {
-            const int i = c + j * kWave;
-            thr_next[j] = (t < n_sweeps && i < nranks) ? pl->thr[(size_t)t * nranks + i] : 0u;
-        }
-    };
-    fetch_thr(0);
-
-    auto step = [&](uint32_t u_site, uint32_t u_acc, int32_t s) {
-        const uint32_t f = __umulhi(u_site, (uint32_t)nstab);
-        const uint2 d = desc_s[f];
-        const uint32_t q0 = d.x & 0xFFFFu, q1 = d.x >> 16, q2 = d.y & 0xFFFFu, q3 = (d.y >> 16) & 0x7FFu;
-        uint32_t *a0 = st + (q0 >> 4) * kWave + c, *a1 = st + (q1 >> 4) * kWave + c;
-        uint32_t *a2 = st + (q2 >> 4) * kWave + c, *a3 = st + (q3 >> 4) * kWave + c;
-        const uint32_t s0 = 2u * (q0 & 15u), s1 = 2u * (q1 & 15u), s2 = 2u * (q2 & 15u), s3 = 2u * (q3 & 15u);
-        const uint32_t pat = ((*a0 >> s0) & 3u) | (((*a1 >> s1) & 3u) << 2) | (((*a2 >> s2) & 3u) << 4) |
-                             (((*a3 >> s3) & 3u) << 6);
-        const uint32_t rank = lut_s[((d.y >> 27) << 8) | pat];
-        const int2 et = et_s[rank];
-        if (rank < kneg || u_acc < (uint32_t)et.y) {
-            // slots 0 and 3 carry X, slots 1 and 2 carry Z; slots of one
-            // generator may share a word, so each is read, flipped and written
-            *a0 ^= 2u << s0;
-            *a1 ^= 1u << s1;
-            *a2 ^= 1u << s2;
-            *a3 ^= 2u << s3;
-            E += et.x;
-        }
-        if (E < Emin) {
-            Emin = E;
-            stop = s + 1;
-            if (keep) keep_min();
-        }
-    };
-
-    for (int t = 0; t < n_sweeps; ++t) {
-#pragma unroll
-        for (int j = 0; j < kThrPerLane; ++j)
-            if (c + j * kWave < nranks) et_s[c + j * kWave].y = (int)thr_next[j];
-        wave_lds_fence();
-        fetch_thr(t + 1);
-        const int32_t s0 = t * nstab;
-        for (int m = 0; m < nstab; m += 2) {
-            const uint4 r = philox4x32_10(make_uint4(uid, cc, 0x80000000u + (uint32_t)t, (uint32_t)m >> 1),
-                                          seed_lo, seed_hi);
-            step(r.x, r.y, s0 + m);
-            if (m + 1 < nstab) step(r.z, r.w, s0 + m + 1);
-        }
-        wave_lds_fence();
-    }
-    if (J.active) {
-        J.emin[J.ci] = Emin;
-        J.stop[J.ci] = stop;
-        J.efin[J.ci] = E;
-        if (J.states) save_state(J.states + (size_t)J.ci * nq);
-    }
-    wave_lds_fence();
-}
-
-// ---------------------------------------------------------------------------
 // Packed-row core (rotated lattices, d <= 29): one chain per lane.  The padded
 // grid (columns and rows -1..d) is stored as 2-bit codes, each lattice row in
 // NW 32-bit words; word w of row Y of the chain in lane l sits at
@@ -949,15 +828,8 @@ __device__ __forceinline__ LaneHead lane_head(const LaneKey &lk, uint32_t cc, ui
     return h;
 }
 
-// HOIST: leave the block's first product, which is the same in every sweep, to
-// the compiler, which keeps it in two registers per block for the whole run;
-// otherwise it is taken anew each time.
-template <int B, bool HOIST>
-__device__ __forceinline__ uint4 lane_philox_block(const LaneKey &lk, const LaneHead &h, uint32_t k0,
-                                                     uint32_t k1)
+__device__ __forceinline__ uint4 lane_philox_from(uint32_t z1, const LaneHead &h, uint32_t k0, uint32_t k1)
 {
-    uint32_t z1 = B == 0 ? lk.hk1 : lk.hk1 ^ (uint32_t)B;          // round 0 output z
-    if constexpr (!HOIST) asm volatile("" : "+v"(z1));
     const uint64_t p1 = (uint64_t)z1 * kPhM1;                      // round 1
     const uint32_t x2 = (uint32_t)(p1 >> 32) ^ h.y1k;
     const uint64_t p0 = (uint64_t)x2 * kPhM0;                      // round 2
@@ -975,6 +847,25 @@ __device__ __forceinline__ uint4 lane_philox_block(const LaneKey &lk, const Lane
         k1 += kPhW1;
     }
     return c;
+}
+
+// HOIST: leave the block's first product, which is the same in every sweep, to
+// the compiler, which keeps it in two registers per block for the whole run;
+// otherwise it is taken anew each time.
+template <int B, bool HOIST>
+__device__ __forceinline__ uint4 lane_philox_block(const LaneKey &lk, const LaneHead &h, uint32_t k0,
+                                                   uint32_t k1)
+{
+    uint32_t z1 = B == 0 ? lk.hk1 : lk.hk1 ^ (uint32_t)B;          // round 0 output z
+    if constexpr (!HOIST) asm volatile("" : "+v"(z1));
+    return lane_philox_from(z1, h, k0, k1);
+}
+
+// block b known at run time
+__device__ __forceinline__ uint4 lane_philox_block_at(const LaneKey &lk, const LaneHead &h, uint32_t b, uint32_t k0,
+                                                      uint32_t k1)
+{
+    return lane_philox_from(lk.hk1 ^ b, h, k0, k1);
 }
 
 // Draws of one (sweep, colour class) by Philox block, for tasks whose chains
@@ -1397,14 +1288,12 @@ __device__ inline void load_rows_tables(const PlanDev *pl, uint8_t *smem)
     wave_lds_fence();
 }
 
-// by_face: descriptors in face-id order (random-site core) instead of by
-// (colour class, rank)
-__device__ inline void load_plan_tables(const PlanDev *pl, uint8_t *smem, bool by_face = false)
+__device__ inline void load_plan_tables(const PlanDev *pl, uint8_t *smem)
 {
     const int lane = threadIdx.x;
     const LdsLayout lo = lds_layout(pl->M, pl->ntypes, pl->nranks);
     uint2 *desc_s = reinterpret_cast<uint2 *>(smem + lo.desc);
-    const uint2 *desc_g = reinterpret_cast<const uint2 *>(by_face ? pl->face_desc : pl->desc);
+    const uint2 *desc_g = reinterpret_cast<const uint2 *>(pl->desc);
     for (int i = lane; i < 4 * pl->M; i += kWave) desc_s[i] = desc_g[i];
     const uint32_t *lut_g = reinterpret_cast<const uint32_t *>(pl->lut);
     uint32_t *lut_s = reinterpret_cast<uint32_t *>(smem + lo.lut);
@@ -1447,27 +1336,6 @@ __device__ __forceinline__ void batch_kernel_body(const AnnealArgs &A)
             // a replay from a checkpoint runs one chain per wavefront (uniform t0)
             bytes_core<lg, REPLAY>(G.plan, J, REPLAY ? J.t0 : 0, n_sweeps, A.seed_lo, A.seed_hi, smem);
         }
-    }
-}
-
-// Batch body of the random-site core: tasks of 64 chains; the face
-// descriptors are staged by face id.
-__device__ __forceinline__ void site_kernel_body(const AnnealArgs &A)
-{
-    extern __shared__ __align__(16) uint8_t smem[];
-    const PlanDev *loaded = nullptr;
-    for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
-        int gi = 0;
-        while (gi + 1 < A.n_groups && (int64_t)task >= A.g[gi + 1].task_begin) ++gi;
-        const GroupArgs &G = A.g[gi];
-        const int64_t unit0 = ((int64_t)task - G.task_begin) << 6;
-        if (G.plan != loaded) {
-            wave_lds_fence();
-            load_plan_tables(G.plan, smem, true);
-            loaded = G.plan;
-        }
-        const ChainJob J = batch_job(G, unit0 + threadIdx.x, false);
-        site_core(G.plan, J, A.seed_lo, A.seed_hi, smem, G.min_snap, G.n_chains);
     }
 }
 
@@ -1689,6 +1557,11 @@ void launch_grid_recovery(const uint32_t *snap, int words, const int32_t *best_c
                           const PlanDev *pl, uint8_t *recovery, hipStream_t stream);
 typedef void (*ServeKernel)(const ServeTask *, uint32_t, uint32_t);
 ServeKernel serve_grid_kernel(int mv);
+// random-site kernels (wide: some row of the lattice takes several words) and
+// the recovery gather from the states they keep
+AnnealKernel site_kernel(bool wide, bool replay);
+void launch_site_recovery(const uint32_t *snap, int64_t n_chains, const int32_t *best_chain, int n_rep, int nq,
+                          int64_t n_syn, const PlanDev *pl, uint8_t *recovery, hipStream_t stream);
 
 // The specialised kernels live in several translation units (compiled in
 // parallel): the annealing kernels by distance (each part returns its kernels

@@ -361,6 +361,7 @@ __device__ __forceinline__ void grid_core(const PlanDev *pl, const ChainJob &J, 
         draw_done();
     }
     for (int t = t_begin; t < t_end; ++t) {
+        lds_order();
 #pragma unroll
         for (int j = 0; j < kThr; ++j) lds_write32(tpos[j], thr_next[j]);
         fetch_thr(t + 1);

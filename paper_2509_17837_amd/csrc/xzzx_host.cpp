@@ -225,9 +225,17 @@ size_t Plan::lds_bytes_ladder() const
     return (off + 15) & ~size_t(15);
 }
 
-// Random-site kernel: the tables as above (descriptors in face-id order),
-// then 64 chains of nq / 16 + 1 packed words.
-size_t Plan::lds_bytes_site() const
+// Random-site kernel: the entries and a spare one, the descriptors, the states
+// of `waves` wavefronts.
+size_t Plan::lds_bytes_site(int waves) const
+{
+    return ((8 * ((size_t)hdev.grid_slots + 1) + 15) & ~size_t(15)) + ((8 * (size_t)lat.nstab + 255) & ~size_t(255)) +
+           4 * (size_t)kWave * hdev.site_words * waves;
+}
+
+// The lattices the random-site order takes: descriptors, shape tables, entries
+// and 64 chains of nq / 16 + 1 words within 64 KiB.
+size_t Plan::lds_site_limit() const
 {
     size_t off = 0;
     off += sizeof(Desc) * 4 * lat.per_class;
@@ -452,7 +460,14 @@ struct GridTables {
     std::vector<uint2> move;        // [4][mpad + 1]
     std::vector<uint32_t> entry;
     std::vector<uint16_t> cell;
+    // random-site core
+    int site_words = 0, site_wide = 0;
+    std::vector<uint2> site_desc;
+    std::vector<uint16_t> site_pos;
 };
+
+static bool build_site(const Lattice &L, GridTables &T, const std::vector<int> &base,
+                       const std::vector<int> &shape_of_face, const std::function<int(int)> &corner);
 
 // The lattice as a grid of bytes in which every generator is a 2 x 2 block:
 // rotated, qubit (x, y) in row y + 1 and column x + 1 of rows of d + 1 bytes
@@ -548,7 +563,76 @@ static bool build_grid(const Lattice &L, const std::vector<int32_t> &dE, const s
             if ((corner(f) & 1) != (k & 1)) return false;
             T.move[k * (mpad + 1) + m] = make_uint2((uint32_t)corner(f) | ((uint32_t)(8 * base[shape_of_face[f]]) << 16), flip);
         }
-    return true;
+    return build_site(L, T, base, shape_of_face, corner);
+}
+
+// The random-site core's packing: each row of the grid a run of 2-bit codes
+// from bit 2 or later of a word, so a generator's two cells of a row are four
+// adjacent bits, and a cell left of the run falls on bits of the same word.
+// Rows that fit share words, but never with the row above or below (the core
+// writes both rows of a block back); a row too long for a word takes the next
+// ones to itself (site_wide: the core then reads and writes word pairs, the
+// upper row's first, so the word after the lower row's is not the upper's).  Rows
+// of a block that hold none of its qubits are a scratch word.
+static bool build_site(const Lattice &L, GridTables &T, const std::vector<int> &base,
+                       const std::vector<int> &shape_of_face, const std::function<int(int)> &corner)
+{
+    const int rows = L.layout == XZZX_ROTATED ? L.d + 2 : 2 * L.d - 1;
+    std::vector<int> lo(rows, INT32_MAX), hi(rows, -1), word(rows, -1), bit(rows, 0), used, width(rows, 0);
+    for (int q = 0; q < L.nq; ++q) {
+        const int r = T.cell[q] / T.pitch, c = T.cell[q] % T.pitch;
+        lo[r] = std::min(lo[r], c);
+        hi[r] = std::max(hi[r], c);
+        ++width[r];
+    }
+    for (int r = 0; r < rows; ++r) {
+        if (hi[r] < 0) continue;
+        if (hi[r] - lo[r] + 1 != width[r]) return false;   // a gap
+        const int bits = 2 * width[r];
+        if (2 + bits > 32) {
+            T.site_wide = 1;
+            word[r] = (int)used.size();
+            bit[r] = 2;
+            for (int k = 0; k < (2 + bits + 31) / 32; ++k) used.push_back(32);
+            continue;
+        }
+        for (int w = 0; w < (int)used.size() && word[r] < 0; ++w)
+            if (used[w] + bits <= 32 && (r == 0 || (word[r - 1] != w && word[r - 1] != w + 1))) {
+                word[r] = w;
+                bit[r] = used[w];
+            }
+        if (word[r] < 0) { word[r] = (int)used.size(); bit[r] = 2; used.push_back(2); }
+        used[word[r]] = bit[r] + bits;
+    }
+    const int scratch = (int)used.size();
+    T.site_words = scratch + 1 + T.site_wide;   // a pair reads one word further
+    if (T.site_words > 255) return false;
+    T.site_pos.resize(L.nq);
+    for (int q = 0; q < L.nq; ++q) {
+        const int r = T.cell[q] / T.pitch, c = T.cell[q] % T.pitch;
+        T.site_pos[q] = (uint16_t)(32 * word[r] + bit[r] + 2 * (c - lo[r]));
+    }
+    T.site_desc.resize(L.nstab);
+    for (int f = 0; f < L.nstab; ++f) {
+        const int r0 = corner(f) / T.pitch, c0 = corner(f) % T.pitch;
+        uint32_t at[2] = {32u * scratch, 32u * scratch}, cells = 0;
+        for (int s = 0; s < 4; ++s) {
+            const int q = L.fq[4 * f + s];
+            if (q < 0) continue;
+            const int r = s >> 1, r1 = r0 + r, p = 32 * word[r1] + bit[r1] + 2 * (c0 - lo[r1]);
+            // the nibble's bits of this cell are the qubit's
+            if (p < 0 || p + 2 * (s & 1) != T.site_pos[q]) return false;
+            // a cell left of the run shares its word; one that starts in another word needs a pair
+            if ((p + 2 * (s & 1)) / 32 != p / 32 && !T.site_wide) return false;
+            at[r] = (uint32_t)p;
+            cells |= 3u << (2 * s);
+        }
+        if (at[0] / 32 == at[1] / 32 || (T.site_wide && at[0] / 32 == at[1] / 32 + 1)) return false;
+        T.site_desc[f] = make_uint2((at[0] / 32 * 256) | ((at[1] / 32 * 256) << 16),
+                                    (at[0] % 32) | ((at[1] % 32) << 6) | (cells << 12) |
+                                        ((uint32_t)base[shape_of_face[f]] << 20));
+    }
+    return *std::max_element(base.begin(), base.end()) < 4096;
 }
 
 static inline Desc pack_desc(const Lattice &L, int f, int shape)
@@ -711,7 +795,8 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
 
     GridTables grid;
     P.grid_ok = build_grid(L, all, lut, shape_of_face, shapes, P.kneg, grid) ? 1 : 0;
-    if (!P.grid_ok) grid = GridTables();
+    if (!P.grid_ok) { set_error("inconsistent grid tables"); return XZZX_EINVAL; }   // holds for both layouts
+    P.site_wide = grid.site_wide;
 
     Graph G[2];
     int rc = build_graphs(L, wg, G);
@@ -733,6 +818,8 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
     const size_t o_gmove = take(grid.move.size() * sizeof(uint2));
     const size_t o_gentry = take(grid.entry.size() * 4);
     const size_t o_gcell = take(grid.cell.size() * 2);
+    const size_t o_sdesc = take(grid.site_desc.size() * sizeof(uint2));
+    const size_t o_spos = take(grid.site_pos.size() * 2);
     size_t o_cf[2], o_dint[2], o_db[2], o_adj[2];
     for (int g = 0; g < 2; ++g) {
         o_cf[g] = take(G[g].n * 4);
@@ -757,6 +844,8 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
     put(o_gmove, grid.move.data(), grid.move.size() * sizeof(uint2));
     put(o_gentry, grid.entry.data(), grid.entry.size() * 4);
     put(o_gcell, grid.cell.data(), grid.cell.size() * 2);
+    put(o_sdesc, grid.site_desc.data(), grid.site_desc.size() * sizeof(uint2));
+    put(o_spos, grid.site_pos.data(), grid.site_pos.size() * 2);
     for (int g = 0; g < 2; ++g) {
         put(o_cf[g], G[g].col_face.data(), G[g].n * 4);
         put(o_dint[g], G[g].dint.data(), (size_t)G[g].n * G[g].n * 4);
@@ -803,6 +892,9 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
     h.grid_move = reinterpret_cast<const uint2 *>(base + o_gmove);
     h.grid_entry = reinterpret_cast<const uint32_t *>(base + o_gentry);
     h.grid_cell = reinterpret_cast<const uint16_t *>(base + o_gcell);
+    h.site_words = grid.site_words;
+    h.site_desc = reinterpret_cast<const uint2 *>(base + o_sdesc);
+    h.site_pos = reinterpret_cast<const uint16_t *>(base + o_spos);
     for (int g = 0; g < 2; ++g) {
         h.ncol[g] = G[g].n;
         h.col_face[g] = reinterpret_cast<const int32_t *>(base + o_cf[g]);
@@ -1125,7 +1217,7 @@ int xzzx_plan_set_order(xzzx_plan *plan, int order)
             set_error("random-site steps of a chain must number below 2^31");
             return XZZX_ERANGE;
         }
-        if (plan->P.lds_bytes_site() > 65536) { set_error("random-site chains do not fit in LDS"); return XZZX_ERANGE; }
+        if (std::max(plan->P.lds_site_limit(), plan->P.lds_bytes_site(1)) > 65536) { set_error("random-site chains do not fit in LDS"); return XZZX_ERANGE; }
     }
     plan->P.order = order;
     return XZZX_OK;

@@ -235,6 +235,12 @@ struct PlanDev {
                                    // ranks past the class are idle moves
     const uint32_t *grid_entry;    // [grid_entries] LDS entry | rank << 16
     const uint16_t *grid_cell;     // [nq] byte of each qubit
+    // random-site core: the state packed row by row (see build_site)
+    int site_words;                // 32-bit words of a chain's state
+    const uint2 *site_desc;        // [nstab] by face id: the block's rows' words (byte offsets of 64-word
+                                   // columns, 16 bits each); bit of the upper and (<< 6) the lower row's
+                                   // nibble, present cells << 12, entry table << 20
+    const uint16_t *site_pos;      // [nq] bit of each qubit (32 word + bit)
     // greedy matching, per decoding-graph colour g
     int ncol[2];
     const int32_t *col_face[2];    // node -> face id (ascending)
@@ -261,6 +267,7 @@ struct Plan {
     int planar_ok = 0;             // the planar kernel specialised to d applies
     int planar_d = 0;              // d while that kernel is in use, else 0
     int grid_ok = 0;               // the grid core applies (its tables are in place)
+    int site_wide = 0;             // random-site core: some row takes several words
     int grid_auto = 1;             // no kernel or lane count was asked for: small launches may use the grid core
     int ladder_k = 0;              // replica exchange: levels per ladder (0 = off)
     double ladder_lo = 0, ladder_hi = 0;
@@ -276,7 +283,8 @@ struct Plan {
     size_t lds_bytes_grid(int lanes) const;
     int grid_moves(int lanes) const;   // moves per lane and class of the grid core (0: too many)
     size_t lds_bytes_rows() const;
-    size_t lds_bytes_site() const;
+    size_t lds_bytes_site(int waves) const;
+    size_t lds_site_limit() const;   // bounds the lattices the random-site order takes
 };
 
 

@@ -526,12 +526,11 @@ template <int LOGG>
 __global__ __launch_bounds__(kWave) void k_anneal(AnnealArgs A) { batch_kernel_body<false, LOGG, false>(A); }
 template <int LOGG>
 __global__ __launch_bounds__(kWave) void k_replay(AnnealArgs A) { batch_kernel_body<false, LOGG, true>(A); }
-__global__ __launch_bounds__(kWave) void k_anneal_site(AnnealArgs A) { site_kernel_body(A); }
 
-// Random-site order: each syndrome's recovery is its best chain's state kept
-// at that chain's first E_min (packed words [word][chain]); one thread per
-// (syndrome, qubit).
-__global__ void k_site_recovery(const uint32_t *__restrict__ snap, int64_t n_chains,
+// Generic ladder kernel: each syndrome's recovery is its best chain's state kept
+// at that chain's first E_min (packed words [word][chain], qubit q at bits
+// 2 (q mod 16) of word q div 16); one thread per (syndrome, qubit).
+__global__ void k_packed_recovery(const uint32_t *__restrict__ snap, int64_t n_chains,
                                 const int32_t *__restrict__ best_chain, int n_rep, int nq, int64_t n_syn,
                                 uint8_t *__restrict__ recovery)
 {
@@ -872,17 +871,18 @@ static int ladder_planar_d(const xzzx_group &g)
     return P.planar_d;
 }
 
-// Words per chain of the state kept at E_min: random-site chains and the
-// generic ladder kernel (packed, the position nq scratch), the planar kernels
-// specialised to d and the rotated ladder kernels specialised to d (their
-// rows); 0 for other groups.  A plan's kernel must not change between the
+// Words per chain of the state kept at E_min: random-site chains (their packed
+// rows), the generic ladder kernel (packed, the position nq scratch), the
+// planar kernels specialised to d and the rotated ladder kernels specialised
+// to d (their rows); 0 for other groups.  A plan's kernel must not change between the
 // stages of one decode.
 static int64_t min_snap_words(const xzzx_group &g, bool lean)
 {
     const Plan &P = g.plan->P;
     if (ladder_rows_d(g, lean)) return ladder_rows_state_words(ladder_rows_d(g, lean));
     if (ladder_planar_d(g)) return planar_state_words(ladder_planar_d(g));
-    if (P.order == XZZX_ORDER_RANDOM_SITE || P.ladder_k) return P.lat.nq / 16 + 1;
+    if (P.order == XZZX_ORDER_RANDOM_SITE) return lean ? 0 : P.hdev.site_words;
+    if (P.ladder_k) return P.lat.nq / 16 + 1;
     if (P.use_rows && P.planar_d) return planar_state_words(P.planar_d);
     return 0;
 }
@@ -989,7 +989,9 @@ static size_t group_ws_bytes(const xzzx_group &g, bool decode, int grid, bool le
     if (!g.d_best_chain) b += align256(ns * 4);
     if (grid) return b + align256((size_t)P.hdev.grid_words * nc * 4);
     if (!lean || !spans(g)) b += align256((size_t)checkpoints_of(g) * P.lat.d * P.static_words * nc * 4);
-    b += align256((size_t)min_snap_words(g, lean) * nc * 4);
+    // (random-site calls have been accepted with nq / 16 + 1 words per chain)
+    const size_t snap = lean && P.order == XZZX_ORDER_RANDOM_SITE ? P.lat.nq / 16 + 1 : min_snap_words(g, lean);
+    b += align256(snap * nc * 4);
     return b;
 }
 
@@ -997,7 +999,8 @@ static size_t group_ws_bytes(const xzzx_group &g, bool decode, int grid, bool le
 // accepted with (`least`): the grid core's states may take more than the
 // other kernels' checkpoints, and a call whose workspace is short of them
 // runs on those kernels instead; groups whose tasks span syndromes then keep
-// no checkpoints, and their recoveries are replayed from the references.
+// no checkpoints and random-site groups no states, and their recoveries are
+// replayed from the references.
 static void ws_bytes(const xzzx_group *groups, int n_groups, bool decode, const std::vector<int> &grid, size_t *full,
                      size_t *least)
 {
@@ -1053,10 +1056,10 @@ static int validate_groups(const xzzx_group *groups, int n_groups, bool decode)
     return XZZX_OK;
 }
 
-static int anneal_grid(const void *kernel, size_t lds_bytes, uint32_t n_tasks, unsigned *grid)
+static int anneal_grid(const void *kernel, int block, size_t lds_bytes, uint32_t n_tasks, unsigned *grid)
 {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kWave, lds_bytes) != hipSuccess || per_cu <= 0)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, lds_bytes) != hipSuccess || per_cu <= 0)
         per_cu = 1;
     const uint64_t full = (uint64_t)device_cus() * (uint64_t)per_cu;
     *grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(full, n_tasks));
@@ -1101,6 +1104,22 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
     size_t lds = 0;
     int ng = 0;
     const int lg = log2_int(lanes);
+    // random-site workgroups: up to eight wavefronts share the descriptors and
+    // entries, which fits the device's most wavefronts; one each where there
+    // are too few to give every SIMD two, so that they spread over the CUs
+    int site_waves = 1;
+    bool site_wide = false;
+    if (site) {
+        int64_t waves = 0;
+        size_t most = 0;
+        for (int i : order) waves += (units_of(i) + kWave - 1) / kWave;
+        site_wide = !order.empty() && groups[order[0]].plan->P.site_wide;   // the same for a set
+        for (int w = 2; w <= 8; w *= 2) {
+            most = 0;
+            for (int i : order) most = std::max(most, groups[i].plan->P.lds_bytes_site(w));
+            if (mode == AnnealMode::Persistent && waves >= 8LL * device_cus() && most <= 65536) site_waves = w;
+        }
+    }
     for (int i : order) {
         const xzzx_group &g = groups[i];
         const Plan &P = g.plan->P;
@@ -1127,14 +1146,14 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
         const int64_t units = units_of(i);
         G.n_units = units;
         G.task_begin = (int64_t)tasks;
-        const int C = kWave / lanes;
+        const int C = site ? site_waves * kWave : kWave / lanes;
         tasks += (uint64_t)((units + C - 1) / C);
         lds = std::max(lds, (ladder && (static_d || planar_d))
                                 ? 8 * (size_t)P.ladder_k * P.nranks()
                             : (static_d || planar_d) ? (size_t)0
                             : grid_mv ? P.lds_bytes_grid(lanes)
                             : ladder ? P.lds_bytes_ladder()
-                            : site   ? P.lds_bytes_site()
+                            : site   ? P.lds_bytes_site(site_waves)
                             : rows   ? P.lds_bytes_rows()
                                      : P.lds_bytes_anneal(lanes));
     }
@@ -1148,7 +1167,7 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
                               : (ladder && static_d) ? ladder_rows_kernel(static_d, span)
                               : (ladder && planar_d) ? ladder_planar_kernel(planar_d)
                               : ladder     ? ladder_kernel()
-                              : site     ? k_anneal_site
+                              : site     ? site_kernel(site_wide, replay)
                               : planar_d ? planar_rows_kernel(planar_d)
                               : static_d ? static_rows_kernel(static_d, span)
                               : rows     ? k_anneal_rows
@@ -1156,15 +1175,15 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
     if (mode == AnnealMode::Plain) {
         A.counter = nullptr;
         A.grid = (uint32_t)tasks;
-        hipLaunchKernelGGL(kern, dim3((unsigned)tasks), dim3(kWave), lds, stream, A);
+        hipLaunchKernelGGL(kern, dim3((unsigned)tasks), dim3(kWave * site_waves), lds, stream, A);
         return check_hip(hipGetLastError(), "plain anneal launch");
     }
     unsigned grid = 0;
-    int rc = anneal_grid((const void *)kern, lds, A.n_tasks, &grid);
+    int rc = anneal_grid((const void *)kern, kWave * site_waves, lds, A.n_tasks, &grid);
     if (rc) return rc;
     A.grid = grid;
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, d_counter, 1);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kWave), lds, stream, A);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kWave * site_waves), lds, stream, A);
     return check_hip(hipGetLastError(), "anneal launch");
 }
 
@@ -1272,8 +1291,8 @@ static int fork_join(hipStream_t stream, int n, F launch, bool serial = false)
 // replay re-runs one chain per syndrome with the byte-state kernel, spreading
 // a chain over more lanes when that is needed to give every CU several
 // wavefronts.  Each launch has its own queue counter: launch i of an annealing
-// stage d_counters[i]; a replay (with its own d_counters base) uses [0] and
-// [2].
+// stage d_counters[i]; a replay (with its own d_counters base) uses [0], [2], [4]
+// and [5].
 constexpr int kReplayCounters = 16;   // words before the replay's counters
 static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_groups, AnnealMode mode,
                          uint64_t seed, int64_t unit_offset, int64_t units_override, uint32_t *d_counters,
@@ -1283,7 +1302,7 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
     std::vector<int> bytes_sel[7];
     std::vector<int> static_sel[2][kStaticMaxD + 1];   // [tasks span syndromes][d]
     std::vector<int> replay_cp;   // replays starting from checkpoints: one chain per wavefront
-    std::vector<int> site_sel;    // random-site plans: one chain (replay: syndrome) per lane
+    std::vector<int> site_sel[2]; // random-site plans, by site_wide: one chain (replay: syndrome) per lane
     std::vector<int> planar_sel[kPlanarStaticMaxD + 1];   // planar kernels specialised to d
     std::vector<int> gather_sel;  // replay: recoveries gathered from the states kept at E_min
     std::vector<int> grid_sel[5][4];   // grid core, by lanes per chain (4..64) and moves per lane (1, 2, 4, 8)
@@ -1300,10 +1319,10 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
         }
         if (ws[i].grid || P.order == XZZX_ORDER_RANDOM_SITE || P.ladder_k ||
             (mode == AnnealMode::Replay && min_snap_words(groups[i], ws[i].lean))) {
-            if (mode == AnnealMode::Replay) gather_sel.push_back(i);
+            if (mode == AnnealMode::Replay) (ws[i].min_snap ? gather_sel : site_sel[P.site_wide]).push_back(i);
             else if (const int ld = ladder_rows_d(groups[i], ws[i].lean)) ladder_rows_sel[spans(groups[i])][ld].push_back(i);
             else if (ladder_planar_d(groups[i])) ladder_planar_sel[ladder_planar_d(groups[i])].push_back(i);
-            else (P.ladder_k ? ladder_sel : site_sel).push_back(i);
+            else (P.ladder_k ? ladder_sel : site_sel[P.site_wide]).push_back(i);
             continue;
         }
         total_syn += groups[i].n_syn;
@@ -1329,6 +1348,10 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
         if (!rc)
             rc = launch_set(groups, ws, replay_cp, false, kWave, mode, seed, unit_offset, units_override,
                             d_counters + 2, stream);
+        // random-site groups without kept states: one chain (syndrome) per lane
+        for (int wide = 0; wide < 2 && !rc; ++wide)
+            rc = launch_set(groups, ws, site_sel[wide], false, 1, mode, seed, unit_offset, units_override,
+                            d_counters + 4 + wide, stream, 0, true);
         // groups that kept each chain's state at its E_min: gather
         for (int i : gather_sel) {
             if (rc) break;
@@ -1344,8 +1367,11 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
                 hipLaunchKernelGGL(k_static_recovery, grid, dim3(256), 0, stream, ws[i].min_snap,
                                    (int)min_snap_words(g, ws[i].lean), ws[i].best_chain, g.n_rep, ld, g.n_syn,
                                    2 * (ld + 1) <= 32 ? 1 : 2, g.d_recovery);
-            else if (P.order == XZZX_ORDER_RANDOM_SITE || (P.ladder_k && !ladder_planar_d(g)))
-                hipLaunchKernelGGL(k_site_recovery, grid, dim3(256), 0, stream, ws[i].min_snap, nc, ws[i].best_chain,
+            else if (P.order == XZZX_ORDER_RANDOM_SITE)
+                launch_site_recovery(ws[i].min_snap, nc, ws[i].best_chain, g.n_rep, P.lat.nq, g.n_syn, P.ddev,
+                                     g.d_recovery, stream);
+            else if (P.ladder_k && !ladder_planar_d(g))
+                hipLaunchKernelGGL(k_packed_recovery, grid, dim3(256), 0, stream, ws[i].min_snap, nc, ws[i].best_chain,
                                    g.n_rep, P.lat.nq, g.n_syn, g.d_recovery);
             else
                 hipLaunchKernelGGL(k_rows_recovery, grid, dim3(256), 0, stream, ws[i].min_snap, (int)min_snap_words(g, ws[i].lean),
@@ -1369,7 +1395,8 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
     };
     std::vector<Set> sets;
     if (!rows_sel.empty()) sets.push_back({&rows_sel, true, 1, 0, false, 0, false, 0});
-    if (!site_sel.empty()) sets.push_back({&site_sel, false, 1, 0, true, 0, false, 0});
+    for (auto &sel : site_sel)
+        if (!sel.empty()) sets.push_back({&sel, false, 1, 0, true, 0, false, 0});
     if (!ladder_sel.empty()) sets.push_back({&ladder_sel, false, 1, 0, false, 0, true, 0});
     for (int d = 3; d <= kPlanarStaticMaxD; d += 2)
         if (!planar_sel[d].empty()) sets.push_back({&planar_sel[d], true, 1, 0, false, d, false, 0});

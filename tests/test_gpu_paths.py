@@ -140,3 +140,22 @@ def test_extreme_temperatures(layout, d, how):
                    prob.anneal_seed, want_chains=True, want_final=True)
     torch.cuda.synchronize()
     compare_decode(prob, out, prob.oracle_decode(**kw))
+
+
+@pytest.mark.parametrize("layout,d,n_syn", [(0, 3, 1001), (1, 9, 1001), (0, 13, 37), (0, 17, 5), (1, 31, 3)])
+def test_random_site_workgroups(layout, d, n_syn):
+    """The random-site kernel: rows that share words and rows of several words,
+    one wavefront a workgroup and (from 8 wavefronts per CU) eight, the last
+    workgroup mostly empty; all outputs and, without a final state, the replay."""
+    print(f"[paths] site layout={layout} d={d} n_syn={n_syn}", flush=True)
+    prob = Problem(layout, d, 0.15, 10.0, n_syn, 33, 3, seed=40 + d, conv=layout)
+    plan = gpu_plan(prob)
+    plan.set_order(X.ORDER_RANDOM_SITE)
+    ref = prob.oracle_decode(order=O.ORDER_RANDOM_SITE)
+    syn, uid = to_dev(prob.syn), to_dev(prob.uid.view(np.int32))
+    for short in (0, 1):
+        g, out = D.make_group(plan, prob.n_rep, uid, syn=syn, want_chains=True, want_final=not short)
+        ws = D.workspace([g])
+        D.decode_groups([g], prob.greedy_seed, prob.anneal_seed, ws=ws[:ws.numel() - short])
+        torch.cuda.synchronize()
+        compare_decode(prob, out, ref)
