@@ -120,8 +120,8 @@ __global__ __launch_bounds__(kSynThreads) void k_syndrome(const PlanDev *__restr
 }
 
 // ---------------------------------------------------------------------------
-// Greedy matching (Algs. 5-6) -- one wavefront per (syndrome, replica), one
-// colour per half wavefront or the colours in turn (see k_greedy).
+// Greedy matching (Algs. 5-6) -- one workgroup per syndrome (or per share of
+// its replicas), one wavefront per replica.
 //
 // The sequential rule -- take the free pair of least (weight, key, pair id) --
 // is evaluated as repeated mutual-best elimination: every free defect finds
@@ -131,12 +131,49 @@ __global__ __launch_bounds__(kSynThreads) void k_syndrome(const PlanDev *__restr
 // the rest, so both procedures produce the same matching.  Paths follow the
 // canonical tight-edge walk (smallest edge id) and are XOR-ed into the
 // configuration with LDS atomics (paths may overlap).
+//
+// Only the keys differ between replicas.  So the workgroup first finds, all
+// wavefronts together, the defects, the pair weights (kept in LDS where they
+// fit) and each defect's partners at its least weight; a replica's first round
+// draws the keys of those ties alone, spread evenly over the lanes.  Then each
+// wavefront goes on by itself (later rounds, paths, output) without barriers.
+// The first round's scan was 40-70 % of the time when every replica did it,
+// gathering distances through L1 at a line per lane.
+// Bound now by latency and instruction issue of the later rounds and the walks.
+// Measured before -> now (references alone): d = 21, 1021 syndromes x 10: 578 ->
+// 259 us; d = 31, 512 x 32: 3.71 -> 1.16 ms; d = 11, 8192 x 32: 1211 -> 688 us;
+// planar d = 9, 12288 x 10: 613 -> 367 us; d = 11, 20000 x 1: 160 -> 138 us.
 // ---------------------------------------------------------------------------
-// partners at the least weight a greedy scan lists before keying them, and
-// partners whose interior distances a scan loads at once (the table is in
-// HBM or L2: the loads of a batch overlap)
-constexpr int kGreedyTies = 8;
+// partners whose distances a scan loads at once (the table is in HBM or L2:
+// the loads of a batch overlap)
 constexpr int kGreedyBatch = 4;
+// lanes per defect in the shared scan, wavefronts (replicas) per workgroup
+constexpr int kGreedyRow = 8;
+constexpr int kGreedyWaves = 16;
+
+// LDS of a greedy workgroup, byte offsets.  Shared, per colour set: the tied
+// pairs of the first round, boundary distances, the weight cache, the defects
+// and their first partners; then per wavefront: 8 bytes a defect (see
+// GreedyNode), the configuration and the free flags.
+struct GreedyLds {
+    uint32_t ents, db, weights, defects, first, waves;   // shared arrays, then the wavefronts' parts
+    uint32_t cfg, flags, per_wave;                       // within a wavefront's part
+};
+__host__ __device__ inline GreedyLds greedy_lds_layout(int sets, int stride, int nwords, int cache_entries)
+{
+    GreedyLds L;
+    const uint32_t n = (uint32_t)(sets * stride);
+    L.ents = 0;
+    L.db = L.ents + 4 * 3 * n;
+    L.weights = L.db + 4 * n;
+    L.defects = L.weights + 4 * (uint32_t)(sets * cache_entries);
+    L.first = L.defects + 2 * n;
+    L.waves = (L.first + 2 * n + 7u) & ~7u;
+    L.cfg = 8 * n;
+    L.flags = L.cfg + 4 * (uint32_t)nwords;
+    L.per_wave = (L.flags + n + 7u) & ~7u;
+    return L;
+}
 
 struct GreedyArgs {
     const PlanDev *plan;
@@ -148,14 +185,16 @@ struct GreedyArgs {
     const int32_t *slot_map;   // optional: syndrome s writes to slot slot_map[s]
     int64_t refs_stride;       // bytes between slots (with slot_map)
     int64_t qraw_stride;
-    int64_t n_syn;
     int n_rep;
     int mode;
     uint32_t seed_lo, seed_hi;
-    int max_nodes;
-    int rep_div;               // ladders: replica r draws the keys of replica r / rep_div (0 or 1: itself)
+    int stride;                // defects a colour can have, and the virtual node, rounded up
+    int rep_div;               // ladders: replicas of equal r / rep_div share a reference (1: each its own)
     int cache_entries;         // LDS words per colour for the pair weights (0: none)
-    int64_t block0;            // (syndrome, replica) pair of workgroup 0 of this launch
+    int n_units;               // references per syndrome: n_rep / rep_div, rounded up
+    int shares;                // workgroups per syndrome
+    int unit_step;             // wavefronts per syndrome: a wavefront's references are so many apart
+    int64_t block0;            // workgroup 0 of this launch
 };
 
 __device__ __forceinline__ void xor_edge(uint32_t *cfgw, int eid)
@@ -165,304 +204,396 @@ __device__ __forceinline__ void xor_edge(uint32_t *cfgw, int eid)
     atomicXor(&cfgw[q >> 2], code << (8 * (q & 3)));
 }
 
-// Canonical walks.  Each step reads the node's four adjacency entries (in
-// edge-id order) and their far ends' distances at once, then takes the first
-// tight edge; the distance of the next node is known (dx - weight), so a step
-// costs two dependent rounds of loads rather than one per entry tried.
-__device__ void walk_interior(const PlanDev *pl, int g, int u, int v, uint32_t *cfgw)
+// The canonical walk from x along tight edges of `dist` (smallest edge id
+// first) to the target node, or, with none (-1), out through the boundary.
+// Each step reads the node's four adjacency entries (in edge-id order) and
+// their far ends' distances at once, then takes the first tight edge; the
+// distance of the next node is known, so a step costs two dependent rounds of
+// loads rather than one per entry tried.
+__device__ __forceinline__ void walk(const PlanDev *pl, int g, const int32_t *dist, int x, int target, uint32_t *cfgw)
 {
     const int n = pl->ncol[g];
-    const int32_t *du = pl->dint[g] + (size_t)u * n;
     const int4 *adj = pl->adj[g];
-    int x = v;
-    int32_t dx = du[x];
-    for (int step = 0; step < n && x != u; ++step) {
+    int32_t dx = dist[x];
+    for (int step = 0; step <= n && x != target; ++step) {
         int4 e[4];
         int32_t de[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) e[s] = adj[4 * x + s];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) de[s] = (e[s].x >= 0 && e[s].y >= 0) ? du[e[s].y] : -1;
-        int nxt = -1;
+        for (int s = 0; s < 4; ++s) de[s] = e[s].y >= 0 ? dist[e[s].y] : 0;   // an edge to the boundary: distance 0
+        int edge = -1, next = -1;
+        int32_t dn = 0;
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-            if (nxt < 0 && e[s].x >= 0 && e[s].y >= 0 && de[s] + e[s].z == dx) {
-                xor_edge(cfgw, e[s].x);
-                nxt = e[s].y;
-                dx = de[s];
+        for (int s = 3; s >= 0; --s)
+            if (e[s].x >= 0 && (target < 0 || e[s].y >= 0) && de[s] + e[s].z == dx) {
+                edge = e[s].x;
+                next = e[s].y;
+                dn = de[s];
             }
-        if (nxt < 0) return;
-        x = nxt;
+        if (edge < 0) return;
+        xor_edge(cfgw, edge);
+        if (next < 0) return;
+        x = next;
+        dx = dn;
     }
 }
 
-__device__ void walk_boundary(const PlanDev *pl, int g, int u, uint32_t *cfgw)
+template <int CTRL>
+__device__ __forceinline__ uint32_t quad_swap(uint32_t v)   // of lane ^ 1 (0xB1) or lane ^ 2 (0x4E)
 {
-    const int n = pl->ncol[g];
-    const int32_t *db = pl->db[g];
-    const int4 *adj = pl->adj[g];
-    int x = u;
-    int32_t dx = db[x];
-    for (int step = 0; step <= n; ++step) {
-        int4 e[4];
-        int32_t de[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) e[s] = adj[4 * x + s];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) de[s] = (e[s].x >= 0 && e[s].y >= 0) ? db[e[s].y] : -1;
-        // the first tight entry in edge-id order: a boundary half-edge ends the walk
-        int nxt = -1;
-        bool done = false;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            if (done || nxt >= 0 || e[s].x < 0) continue;
-            if (e[s].y < 0) {
-                if (e[s].z == dx) { xor_edge(cfgw, e[s].x); done = true; }
-            } else if (de[s] + e[s].z == dx) {
-                xor_edge(cfgw, e[s].x);
-                nxt = e[s].y;
-                dx = de[s];
-            }
-        }
-        if (done || nxt < 0) return;
-        x = nxt;
-    }
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
+
+// A wavefront's 8 bytes per defect.  In the first round the least (key << 32 |
+// partner), for a 64-bit LDS minimum; after it `best` stays the partner and the
+// rest holds three lists: the defects to search for, the free ones, and the
+// matched pairs (pair p in entries 2p and 2p + 1).
+struct GreedyNode {
+    uint16_t best, need, free_list, pair;
+};
+
+// what the shared scan found for a defect: its first partner at the least
+// weight, and whether others tie with it (listed, or, past the list's end, not)
+constexpr uint32_t kGreedyListed = 0x4000u, kGreedyScan = 0x8000u, kGreedyPartner = 0x3FFFu;
 
 // SPLIT: the two decoding-graph colours are independent matchings, so each
-// half of the wavefront (32 lanes) runs one, and both XOR their paths into the
+// half of a wavefront (32 lanes) runs one, and both XOR their paths into the
 // shared configuration -- twice the lanes at work where a colour has no more
 // than a few dozen defects.  Otherwise the whole wavefront runs the colours one
-// after the other.  The kernel waits on memory most of the time, so the split
-// form is held to eight wavefronts per SIMD (64 VGPRs; at its natural 68 it
-// ran seven, and the d = 11 and planar d = 9 greedy stages took 4-5 % longer).
-template <bool SPLIT>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(SPLIT ? 8 : 1, 8))) void k_greedy(GreedyArgs A)
+// after the other.
+// SEVERAL (with SPLIT): a wavefront takes several references of its syndrome
+// in turn.
+// The kernel waits on memory and LDS most of the time, so the split form is
+// held to eight wavefronts per SIMD (64 VGPRs); with several references the
+// loop's state spills at that, and seven were 6-12 % faster.
+template <bool SPLIT, bool SEVERAL>
+__global__ __launch_bounds__(kGreedyWaves *kWave)
+    __attribute__((amdgpu_waves_per_eu(SEVERAL ? 7 : SPLIT ? 8 : 4, 8))) void k_greedy(GreedyArgs A)
 {
     extern __shared__ __align__(16) uint8_t smem[];
-    const PlanDev *pl = A.plan;
-    const int lane = threadIdx.x;
-    const int nq = pl->nq;
-    const int64_t sr = A.block0 + blockIdx.x;
-    const int64_t s = sr / A.n_rep;
-    const uint32_t r = (uint32_t)(sr - s * A.n_rep);
-    const uint32_t rkey = A.rep_div > 1 ? r / (uint32_t)A.rep_div : r;
-    const uint32_t uid = A.uid[s];
-    const int nwords = (nq + 3) / 4;
-    constexpr int kHalf = SPLIT ? kWave / 2 : kWave;   // lanes per colour
-    const int hl = lane % kHalf;
-    const int stride = A.max_nodes + 1;
-    uint32_t *cfgw = reinterpret_cast<uint32_t *>(smem);
-    // per colour: D, best, pairs, dbD, the free flags and the list of free
-    // defects (the colours in turn share one set)
+    __shared__ int s_nd[2], s_ents[2], s_scan[2];
     constexpr int kSets = SPLIT ? 2 : 1;
-    int16_t *cands = reinterpret_cast<int16_t *>(reinterpret_cast<int32_t *>(smem + 4 * nwords) + kSets * 4 * stride);
-    // the free flags (bytes), then the free lists (int16, 2-byte aligned),
-    // then the pair-weight cache, 16-byte aligned
-    const uint32_t flags_off = 4u * nwords + kSets * 4 * 4 * stride + 2 * kWave * kGreedyTies;
-    const uint32_t list_off = (flags_off + kSets * stride + 1u) & ~1u;
-    const uint32_t cache_off = (list_off + kSets * 2 * stride + 15u) & ~15u;
-    __shared__ int s_count[2];
-
-    for (int i = lane; i < nwords; i += kWave) cfgw[i] = 0;
-    if (lane == 0) { s_count[0] = 0; s_count[1] = 0; }
+    constexpr int kHalf = SPLIT ? kWave / 2 : kWave;   // lanes per colour
+    const PlanDev *pl = A.plan;
+    const int lane = threadIdx.x % kWave, wave = (int)uni(threadIdx.x / kWave), n_waves = blockDim.x / kWave;
+    const int hl = lane % kHalf;
+    const int nq = pl->nq, nwords = (nq + 3) / 4, stride = A.stride;
+    const int64_t blk = A.block0 + blockIdx.x;
+    const int64_t s = blk / A.shares;
+    const int unit0 = (int)(blk - s * A.shares) * n_waves + wave;
+    const uint32_t uid = A.uid[s];
+    const GreedyLds L = greedy_lds_layout(kSets, stride, nwords, A.cache_entries);
+    uint8_t *mine = smem + L.waves + (uint32_t)wave * L.per_wave;
+    uint32_t *cfgw = reinterpret_cast<uint32_t *>(mine + L.cfg);
+    const bool randomized = A.mode == XZZX_GREEDY_RANDOM;
     const uint8_t *sy = A.syn + s * A.syn_stride;
-    const int n_both = max(pl->ncol[0], pl->ncol[1]);
+    const int ent_cap = 3 * stride;
+
+    // the reference in cfgw and its symplectic products with L_Z and L_X, for
+    // each replica that shares it
+    auto write_out = [&](int unit) {
+        const uint8_t *cb = reinterpret_cast<const uint8_t *>(cfgw);
+        const int r0 = unit * A.rep_div, r1 = min(A.n_rep, r0 + A.rep_div);
+        uint8_t *out = A.slot_map ? A.refs + A.slot_map[s] * A.refs_stride : A.refs + (size_t)s * A.n_rep * nq;
+        uint8_t *qraw_out = A.slot_map ? A.qraw + A.slot_map[s] * A.qraw_stride : A.qraw + s * A.n_rep;
+        uint32_t vz = 0, vx = 0;
+        wave_lds_fence();
+        for (int q = lane; q < nq; q += kWave) {
+            const uint32_t c = cb[q];
+            for (int r = r0; r < r1; ++r) out[(size_t)r * nq + q] = (uint8_t)c;
+            const uint32_t z = pl->lz[q], x = pl->lx[q];
+            vz ^= (((c >> 1) & z) ^ (c & (z >> 1))) & 1;
+            vx ^= (((c >> 1) & x) ^ (c & (x >> 1))) & 1;
+        }
+        const int az = __popcll(__ballot(vz)) & 1;
+        const int ax = __popcll(__ballot(vx)) & 1;
+        for (int r = r0 + lane; r < r1; r += kWave) qraw_out[r] = (uint8_t)(az | (ax << 1));
+        wave_lds_fence();
+    };
     for (int gg = 0; gg < (SPLIT ? 1 : 2); ++gg) {
-        const int g = SPLIT ? lane / kHalf : gg;
-        const int set = SPLIT ? g : 0;
-        int32_t *D = reinterpret_cast<int32_t *>(smem + 4 * nwords) + set * 4 * stride;
-        int32_t *best = D + stride;
-        int32_t *pairs = best + stride;
-        int32_t *dbD = pairs + stride;   // boundary distance of each defect
-        uint8_t *freef = smem + flags_off + set * stride;
-        int16_t *fl = reinterpret_cast<int16_t *>(smem + list_off) + set * stride;
+        // a pair (i, j) weighs the interior distance or the two boundary
+        // distances, whichever is less; a pair with the virtual node (an
+        // odd count) weighs the real defect's boundary distance
+        auto pair_weight = [&](const int32_t *dbD, int nd, int i, int j, int32_t dij) -> uint32_t {
+            return i == nd ? (uint32_t)dbD[j] : j == nd ? (uint32_t)dbD[i] : (uint32_t)min(dij, dbD[i] + dbD[j]);
+        };
+        auto ents_of = [&](int set) { return reinterpret_cast<uint32_t *>(smem + L.ents) + set * ent_cap; };
+        auto db_of = [&](int set) { return reinterpret_cast<int32_t *>(smem + L.db) + set * stride; };
+        auto weights_of = [&](int set) { return reinterpret_cast<uint32_t *>(smem + L.weights) + set * A.cache_entries; };
+        auto defects_of = [&](int set) { return reinterpret_cast<uint16_t *>(smem + L.defects) + set * stride; };
+        auto first_of = [&](int set) { return reinterpret_cast<uint16_t *>(smem + L.first) + set * stride; };
+        // rows of an odd stride: the lanes' reads of one column fall in distinct banks
+        auto cached_of = [&](int na) { return (int64_t)na * (na | 1) <= (int64_t)A.cache_entries; };
+
+        // ---- shared: the defects of each colour, ascending node index ----
+        if (gg) __syncthreads();   // the wavefronts have left the other colour
+        for (int set = wave; set < kSets; set += n_waves) {
+            const int g = SPLIT ? set : gg;
+            const int n = pl->ncol[g];
+            const int32_t *cf = pl->col_face[g], *db = pl->db[g];
+            int nd = 0;
+            for (int base = 0; base < n; base += kWave * kGreedyBatch) {
+                bool flag[kGreedyBatch];
+                int32_t face[kGreedyBatch], dbv[kGreedyBatch];
+#pragma unroll
+                for (int k = 0; k < kGreedyBatch; ++k) {
+                    const int v = min(base + k * kWave + lane, n - 1);
+                    face[k] = cf[v];
+                    dbv[k] = db[v];
+                }
+#pragma unroll
+                for (int k = 0; k < kGreedyBatch; ++k) flag[k] = base + k * kWave + lane < n && sy[face[k]];
+#pragma unroll
+                for (int k = 0; k < kGreedyBatch; ++k) {
+                    const uint64_t mask = __ballot(flag[k]);
+                    const int pos = nd + __popcll(mask & ((1ull << lane) - 1ull));
+                    if (flag[k]) {
+                        defects_of(set)[pos] = (uint16_t)(base + k * kWave + lane);
+                        db_of(set)[pos] = dbv[k];
+                    }
+                    nd += __popcll(mask);
+                }
+            }
+            if (lane == 0) { s_nd[set] = nd; s_ents[set] = 0; s_scan[set] = 0; }
+        }
+        __syncthreads();
+
+        // ---- shared: weights, and each defect's partners at the least one ----
+        if (A.mode != XZZX_GREEDY_BOUNDARY) {
+            const int na0 = s_nd[0] + (s_nd[0] & 1), rows = na0 + (SPLIT ? s_nd[kSets - 1] + (s_nd[kSets - 1] & 1) : 0);
+            const int sub = lane % kGreedyRow;
+            for (int row = threadIdx.x / kGreedyRow; row < rows; row += blockDim.x / kGreedyRow) {
+                const int set = row >= na0 ? 1 : 0;
+                const int g = SPLIT ? set : gg, i = row - set * na0;
+                const int nd = s_nd[set], na = nd + (nd & 1), rs = na | 1;   // odd count: the boundary joins as node nd
+                const int32_t *dbD = db_of(set);
+                const uint16_t *D = defects_of(set);
+                const int32_t *drow = pl->dint[g] + (size_t)(i == nd ? 0 : D[i]) * pl->ncol[g];
+                const bool cached = cached_of(na);
+                uint32_t *wrow = weights_of(set) + i * rs;
+                uint32_t bw = 0xFFFFFFFFu, bj = kGreedyPartner;
+                int nt = 0;   // this lane's partners at weight bw
+                for (int j0 = sub; j0 < na; j0 += kGreedyRow * kGreedyBatch) {
+                    int32_t dv[kGreedyBatch];
+#pragma unroll
+                    for (int k = 0; k < kGreedyBatch; ++k) {
+                        const int j = j0 + kGreedyRow * k;
+                        dv[k] = drow[j < nd ? D[j] : 0];
+                    }
+#pragma unroll
+                    for (int k = 0; k < kGreedyBatch; ++k) {
+                        const int j = j0 + kGreedyRow * k;
+                        if (j >= na || j == i) continue;
+                        const uint32_t w = pair_weight(dbD, nd, i, j, dv[k]);
+                        if (cached) wrow[j] = w;
+                        if (w > bw) continue;
+                        if (w < bw) { bw = w; nt = 0; }
+                        if (nt == 0) bj = (uint32_t)j;
+                        ++nt;
+                    }
+                }
+                uint32_t least = bw;
+#pragma unroll
+                for (int m = 1; m < kGreedyRow; m *= 2) least = min(least, (uint32_t)__shfl_xor((int)least, m));
+                if (bw != least) { nt = 0; bj = kGreedyPartner; }
+                int before = nt;   // ties of the row's lanes up to this one
+#pragma unroll
+                for (int m = 1; m < kGreedyRow; m *= 2) {
+                    bj = min(bj, (uint32_t)__shfl_xor((int)bj, m));
+                    const int o = __shfl_up(before, m, kGreedyRow);
+                    before += sub >= m ? o : 0;
+                }
+                const int all = __shfl(before, kGreedyRow - 1, kGreedyRow);
+                before -= nt;
+                uint32_t mark = 0;
+                if (randomized && all > 1) {
+                    int at = 0;
+                    if (sub == 0) at = atomicAdd(&s_ents[set], all);
+                    at = __shfl(at, 0, kGreedyRow);
+                    mark = at + all <= ent_cap ? kGreedyListed : kGreedyScan;
+                    uint32_t *ents = ents_of(set);
+                    if (mark == kGreedyScan) {
+                        // no room: the places left stay empty
+                        for (int e = at + sub; e < ent_cap; e += kGreedyRow) ents[e] = 0xFFFFFFFFu;
+                        if (sub == 0) s_scan[set] = 1;
+                    } else if (nt > 0) {
+                        at += before;
+                        for (int j = sub; j < na; j += kGreedyRow) {
+                            if (j == i) continue;
+                            const uint32_t w = cached ? wrow[j] : pair_weight(dbD, nd, i, j, drow[j < nd ? D[j] : 0]);
+                            if (w == least) ents[at++] = ((uint32_t)i << 16) | (uint32_t)j;
+                        }
+                    }
+                }
+                if (sub == 0) first_of(set)[i] = (uint16_t)(bj | mark);
+            }
+            __syncthreads();
+        }
+        // ---- this wavefront's replicas (one, where the colours go in turn) ----
+        const int set = SPLIT ? lane / kHalf : 0, g = SPLIT ? set : gg;
+        const int nd = s_nd[set], na = nd + (nd & 1), rs = na | 1;
         const int n = pl->ncol[g];
-        const int32_t *cf = pl->col_face[g];
-        const int32_t *dint = pl->dint[g];
-        const int32_t *db = pl->db[g];
-        // defects of this colour, ascending node index
-        int nd = 0;
-        for (int base = 0; base < (SPLIT ? n_both : n); base += kHalf) {
-            const int v = base + hl;
-            const bool flag = v < n && sy[cf[v]];
-            const uint64_t mask = SPLIT ? ((__ballot(flag) >> (g * kHalf)) & 0xFFFFFFFFull) : __ballot(flag);
-            const int pos = nd + __popcll(mask & ((1ull << hl) - 1ull));
-            if (flag) D[pos] = v;
-            nd += __popcll(mask);
-        }
-        __syncthreads();
-        if (A.mode == XZZX_GREEDY_BOUNDARY) {
-            for (int i = hl; i < nd; i += kHalf) walk_boundary(pl, g, D[i], cfgw);
-        } else {
-            const int na = nd + (nd & 1);   // odd count: the virtual boundary joins as node nd
-            for (int i = hl; i < na; i += kHalf) freef[i] = 1;
-            for (int i = hl; i < nd; i += kHalf) dbD[i] = db[D[i]];
-            __syncthreads();
-            int nfree = na;
-            const bool randomized = A.mode == XZZX_GREEDY_RANDOM;
-            // a pair (i, j) weighs the interior distance or the two boundary
-            // distances, whichever is less; a pair with the virtual node (an
-            // odd count) weighs the real defect's boundary distance
-            auto weight_of_pair = [&](int i, int j, int32_t dj) -> uint32_t {
-                return i == nd ? (uint32_t)dbD[j] : j == nd ? (uint32_t)dbD[i] : (uint32_t)min(dj, dbD[i] + dbD[j]);
+        const int32_t *dint = pl->dint[g], *db = pl->db[g];
+        const uint16_t *D = defects_of(set);
+        const int32_t *dbD = db_of(set);
+        const uint32_t *wc = weights_of(set);
+        const bool cached = cached_of(na);
+        GreedyNode *node = reinterpret_cast<GreedyNode *>(mine) + set * stride;
+        uint8_t *freef = mine + L.flags + set * stride;
+        // of a colour's defects, the ones flagged (per half wavefront)
+        auto half_mask = [&](bool flag) -> uint64_t {
+            const uint64_t m = __ballot(flag);
+            return SPLIT ? (m >> (set * kHalf)) & 0xFFFFFFFFull : m;
+        };
+        const uint64_t below = (1ull << hl) - 1ull;
+        const int na_all = SPLIT ? max(__shfl(na, 0, kWave), __shfl(na, kHalf, kWave)) : na;
+        for (int unit = unit0; unit < A.n_units; unit = SEVERAL ? unit + A.unit_step : A.n_units) {
+            if (SPLIT || gg == 0)
+                for (int i = lane; i < nwords; i += kWave) cfgw[i] = 0;
+            wave_lds_fence();
+            if (A.mode == XZZX_GREEDY_BOUNDARY) {
+                for (int i = hl; i < nd; i += kHalf) walk(pl, g, db, D[i], -1, cfgw);
+                if (SPLIT || gg == 1) write_out(unit);
+                continue;
+            }
+            auto pair_key = [&](int i, int j) {
+                const uint32_t id = (uint32_t)(min(i, j) * na + max(i, j));
+                return philox4x32_10(make_uint4(uid, (uint32_t)unit, 0x100u + (uint32_t)g, id), A.seed_lo, A.seed_hi).x;
             };
-            // every pair weight in LDS when the defects fit the cache (rows of
-            // an odd stride: the lanes' reads of one column fall in distinct
-            // banks), so the rounds after the first scan LDS, not the table in
-            // L2; the weights are the same either way
-            uint32_t *wc = reinterpret_cast<uint32_t *>(smem + cache_off) + set * A.cache_entries;
-            const int rs = na | 1;
-            const bool cached = (int64_t)na * rs <= (int64_t)A.cache_entries;
-            if (cached) {
-                for (int i = hl; i < na; i += kHalf) {
-                    const int32_t *drow = dint + (size_t)(i == nd ? 0 : D[i]) * n;
-                    for (int j0 = 0; j0 < na; j0 += kGreedyBatch) {
-                        int32_t dv[kGreedyBatch];
-#pragma unroll
-                        for (int k = 0; k < kGreedyBatch; ++k) dv[k] = drow[j0 + k < nd ? D[j0 + k] : 0];
-#pragma unroll
-                        for (int k = 0; k < kGreedyBatch; ++k)
-                            if (j0 + k < na) wc[i * rs + j0 + k] = weight_of_pair(i, j0 + k, dv[k]);
-                    }
-                }
+            // the least of each defect's first ties
+            for (int i = hl; i < na; i += kHalf) {
+                const uint32_t f = first_of(set)[i];
+                reinterpret_cast<uint64_t *>(node)[i] = (f & (kGreedyListed | kGreedyScan)) ? ~0ull : (uint64_t)f;
+                freef[i] = 1;
             }
-            __syncthreads();
-            // every round matches at least the least free pair, so na/2 rounds
-            // suffice (rounds continue while either half has work).  Free
-            // defects only leave, so a defect whose least partner is still free
-            // keeps it; only the others search again.
-            const int na_all = SPLIT ? max(__shfl(na, 0, kWave), __shfl(na, kHalf, kWave)) : na;
-            for (int round = 0; __ballot(nfree > 0 && round <= na / 2) != 0; ++round) {
-                // the free defects of this colour, ascending: the defects and
-                // the partners the round scans come from this list, so a late
-                // round skips the ones already matched (the same candidates in
-                // the same order; the greedy stage at d = 31 took half the
-                // time)
-                int nfl = 0;
+            wave_lds_fence();
+            for (int e = hl; e < min(s_ents[set], ent_cap); e += kHalf) {
+                const uint32_t ij = ents_of(set)[e];
+                if (ij == 0xFFFFFFFFu) continue;
+                const uint32_t i = ij >> 16, j = ij & 0xFFFFu;
+                atomicMin(reinterpret_cast<unsigned long long *>(node) + i, ((uint64_t)pair_key((int)i, (int)j) << 32) | j);
+            }
+            wave_lds_fence();
+            // every round matches at least the least free pair, so na / 2 rounds
+            // suffice (rounds continue while either half has work).  Free defects
+            // only leave, so a defect whose least partner is still free keeps it;
+            // only the others search again.
+            int np = 0;
+            for (int round = 0; round <= na_all / 2; ++round) {
+                if (round > 0 || __ballot(s_scan[set]) != 0) {
+                    // the free defects, and of those the ones to search for, ascending
+                    int nfl = 0, nn = 0;
+                    for (int base = 0; base < na_all; base += kHalf) {
+                        const int v = base + hl;
+                        const bool free_v = v < na && freef[v];
+                        const bool need = free_v && (round > 0 ? !freef[node[v].best] : (first_of(set)[v] & kGreedyScan) != 0);
+                        const uint64_t mf = half_mask(free_v), mn = half_mask(need);
+                        if (free_v) node[nfl + __popcll(mf & below)].free_list = (uint16_t)v;
+                        if (need) node[nn + __popcll(mn & below)].need = (uint16_t)v;
+                        nfl += __popcll(mf);
+                        nn += __popcll(mn);
+                    }
+                    wave_lds_fence();
+                    // each one's least (weight, key, id) over the free partners, four
+                    // lanes a defect: the least weight, then keys for the partners at
+                    // it only.  Ids ascend with the partner, so equal keys go to the
+                    // least.
+                    for (int t = hl / 4; t < nn; t += kHalf / 4) {
+                        const int i = node[t].need, sub = lane % 4;
+                        const int32_t *drow = dint + (size_t)(i == nd ? 0 : D[i]) * n;
+                        const uint32_t *wrow = wc + i * rs;
+                        uint32_t bw = 0xFFFFFFFFu, bj = 0xFFFFu;
+                        uint64_t ties = 0;   // this lane's last four partners at weight bw
+                        int nt = 0;
+                        for (int t0 = sub; t0 < nfl; t0 += 4 * kGreedyBatch) {
+                            int32_t dv[kGreedyBatch];
+                            int jj[kGreedyBatch];
+    #pragma unroll
+                            for (int k = 0; k < kGreedyBatch; ++k) jj[k] = t0 + 4 * k < nfl ? (int)node[t0 + 4 * k].free_list : i;
+    #pragma unroll
+                            for (int k = 0; k < kGreedyBatch; ++k)
+                                dv[k] = cached ? (int32_t)wrow[jj[k]] : drow[jj[k] < nd ? D[jj[k]] : 0];
+    #pragma unroll
+                            for (int k = 0; k < kGreedyBatch; ++k) {
+                                const int j = jj[k];
+                                if (j == i) continue;
+                                const uint32_t w = cached ? (uint32_t)dv[k] : pair_weight(dbD, nd, i, j, dv[k]);
+                                if (w > bw) continue;
+                                if (w < bw) { bw = w; nt = 0; }
+                                if (nt == 0) bj = (uint32_t)j;
+                                ties = (ties << 16) | (uint64_t)j;
+                                ++nt;
+                            }
+                        }
+                        uint32_t least = min(bw, quad_swap<0xB1>(bw));
+                        least = min(least, quad_swap<0x4E>(least));
+                        if (bw != least) { nt = 0; bj = 0xFFFFu; }
+                        int all = nt + (int)quad_swap<0xB1>((uint32_t)nt);
+                        all += (int)quad_swap<0x4E>((uint32_t)all);
+                        uint32_t bk = 0;
+                        if (randomized && all > 1) {
+                            bk = 0xFFFFFFFFu;
+                            auto try_partner = [&](uint32_t j) {
+                                const uint32_t key = pair_key(i, (int)j);
+                                if (key < bk || (key == bk && j < bj)) { bk = key; bj = j; }
+                            };
+                            bj = 0xFFFFu;
+                            if (nt <= 4) {
+                                for (int m = 0; m < nt; ++m, ties >>= 16) try_partner((uint32_t)ties & 0xFFFFu);
+                            } else {
+                                for (int m = sub; m < nfl; m += 4) {
+                                    const int j = (int)node[m].free_list;
+                                    if (j == i) continue;
+                                    const int32_t dj = cached ? 0 : drow[j < nd ? D[j] : 0];
+                                    if ((cached ? wrow[j] : pair_weight(dbD, nd, i, j, dj)) == least) try_partner((uint32_t)j);
+                                }
+                            }
+                        }
+                        // the quad's least (key, partner)
+                        uint32_t ok = quad_swap<0xB1>(bk), oj = quad_swap<0xB1>(bj);
+                        if (ok < bk || (ok == bk && oj < bj)) { bk = ok; bj = oj; }
+                        ok = quad_swap<0x4E>(bk);
+                        oj = quad_swap<0x4E>(bj);
+                        if (ok < bk || (ok == bk && oj < bj)) { bk = ok; bj = oj; }
+                        if (sub == 0) node[i].best = (uint16_t)bj;
+                    }
+                    wave_lds_fence();
+                }
+                // pairs that are each other's least
+                const int before = np;
                 for (int base = 0; base < na_all; base += kHalf) {
-                    const int v = base + hl;
-                    const bool flag = v < na && freef[v];
-                    const uint64_t mask = SPLIT ? ((__ballot(flag) >> (g * kHalf)) & 0xFFFFFFFFull) : __ballot(flag);
-                    const int pos = nfl + __popcll(mask & ((1ull << hl) - 1ull));
-                    if (flag) fl[pos] = (int16_t)v;
-                    nfl += __popcll(mask);
-                }
-                __syncthreads();
-                for (int t = hl; t < nfl; t += kHalf) {
-                    const int i = fl[t];
-                    if (round > 0 && best[i] >= 0 && freef[best[i]]) continue;
-                    // least (w, key, id) over free partners j, in two passes: the
-                    // least weight and the partners at it (in ascending j, so
-                    // ascending pair id), then keys for those partners only -- a
-                    // single scan that drew a key on every tie so far made the
-                    // wavefront draw one for nearly every partner.  The interior
-                    // distances of a batch of partners are loaded before any is used.
-                    const bool iv = i == nd;   // the virtual boundary node
-                    const int32_t *drow = dint + (size_t)(iv ? 0 : D[i]) * n;
-                    const uint32_t *wrow = wc + i * rs;
-                    int16_t *cand = cands + lane * kGreedyTies;
-                    auto weight = [&](int j, int32_t dj) -> uint32_t {
-                        return cached ? wrow[j] : weight_of_pair(i, j, dj);
-                    };
-                    uint32_t bw = 0xFFFFFFFFu;
-                    int nt = 0;   // partners at weight bw
-                    for (int t0 = 0; t0 < nfl; t0 += kGreedyBatch) {
-                        int32_t dv[kGreedyBatch];
-                        int jj[kGreedyBatch];
-#pragma unroll
-                        for (int k = 0; k < kGreedyBatch; ++k) jj[k] = t0 + k < nfl ? fl[t0 + k] : na;
-#pragma unroll
-                        for (int k = 0; k < kGreedyBatch; ++k)
-                            dv[k] = cached ? 0 : drow[jj[k] < nd ? D[jj[k]] : 0];
-#pragma unroll
-                        for (int k = 0; k < kGreedyBatch; ++k) {
-                            const int j = jj[k];
-                            if (j >= na || j == i) continue;
-                            const uint32_t w = weight(j, dv[k]);
-                            if (w > bw) continue;
-                            if (w < bw) { bw = w; nt = 0; }
-                            if (nt < kGreedyTies) cand[nt] = (int16_t)j;
-                            ++nt;
-                        }
+                    const int i = base + hl;
+                    const int j = i < na && freef[i] ? (int)node[i].best : 0;
+                    const bool flag = j > i && (int)node[j].best == i;
+                    const uint64_t mask = half_mask(flag);
+                    if (flag) {
+                        const int p = np + __popcll(mask & below);
+                        node[2 * p].pair = (uint16_t)i;
+                        node[2 * p + 1].pair = (uint16_t)j;
                     }
-                    int bj = nt > 0 ? cand[0] : -1;
-                    if (randomized && nt > 1) {
-                        auto pair_id = [&](int j) { return (uint32_t)(min(i, j) * na + max(i, j)); };
-                        auto pair_key = [&](uint32_t id) {
-                            return philox4x32_10(make_uint4(uid, rkey, 0x100u + (uint32_t)g, id), A.seed_lo, A.seed_hi).x;
-                        };
-                        uint32_t bid = pair_id(bj), bk = pair_key(bid);
-                        if (nt <= kGreedyTies) {
-                            for (int t = 1; t < nt; ++t) {
-                                const int j = cand[t];
-                                const uint32_t id = pair_id(j), key = pair_key(id);
-                                if (key < bk) { bk = key; bid = id; bj = j; }   // ids ascend: ties keep the first
-                            }
-                        } else {
-                            // more ties than the list holds: scan again
-                            for (int j = bj + 1; j < na; ++j) {
-                                if (j == i || !freef[j]) continue;
-                                const int32_t dj = (!cached && !iv && j < nd) ? drow[D[j]] : 0;
-                                if (weight(j, dj) != bw) continue;
-                                const uint32_t id = pair_id(j), key = pair_key(id);
-                                if (key < bk) { bk = key; bid = id; bj = j; }
-                            }
-                        }
-                    }
-                    best[i] = bj;
+                    np += __popcll(mask);
                 }
-                __syncthreads();
-                for (int t = hl; t < nfl; t += kHalf) {
-                    const int i = fl[t];
-                    const int j = best[i];
-                    if (j > i && best[j] == i) {
-                        const int p = atomicAdd(&s_count[g], 1);
-                        pairs[p] = i | (j << 16);
-                    }
+                wave_lds_fence();
+                for (int p = before + hl; p < np; p += kHalf) {
+                    freef[node[2 * p].pair] = 0;
+                    freef[node[2 * p + 1].pair] = 0;
                 }
-                __syncthreads();
-                const int np = s_count[g];
-                for (int p = hl; p < np; p += kHalf) {
-                    freef[pairs[p] & 0xFFFF] = 0;
-                    freef[pairs[p] >> 16] = 0;
-                }
-                __syncthreads();
-                nfree = na - 2 * np;
+                wave_lds_fence();
+                if (__ballot(2 * np < na) == 0) break;
             }
-            const int np = s_count[g];
-            for (int p = hl; p < np; p += kHalf) {
-                const int i = pairs[p] & 0xFFFF, j = pairs[p] >> 16;
-                if (j == nd) {
-                    walk_boundary(pl, g, D[i], cfgw);
-                } else {
-                    const int u = D[i], v = D[j];
-                    if (dint[(size_t)u * n + v] <= db[u] + db[v]) {
-                        walk_interior(pl, g, u, v, cfgw);
-                    } else {
-                        walk_boundary(pl, g, u, cfgw);
-                        walk_boundary(pl, g, v, cfgw);
-                    }
-                }
+            // the paths, two lanes a pair: the interior one, or one to the boundary
+            // from each (real) end
+            for (int t = hl; t < 2 * np; t += kHalf) {
+                const int i = node[t & ~1].pair, j = node[t | 1].pair;
+                const int u = D[i], v = j == nd ? u : D[j];
+                const bool inner = j != nd && dint[(size_t)u * n + v] <= db[u] + db[v];
+                if ((t & 1) && (inner || j == nd)) continue;
+                walk(pl, g, inner ? dint + (size_t)u * n : db, inner || (t & 1) ? v : u, inner ? u : -1, cfgw);
             }
+            if (SPLIT || gg == 1) write_out(unit);
         }
-        __syncthreads();
     }
-    // write the reference and its symplectic products with L_Z and L_X
-    uint8_t *out = A.slot_map ? A.refs + A.slot_map[s] * A.refs_stride + (size_t)r * nq : A.refs + (size_t)sr * nq;
-    uint8_t *qraw_out = A.slot_map ? A.qraw + A.slot_map[s] * A.qraw_stride + r : A.qraw + sr;
-    const uint8_t *cb = reinterpret_cast<const uint8_t *>(cfgw);
-    uint32_t vz = 0, vx = 0;
-    for (int q = lane; q < nq; q += kWave) {
-        const uint32_t c = cb[q];
-        out[q] = (uint8_t)c;
-        const uint32_t z = pl->lz[q], x = pl->lx[q];
-        vz ^= (((c >> 1) & z) ^ (c & (z >> 1))) & 1;
-        vx ^= (((c >> 1) & x) ^ (c & (x >> 1))) & 1;
-    }
-    const int az = __popcll(__ballot(vz)) & 1;
-    const int ax = __popcll(__ballot(vx)) & 1;
-    if (lane == 0) *qraw_out = (uint8_t)(az | (ax << 1));
 }
 
 // Pauli class index (I=0, X=1, Y=2, Z=3) <-> (x, z) bits, and products.
@@ -774,29 +905,61 @@ static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // the whole wavefront per colour on larger lattices.
 static bool greedy_split(const Plan &P) { return std::max(P.hdev.ncol[0], P.hdev.ncol[1]) <= 128; }
 
-// LDS of a greedy workgroup: the configuration, per colour set D, best,
-// pairs, dbD, the free flags and the free list (one set per colour when the
-// halves of the wavefront match the colours at once, else one), the tie
-// lists, and, with `cache` (launches of few wavefronts, where latency matters
-// more than occupancy), the pair-weight cache of each set: 16 KiB per colour
-// when the colours run side by side (up to 63 defects), 48 KiB otherwise (up
-// to 109).
-static int greedy_lds(const Plan &P, bool cache, GreedyArgs *A)
-{
-    const int mn = std::max(P.hdev.ncol[0], P.hdev.ncol[1]);
-    A->max_nodes = mn;
-    const int sets = greedy_split(P) ? 2 : 1;
-    const int flags = 4 * ((P.lat.nq + 3) / 4) + sets * 4 * 4 * (mn + 1) + 2 * kWave * kGreedyTies;
-    const int base = ((flags + sets * (mn + 1) + 1) & ~1) + sets * 2 * (mn + 1);
-    A->cache_entries = cache ? (sets == 2 ? 4096 : 12288) : 0;
-    return ((base + 15) & ~15) + sets * 4 * A->cache_entries + 16;
-}
-
-// launches of at most this many (syndrome, replica) wavefronts cache the pair
-// weights in LDS (larger ones keep the occupancy instead: a serving slice
-// admitting thousands of requests ran its greedy launches 20 % slower with
-// the cache)
+// references a launch takes one to a wavefront: four times the wavefronts the
+// device holds.  With more, a wavefront takes several in turn, so that fewer
+// are dispatched and set up (planar d = 9, 12288 x 10: 438 us with one each,
+// 367 with three, 499 where twice as many left some workgroups two; half as
+// many left too few wavefronts to hide latency, 524).
+constexpr int64_t kGreedyFill = 32768;
+// launches of at most this many references cache the pair weights in LDS
+// whatever the workgroup's size (see below)
 constexpr int64_t kGreedyCacheWaves = 2048;
+
+// The greedy references of n syndromes, A's outputs and syndromes set by the
+// caller.  A workgroup's wavefronts share a syndrome's scan, so it takes as
+// many of its replicas as the LDS holds, at most kGreedyWaves, spread evenly
+// over the workgroups.  The weights of up to about half the nodes as defects
+// (more are rare: each fires with probability below one half) are cached where
+// the workgroup has wavefronts enough to share them, or the launch is small
+// and latency matters more than occupancy; a share of 64 KiB in all.
+static int launch_greedy(const Plan &P, GreedyArgs A, int64_t n_syn, uint64_t seed, int mode, hipStream_t stream)
+{
+    const bool split = greedy_split(P);
+    const int sets = split ? 2 : 1, nwords = (P.lat.nq + 3) / 4;
+    const int nodes = std::max(P.hdev.ncol[0], P.hdev.ncol[1]);
+    A.plan = P.ddev;
+    A.mode = mode;
+    A.seed_lo = (uint32_t)seed;
+    A.seed_hi = (uint32_t)(seed >> 32);
+    A.stride = (nodes + 2) & ~1;
+    A.n_units = (A.n_rep + A.rep_div - 1) / A.rep_div;
+    const GreedyLds base = greedy_lds_layout(sets, A.stride, nwords, 0);
+    const int fit = std::max(1, std::min(kGreedyWaves, (int)((65536 - base.waves) / base.per_wave)));
+    const int64_t refs = n_syn * A.n_units;
+    const int each = split ? (int)std::max<int64_t>(1, std::min<int64_t>(refs / kGreedyFill, A.n_units)) : 1;
+    const int per_syn = (A.n_units + each - 1) / each;
+    A.shares = (per_syn + fit - 1) / fit;
+    const int waves = (per_syn + A.shares - 1) / A.shares;
+    A.unit_step = A.shares * waves;
+    A.cache_entries = 0;
+    if (A.n_units >= 4 * A.shares || refs <= kGreedyCacheWaves) {
+        const int rows = nodes * 7 / 16 + 8, room = 65536 - 64 - (int)(base.waves + waves * base.per_wave);
+        A.cache_entries = std::max(0, std::min(rows * (rows | 1), room / (4 * sets)));
+    }
+    const uint32_t lds = greedy_lds_layout(sets, A.stride, nwords, A.cache_entries).waves + waves * base.per_wave;
+    void (*kernel)(GreedyArgs) = k_greedy<false, false>;
+    if (split) kernel = each > 1 ? k_greedy<true, true> : k_greedy<true, false>;
+    // one launch addresses fewer than 2^32 work-items
+    const int64_t blocks = n_syn * A.shares, most = kMaxLaunchWaves / waves;
+    for (int64_t b0 = 0; b0 < blocks; b0 += most) {
+        A.block0 = b0;
+        const int64_t nb = std::min<int64_t>(most, blocks - b0);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(waves * kWave), lds, stream, A);
+        const int rc = check_hip(hipGetLastError(), "k_greedy launch");
+        if (rc) return rc;
+    }
+    return XZZX_OK;
+}
 
 static int launch_greedy(const Plan &P, const uint8_t *d_syn, const uint32_t *d_uid, int64_t n_syn,
                          int n_rep, uint64_t seed, int mode, uint8_t *d_refs, uint8_t *d_qraw,
@@ -804,31 +967,14 @@ static int launch_greedy(const Plan &P, const uint8_t *d_syn, const uint32_t *d_
 {
     if (n_syn == 0) return XZZX_OK;
     GreedyArgs A{};
-    A.plan = P.ddev;
     A.syn = d_syn;
     A.uid = d_uid;
     A.refs = d_refs;
     A.qraw = d_qraw;
-    A.n_syn = n_syn;
     A.n_rep = n_rep;
-    A.mode = mode;
-    A.rep_div = P.ladder_k;
+    A.rep_div = std::max(P.ladder_k, 1);
     A.syn_stride = P.lat.nstab;
-    A.seed_lo = (uint32_t)seed;
-    A.seed_hi = (uint32_t)(seed >> 32);
-    // one launch addresses fewer than 2^32 work-items: the (syndrome, replica)
-    // pairs go in chunks of at most that many wavefronts
-    const int64_t blocks = n_syn * n_rep;
-    const int lds = greedy_lds(P, blocks <= kGreedyCacheWaves, &A);
-    for (int64_t b0 = 0; b0 < blocks; b0 += kMaxLaunchWaves) {
-        A.block0 = b0;
-        const int64_t nb = std::min<int64_t>(kMaxLaunchWaves, blocks - b0);
-        hipLaunchKernelGGL(greedy_split(P) ? k_greedy<true> : k_greedy<false>, dim3((unsigned)nb), dim3(kWave), lds,
-                           stream, A);
-        const int rc = check_hip(hipGetLastError(), "k_greedy launch");
-        if (rc) return rc;
-    }
-    return XZZX_OK;
+    return launch_greedy(P, A, n_syn, seed, mode, stream);
 }
 
 static int launch_qcls(const uint8_t *d_qraw, int64_t n_syn, int n_rep, uint8_t *d_qcls, hipStream_t stream)
@@ -1583,7 +1729,6 @@ int serve_greedy(const Plan &P, const uint8_t *d_syn, int64_t syn_stride, const 
 {
     if (n <= 0) return XZZX_OK;
     GreedyArgs A{};
-    A.plan = P.ddev;
     A.syn = d_syn;
     A.syn_stride = syn_stride;
     A.uid = d_uid;
@@ -1592,15 +1737,9 @@ int serve_greedy(const Plan &P, const uint8_t *d_syn, int64_t syn_stride, const 
     A.slot_map = d_slot_map;
     A.refs_stride = refs_stride;
     A.qraw_stride = qraw_stride;
-    A.n_syn = n;
     A.n_rep = n_rep;
-    A.mode = mode;
-    A.seed_lo = (uint32_t)seed;
-    A.seed_hi = (uint32_t)(seed >> 32);
-    const int lds = greedy_lds(P, (int64_t)n * n_rep <= kGreedyCacheWaves, &A);
-    hipLaunchKernelGGL(greedy_split(P) ? k_greedy<true> : k_greedy<false>, dim3((unsigned)(n * n_rep)), dim3(kWave),
-                       lds, stream, A);
-    return check_hip(hipGetLastError(), "serving greedy launch");
+    A.rep_div = 1;
+    return launch_greedy(P, A, n, seed, mode, stream);
 }
 
 int serve_slice(const ServeLaunch *launches, int n_launches, uint64_t seed, hipStream_t stream)

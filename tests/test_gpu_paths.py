@@ -159,3 +159,30 @@ def test_random_site_workgroups(layout, d, n_syn):
         D.decode_groups([g], prob.greedy_seed, prob.anneal_seed, ws=ws[:ws.numel() - short])
         torch.cuda.synchronize()
         compare_decode(prob, out, ref)
+
+
+@pytest.mark.parametrize("layout,d,n_syn,R", [(0, 5, 3001, 23), (1, 9, 2200, 30), (0, 3, 66001, 2), (0, 15, 40, 17),
+                                              (0, 21, 7, 33), (0, 31, 5, 12), (1, 31, 2, 5), (0, 17, 1, 1)])
+@pytest.mark.parametrize("mode", [X.GREEDY_RANDOM, X.GREEDY_SAME, X.GREEDY_BOUNDARY])
+def test_greedy_workgroups(layout, d, n_syn, R, mode):
+    """Greedy references where wavefronts share a syndrome: one or several
+    references a wavefront, one or several workgroups a syndrome, weights in LDS
+    and not; every node a defect (more ties than the list of the first round
+    holds, and weights beyond the cache), every second one, one and none."""
+    print(f"[paths] greedy layout={layout} d={d} n_syn={n_syn} R={R} mode={mode}", flush=True)
+    prob = Problem(layout, d, 0.18, 0.5, n_syn, R, 1, seed=70 + d, conv=layout)
+    k = min(5, n_syn)
+    prob.syn[0] = 1
+    for i, step in ((1, 2), (2, 0), (3, prob.olat.nstab)):
+        if i < k:
+            prob.syn[i] = 0
+            if step:
+                prob.syn[i, ::step] = 1
+    plan = gpu_plan(prob)
+    refs, qcls = D.greedy_init(plan, to_dev(prob.syn), to_dev(prob.uid.view(np.int32)), R, prob.greedy_seed, mode)
+    refs, qcls = refs.cpu().numpy(), qcls.cpu().numpy()
+    for i in sorted({*range(k), n_syn // 2, n_syn - 1}):
+        for r in range(R):
+            want = prob.oracle_greedy(i, r, mode)
+            assert np.array_equal(refs[i, r], want), (i, r)
+            assert qcls[i, r] == prob.olat.cls(want, refs[i, 0]), (i, r)
