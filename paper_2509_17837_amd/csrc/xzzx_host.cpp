@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <array>
 #include <cmath>
+#include <limits>
 #include <cstring>
 #include <functional>
 #include <map>
@@ -1117,6 +1118,7 @@ int xzzx_plan_set_ladder(xzzx_plan *plan, int levels, double beta_lo, double bet
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev != P.device) { P.ladder_k = old_k; set_error("plan was created on another device"); return XZZX_EINVAL; }
     void *mem = nullptr;
+    float rate = 0.0f;
     if (levels) {
         // levels beta_k = beta_lo + k delta, and the exchange rule's powers
         const int nranks = P.nranks();
@@ -1130,6 +1132,15 @@ int xzzx_plan_set_ladder(xzzx_plan *plan, int levels, double beta_lo, double bet
         const double r0 = std::ldexp(std::exp(-delta * 0x1p-16), 64);
         R[0] = r0 >= 18446744073709551615.0 ? UINT64_MAX : (uint64_t)r0;
         for (int i = 1; i < 32; ++i) R[i] = (uint64_t)(((unsigned __int128)R[i - 1] * R[i - 1]) >> 64);
+        // the exponent per unit of energy, where the powers follow it (see swap_below)
+        const double c = delta * 0x1p-16 * 1.4426950408889634;
+        bool follows = true;
+        for (int i = 0; i < 32; ++i) {
+            const double x = std::ldexp(c, i);
+            if (R[i] >= 1u << 30) follows &= std::fabs(std::log2((double)R[i]) - 64.0 + x) <= 0x1p-21;
+            else follows &= x >= 33.5;
+        }
+        rate = follows ? (float)c : std::numeric_limits<float>::quiet_NaN();
         const size_t bytes = 256 + thr.size() * 4;
         if (hipMalloc(&mem, bytes) != hipSuccess) { P.ladder_k = old_k; set_error("hipMalloc of ladder tables failed"); return XZZX_ENOMEM; }
         std::vector<uint8_t> host(bytes, 0);
@@ -1146,6 +1157,7 @@ int xzzx_plan_set_ladder(xzzx_plan *plan, int levels, double beta_lo, double bet
     PlanDev &h = P.hdev;
     h.ladder_k = levels;
     h.ladder_pow = levels ? static_cast<const uint64_t *>(mem) : nullptr;
+    h.ladder_rate = rate;
     h.ladder_thr = levels ? reinterpret_cast<const uint32_t *>(static_cast<uint8_t *>(mem) + 256) : nullptr;
     if (hipMemcpy(P.ddev, &h, sizeof(PlanDev), hipMemcpyHostToDevice) != hipSuccess) {
         if (mem) (void)hipFree(mem);

@@ -219,6 +219,7 @@ struct PlanDev {
     int ladder_k;                  // replica exchange: levels per ladder (0 = off)
     const uint32_t *ladder_thr;    // [ladder_k][nranks] acceptance thresholds of each level
     const uint64_t *ladder_pow;    // [32] fixed-point powers R_i of the exchange rule
+    float ladder_rate;             // R_i / 2^64 = 2^-(ladder_rate 2^i) within 2^-21 in the exponent (NaN: not so)
     const Desc *desc;              // [4][M] by (class, rank)
     const Desc *face_desc;         // [nstab] by face id
     const uint8_t *lut;            // [ntypes][256] move-energy rank of a slot pattern

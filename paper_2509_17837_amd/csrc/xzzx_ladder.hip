@@ -135,7 +135,8 @@ __device__ inline void ladder_core(const PlanDev *pl, const ChainJob &J, uint32_
                                                seed_lo, seed_hi);
                 const uint32_t uws[4] = {rr.x, rr.y, rr.z, rr.w};
                 const uint32_t u = uws[p & 3u];
-                if (e_hi >= e_lo || u < swap_threshold(pl->ladder_pow, (uint32_t)(e_lo - e_hi))) level = plevel;
+                if (e_hi >= e_lo || swap_below(pl->ladder_pow, pl->ladder_rate, (uint32_t)(e_lo - e_hi), u))
+                    level = plevel;
             }
             wave_lds_fence();
         }

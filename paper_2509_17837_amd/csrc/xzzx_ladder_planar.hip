@@ -25,6 +25,7 @@ __device__ __forceinline__ void ladder_planar_core(const PlanDev *pl, const Chai
     const LaneKey lk = lane_key(uid, k1);
     // ladder position: replica r = bK + j starts at level j; coset P
     const uint32_t rep = cc >> 2, P = cc & 3u;
+    const float rate = pl->ladder_rate;
     const uint32_t ladder_id = 4u * (rep / (uint32_t)K) + P;
     int level = (int)(rep % (uint32_t)K);
 
@@ -53,7 +54,7 @@ __device__ __forceinline__ void ladder_planar_core(const PlanDev *pl, const Chai
         planar_class<D, 3>(r, lk, cc, c2 + 3u, k0, k1, lut_s, et_l, acc);
         E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 4; if (keep) store_rows(keep, r); }
-        if (K > 1) level = ladder_exchange(level, E, K, P, uid, ladder_id, t, k0, k1, pl->ladder_pow);
+        if (K > 1) level = ladder_exchange(level, E, K, P, uid, ladder_id, t, k0, k1, pl->ladder_pow, rate);
     }
     if (J.active) {
         J.emin[J.ci] = Emin;

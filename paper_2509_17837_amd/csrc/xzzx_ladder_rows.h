@@ -35,6 +35,7 @@ __device__ __forceinline__ void ladder_rows_core(const PlanDev *pl, const ChainJ
     const uint32_t uid = SPAN ? J.uid : uni(J.uid), cc = J.cc;
     const uint32_t k0 = uni(seed_lo), k1 = uni(seed_hi);
     const auto draw_of = chain_draws<SPAN>(uid, cc, k0, k1);
+    const float rate = pl->ladder_rate;
     // ladder position: replica r = bK + j starts at level j; coset P
     const uint32_t rep = cc >> 2, P = cc & 3u;
     const uint32_t ladder_id = 4u * (rep / (uint32_t)K) + P;
@@ -65,7 +66,7 @@ __device__ __forceinline__ void ladder_rows_core(const PlanDev *pl, const ChainJ
         static_class<D, 3>(r, draw_of(c2 + 3u), lut_s, et_l, acc, Blocks{});
         E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 4; if (keep) store_rows(keep, r); }
-        if (K > 1) level = ladder_exchange(level, E, K, P, uid, ladder_id, t, k0, k1, pl->ladder_pow);
+        if (K > 1) level = ladder_exchange(level, E, K, P, uid, ladder_id, t, k0, k1, pl->ladder_pow, rate);
     }
     if (J.active) {
         J.emin[J.ci] = Emin;

@@ -186,3 +186,19 @@ def test_greedy_workgroups(layout, d, n_syn, R, mode):
             want = prob.oracle_greedy(i, r, mode)
             assert np.array_equal(refs[i, r], want), (i, r)
             assert qcls[i, r] == prob.olat.cls(want, refs[i, 0]), (i, r)
+
+
+@pytest.mark.parametrize("layout,d,R", [(0, 5, 16), (1, 5, 4), (0, 9, 20), (0, 17, 4)])
+@pytest.mark.parametrize("lo,hi", [(0.7, 0.7), (0.5, 0.5 + 1e-9), (0.5, 0.51), (0.2, 2.0), (0.0, 3e3), (0.0, 1e9)])
+def test_exchange_rule(layout, d, R, lo, hi):
+    """Exchanges are decided by a bound and, between its two sides, by the
+    fixed-point product: equal levels (every exchange nearly certain), spacings
+    from the least to one whose first power underflows."""
+    print(f"[paths] exchange layout={layout} d={d} R={R} beta={lo}..{hi}", flush=True)
+    prob = Problem(layout, d, 0.2, 5.0, 4, R, 40, seed=50 + d, conv=layout)
+    plan = gpu_plan(prob)
+    plan.set_ladder(4, lo, hi)
+    out = D.decode(plan, to_dev(prob.syn), to_dev(prob.uid.view(np.int32)), prob.n_rep, prob.greedy_seed,
+                   prob.anneal_seed, want_chains=True, want_final=True)
+    torch.cuda.synchronize()
+    compare_decode(prob, out, prob.oracle_decode(order=O.ORDER_LADDER, ladder=(4, lo, hi)))
