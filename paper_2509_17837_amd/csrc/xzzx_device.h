@@ -1567,18 +1567,12 @@ AnnealKernel ladder_rows_kernel(int d, bool span);
 AnnealKernel ladder_rows_kernel_large(int d, bool span);   // d = 17 .. 31 (NULL otherwise)
 AnnealKernel ladder_planar_kernel(int d);
 int ladder_rows_state_words(int d);
-// grid core (one chain over `lanes` lanes, `mv` moves per lane and class) and
-// its recovery gather
+// grid core (one chain over `lanes` lanes, `mv` moves per lane and class)
 AnnealKernel grid_kernel(int lanes, int mv);
-void launch_grid_recovery(const uint32_t *snap, int words, const int32_t *best_chain, int n_rep, int nq, int64_t n_syn,
-                          const PlanDev *pl, uint8_t *recovery, hipStream_t stream);
 typedef void (*ServeKernel)(const ServeTask *, uint32_t, uint32_t);
 ServeKernel serve_grid_kernel(int mv);
-// random-site kernels (wide: some row of the lattice takes several words) and
-// the recovery gather from the states they keep
+// random-site kernels (wide: some row of the lattice takes several words)
 AnnealKernel site_kernel(bool wide, bool replay);
-void launch_site_recovery(const uint32_t *snap, int64_t n_chains, const int32_t *best_chain, int n_rep, int nq,
-                          int64_t n_syn, const PlanDev *pl, uint8_t *recovery, hipStream_t stream);
 
 // The specialised kernels live in several translation units (compiled in
 // parallel): the annealing kernels by distance (each part returns its kernels

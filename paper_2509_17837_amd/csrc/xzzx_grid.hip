@@ -84,25 +84,4 @@ ServeKernel serve_grid_kernel(int mv)
     }
 }
 
-// Each syndrome's recovery is its best chain's grid at that chain's first
-// E_min (code << 3 per cell); one thread per (syndrome, qubit).
-__global__ void k_grid_recovery(const uint8_t *__restrict__ snap, int bytes, const int32_t *__restrict__ best_chain,
-                                int n_rep, int nq, int64_t n_syn, const PlanDev *__restrict__ pl,
-                                uint8_t *__restrict__ recovery)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_syn * nq) return;
-    const int64_t s = idx / nq;
-    const int q = (int)(idx - s * nq);
-    const int64_t ci = s * 4 * n_rep + best_chain[s];
-    recovery[idx] = snap[ci * bytes + pl->grid_cell[q]] >> 3;
-}
-
-void launch_grid_recovery(const uint32_t *snap, int words, const int32_t *best_chain, int n_rep, int nq, int64_t n_syn,
-                          const PlanDev *pl, uint8_t *recovery, hipStream_t stream)
-{
-    hipLaunchKernelGGL(k_grid_recovery, dim3((unsigned)((n_syn * nq + 255) / 256)), dim3(256), 0, stream,
-                       reinterpret_cast<const uint8_t *>(snap), 4 * words, best_chain, n_rep, nq, n_syn, pl, recovery);
-}
-
 }  // namespace xzzx

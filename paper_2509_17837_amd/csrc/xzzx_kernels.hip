@@ -15,7 +15,8 @@
 //   k_replay<L>    re-runs each syndrome's best chain up to the phase of its
 //                  minimum (from a checkpoint where the specialised kernel left
 //                  one) and stores that state: the recovery.
-//   k_reduce       Eqs. (18)-(21): per-coset minima, P*, best chain.
+//   k_finish       Eqs. (18)-(21): per-coset minima, P*, best chain; the
+//                  recovery, where the kernels kept each chain's best state.
 //   k_serve_*      the serving loop's slices, finish and result gather.
 //
 // The host half turns xzzx_group descriptions into launches: one persistent
@@ -239,8 +240,10 @@ __device__ __forceinline__ void walk(const PlanDev *pl, int g, const int32_t *di
     }
 }
 
+// v of lane ^ 1 (0xB1), of lane ^ 2 (0x4E), or of the lane 4 or 8 further
+// round its 16 (0x124, 0x128)
 template <int CTRL>
-__device__ __forceinline__ uint32_t quad_swap(uint32_t v)   // of lane ^ 1 (0xB1) or lane ^ 2 (0x4E)
+__device__ __forceinline__ uint32_t lane_move(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
@@ -526,11 +529,11 @@ __global__ __launch_bounds__(kGreedyWaves *kWave)
                                 ++nt;
                             }
                         }
-                        uint32_t least = min(bw, quad_swap<0xB1>(bw));
-                        least = min(least, quad_swap<0x4E>(least));
+                        uint32_t least = min(bw, lane_move<0xB1>(bw));
+                        least = min(least, lane_move<0x4E>(least));
                         if (bw != least) { nt = 0; bj = 0xFFFFu; }
-                        int all = nt + (int)quad_swap<0xB1>((uint32_t)nt);
-                        all += (int)quad_swap<0x4E>((uint32_t)all);
+                        int all = nt + (int)lane_move<0xB1>((uint32_t)nt);
+                        all += (int)lane_move<0x4E>((uint32_t)all);
                         uint32_t bk = 0;
                         if (randomized && all > 1) {
                             bk = 0xFFFFFFFFu;
@@ -551,10 +554,10 @@ __global__ __launch_bounds__(kGreedyWaves *kWave)
                             }
                         }
                         // the quad's least (key, partner)
-                        uint32_t ok = quad_swap<0xB1>(bk), oj = quad_swap<0xB1>(bj);
+                        uint32_t ok = lane_move<0xB1>(bk), oj = lane_move<0xB1>(bj);
                         if (ok < bk || (ok == bk && oj < bj)) { bk = ok; bj = oj; }
-                        ok = quad_swap<0x4E>(bk);
-                        oj = quad_swap<0x4E>(bj);
+                        ok = lane_move<0x4E>(bk);
+                        oj = lane_move<0x4E>(bj);
                         if (ok < bk || (ok == bk && oj < bj)) { bk = ok; bj = oj; }
                         if (sub == 0) node[i].best = (uint16_t)bj;
                     }
@@ -658,54 +661,6 @@ __global__ __launch_bounds__(kWave) void k_anneal(AnnealArgs A) { batch_kernel_b
 template <int LOGG>
 __global__ __launch_bounds__(kWave) void k_replay(AnnealArgs A) { batch_kernel_body<false, LOGG, true>(A); }
 
-// Generic ladder kernel: each syndrome's recovery is its best chain's state kept
-// at that chain's first E_min (packed words [word][chain], qubit q at bits
-// 2 (q mod 16) of word q div 16); one thread per (syndrome, qubit).
-__global__ void k_packed_recovery(const uint32_t *__restrict__ snap, int64_t n_chains,
-                                const int32_t *__restrict__ best_chain, int n_rep, int nq, int64_t n_syn,
-                                uint8_t *__restrict__ recovery)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_syn * nq) return;
-    const int64_t s = idx / nq;
-    const int q = (int)(idx - s * nq);
-    const int64_t ci = s * 4 * n_rep + best_chain[s];
-    recovery[idx] = (uint8_t)((snap[(int64_t)(q >> 4) * n_chains + ci] >> (2 * (q & 15))) & 3u);
-}
-
-// Planar kernel specialised to d: the same from its rows, chain-major with
-// `words` words per chain (word Y * nw + c / 16 holds the qubit at row Y,
-// column c), one thread per (syndrome, qubit).
-__global__ void k_rows_recovery(const uint32_t *__restrict__ snap, int words,
-                                const int32_t *__restrict__ best_chain, int n_rep, int nq, int64_t n_syn,
-                                const PlanDev *__restrict__ pl, int nw, uint8_t *__restrict__ recovery)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_syn * nq) return;
-    const int64_t s = idx / nq;
-    const int q = (int)(idx - s * nq);
-    const int64_t ci = s * 4 * n_rep + best_chain[s];
-    const uint32_t p = pl->qpos[q];
-    const uint32_t word = snap[ci * words + (int64_t)((p >> 8) * nw + ((p & 0xFFu) >> 4))];
-    recovery[idx] = (uint8_t)((word >> (2 * (p & 15u))) & 3u);
-}
-// Rotated ladder kernel specialised to d: the same from its rows,
-// chain-major with `words` words per chain (word y * nw + x / 16 holds the
-// qubit at row y, column x), one thread per (syndrome, qubit).
-__global__ void k_static_recovery(const uint32_t *__restrict__ snap, int words,
-                                  const int32_t *__restrict__ best_chain, int n_rep, int d, int64_t n_syn, int nw,
-                                  uint8_t *__restrict__ recovery)
-{
-    const int nq = d * d;
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_syn * nq) return;
-    const int64_t s = idx / nq;
-    const int q = (int)(idx - s * nq);
-    const int y = q / d, x = q - y * d;
-    const int64_t ci = s * 4 * n_rep + best_chain[s];
-    const uint32_t word = snap[ci * words + (int64_t)(y * nw + (x >> 4))];
-    recovery[idx] = (uint8_t)((word >> (2 * (x & 15))) & 3u);
-}
 __global__ __launch_bounds__(kWave) void k_anneal_rows(AnnealArgs A) { batch_kernel_body<true, 0, false>(A); }
 
 static AnnealKernel static_rows_kernel(int d, bool span)
@@ -785,58 +740,123 @@ __global__ void k_zero_u32(uint32_t *p, int n)
 // E_min over the chains of coset P; P* = argmin with ties to the lowest index;
 // the best chain is the lowest chain of coset P* attaining E_P*.
 // ---------------------------------------------------------------------------
-struct ReduceArgs {
+// How a kernel lays out the states it keeps at each chain's first E_min (ci:
+// the chain, n_chains: the group's): packed words [q div 16][ci], qubit q at
+// bits 2 (q mod 16) (generic ladder kernel); rows chain-major, `words` words a
+// chain, word Y * row_words + c / 16 holding row Y, column c, of the planar
+// lattice's qpos or (rotated) of qubit dY + c; the grid core's bytes, code << 3
+// per cell, `words` words a chain; the random-site kernel's words [w][ci].
+enum class Kept { None, Packed, PlanarRows, RotatedRows, Grid, Site };
+
+struct FinishGroup {
     const PlanDev *plan;
     const uint8_t *qcls;
     const uint8_t *refs;
     const int32_t *emin;
+    const uint32_t *snap;      // states kept at E_min (kept != None)
     int32_t *e_best;
     uint8_t *cls;
     int32_t *best_chain;
     int32_t *e_cls;
     uint8_t *paper_recovery;
+    uint8_t *recovery;
     int64_t n_syn;
+    int64_t wave_begin;        // wavefronts of the launch before this group's (one a syndrome)
     int n_rep;
+    Kept kept;
+    int words, row_words;
+    int d;                     // RotatedRows
+};
+constexpr int kFinishWaves = 4;   // per workgroup
+struct FinishArgs {
+    FinishGroup g[kMaxGroups];
+    int n_groups;
+    int64_t n_waves;
 };
 
-__global__ __launch_bounds__(kWave) void k_reduce(ReduceArgs A)
+__device__ __forceinline__ void least_of(uint64_t &best, uint32_t hi, uint32_t lo)
 {
-    const int lane = threadIdx.x;
-    const int64_t s = blockIdx.x;
-    const int nc = 4 * A.n_rep;
-    uint64_t best[4] = {~0ull, ~0ull, ~0ull, ~0ull};
-    for (int c = lane; c < nc; c += kWave) {
-        const int cls = cls_mul(A.qcls[s * A.n_rep + (c >> 2)], c & 3);
-        const uint64_t key = ((uint64_t)(uint32_t)A.emin[s * nc + c] << 32) | (uint32_t)c;
-#pragma unroll
-        for (int P = 0; P < 4; ++P)
-            if (cls == P) best[P] = min(best[P], key);
+    best = min(best, ((uint64_t)hi << 32) | lo);
+}
+
+// Eqs. (18)-(21) and, where the kernels kept each chain's state at its E_min,
+// the recovery: one wavefront a syndrome, all groups of a call in one launch.
+// A reference's four chains start in four different classes, so a lane reads
+// the chain of class lane mod 4 and the classes reduce side by side.  It took
+// two launches a group, in turn, most of it 24 64-bit shuffles one after the
+// other (planar d = 9, six groups of 2048 syndromes with 40 chains: 19 and 6 us
+// a group, now 15.5 for all; d = 3, 1000 syndromes with 4 chains: 17 + 5, now 4.8).
+__global__ __launch_bounds__(kFinishWaves *kWave) void k_finish(FinishArgs A)
+{
+    const int lane = threadIdx.x % kWave;
+    const int64_t wave = (int64_t)blockIdx.x * kFinishWaves + (int)uni(threadIdx.x / kWave);
+    if (wave >= A.n_waves) return;
+    int gi = 0;
+    while (gi + 1 < A.n_groups && wave >= A.g[gi + 1].wave_begin) ++gi;
+    const FinishGroup &G = A.g[gi];
+    const int64_t s = wave - G.wave_begin;
+    const int nc = 4 * G.n_rep;
+    uint64_t best = ~0ull;
+    for (int c0 = lane; c0 < nc; c0 += kWave) {
+        const int c = (c0 & ~3) | cls_mul(G.qcls[s * G.n_rep + (c0 >> 2)], c0 & 3);
+        least_of(best, (uint32_t)G.emin[s * nc + c], (uint32_t)c);
     }
-#pragma unroll
-    for (int P = 0; P < 4; ++P)
-#pragma unroll
-        for (int sh = 1; sh < kWave; sh <<= 1) {
-            const uint64_t o = __shfl_xor(best[P], sh, kWave);
-            best[P] = min(best[P], o);
-        }
-    int ps = 0;
-#pragma unroll
-    for (int P = 1; P < 4; ++P)
-        if ((best[P] >> 32) < (best[ps] >> 32)) ps = P;
+    // over the lanes of one class: rotations within 16 lanes, then across
+    least_of(best, lane_move<0x124>((uint32_t)(best >> 32)), lane_move<0x124>((uint32_t)best));
+    least_of(best, lane_move<0x128>((uint32_t)(best >> 32)), lane_move<0x128>((uint32_t)best));
+    best = min(best, (uint64_t)__shfl_xor((unsigned long long)best, 16, kWave));
+    best = min(best, (uint64_t)__shfl_xor((unsigned long long)best, 32, kWave));
+    if (G.e_cls && lane < 4) G.e_cls[s * 4 + lane] = best == ~0ull ? INT32_MAX : (int32_t)(best >> 32);
+    // the class of least energy, the first of equals
+    uint32_t e = (uint32_t)(best >> 32), chain = (uint32_t)best, ps = lane & 3u;
+    auto take = [&](uint32_t oe, uint32_t oc, uint32_t op) {
+        if (oe < e || (oe == e && op < ps)) { e = oe; chain = oc; ps = op; }
+    };
+    take(lane_move<0xB1>(e), lane_move<0xB1>(chain), lane_move<0xB1>(ps));
+    take(lane_move<0x4E>(e), lane_move<0x4E>(chain), lane_move<0x4E>(ps));
     if (lane == 0) {
-        A.e_best[s] = (int32_t)(best[ps] >> 32);
-        A.cls[s] = (uint8_t)ps;
-        A.best_chain[s] = (int32_t)(best[ps] & 0xFFFFFFFFu);
-        if (A.e_cls)
-            for (int P = 0; P < 4; ++P) A.e_cls[s * 4 + P] = best[P] == ~0ull ? INT32_MAX : (int32_t)(best[P] >> 32);
+        G.e_best[s] = (int32_t)e;
+        G.cls[s] = (uint8_t)ps;
+        G.best_chain[s] = (int32_t)chain;
     }
-    if (A.paper_recovery) {
-        const PlanDev *pl = A.plan;
-        const int nq = pl->nq;
+    const PlanDev *pl = G.plan;
+    const int nq = pl->nq;
+    if (G.paper_recovery) {
         const bool ux = (ps == 1 || ps == 2), uz = (ps == 2 || ps == 3);
-        const uint8_t *r0 = A.refs + (size_t)s * A.n_rep * nq;
+        const uint8_t *r0 = G.refs + (size_t)s * G.n_rep * nq;
         for (int q = lane; q < nq; q += kWave)
-            A.paper_recovery[(size_t)s * nq + q] = r0[q] ^ (ux ? pl->lx[q] : 0) ^ (uz ? pl->lz[q] : 0);
+            G.paper_recovery[(size_t)s * nq + q] = r0[q] ^ (ux ? pl->lx[q] : 0) ^ (uz ? pl->lz[q] : 0);
+    }
+    if (G.kept == Kept::None) return;
+    const int64_t n_chains = G.n_syn * nc, ci = s * nc + uni(chain);
+    uint8_t *out = G.recovery + (size_t)s * nq;
+    const uint32_t *own = G.snap + ci * G.words;
+    switch (G.kept) {
+    case Kept::Packed:
+        for (int q = lane; q < nq; q += kWave) out[q] = (uint8_t)((G.snap[(q >> 4) * n_chains + ci] >> (2 * (q & 15))) & 3u);
+        break;
+    case Kept::PlanarRows:
+        for (int q = lane; q < nq; q += kWave) {
+            const uint32_t p = pl->qpos[q];
+            out[q] = (uint8_t)((own[(p >> 8) * G.row_words + ((p & 0xFFu) >> 4)] >> (2 * (p & 15u))) & 3u);
+        }
+        break;
+    case Kept::RotatedRows: {
+        const uint32_t d = (uint32_t)G.d;
+        for (int q = lane; q < nq; q += kWave) {
+            const uint32_t y = (uint32_t)q / d, x = (uint32_t)q - y * d;
+            out[q] = (uint8_t)((own[y * G.row_words + (x >> 4)] >> (2 * (x & 15))) & 3u);
+        }
+        break;
+    }
+    case Kept::Grid:
+        for (int q = lane; q < nq; q += kWave) out[q] = reinterpret_cast<const uint8_t *>(own)[pl->grid_cell[q]] >> 3;
+        break;
+    default:
+        for (int q = lane; q < nq; q += kWave) {
+            const uint32_t p = pl->site_pos[q];
+            out[q] = (uint8_t)((G.snap[(int64_t)(p >> 5) * n_chains + ci] >> (p & 31u)) & 3u);
+        }
     }
 }
 
@@ -1432,6 +1452,19 @@ static int fork_join(hipStream_t stream, int n, F launch, bool serial = false)
     return rc;
 }
 
+// where the group's annealing left each chain's state at its E_min (None: the
+// recovery comes from a replay)
+static Kept kept_state(const xzzx_group &g, const GroupWs &w)
+{
+    const Plan &P = g.plan->P;
+    if (!w.min_snap) return Kept::None;
+    if (w.grid) return Kept::Grid;
+    if (P.order == XZZX_ORDER_RANDOM_SITE) return Kept::Site;
+    if (ladder_rows_d(g, w.lean)) return Kept::RotatedRows;
+    if (P.ladder_k && !ladder_planar_d(g)) return Kept::Packed;
+    return min_snap_words(g, w.lean) ? Kept::PlanarRows : Kept::None;
+}
+
 // Annealing of every non-empty group.  Packed-row groups share one persistent
 // launch; byte-state groups are launched per lanes-per-chain value.  The
 // replay re-runs one chain per syndrome with the byte-state kernel, spreading
@@ -1450,7 +1483,6 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
     std::vector<int> replay_cp;   // replays starting from checkpoints: one chain per wavefront
     std::vector<int> site_sel[2]; // random-site plans, by site_wide: one chain (replay: syndrome) per lane
     std::vector<int> planar_sel[kPlanarStaticMaxD + 1];   // planar kernels specialised to d
-    std::vector<int> gather_sel;  // replay: recoveries gathered from the states kept at E_min
     std::vector<int> grid_sel[5][4];   // grid core, by lanes per chain (4..64) and moves per lane (1, 2, 4, 8)
     std::vector<int> ladder_sel;  // replica exchange: one chain per lane
     std::vector<int> ladder_rows_sel[2][kLadderRowsMaxD + 1];   // ... on the rotated kernels specialised to d
@@ -1465,8 +1497,9 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
         }
         if (ws[i].grid || P.order == XZZX_ORDER_RANDOM_SITE || P.ladder_k ||
             (mode == AnnealMode::Replay && min_snap_words(groups[i], ws[i].lean))) {
-            if (mode == AnnealMode::Replay) (ws[i].min_snap ? gather_sel : site_sel[P.site_wide]).push_back(i);
-            else if (const int ld = ladder_rows_d(groups[i], ws[i].lean)) ladder_rows_sel[spans(groups[i])][ld].push_back(i);
+            if (mode == AnnealMode::Replay) {
+                if (kept_state(groups[i], ws[i]) == Kept::None) site_sel[P.site_wide].push_back(i);
+            } else if (const int ld = ladder_rows_d(groups[i], ws[i].lean)) ladder_rows_sel[spans(groups[i])][ld].push_back(i);
             else if (ladder_planar_d(groups[i])) ladder_planar_sel[ladder_planar_d(groups[i])].push_back(i);
             else (P.ladder_k ? ladder_sel : site_sel[P.site_wide]).push_back(i);
             continue;
@@ -1498,32 +1531,6 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
         for (int wide = 0; wide < 2 && !rc; ++wide)
             rc = launch_set(groups, ws, site_sel[wide], false, 1, mode, seed, unit_offset, units_override,
                             d_counters + 4 + wide, stream, 0, true);
-        // groups that kept each chain's state at its E_min: gather
-        for (int i : gather_sel) {
-            if (rc) break;
-            const xzzx_group &g = groups[i];
-            const Plan &P = g.plan->P;
-            const int64_t n = g.n_syn * (int64_t)P.lat.nq, nc = g.n_syn * 4 * (int64_t)g.n_rep;
-            if ((n + 255) / 256 * 256 > kMaxLaunchItems) { set_error("too many recovery bytes in one group"); return XZZX_ERANGE; }
-            const dim3 grid((unsigned)((n + 255) / 256));
-            if (ws[i].grid)
-                launch_grid_recovery(ws[i].min_snap, P.hdev.grid_words, ws[i].best_chain, g.n_rep, P.lat.nq, g.n_syn,
-                                     P.ddev, g.d_recovery, stream);
-            else if (const int ld = ladder_rows_d(g, ws[i].lean))
-                hipLaunchKernelGGL(k_static_recovery, grid, dim3(256), 0, stream, ws[i].min_snap,
-                                   (int)min_snap_words(g, ws[i].lean), ws[i].best_chain, g.n_rep, ld, g.n_syn,
-                                   2 * (ld + 1) <= 32 ? 1 : 2, g.d_recovery);
-            else if (P.order == XZZX_ORDER_RANDOM_SITE)
-                launch_site_recovery(ws[i].min_snap, nc, ws[i].best_chain, g.n_rep, P.lat.nq, g.n_syn, P.ddev,
-                                     g.d_recovery, stream);
-            else if (P.ladder_k && !ladder_planar_d(g))
-                hipLaunchKernelGGL(k_packed_recovery, grid, dim3(256), 0, stream, ws[i].min_snap, nc, ws[i].best_chain,
-                                   g.n_rep, P.lat.nq, g.n_syn, g.d_recovery);
-            else
-                hipLaunchKernelGGL(k_rows_recovery, grid, dim3(256), 0, stream, ws[i].min_snap, (int)min_snap_words(g, ws[i].lean),
-                                   ws[i].best_chain, g.n_rep, P.lat.nq, g.n_syn, P.ddev, P.row_words, g.d_recovery);
-            rc = check_hip(hipGetLastError(), "recovery gather launch");
-        }
         return rc;
     }
     // the launches of one call (one per kernel family and distance) run
@@ -1583,24 +1590,54 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
     return fork_join(stream, (int)sets.size(), one, serial);
 }
 
-static int launch_reduce(const xzzx_group &g, const GroupWs &w, hipStream_t stream)
+// reductions of the groups, and recoveries of those whose kernels kept states
+static int launch_finish(const xzzx_group *groups, const GroupWs *ws, int n_groups, hipStream_t stream)
 {
-    if (g.n_syn == 0) return XZZX_OK;
-    ReduceArgs A{};
-    A.plan = g.plan->P.ddev;
-    A.qcls = w.qcls;
-    A.refs = w.refs;
-    A.emin = w.emin;
-    A.e_best = g.d_e_best;
-    A.cls = g.d_cls;
-    A.best_chain = w.best_chain;
-    A.e_cls = g.d_e_cls;
-    A.paper_recovery = g.d_paper_recovery;
-    A.n_syn = g.n_syn;
-    A.n_rep = g.n_rep;
-    if (g.n_syn * kWave > kMaxLaunchItems) { set_error("too many syndromes in one group for one launch"); return XZZX_ERANGE; }
-    hipLaunchKernelGGL(k_reduce, dim3((unsigned)g.n_syn), dim3(kWave), 0, stream, A);
-    return check_hip(hipGetLastError(), "k_reduce launch");
+    FinishArgs A{};
+    auto flush = [&]() -> int {
+        if (A.n_waves == 0) return XZZX_OK;
+        hipLaunchKernelGGL(k_finish, dim3((unsigned)((A.n_waves + kFinishWaves - 1) / kFinishWaves)),
+                           dim3(kFinishWaves * kWave), 0, stream, A);
+        A.n_groups = 0;
+        A.n_waves = 0;
+        return check_hip(hipGetLastError(), "k_finish launch");
+    };
+    for (int i = 0; i < n_groups; ++i) {
+        const xzzx_group &g = groups[i];
+        const Plan &P = g.plan->P;
+        if (g.n_syn <= 0) continue;
+        if (g.n_syn * kWave > kMaxLaunchItems) { set_error("too many syndromes in one group for one launch"); return XZZX_ERANGE; }
+        const Kept kept = kept_state(g, ws[i]);
+        if (kept != Kept::None && (g.n_syn * (int64_t)P.lat.nq + 255) / 256 * 256 > kMaxLaunchItems) {
+            set_error("too many recovery bytes in one group");
+            return XZZX_ERANGE;
+        }
+        if (A.n_waves + g.n_syn > kMaxLaunchWaves - kFinishWaves) {
+            const int rc = flush();
+            if (rc) return rc;
+        }
+        FinishGroup &G = A.g[A.n_groups++];
+        G.plan = P.ddev;
+        G.qcls = ws[i].qcls;
+        G.refs = ws[i].refs;
+        G.emin = ws[i].emin;
+        G.snap = ws[i].min_snap;
+        G.e_best = g.d_e_best;
+        G.cls = g.d_cls;
+        G.best_chain = ws[i].best_chain;
+        G.e_cls = g.d_e_cls;
+        G.paper_recovery = g.d_paper_recovery;
+        G.recovery = g.d_recovery;
+        G.n_syn = g.n_syn;
+        G.wave_begin = A.n_waves;
+        G.n_rep = g.n_rep;
+        G.kept = kept;
+        G.words = kept == Kept::Grid ? P.hdev.grid_words : (int)min_snap_words(g, ws[i].lean);
+        G.d = kept == Kept::RotatedRows ? ladder_rows_d(g, ws[i].lean) : 0;
+        G.row_words = G.d ? (2 * (G.d + 1) <= 32 ? 1 : 2) : P.row_words;
+        A.n_waves += g.n_syn;
+    }
+    return flush();
 }
 
 // The reference stage of the anneal-only entry point: the class of every
@@ -1713,10 +1750,8 @@ static int run_decode(const xzzx_group *groups, int n_groups, uint64_t greedy_se
         if (rc) return rc;
     }
     if (!(stages & XZZX_FLAG_STAGE_FINISH)) return XZZX_OK;
-    for (int i = 0; i < n_groups; ++i) {
-        rc = launch_reduce(groups[i], ws[i], stream);
-        if (rc) return rc;
-    }
+    rc = launch_finish(groups, ws.data(), n_groups, stream);
+    if (rc) return rc;
     return launch_anneal(groups, ws.data(), n_groups, AnnealMode::Replay, anneal_seed, 0, -1, counter + kReplayCounters,
                          stream, serial);
 }

@@ -214,26 +214,4 @@ AnnealKernel site_kernel(bool wide, bool replay)
     return wide ? k_anneal_site<true> : k_anneal_site<false>;
 }
 
-// Each syndrome's recovery is its best chain's state kept at that chain's
-// first E_min; one thread per (syndrome, qubit).
-__global__ void k_site_recovery(const uint32_t *__restrict__ snap, int64_t n_chains,
-                                const int32_t *__restrict__ best_chain, int n_rep, int nq, int64_t n_syn,
-                                const PlanDev *__restrict__ pl, uint8_t *__restrict__ recovery)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_syn * nq) return;
-    const int64_t s = idx / nq;
-    const int q = (int)(idx - s * nq);
-    const int64_t ci = s * 4 * n_rep + best_chain[s];
-    const uint32_t p = pl->site_pos[q];
-    recovery[idx] = (uint8_t)((snap[(int64_t)(p >> 5) * n_chains + ci] >> (p & 31u)) & 3u);
-}
-
-void launch_site_recovery(const uint32_t *snap, int64_t n_chains, const int32_t *best_chain, int n_rep, int nq,
-                          int64_t n_syn, const PlanDev *pl, uint8_t *recovery, hipStream_t stream)
-{
-    hipLaunchKernelGGL(k_site_recovery, dim3((unsigned)((n_syn * nq + 255) / 256)), dim3(256), 0, stream, snap, n_chains,
-                       best_chain, n_rep, nq, n_syn, pl, recovery);
-}
-
 }  // namespace xzzx

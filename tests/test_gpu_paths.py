@@ -202,3 +202,37 @@ def test_exchange_rule(layout, d, R, lo, hi):
                    prob.anneal_seed, want_chains=True, want_final=True)
     torch.cuda.synchronize()
     compare_decode(prob, out, prob.oracle_decode(order=O.ORDER_LADDER, ladder=(4, lo, hi)))
+
+
+def test_finish_of_mixed_groups():
+    """One call over groups of every kind of recovery (states kept by the grid
+    core, the planar and ladder kernels and the random-site kernel, and replays),
+    with one to more than 64 chains a syndrome."""
+    kinds = [("auto", 0, 5, 3, 1), ("auto", 1, 7, 2, 5), ("rows", 0, 7, 5, 3), ("rows", 0, 5, 9, 17),
+             ("rows", 1, 5, 4, 2), ("rows", 1, 9, 1, 33), ("site", 0, 5, 6, 3), ("site", 1, 9, 2, 5),
+             ("ladder", 0, 5, 3, 4), ("ladder", 0, 17, 2, 20), ("ladder", 1, 7, 3, 6), ("ladder", 1, 17, 2, 4),
+             ("bytes", 0, 9, 3, 2), ("bytes", 1, 3, 7, 1), ("rows", 0, 31, 1, 2), ("auto", 1, 17, 1, 1)]
+    made = []
+    for kind, layout, d, n, R in kinds:
+        prob = Problem(layout, d, 0.15, 5.0, n, R, 6, seed=123, conv=layout)
+        plan = gpu_plan(prob)
+        kw = {}
+        if kind == "rows":
+            plan.set_kernel(X.KERNEL_ROWS)
+        elif kind == "bytes":
+            plan.set_lanes(2)
+        elif kind == "site":
+            plan.set_order(X.ORDER_RANDOM_SITE)
+            kw = dict(order=O.ORDER_RANDOM_SITE)
+        elif kind == "ladder":
+            plan.set_ladder(2, 0.5, 2.0)
+            kw = dict(order=O.ORDER_LADDER, ladder=(2, 0.5, 2.0))
+        g, out = D.make_group(plan, R, to_dev(prob.uid.view(np.int32)), syn=to_dev(prob.syn), want_chains=True,
+                              want_final=True)
+        made.append((prob, g, out, kw))
+    seeds = made[0][0]
+    D.decode_groups([g for _, g, _, _ in made], seeds.greedy_seed, seeds.anneal_seed)
+    torch.cuda.synchronize()
+    for (prob, _, out, kw), what in zip(made, kinds):
+        print(f"[paths] finish {what}", flush=True)
+        compare_decode(prob, out, prob.oracle_decode(**kw))
