@@ -39,9 +39,9 @@ OPS_PER_ATTEMPT = 19
 # vector figure (an FMA counts two).  bench.py --peaks measures it.
 ALU_PEAK_OPS = 256 * 128 * 2.4e9
 # LDS bytes a flip attempt reads in the packed-row kernels specialised to d:
-# the generator's (shape, pattern) -> entry offset lookup (2 B) and the
-# 12 bytes of its (dE, threshold, always-accept) entry.
-LDS_BYTES_PER_ATTEMPT = 14
+# the generator's (shape, pattern) -> entry offset lookup (2 B) and its
+# (threshold, dE) entry (8 B).
+LDS_BYTES_PER_ATTEMPT = 10
 # MI355X LDS read peak from its unit counts and clock: 256 CUs x 64 banks x
 # 4 bytes per clock x 2.4 GHz = 157.3 TB/s, the rate of 128-bit reads
 # (bench.py --peaks measures 1.3-1.4e14 B/s for them; 32- and 64-bit reads

@@ -173,8 +173,8 @@ constexpr size_t kStaticLdsBytes = 2 * 256 * 6 + 8 * kStaticRanks;
 constexpr int kLadderRowsMaxD = 31;
 // The specialised kernel's state checkpoints (the replay of a syndrome's
 // best chain starts from the last one before its E_min phase): every
-// kCheckpointEvery sweeps, or sparser so that a chain keeps at most
-// kMaxCheckpoints of them.
+// kCheckpointEvery sweeps, denser in short schedules, or sparser so that a
+// chain keeps at most kMaxCheckpoints of them.
 constexpr int kCheckpointEvery = 64;
 constexpr int kMaxCheckpoints = 32;
 // sweeps between the states the serving loop's byte-state kernel keeps for
