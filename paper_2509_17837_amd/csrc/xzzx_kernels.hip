@@ -954,15 +954,17 @@ static int launch_greedy(const Plan &P, GreedyArgs A, int64_t n_syn, uint64_t se
     A.stride = (nodes + 2) & ~1;
     A.n_units = (A.n_rep + A.rep_div - 1) / A.rep_div;
     const GreedyLds base = greedy_lds_layout(sets, A.stride, nwords, 0);
-    const int fit = std::max(1, std::min(kGreedyWaves, (int)((65536 - base.waves) / base.per_wave)));
+    // boundary references share no scan: a wavefront each, over as many CUs
+    const bool alone = mode == XZZX_GREEDY_BOUNDARY;
+    const int fit = alone ? 1 : std::max(1, std::min(kGreedyWaves, (int)((65536 - base.waves) / base.per_wave)));
     const int64_t refs = n_syn * A.n_units;
-    const int each = split ? (int)std::max<int64_t>(1, std::min<int64_t>(refs / kGreedyFill, A.n_units)) : 1;
+    const int each = split && !alone ? (int)std::max<int64_t>(1, std::min<int64_t>(refs / kGreedyFill, A.n_units)) : 1;
     const int per_syn = (A.n_units + each - 1) / each;
     A.shares = (per_syn + fit - 1) / fit;
     const int waves = (per_syn + A.shares - 1) / A.shares;
     A.unit_step = A.shares * waves;
     A.cache_entries = 0;
-    if (A.n_units >= 4 * A.shares || refs <= kGreedyCacheWaves) {
+    if (!alone && (A.n_units >= 4 * A.shares || refs <= kGreedyCacheWaves)) {
         const int rows = nodes * 7 / 16 + 8, room = 65536 - 64 - (int)(base.waves + waves * base.per_wave);
         A.cache_entries = std::max(0, std::min(rows * (rows | 1), room / (4 * sets)));
     }
@@ -1070,20 +1072,21 @@ static bool uses_static(const xzzx_group &g)
 // interval that leaves at most kMaxCheckpoints before the last sweep.  Short
 // schedules keep about eight, at least 16 sweeps apart: the replay covers up to
 // an interval, and beside 100 sweeps one of 64 showed (d = 13, 4099 syndromes of
-// 40 chains: a pass took 2.18 ms, now 2.08).
-static int checkpoint_interval(const Plan &P)
+// 40 chains: a pass took 2.18 ms, now 2.08); not with a short workspace (lean).
+static int checkpoint_interval(const Plan &P, bool lean)
 {
     const int last = P.n_sweeps - 1;
-    const int every = std::min(kCheckpointEvery, std::max(kCheckpointEvery / 4, (last + 7) / 8));
+    const int dense = std::min(kCheckpointEvery, std::max(kCheckpointEvery / 4, (last + 7) / 8));
+    const int every = lean ? kCheckpointEvery : dense;
     return std::max(every, (last + kMaxCheckpoints - 1) / kMaxCheckpoints);
 }
 
 // Checkpoints a specialised group keeps: the states at the start of sweeps
 // c, 2c, ... before the last sweep, for c = checkpoint_interval.
-static int checkpoints_of(const xzzx_group &g)
+static int checkpoints_of(const xzzx_group &g, bool lean)
 {
     if (!uses_static(g) || g.plan->P.n_sweeps <= 0) return 0;
-    return (g.plan->P.n_sweeps - 1) / checkpoint_interval(g.plan->P);
+    return (g.plan->P.n_sweeps - 1) / checkpoint_interval(g.plan->P, lean);
 }
 
 static int device_cus()
@@ -1158,7 +1161,7 @@ static size_t group_ws_bytes(const xzzx_group &g, bool decode, int grid, bool le
     if (!g.d_chain_e) b += align256(nc * 4);
     if (!g.d_best_chain) b += align256(ns * 4);
     if (grid) return b + align256((size_t)P.hdev.grid_words * nc * 4);
-    if (!lean || !spans(g)) b += align256((size_t)checkpoints_of(g) * P.lat.d * P.static_words * nc * 4);
+    if (!lean || !spans(g)) b += align256((size_t)checkpoints_of(g, lean) * P.lat.d * P.static_words * nc * 4);
     // (random-site calls have been accepted with nq / 16 + 1 words per chain)
     const size_t snap = lean && P.order == XZZX_ORDER_RANDOM_SITE ? P.lat.nq / 16 + 1 : min_snap_words(g, lean);
     b += align256(snap * nc * 4);
@@ -1197,7 +1200,7 @@ static GroupWs carve_group(const xzzx_group &g, bool decode, int grid, bool lean
     w.stop = g.d_chain_stop ? g.d_chain_stop : reinterpret_cast<int32_t *>(take(nc * 4));
     w.efin = g.d_chain_e ? g.d_chain_e : reinterpret_cast<int32_t *>(take(nc * 4));
     w.best_chain = g.d_best_chain ? g.d_best_chain : reinterpret_cast<int32_t *>(take(ns * 4));
-    const size_t ncp = grid || (lean && spans(g)) ? 0 : (size_t)checkpoints_of(g);
+    const size_t ncp = grid || (lean && spans(g)) ? 0 : (size_t)checkpoints_of(g, lean);
     const size_t snap = grid ? (size_t)P.hdev.grid_words : (size_t)min_snap_words(g, lean);
     w.cp_rows = ncp ? reinterpret_cast<uint32_t *>(take(ncp * P.lat.d * P.static_words * nc * 4)) : nullptr;
     w.min_snap = snap ? reinterpret_cast<uint32_t *>(take(snap * nc * 4)) : nullptr;
@@ -1309,7 +1312,7 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
         // checkpoints: written by the specialised kernel, read by the replay
         const bool cp = ws[i].cp_rows && (static_d || replay);
         G.cp_rows = cp ? ws[i].cp_rows : nullptr;
-        G.cp_every = cp ? checkpoint_interval(P) : 0;
+        G.cp_every = cp ? checkpoint_interval(P, ws[i].lean) : 0;
         G.n_chains = g.n_syn * 4 * g.n_rep;
         G.min_snap = (site || planar_d || ladder || grid_mv) ? ws[i].min_snap : nullptr;
         G.unit_offset = unit_offset;

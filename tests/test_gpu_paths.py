@@ -236,3 +236,22 @@ def test_finish_of_mixed_groups():
     for (prob, _, out, kw), what in zip(made, kinds):
         print(f"[paths] finish {what}", flush=True)
         compare_decode(prob, out, prob.oracle_decode(**kw))
+
+
+@pytest.mark.parametrize("sweeps", [16, 17, 18, 100, 129, 513])
+def test_checkpoint_intervals(sweeps):
+    """Checkpoints of short schedules (none at 16 sweeps; one, at the start of
+    the last sweep, at 17; at most eight) and, with a workspace short of the
+    full size, the sparser ones (at 16 and 513 sweeps the two are the same, and
+    the full size is the least)."""
+    prob = Problem(0, 9, 0.2, 10.0, 5, 16, sweeps, seed=500 + sweeps)
+    plan = gpu_plan(prob)
+    plan.set_kernel(X.KERNEL_ROWS)
+    ref = prob.oracle_decode()
+    syn, uid = to_dev(prob.syn), to_dev(prob.uid.view(np.int32))
+    for short in (0, 1) if 16 < sweeps < 513 else (0,):
+        g, out = D.make_group(plan, prob.n_rep, uid, syn=syn, want_chains=True, want_final=True)
+        ws = D.workspace([g])
+        D.decode_groups([g], prob.greedy_seed, prob.anneal_seed, ws=ws[:ws.numel() - short])
+        torch.cuda.synchronize()
+        compare_decode(prob, out, ref)
