@@ -1355,7 +1355,16 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
     int rc = anneal_grid((const void *)kern, kWave * site_waves, lds, A.n_tasks, &grid);
     if (rc) return rc;
     A.grid = grid;
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, d_counter, 1);
+    // The clear takes a workgroup of one wavefront for every SIMD.  After
+    // workgroups of several wavefronts (the greedy stage's) the dispatcher puts
+    // two of the next single-wavefront ones on some SIMDs and none on others,
+    // until a launch of such has passed through the same queue (read from the
+    // hardware ids of four launches of 1024: 20 to 80 SIMDs hold two of a
+    // launch, most seven wavefronts in all; after this clear all hold one of
+    // each).  Chains last long and a SIMD with one more ends last: five
+    // distances d = 5..21 of 256 syndromes and 256 chains took 214 ms, now 150;
+    // ladders at d = 11, four wavefronts a SIMD, 16.6 ms, now 16.0.
+    hipLaunchKernelGGL(k_zero_u32, dim3(4 * (unsigned)device_cus()), dim3(kWave), 0, stream, d_counter, 1);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kWave * site_waves), lds, stream, A);
     return check_hip(hipGetLastError(), "anneal launch");
 }
