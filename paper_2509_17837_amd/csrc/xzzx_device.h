@@ -686,7 +686,7 @@ __device__ inline void rows_core(const PlanDev *pl, const ChainJob &J, int t_beg
 // dE modulo 2^31 and, in bit 31, the threshold's top bit (1 where the move
 // always accepts).  Energies are sums of weights, in [0, 2^31) (the plan
 // checks it), so they are exact modulo 2^31.
-__device__ __forceinline__ uint2 move_entry(int32_t de, uint32_t thr)
+__host__ __device__ __forceinline__ uint2 move_entry(int32_t de, uint32_t thr)
 {
     const uint32_t e = (uint32_t)de & 0x7FFFFFFFu;
     return de <= 0 ? make_uint2(0u, e | 0x80000000u) : make_uint2(thr, e | (thr & 0x80000000u));
@@ -704,8 +704,14 @@ __device__ __forceinline__ uint32_t accept_mask(uint32_t u, const uint2 &e)
     return (uint32_t)((int32_t)__builtin_amdgcn_bitop3_b32(u, e.y, u - e.x, 0x8E) >> 31);
 }
 
-// E plus the accepted moves' words y.
-__device__ __forceinline__ int32_t add_energy(int32_t E, int32_t acc) { return (E + acc) & 0x7FFFFFFF; }
+// The accepted moves' words y are summed, and the sum added to E, modulo 2^32:
+// the words' top bits are no part of the energy and two of them already carry
+// out, so the sums are unsigned.
+__host__ __device__ __forceinline__ void take_move(uint32_t &acc, const uint2 &e, uint32_t sel) { acc += e.y & sel; }
+__host__ __device__ __forceinline__ int32_t add_energy(int32_t E, uint32_t acc)
+{
+    return (int32_t)(((uint32_t)E + acc) & 0x7FFFFFFFu);
+}
 
 // The thresholds of a sweep in the entries with dE > 0 (ranks kneg and up).
 __device__ __forceinline__ void set_thresholds(uint2 *et_s, const uint32_t *thr, int kneg, int nranks)
@@ -1007,7 +1013,7 @@ __device__ __forceinline__ uint2 static_lookup(const uint32_t (&r)[StaticRows<D>
 
 // Acceptance of the move with draw u and entry e, its flips and energy.
 template <int D, int K, int B, int W>
-__device__ __forceinline__ void static_apply(uint32_t (&r)[StaticRows<D>::N], uint32_t u, const uint2 &e, int32_t &acc,
+__device__ __forceinline__ void static_apply(uint32_t (&r)[StaticRows<D>::N], uint32_t u, const uint2 &e, uint32_t &acc,
                                              uint32_t zero)
 {
     using G = StaticGen<D, K, B, W>;
@@ -1017,13 +1023,13 @@ __device__ __forceinline__ void static_apply(uint32_t (&r)[StaticRows<D>::N], ui
         const uint32_t sel = accept_mask(u, e);
         if constexpr (G::has_a) row_flip_static<NW, G::BO, 6u>(ra, sel, zero);   // X_left | Z_up
         if constexpr (G::has_b) row_flip_static<NW, G::BO, 9u>(rb, sel, zero);   // Z_down | X_right
-        acc += (int32_t)(e.y & sel);
+        take_move(acc, e, sel);
     }
 }
 
 template <int D, int K, int B>
 __device__ __forceinline__ void static_block(uint32_t (&r)[StaticRows<D>::N], const uint4 &u, const uint16_t *lut_s,
-                                             const uint2 *et_s, int32_t &acc)
+                                             const uint2 *et_s, uint32_t &acc)
 {
     // The four generators of a block belong to one colour class and act on
     // disjoint qubits: a flip of one leaves the others' slot bits as they
@@ -1050,7 +1056,7 @@ __device__ __forceinline__ void static_block(uint32_t (&r)[StaticRows<D>::N], co
 
 template <int D, int K, typename Draw, int... Bs>
 __device__ __forceinline__ void static_class(uint32_t (&r)[StaticRows<D>::N], const Draw &draw, const uint16_t *lut_s,
-                                             const uint2 *et_s, int32_t &acc, std::integer_sequence<int, Bs...>)
+                                             const uint2 *et_s, uint32_t &acc, std::integer_sequence<int, Bs...>)
 {
     (static_block<D, K, Bs>(r, draw.template block<Bs>(), lut_s, et_s, acc), ...);
 }
@@ -1148,7 +1154,7 @@ __device__ __forceinline__ void rows_static_core(const PlanDev *pl, const ChainJ
             set_thresholds(et_s, pl->thr + (size_t)t * nranks, kneg, nranks);
             wave_lds_fence();
             const uint32_t c2 = 4u * (uint32_t)t;
-            int32_t acc = 0;
+            uint32_t acc = 0;
             static_class<D, 0>(r, draw_of(c2), lut_s, et_s, acc, Blocks{});
             E = add_energy(E, acc);
             if (E < Emin) { Emin = E; stop = 4 * t + 1; }

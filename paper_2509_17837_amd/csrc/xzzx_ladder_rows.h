@@ -50,7 +50,7 @@ __device__ __forceinline__ void ladder_rows_core(const PlanDev *pl, const ChainJ
     for (int t = 0; t < n_sweeps; ++t) {
         const uint2 *et_l = et_s + level * nranks;
         const uint32_t c2 = 4u * (uint32_t)t;
-        int32_t acc = 0;
+        uint32_t acc = 0;
         static_class<D, 0>(r, draw_of(c2), lut_s, et_l, acc, Blocks{});
         E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 1; if (keep) store_rows(keep, r); }

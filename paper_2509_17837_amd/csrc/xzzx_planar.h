@@ -47,7 +47,7 @@ __device__ __forceinline__ uint2 planar_lookup(const uint32_t (&r)[PlanarRows<D>
 }
 
 template <int D, int K, int B, int W>
-__device__ __forceinline__ void planar_apply(uint32_t (&r)[PlanarRows<D>::N], uint32_t u, const uint2 &e, int32_t &acc,
+__device__ __forceinline__ void planar_apply(uint32_t (&r)[PlanarRows<D>::N], uint32_t u, const uint2 &e, uint32_t &acc,
                                              uint32_t zero)
 {
     using G = PlanarGen<D, K, B, W>;
@@ -56,7 +56,7 @@ __device__ __forceinline__ void planar_apply(uint32_t (&r)[PlanarRows<D>::N], ui
         const uint32_t sel = accept_mask(u, e);
         row_flip_static<NW, G::BO, 6u>(r + G::Y * NW, sel, zero);         // X top-left | Z top-right
         row_flip_static<NW, G::BO, 9u>(r + (G::Y + 1) * NW, sel, zero);   // Z bottom-left | X bottom-right
-        acc += (int32_t)(e.y & sel);
+        take_move(acc, e, sel);
     }
 }
 
@@ -73,7 +73,7 @@ __device__ __forceinline__ void planar_lookups(const uint32_t (&r)[PlanarRows<D>
 
 template <int D, int K, int B>
 __device__ __forceinline__ void planar_applies(uint32_t (&r)[PlanarRows<D>::N], const uint4 &u, const uint2 (&e)[4],
-                                               int32_t &acc)
+                                               uint32_t &acc)
 {
     const uint32_t zero = PlanarRows<D>::NW == 1 ? 0u : opaque_zero();
     planar_apply<D, K, B, 0>(r, u.x, e[0], acc, zero);
@@ -92,7 +92,7 @@ __device__ __forceinline__ void planar_applies(uint32_t (&r)[PlanarRows<D>::N], 
 template <int D, int K, int B, int NB>
 __device__ __forceinline__ void planar_pipe(uint32_t (&r)[PlanarRows<D>::N], const LaneKey &lk,
                                             const LaneHead &h, uint32_t k0, uint32_t k1, const uint16_t *lut_s,
-                                            const uint2 *et_s, int32_t &acc, const uint2 (&e)[4])
+                                            const uint2 *et_s, uint32_t &acc, const uint2 (&e)[4])
 {
     const uint4 u = lane_philox_block<B, true>(lk, h, k0, k1);
     if constexpr (B + 1 < NB) {
@@ -110,7 +110,7 @@ __device__ __forceinline__ void planar_pipe(uint32_t (&r)[PlanarRows<D>::N], con
 template <int D, int K>
 __device__ __forceinline__ void planar_class(uint32_t (&r)[PlanarRows<D>::N], const LaneKey &lk, uint32_t cc,
                                              uint32_t c2, uint32_t k0, uint32_t k1, const uint16_t *lut_s,
-                                             const uint2 *et_s, int32_t &acc)
+                                             const uint2 *et_s, uint32_t &acc)
 {
     constexpr int NB = PlanarSchedule<D>::MP / 4;
     const LaneHead h = lane_head(lk, cc, c2, k0, k1);

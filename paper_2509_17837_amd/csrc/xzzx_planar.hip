@@ -34,7 +34,7 @@ __device__ __forceinline__ void planar_static_core(const PlanDev *pl, const Chai
         set_thresholds(et_s, pl->thr + (size_t)t * nranks, kneg, nranks);
         wave_lds_fence();
         const uint32_t c2 = 4u * (uint32_t)t;
-        int32_t acc = 0;
+        uint32_t acc = 0;
         planar_class<D, 0>(r, lk, cc, c2, k0, k1, lut_s, et_s, acc);
         E = add_energy(E, acc);
         if (E < Emin) { Emin = E; stop = 4 * t + 1; if (keep) keep_min(); }

@@ -123,7 +123,7 @@ __device__ __forceinline__ void site_core(const PlanDev *pl, const ChainJob &J, 
         if (WIDE) *(P)(uintptr_t)(a + 256u) = ra.y ^ ((fa >> 1) >> (~d.y & 31u));
         *(P)(uintptr_t)b = rb.x ^ (fb << (bo_b & 31u));
         if (WIDE) *(P)(uintptr_t)(b + 256u) = rb.y ^ ((fb >> 1) >> (~bo_b & 31u));
-        E = add_energy(E, (int32_t)(e.y & sel));
+        E = add_energy(E, e.y & sel);
         if (E < Emin) {
             Emin = E;
             stop = s + 1;
