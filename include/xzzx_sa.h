@@ -251,14 +251,18 @@ int xzzx_plan_set_ladder(xzzx_plan *plan, int levels, double beta_lo, double bet
  * probe_sweeps sweeps of the schedule, decodes n_syn random syndromes with
  * n_rep replicas once per candidate on `stream` (annealing stage timed with
  * HIP events, best of 3), and applies the fastest candidate to `plan`.
- * Candidates: the packed-row kernel where it applies, and the byte-state
- * kernel with 1, 2, 4, ..., 64 lanes per chain where its LDS fits.
- * times_ms[8] (may be NULL) receives the time of each candidate, index 0 for
- * the packed-row kernel and 1 + log2(lanes) for the byte-state kernel (-1 if
- * not tried).  Allocates and frees its own device buffers. */
+ * Candidates: XZZX_KERNEL_ROWS where it applies, xzzx_plan_set_lanes with 1,
+ * 2, 4, ..., 64 lanes per chain where its LDS fits, and XZZX_KERNEL_AUTO,
+ * each timed as the plan runs with it selected.  A plan whose default is
+ * within 10 % of the fastest is left at the default, which goes by the size of
+ * each call.
+ * times_ms[8] receives the time of each candidate but the default, index 0 for
+ * the packed-row kernel and 1 + log2(lanes) for chosen lanes (-1 if not
+ * tried).  Allocates and frees its own device buffers. */
 typedef struct {
-    int kernel;            /* chosen XZZX_KERNEL_ROWS or XZZX_KERNEL_BYTES */
-    int lanes_per_chain;   /* chosen lanes (byte-state kernel) */
+    int kernel;            /* chosen (the default: what it runs at the probe's size): XZZX_KERNEL_ROWS,
+                              XZZX_KERNEL_ROWS_GENERIC or XZZX_KERNEL_BYTES */
+    int lanes_per_chain;   /* chosen lanes (XZZX_KERNEL_BYTES) */
     float times_ms[8];
 } xzzx_tune_result;
 int xzzx_plan_autotune(xzzx_plan *plan, int n_rep, int n_syn, int probe_sweeps, void *stream,

@@ -371,3 +371,12 @@ struct xzzx_lattice {
 struct xzzx_plan {
     xzzx::Plan P;
 };
+
+// The annealing kernel of each group of a call with a workspace of so many
+// bytes (XZZX_KERNEL_*, or kRouteGrid), and its lanes per chain: what the
+// autotuner reports, and what tests of a kernel assert that they reach.
+namespace xzzx {
+constexpr int32_t kRouteGrid = 16;
+}
+extern "C" int xzzx_decode_routes(const xzzx_group *groups, int n_groups, size_t workspace_bytes, int32_t *kernel,
+                                  int32_t *lanes);

@@ -1894,6 +1894,27 @@ int xzzx_decode_workspace(const xzzx_group *groups, int n_groups, size_t *bytes)
     return XZZX_OK;
 }
 
+int xzzx_decode_routes(const xzzx_group *groups, int n_groups, size_t workspace_bytes, int32_t *kernel, int32_t *lanes)
+{
+    std::vector<int> grid = grid_routes(groups, n_groups);
+    size_t full = 0, least = 0;
+    ws_bytes(groups, n_groups, true, grid, &full, &least);
+    if (workspace_bytes < least) { set_error("workspace too small"); return XZZX_ENOMEM; }
+    for (int i = 0; i < n_groups; ++i) {
+        const Plan &P = groups[i].plan->P;
+        const int on_grid = workspace_bytes < full ? 0 : grid[i];
+        lanes[i] = 1;
+        if (P.order == XZZX_ORDER_RANDOM_SITE) kernel[i] = XZZX_KERNEL_SITE;
+        else if (P.ladder_k) kernel[i] = XZZX_KERNEL_LADDER;
+        else if (on_grid) kernel[i] = kRouteGrid;
+        else if (P.use_rows) kernel[i] = P.planar_d || P.static_d ? XZZX_KERNEL_ROWS : XZZX_KERNEL_ROWS_GENERIC;
+        else kernel[i] = XZZX_KERNEL_BYTES;
+        if (kernel[i] == kRouteGrid) lanes[i] = on_grid;
+        if (kernel[i] == XZZX_KERNEL_BYTES) lanes[i] = P.lanes;
+    }
+    return XZZX_OK;
+}
+
 int xzzx_decode(const xzzx_group *groups, int n_groups, uint64_t greedy_seed, uint64_t anneal_seed,
                 int greedy_mode, int flags, void *d_workspace, size_t workspace_bytes, void *stream)
 {
