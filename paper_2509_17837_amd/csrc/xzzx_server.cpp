@@ -162,8 +162,8 @@ int lanes_for(const Plan &P, int g)
     return c;
 }
 
-// sequential work of one sweep of one chain: attempts on the packed-row
-// kernels (g = 1); else in units of 0.3 us: the grid core's sweep takes 0.61,
+// sequential work of one sweep of one chain, in units of 0.06 us: the attempts
+// where a chain has a lane of its own (g = 1); the grid core's sweep takes 0.61,
 // 0.95, 1.8-2.2 and 3.6-4.7 us with one, two, four and eight moves per lane;
 // the byte-state kernel's 0.43 us a phase with one generator per lane, 0.92
 // with a block per lane, and about that much more for each further block
@@ -173,10 +173,108 @@ int64_t sweep_cost(const Plan &P, int g)
     const int gr = lanes_for(P, g);
     if (on_grid(P, g)) {
         const int mv = P.grid_moves(gr);
-        return mv == 1 ? 2 : mv == 2 ? 3 : mv == 4 ? 6 : 13;
+        return mv == 1 ? 10 : mv == 2 ? 15 : mv == 4 ? 30 : 65;
     }
-    if (std::max(1, P.lat.per_class) <= gr && gr >= 4) return 6;
-    return 12 * ((class_blocks(P) + gr - 1) / gr);
+    if (std::max(1, P.lat.per_class) <= gr && gr >= 4) return 30;
+    return 60 * ((class_blocks(P) + gr - 1) / gr);
+}
+
+struct Resident {
+    const Plan *plan;
+    int n_rep;
+};
+
+// Lanes per chain in one slice.  Every choice gives the same chain
+// trajectories, so it may change from one slice to the next.
+struct SliceForm {
+    int g = 1;                 // lanes per chain (1: each plan's own kernel)
+    bool wider = false;        // plans that g lanes do not hold on the grid core take the least that do
+    bool one_lane = false;     // plans with a specialised packed-row kernel run on it
+    int always = 0;            // lanes of plans without any packed-row kernel (0: as the others)
+
+    // lanes offered to a request (see lanes_for)
+    int offer(const Plan &P) const
+    {
+        if (P.use_rows && P.static_d) {
+            if (one_lane) return 1;
+        } else if (!P.use_rows && P.grid_auto && on_grid(P, always)) {
+            return always;
+        }
+        int o = g;
+        while (wider && o < kWave && !on_grid(P, o)) o *= 2;
+        return o;
+    }
+    bool rows(const Plan &P) const { return offer(P) == 1 && P.use_rows; }
+    int lanes(const Plan &P) const
+    {
+        const int o = offer(P);
+        return o > 1 ? lanes_for(P, o) : P.use_rows ? 1 : P.lanes;
+    }
+    int moves(const Plan &P) const { return offer(P) > 1 && on_grid(P, offer(P)) ? P.grid_moves(lanes(P)) : 0; }   // 0: not on the grid core
+    size_t lds(const Plan &P) const
+    {
+        return rows(P) ? P.lds_bytes_rows() : moves(P) ? P.lds_bytes_grid(lanes(P)) : P.lds_bytes_anneal(lanes(P));
+    }
+};
+
+// At light load every chain spreads over up to max_lanes_per_chain lanes (lower
+// latency per request); as resident work grows the count halves until the slice
+// fits the wave and LDS budgets, down to each plan's own kernel choice.  Where
+// that leaves a large lattice to the byte-state kernel, it takes its least
+// lanes on the grid core instead if the slice then fits with the others' lanes
+// or half of them (a mix of d = 7..25, 21120 chains: 5.3 -> 3.7 ms).
+//
+// With the budgets left at their defaults two rules come first.
+// - Plans with a specialised packed-row kernel go to one chain per lane at
+//   once when their work fills the device in that form: kOneLaneChainsPerCu
+//   chains per CU of the largest lattice among them, whose sweep on one lane
+//   is the slice's length.  At 65536 chains d = 11 takes 7.1 ms with the halving
+//   and 6.0 so, d = 31 21.3 and 12.6; at 25600 chains d = 11 takes 3.2 and 3.8, d = 21
+//   6.1 and 8.1.  By the number of chains alone, a few requests of d = 25 among
+//   small ones ran on by themselves (d = 7..25, 25600 chains: 5.1 against 10.4 ms).
+// - Plans without any packed-row kernel (planar d > 15) stay on the grid core
+//   with all the lanes, as in a batch: 32768 chains of d = 21 take 18.0 ms with the
+//   halving, 28.2 with their own four lanes, 13.3 so.
+// The other plans' kernel of one chain per lane, the generic one, is slower than
+// the halving (planar d = 9 to 15, 25600 chains: three to five times).
+constexpr int64_t kOneLaneChainsPerCu = 128;
+
+bool fits(const SliceForm &F, const std::vector<Resident> &resident, int64_t wave_budget, size_t lds_budget)
+{
+    int64_t waves = 0;
+    size_t lds_max = 0;
+    for (const Resident &r : resident) {
+        const Plan &P = *r.plan;
+        if (!P.use_rows && P.grid_auto && on_grid(P, F.always)) continue;
+        waves += (4 * r.n_rep * F.lanes(P) + kWave - 1) / kWave;
+        if (!F.rows(P)) lds_max = std::max(lds_max, F.lds(P));
+    }
+    return waves <= wave_budget && (size_t)waves * lds_max <= lds_budget;
+}
+
+SliceForm slice_form(const std::vector<Resident> &resident, const xzzx_server_cfg &cfg, int64_t wave_budget,
+                     size_t lds_budget)
+{
+    SliceForm F;
+    if (!cfg.max_waves && !cfg.lds_budget_bytes && cfg.max_lanes_per_chain > 1) {
+        F.always = cfg.max_lanes_per_chain;
+        int64_t work = 0, most = 0;
+        for (const Resident &r : resident) {
+            if (!r.plan->use_rows || !r.plan->static_d) continue;
+            work += 4 * (int64_t)r.n_rep * r.plan->lat.nstab;
+            most = std::max<int64_t>(most, r.plan->lat.nstab);
+        }
+        F.one_lane = work > kOneLaneChainsPerCu * (wave_budget / 32) * most;
+    }
+    F.g = cfg.max_lanes_per_chain;
+    while (F.g > 1 && !fits(F, resident, wave_budget, lds_budget)) F.g >>= 1;
+    if (cfg.max_lanes_per_chain == kWave && F.g > 1) {
+        SliceForm W = F;
+        W.wider = true;
+        for (int k = 0; k < 2 && W.g > 1; ++k, W.g >>= 1)
+            if (fits(W, resident, wave_budget, lds_budget)) return W;
+    }
+    return F;
 }
 
 size_t request_lds(const Plan &P, int n_rep)
@@ -281,37 +379,15 @@ int xzzx_server::slice()
     std::vector<CostTask> rows_t, bytes_t, static_t[kStaticMaxD + 1], grid_t[9];
     size_t lds_rows = 0, lds_bytes = 0, lds_grid[9] = {};
     std::vector<int> finished;
-    // lanes per chain for this slice: at light load every chain spreads over
-    // up to max_lanes_per_chain lanes of the byte-state kernel (lower latency
-    // per request); as resident work grows the count halves until the slice
-    // fits the wave and LDS budgets, down to each plan's own kernel choice.
-    // Every choice gives the same chain trajectories, so it may change from
-    // one slice to the next.
-    // Where the default wave budget leaves the choice open, that switch is made
-    // at once from kGridChainsPerCu chains per CU, where one chain per lane is
-    // the faster form (fewer lanes on the grid core are not: 65536 chains at
-    // d = 11, 500 sweeps, take 4.5 ms on 32 lanes, 5.9 on 4 and 3.9 on 1).
-    int G = 1;
-    int64_t chains = 0;
-    for (int s : resident) chains += 4 * (int64_t)slots[s].n_rep;
-    const bool full = !cfg.max_waves && chains > kGridChainsPerCu * (wave_budget / 32);
-    for (int g = full ? 1 : cfg.max_lanes_per_chain; g > 1; g >>= 1) {
-        int64_t waves = 0;
-        size_t lds_max = 0;
-        for (int s : resident) {
-            const Slot &sl = slots[s];
-            const int gr = lanes_for(*sl.plan, g);
-            waves += (4 * sl.n_rep * gr + kWave - 1) / kWave;
-            lds_max = std::max(lds_max, on_grid(*sl.plan, g) ? sl.plan->lds_bytes_grid(gr) : sl.plan->lds_bytes_anneal(gr));
-        }
-        if (waves <= wave_budget && (size_t)waves * lds_max <= lds_budget) { G = g; break; }
-    }
+    std::vector<Resident> in_slice;
+    for (int s : resident) in_slice.push_back({slots[s].plan, slots[s].n_rep});
+    const SliceForm form = slice_form(in_slice, cfg, wave_budget, lds_budget);
     // work-balanced slice: a request advances sweeps in inverse proportion to
     // the sequential work of one of its sweeps (generators per lane), so every
     // task of the slice carries about the work of sweeps_per_slice sweeps of
     // the costliest resident request
     int64_t ref_cost = 1;
-    for (int s : resident) ref_cost = std::max(ref_cost, sweep_cost(*slots[s].plan, G));
+    for (int s : resident) ref_cost = std::max(ref_cost, sweep_cost(*slots[s].plan, form.offer(*slots[s].plan)));
     // short slices at light load let arrivals join soon after they come;
     // with more requests resident the slices lengthen (one more
     // sweeps_per_slice per kSliceGrowth requests), so the fixed costs of a
@@ -321,17 +397,18 @@ int xzzx_server::slice()
     for (int s : resident) {
         Slot &sl = slots[s];
         const Plan &P = *sl.plan;
-        const int64_t share = std::max<int64_t>(1, slice_sweeps * ref_cost / sweep_cost(P, G));
+        const int64_t own_cost = sweep_cost(P, form.offer(P));
+        const int64_t share = std::max<int64_t>(1, slice_sweeps * ref_cost / own_cost);
         const int t0 = sl.t, t1 = (int)std::min<int64_t>(P.n_sweeps, t0 + share);
         // a fresh request always gets a first task (it initialises E, E_min
         // and the stored state even for an empty schedule)
         if (t1 > t0 || !sl.started) {
             sl.started = true;
-            const bool rows = G == 1 && P.use_rows;
-            const int gr = G > 1 ? lanes_for(P, G) : (P.use_rows ? 1 : P.lanes);
+            const bool rows = form.rows(P);
+            const int gr = form.lanes(P);
             const int C = kWave / gr;
-            const int mv = G > 1 && on_grid(P, G) ? P.grid_moves(gr) : 0;
-            const size_t lds = rows ? P.lds_bytes_rows() : mv ? P.lds_bytes_grid(gr) : P.lds_bytes_anneal(gr);
+            const int mv = form.moves(P);
+            const size_t lds = form.lds(P);
             const int nc = 4 * sl.n_rep;
             uint8_t *base = slot_ptr(s);
             for (int c0 = 0; c0 < nc; c0 += C) {
@@ -358,7 +435,7 @@ int xzzx_server::slice()
                 T.row_words = rows ? P.row_words : 0;
                 T.grid_mv = mv;
                 T.gs = reinterpret_cast<uint32_t *>(base + off_gs);
-                const int64_t cost = (int64_t)(t1 - t0) * sweep_cost(P, G);
+                const int64_t cost = (int64_t)(t1 - t0) * own_cost;
                 if (rows && P.static_d) static_t[serve_class_max(P.static_d)].emplace_back(cost, T);
                 else if (rows) { rows_t.emplace_back(cost, T); lds_rows = std::max(lds_rows, lds); }
                 else if (mv) { grid_t[mv].emplace_back(cost, T); lds_grid[mv] = std::max(lds_grid[mv], lds); }
@@ -605,6 +682,22 @@ int xzzx_server_create(const xzzx_server_cfg *cfg, xzzx_server **out)
     for (int i = ns - 1; i >= 0; --i) S->free_slots.push_back(i);
     S->worker = std::thread([S] { S->run(); });
     *out = S;
+    return XZZX_OK;
+}
+
+// The kernel (XZZX_KERNEL_*, or kRouteGrid) and lanes per chain of each request
+// in a slice that holds just these requests (for tests of the choice).
+extern "C" int xzzx_server_routes(const xzzx_server *srv, const xzzx_request *reqs, int n, int32_t *kernel, int32_t *lanes)
+{
+    std::vector<Resident> in_slice;
+    for (int i = 0; i < n; ++i) in_slice.push_back({&reqs[i].plan->P, reqs[i].n_rep});
+    const SliceForm form = slice_form(in_slice, srv->cfg, srv->wave_budget, srv->lds_budget);
+    for (int i = 0; i < n; ++i) {
+        const Plan &P = reqs[i].plan->P;
+        kernel[i] = form.moves(P) ? (int)kRouteGrid : !form.rows(P) ? (int)XZZX_KERNEL_BYTES
+                    : P.static_d ? (int)XZZX_KERNEL_ROWS : (int)XZZX_KERNEL_ROWS_GENERIC;
+        lanes[i] = form.lanes(P);
+    }
     return XZZX_OK;
 }
 

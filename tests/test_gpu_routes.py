@@ -84,3 +84,71 @@ def test_autotuner_large_call():
         alone = anneal_ms(g)
         print(f"[routes] {lanes} lanes {alone:.3f} ms", flush=True)
         assert tuned["times_ms"][f"bytes{lanes}"] < 1.4 * alone
+
+
+def serve_routes(srv, plans, n_rep):
+    """[(kernel, lanes per chain)] in a slice that holds one request of each plan."""
+    n = len(plans)
+    reqs = (X.Request * n)(*[X.Request(p.h, None, 0, n_rep) for p in plans])
+    kernel, lanes = (C.c_int32 * n)(), (C.c_int32 * n)()
+    X.check("xzzx_server_routes", X.lib().xzzx_server_routes(srv.h, reqs, n, kernel, lanes))
+    return list(zip(kernel, lanes))
+
+
+def test_serving_forms():
+    """Which requests of a slice run one chain per lane: those with a specialised
+    packed-row kernel, where their work fills the device in that form (more than
+    32768 chains of the largest lattice among them); planar lattices and plans
+    with another kernel chosen do not."""
+    def plan(layout, d, **kw):
+        return gpu_plan(Problem(layout, d, 0.15, 10.0, 0, 1, 10, seed=d, conv=layout), **kw)
+
+    srv = D.Server(max_slots=8, max_rep=16, max_qubits=1861)
+    limited = D.Server(max_slots=8, max_rep=16, max_qubits=1861, max_lanes_per_chain=1)
+    try:
+        r11 = plan(0, 11)
+        assert set(serve_routes(srv, [r11] * 100, 16)) == {(GRID, 32)}
+        assert set(serve_routes(srv, [r11] * 600, 16)) == {(X.KERNEL_ROWS, 1)}
+        assert set(serve_routes(limited, [r11] * 100, 16)) == {(X.KERNEL_ROWS, 1)}
+        for d in (17, 21, 31):
+            p = plan(1, d)
+            assert set(serve_routes(srv, [p] * 1024, 16)) == {(GRID, 64)}
+            assert {k for k, _ in serve_routes(limited, [p] * 1024, 16)} == {X.KERNEL_BYTES}
+        for p in (plan(1, 5), plan(1, 9), plan(1, 15), plan(0, 15, lanes=1)):
+            got = serve_routes(srv, [p] * 400, 16)
+            assert {k for k, _ in got} <= {GRID, X.KERNEL_BYTES} and min(l for _, l in got) >= 8
+        # a third of the chains cannot fill the device with one of d = 25 on each lane
+        wide = [plan(0, d) for d in (7, 13, 25)]
+        assert X.KERNEL_ROWS not in {k for k, _ in serve_routes(srv, [wide[i % 3] for i in range(400)], 16)}
+        assert serve_routes(srv, [wide[i % 3] for i in range(400)], 16)[2] == (GRID, 32)
+        assert serve_routes(srv, [wide[i % 3] for i in range(330)], 16)[2] == (GRID, 32)
+        both = serve_routes(srv, [plan(1, 21), r11] * 600, 16)
+        assert both[0] == (GRID, 64) and both[1] == (X.KERNEL_ROWS, 1)
+    finally:
+        srv.close()
+        limited.close()
+
+
+@pytest.mark.parametrize("kinds", [[(1, 21), (0, 11)], [(1, 9), (0, 25), (0, 5)]])
+def test_serving_under_load_matches_decode(kinds):
+    """Requests past the grid core's range in mixed forms: the results of a batch
+    decode (which the parity tests compare with the oracle)."""
+    probs = [Problem(l, d, 0.15, 10.0, -(-450 // len(kinds)), 16, 12, seed=7, conv=l) for l, d in kinds]
+    plans = [gpu_plan(p) for p in probs]
+    srv = D.Server(max_slots=512, max_rep=16, max_qubits=841, sweeps_per_slice=5, greedy_seed=21, anneal_seed=22)
+    try:
+        reqs = [(k, i) for i in range(probs[0].n_syn) for k in range(len(kinds))]
+        tickets = srv.submit_many([plans[k] for k, _ in reqs], [probs[k].syn[i] for k, i in reqs],
+                                  [int(probs[k].uid[i]) for k, i in reqs], 16)
+        srv.drain()
+        got = [srv.poll(t) for t in tickets]
+    finally:
+        srv.close()
+    for k, (prob, plan) in enumerate(zip(probs, plans)):
+        out = D.decode(plan, to_dev(prob.syn), to_dev(prob.uid.view(np.int32)), 16, 21, 22)
+        torch.cuda.synchronize()
+        mine = [g for g, (kk, _) in zip(got, reqs) if kk == k]
+        assert np.array_equal([g["e_best"] for g in mine], out.e_best.cpu().numpy())
+        assert np.array_equal([g["cls"] for g in mine], out.cls.cpu().numpy())
+        assert np.array_equal(np.stack([g["recovery"] for g in mine]), out.recovery.cpu().numpy())
+
