@@ -151,3 +151,4 @@ def test_serving_under_load_matches_decode(kinds):
         assert np.array_equal([g["e_best"] for g in mine], out.e_best.cpu().numpy())
         assert np.array_equal([g["cls"] for g in mine], out.cls.cpu().numpy())
         assert np.array_equal(np.stack([g["recovery"] for g in mine]), out.recovery.cpu().numpy())
+
