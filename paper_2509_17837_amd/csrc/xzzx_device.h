@@ -1362,15 +1362,6 @@ __device__ __forceinline__ void batch_kernel_body(const AnnealArgs &A)
     }
 }
 
-// Priority of a wavefront on its SIMD by the distance of its chain, when
-// launches of several distances share the device: a sweep of a large lattice
-// takes longest and there are as many sweeps to each, so the largest chains
-// would run on alone at the end if the small ones' wavefronts got an equal
-// share of every SIMD meanwhile.  (Within a launch all are equal.)  With the
-// sets launched longest first, five distances d = 5..21 of 256 syndromes and
-// 256 chains in one call went from 274 to 234 ms.
-constexpr int static_priority(int d) { return d <= 9 ? 0 : d <= 13 ? 1 : d <= 17 ? 2 : 3; }
-
 // Batch body of the specialised packed-row kernel.  Every group of the launch
 // has distance SD; tasks of 64 chains (SPAN: see rows_static_core).
 template <int SD, bool SPAN>
@@ -1378,7 +1369,6 @@ __device__ __forceinline__ void static_rows_body(const AnnealArgs &A)
 {
     __shared__ uint16_t lut_s[256 * 6];
     __shared__ uint2 et_s[kStaticRanks];
-    __builtin_amdgcn_s_setprio(static_priority(SD));
     const PlanDev *loaded = nullptr;
     for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
         int gi = 0;
@@ -1531,7 +1521,6 @@ template <int D>
 __device__ __forceinline__ void serve_static_task(const ServeTask &T, uint32_t slo, uint32_t shi, uint16_t *lut_s,
                                                   uint2 *et_s)
 {
-    __builtin_amdgcn_s_setprio(static_priority(D));
     load_static_tables(T.plan, lut_s, et_s);
     const ChainJob J = serve_job(T, threadIdx.x, false);
     rows_static_core<D, false>(T.plan, J, T.t_begin, T.t_end, slo, shi, lut_s, et_s, 0);

@@ -1584,7 +1584,9 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
             if (!grid_sel[l][m].empty()) sets.push_back({&grid_sel[l][m], false, 4 << l, 0, false, 0, false, 1 << m});
     // the sets whose tasks take longest first: with more sets than queues the
     // last ones start when earlier ones have ended, and the longest tasks
-    // must not be among them
+    // must not be among them (256 syndromes of 256 chains each at d = 5..21, 1000
+    // sweeps: 42.1 ms in ascending order, 31.4 so; d = 19, 25, 31: 29.2 and 27.5.
+    // Wavefronts of large lattices at a higher priority on top took 2 % longer.)
     auto task_work = [&](const Set &S) {
         double w = 0;
         for (int i : *S.sel) w = std::max(w, (double)groups[i].plan->P.n_sweeps * groups[i].plan->P.lat.nstab / S.lanes);
