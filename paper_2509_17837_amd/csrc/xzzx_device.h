@@ -1566,8 +1566,9 @@ int ladder_rows_state_words(int d);
 AnnealKernel grid_kernel(int lanes, int mv);
 typedef void (*ServeKernel)(const ServeTask *, uint32_t, uint32_t);
 ServeKernel serve_grid_kernel(int mv);
-// random-site kernels (wide: some row of the lattice takes several words)
-AnnealKernel site_kernel(bool wide, bool replay);
+// random-site kernels (wide: some row of the lattice takes several words;
+// compact: states kept without gaps, in nq / 16 + 1 words)
+AnnealKernel site_kernel(bool wide, bool compact);
 
 // The specialised kernels live in several translation units (compiled in
 // parallel): the annealing kernels by distance (each part returns its kernels

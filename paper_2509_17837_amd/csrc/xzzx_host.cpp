@@ -464,7 +464,8 @@ struct GridTables {
     // random-site core
     int site_words = 0, site_wide = 0;
     std::vector<uint2> site_desc;
-    std::vector<uint16_t> site_pos;
+    std::vector<uint16_t> site_pos, site_order;
+    std::vector<uint32_t> site_run;
 };
 
 static bool build_site(const Lattice &L, GridTables &T, const std::vector<int> &base,
@@ -612,6 +613,24 @@ static bool build_site(const Lattice &L, GridTables &T, const std::vector<int> &
     for (int q = 0; q < L.nq; ++q) {
         const int r = T.cell[q] / T.pitch, c = T.cell[q] % T.pitch;
         T.site_pos[q] = (uint16_t)(32 * word[r] + bit[r] + 2 * (c - lo[r]));
+    }
+    // the rows' bits in sequence (for kept states without the packing's gaps)
+    std::vector<int> before(rows, 0);
+    for (int r = 0, at = 0; r < rows; ++r) {
+        before[r] = at;
+        at += width[r];
+        for (int p = bit[r], left = 2 * width[r]; left > 0;) {
+            const int n = std::min(left, 32 - (p & 31));
+            T.site_run.push_back((uint32_t)(word[r] + (p >> 5)) | ((uint32_t)(p & 31) << 8) | ((uint32_t)n << 16));
+            p += n;
+            left -= n;
+        }
+    }
+    while (T.site_run.size() % 8) T.site_run.push_back(0u);   // pieces of no bits
+    T.site_order.resize(L.nq);
+    for (int q = 0; q < L.nq; ++q) {
+        const int r = T.cell[q] / T.pitch, c = T.cell[q] % T.pitch;
+        T.site_order[q] = (uint16_t)(before[r] + c - lo[r]);
     }
     T.site_desc.resize(L.nstab);
     for (int f = 0; f < L.nstab; ++f) {
@@ -821,6 +840,8 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
     const size_t o_gcell = take(grid.cell.size() * 2);
     const size_t o_sdesc = take(grid.site_desc.size() * sizeof(uint2));
     const size_t o_spos = take(grid.site_pos.size() * 2);
+    const size_t o_srun = take(grid.site_run.size() * 4);
+    const size_t o_sorder = take(grid.site_order.size() * 2);
     size_t o_cf[2], o_dint[2], o_db[2], o_adj[2];
     for (int g = 0; g < 2; ++g) {
         o_cf[g] = take(G[g].n * 4);
@@ -847,6 +868,8 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
     put(o_gcell, grid.cell.data(), grid.cell.size() * 2);
     put(o_sdesc, grid.site_desc.data(), grid.site_desc.size() * sizeof(uint2));
     put(o_spos, grid.site_pos.data(), grid.site_pos.size() * 2);
+    put(o_srun, grid.site_run.data(), grid.site_run.size() * 4);
+    put(o_sorder, grid.site_order.data(), grid.site_order.size() * 2);
     for (int g = 0; g < 2; ++g) {
         put(o_cf[g], G[g].col_face.data(), G[g].n * 4);
         put(o_dint[g], G[g].dint.data(), (size_t)G[g].n * G[g].n * 4);
@@ -896,6 +919,9 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
     h.site_words = grid.site_words;
     h.site_desc = reinterpret_cast<const uint2 *>(base + o_sdesc);
     h.site_pos = reinterpret_cast<const uint16_t *>(base + o_spos);
+    h.site_runs = (int)grid.site_run.size();
+    h.site_run = reinterpret_cast<const uint4 *>(base + o_srun);
+    h.site_order = reinterpret_cast<const uint16_t *>(base + o_sorder);
     for (int g = 0; g < 2; ++g) {
         h.ncol[g] = G[g].n;
         h.col_face[g] = reinterpret_cast<const int32_t *>(base + o_cf[g]);

@@ -242,6 +242,9 @@ struct PlanDev {
                                    // columns, 16 bits each); bit of the upper and (<< 6) the lower row's
                                    // nibble, present cells << 12, entry table << 20
     const uint16_t *site_pos;      // [nq] bit of each qubit (32 word + bit)
+    int site_runs;                 // the rows' bits one after another, in pieces inside a word (a multiple of eight):
+    const uint4 *site_run;         // [site_runs / 4] word | first bit << 8 | bits << 16
+    const uint16_t *site_order;    // [nq] place of each qubit in that sequence
     // greedy matching, per decoding-graph colour g
     int ncol[2];
     const int32_t *col_face[2];    // node -> face id (ascending)

@@ -745,8 +745,9 @@ __global__ void k_zero_u32(uint32_t *p, int n)
 // bits 2 (q mod 16) (generic ladder kernel); rows chain-major, `words` words a
 // chain, word Y * row_words + c / 16 holding row Y, column c, of the planar
 // lattice's qpos or (rotated) of qubit dY + c; the grid core's bytes, code << 3
-// per cell, `words` words a chain; the random-site kernel's words [w][ci].
-enum class Kept { None, Packed, PlanarRows, RotatedRows, Grid, Site };
+// per cell, `words` words a chain; the random-site kernel's words [w][ci], or
+// (SiteOrder) its rows' bits in sequence, [place div 16][ci].
+enum class Kept { None, Packed, PlanarRows, RotatedRows, Grid, Site, SiteOrder };
 
 struct FinishGroup {
     const PlanDev *plan;
@@ -851,6 +852,12 @@ __global__ __launch_bounds__(kFinishWaves *kWave) void k_finish(FinishArgs A)
     }
     case Kept::Grid:
         for (int q = lane; q < nq; q += kWave) out[q] = reinterpret_cast<const uint8_t *>(own)[pl->grid_cell[q]] >> 3;
+        break;
+    case Kept::SiteOrder:
+        for (int q = lane; q < nq; q += kWave) {
+            const uint32_t o = pl->site_order[q];
+            out[q] = (uint8_t)((G.snap[(int64_t)(o >> 4) * n_chains + ci] >> (2u * (o & 15u))) & 3u);
+        }
         break;
     default:
         for (int q = lane; q < nq; q += kWave) {
@@ -1049,7 +1056,7 @@ static int64_t min_snap_words(const xzzx_group &g, bool lean)
     const Plan &P = g.plan->P;
     if (ladder_rows_d(g, lean)) return ladder_rows_state_words(ladder_rows_d(g, lean));
     if (ladder_planar_d(g)) return planar_state_words(ladder_planar_d(g));
-    if (P.order == XZZX_ORDER_RANDOM_SITE) return lean ? 0 : P.hdev.site_words;
+    if (P.order == XZZX_ORDER_RANDOM_SITE) return lean ? P.lat.nq / 16 + 1 : P.hdev.site_words;
     if (P.ladder_k) return P.lat.nq / 16 + 1;
     if (P.use_rows && P.planar_d) return planar_state_words(P.planar_d);
     return 0;
@@ -1162,18 +1169,15 @@ static size_t group_ws_bytes(const xzzx_group &g, bool decode, int grid, bool le
     if (!g.d_best_chain) b += align256(ns * 4);
     if (grid) return b + align256((size_t)P.hdev.grid_words * nc * 4);
     if (!lean || !spans(g)) b += align256((size_t)checkpoints_of(g, lean) * P.lat.d * P.static_words * nc * 4);
-    // (random-site calls have been accepted with nq / 16 + 1 words per chain)
-    const size_t snap = lean && P.order == XZZX_ORDER_RANDOM_SITE ? P.lat.nq / 16 + 1 : min_snap_words(g, lean);
-    b += align256(snap * nc * 4);
-    return b;
+    return b + align256((size_t)min_snap_words(g, lean) * nc * 4);
 }
 
 // Workspace of a call: what its kernels use at best (`full`), and what it is
 // accepted with (`least`): the grid core's states may take more than the
 // other kernels' checkpoints, and a call whose workspace is short of them
 // runs on those kernels instead; groups whose tasks span syndromes then keep
-// no checkpoints and random-site groups no states, and their recoveries are
-// replayed from the references.
+// no checkpoints, and their recoveries are replayed from the references;
+// random-site groups keep their states in fewer words.
 static void ws_bytes(const xzzx_group *groups, int n_groups, bool decode, const std::vector<int> &grid, size_t *full,
                      size_t *least)
 {
@@ -1340,7 +1344,7 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
                               : (ladder && static_d) ? ladder_rows_kernel(static_d, span)
                               : (ladder && planar_d) ? ladder_planar_kernel(planar_d)
                               : ladder     ? ladder_kernel()
-                              : site     ? site_kernel(site_wide, replay)
+                              : site     ? site_kernel(site_wide, ws[order[0]].lean)
                               : planar_d ? planar_rows_kernel(planar_d)
                               : static_d ? static_rows_kernel(static_d, span)
                               : rows     ? k_anneal_rows
@@ -1475,7 +1479,7 @@ static Kept kept_state(const xzzx_group &g, const GroupWs &w)
     const Plan &P = g.plan->P;
     if (!w.min_snap) return Kept::None;
     if (w.grid) return Kept::Grid;
-    if (P.order == XZZX_ORDER_RANDOM_SITE) return Kept::Site;
+    if (P.order == XZZX_ORDER_RANDOM_SITE) return w.lean ? Kept::SiteOrder : Kept::Site;
     if (ladder_rows_d(g, w.lean)) return Kept::RotatedRows;
     if (P.ladder_k && !ladder_planar_d(g)) return Kept::Packed;
     return min_snap_words(g, w.lean) ? Kept::PlanarRows : Kept::None;
@@ -1486,8 +1490,7 @@ static Kept kept_state(const xzzx_group &g, const GroupWs &w)
 // replay re-runs one chain per syndrome with the byte-state kernel, spreading
 // a chain over more lanes when that is needed to give every CU several
 // wavefronts.  Each launch has its own queue counter: launch i of an annealing
-// stage d_counters[i]; a replay (with its own d_counters base) uses [0], [2], [4]
-// and [5].
+// stage d_counters[i]; a replay (with its own d_counters base) uses [0] and [2].
 constexpr int kReplayCounters = 16;   // words before the replay's counters
 static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_groups, AnnealMode mode,
                          uint64_t seed, int64_t unit_offset, int64_t units_override, uint32_t *d_counters,
@@ -1497,7 +1500,7 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
     std::vector<int> bytes_sel[7];
     std::vector<int> static_sel[2][kStaticMaxD + 1];   // [tasks span syndromes][d]
     std::vector<int> replay_cp;   // replays starting from checkpoints: one chain per wavefront
-    std::vector<int> site_sel[2]; // random-site plans, by site_wide: one chain (replay: syndrome) per lane
+    std::vector<int> site_sel[2]; // random-site plans, by site_wide: one chain per lane
     std::vector<int> planar_sel[kPlanarStaticMaxD + 1];   // planar kernels specialised to d
     std::vector<int> grid_sel[5][4];   // grid core, by lanes per chain (4..64) and moves per lane (1, 2, 4, 8)
     std::vector<int> ladder_sel;  // replica exchange: one chain per lane
@@ -1513,9 +1516,8 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
         }
         if (ws[i].grid || P.order == XZZX_ORDER_RANDOM_SITE || P.ladder_k ||
             (mode == AnnealMode::Replay && min_snap_words(groups[i], ws[i].lean))) {
-            if (mode == AnnealMode::Replay) {
-                if (kept_state(groups[i], ws[i]) == Kept::None) site_sel[P.site_wide].push_back(i);
-            } else if (const int ld = ladder_rows_d(groups[i], ws[i].lean)) ladder_rows_sel[spans(groups[i])][ld].push_back(i);
+            if (mode == AnnealMode::Replay) continue;   // these kept their states
+            if (const int ld = ladder_rows_d(groups[i], ws[i].lean)) ladder_rows_sel[spans(groups[i])][ld].push_back(i);
             else if (ladder_planar_d(groups[i])) ladder_planar_sel[ladder_planar_d(groups[i])].push_back(i);
             else (P.ladder_k ? ladder_sel : site_sel[P.site_wide]).push_back(i);
             continue;
@@ -1543,10 +1545,6 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
         if (!rc)
             rc = launch_set(groups, ws, replay_cp, false, kWave, mode, seed, unit_offset, units_override,
                             d_counters + 2, stream);
-        // random-site groups without kept states: one chain (syndrome) per lane
-        for (int wide = 0; wide < 2 && !rc; ++wide)
-            rc = launch_set(groups, ws, site_sel[wide], false, 1, mode, seed, unit_offset, units_override,
-                            d_counters + 4 + wide, stream, 0, true);
         return rc;
     }
     // the launches of one call (one per kernel family and distance) run

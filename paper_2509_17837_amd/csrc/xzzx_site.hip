@@ -28,14 +28,14 @@
 // 2) and 2 (m mod 2) + 1 are the site draw (site = floor(u N_stab / 2^32),
 // face-id order) and the acceptance draw.  E_min is tracked after every step;
 // stop = t N_stab + m + 1 (0 = the start), and the state at the first E_min is
-// kept in `snap` (word w of chain ci at snap[w * snap_stride + ci]) for the
-// recovery.  Without `snap` (a short workspace) REPLAY re-runs each syndrome's
-// best chain up to its target step and stores that state.
+// kept in `snap` for the recovery: word w of chain ci at snap[w * snap_stride +
+// ci].  With a full workspace the words are the state's own; COMPACT (a short
+// workspace) closes the packing's gaps, so that nq / 16 + 1 words hold them.
 #include "xzzx_grid.h"
 
 namespace xzzx {
 
-// LDS: entries, descriptors, then the wavefronts' states (grid_words of 64
+// LDS: entries, descriptors, then the wavefronts' states (site_words of 64
 // words each, see PlanDev)
 __device__ __forceinline__ uint32_t site_desc_off(const PlanDev *pl) { return (8u * ((uint32_t)pl->grid_slots + 1u) + 15u) & ~15u; }
 __device__ __forceinline__ uint32_t site_state_off(const PlanDev *pl)
@@ -49,7 +49,7 @@ __device__ __forceinline__ uint2 lds_read_pair(uint32_t a)   // words a and a + 
     return make_uint2(*(P)(uintptr_t)a, *(P)(uintptr_t)(a + 256u));
 }
 
-template <bool WIDE, bool REPLAY>
+template <bool WIDE, bool COMPACT>
 __device__ __forceinline__ void site_core(const PlanDev *pl, const ChainJob &J, uint32_t seed_lo, uint32_t seed_hi,
                                           uint8_t *smem, uint32_t *snap, int64_t snap_stride)
 {
@@ -86,13 +86,46 @@ __device__ __forceinline__ void site_core(const PlanDev *pl, const ChainJob &J, 
             dst[q] = (uint8_t)((st[(p >> 5) * kWave] >> (p & 31u)) & 3u);
         }
     };
-    uint32_t *const keep = !REPLAY && snap && J.active ? snap + J.ci : nullptr;
+    uint32_t *const keep = J.active ? snap + J.ci : nullptr;
     auto keep_min = [&]() {
+        if constexpr (COMPACT) {
+            uint64_t acc = 0;
+            uint32_t fill = 0;   // bits of acc in use, uniform
+            uint32_t *dst = keep;
+            auto piece = [&](uint32_t r, uint32_t v) {
+                const uint32_t n = r >> 16;
+                v >>= (r >> 8) & 31u;
+                acc |= (uint64_t)(n < 32u ? v & ((1u << n) - 1u) : v) << fill;
+                fill += n;
+                if (fill >= 32u) {
+                    *dst = (uint32_t)acc;
+                    dst += snap_stride;
+                    acc >>= 32;
+                    fill -= 32u;
+                }
+            };
+            // eight pieces' words are read before any is placed, and the next
+            // eight pieces fetched meanwhile
+            const int n8 = (int)uni(pl->site_runs) / 8;
+            uint4 nx = pl->site_run[0], ny = pl->site_run[1];
+            for (int i = 0; i < n8; ++i) {
+                const uint32_t r[8] = {uni(nx.x), uni(nx.y), uni(nx.z), uni(nx.w), uni(ny.x), uni(ny.y), uni(ny.z), uni(ny.w)};
+                const int next = min(i + 1, n8 - 1);
+                nx = pl->site_run[2 * next];
+                ny = pl->site_run[2 * next + 1];
+                uint32_t v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = st[(r[k] & 0xFFu) * kWave];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) piece(r[k], v[k]);
+            }
+            if (fill) *dst = (uint32_t)acc;
+        } else {
 #pragma unroll 4
-        for (int w = 0; w < words; ++w) keep[w * snap_stride] = st[w * kWave];
+            for (int w = 0; w < words; ++w) keep[w * snap_stride] = st[w * kWave];
+        }
     };
     if (keep) keep_min();
-    if (REPLAY && J.active && J.target == 0) save_state(J.snap);
 
     auto site_desc = [&](uint32_t u) -> uint2 {
         return lds_read64(desc0 + (__umulhi(u, 8u * nstab) & ~7u));   // 8 floor(u N / 2^32)
@@ -129,7 +162,6 @@ __device__ __forceinline__ void site_core(const PlanDev *pl, const ChainJob &J, 
             stop = s + 1;
             if (keep) keep_min();
         }
-        if (REPLAY && J.active && s + 1 == J.target) save_state(J.snap);
     };
 
     const int n_rising = (int)uni(pl->grid_rising);
@@ -158,7 +190,7 @@ __device__ __forceinline__ void site_core(const PlanDev *pl, const ChainJob &J, 
             step(c1, u1, s0 + (int32_t)m + 1);   // N_stab is even
         }
     }
-    if (!REPLAY && J.active) {
+    if (J.active) {
         J.emin[J.ci] = Emin;
         J.stop[J.ci] = stop;
         J.efin[J.ci] = E;
@@ -166,7 +198,7 @@ __device__ __forceinline__ void site_core(const PlanDev *pl, const ChainJob &J, 
     }
 }
 
-template <bool WIDE, bool REPLAY>
+template <bool WIDE, bool COMPACT>
 __device__ __forceinline__ void site_body(const AnnealArgs &A)
 {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -190,8 +222,8 @@ __device__ __forceinline__ void site_body(const AnnealArgs &A)
             for (int i = threadIdx.x; i < pl->nstab; i += blockDim.x) desc[i] = pl->site_desc[i];
             loaded = pl;
         }
-        const ChainJob J = batch_job(G, unit0 + threadIdx.x, REPLAY);
-        site_core<WIDE, REPLAY>(G.plan, J, A.seed_lo, A.seed_hi, smem, G.min_snap, G.n_chains);
+        const ChainJob J = batch_job(G, unit0 + threadIdx.x, false);
+        site_core<WIDE, COMPACT>(G.plan, J, A.seed_lo, A.seed_hi, smem, G.min_snap, G.n_chains);
         if (!A.counter) break;
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -203,15 +235,13 @@ __device__ __forceinline__ void site_body(const AnnealArgs &A)
     }
 }
 
-template <bool WIDE>
-__global__ __launch_bounds__(8 * kWave) void k_anneal_site(AnnealArgs A) { site_body<WIDE, false>(A); }
-template <bool WIDE>
-__global__ __launch_bounds__(8 * kWave) void k_replay_site(AnnealArgs A) { site_body<WIDE, true>(A); }
+template <bool WIDE, bool COMPACT>
+__global__ __launch_bounds__(8 * kWave) void k_anneal_site(AnnealArgs A) { site_body<WIDE, COMPACT>(A); }
 
-AnnealKernel site_kernel(bool wide, bool replay)
+AnnealKernel site_kernel(bool wide, bool compact)
 {
-    if (replay) return wide ? k_replay_site<true> : k_replay_site<false>;
-    return wide ? k_anneal_site<true> : k_anneal_site<false>;
+    if (compact) return wide ? k_anneal_site<true, true> : k_anneal_site<false, true>;
+    return wide ? k_anneal_site<true, false> : k_anneal_site<false, false>;
 }
 
 }  // namespace xzzx

@@ -152,3 +152,29 @@ def test_serving_under_load_matches_decode(kinds):
         assert np.array_equal([g["cls"] for g in mine], out.cls.cpu().numpy())
         assert np.array_equal(np.stack([g["recovery"] for g in mine]), out.recovery.cpu().numpy())
 
+
+def test_random_site_states_in_a_short_workspace():
+    """Random-site calls keep each chain's best state also with the least
+    workspace: the finish reads it, where a replay would run whole schedules."""
+    prob = Problem(1, 9, 0.15, 5.0, 0, 1, 100, seed=9, conv=1)
+    plan = gpu_plan(prob)
+    plan.set_order(X.ORDER_RANDOM_SITE)
+    g, o = group_of(plan, 2048, 10)
+    rng = np.random.default_rng(6)
+    o.keep[2].copy_(torch.from_numpy(rng.integers(0, 2, (2048, plan.nstab), dtype=np.uint8)))
+    full = D.workspace([g])
+    ws = full[:full.numel() - 1]
+    times = {}
+    for stage in (X.STAGE_GREEDY, X.STAGE_ANNEAL, X.STAGE_FINISH, X.STAGE_ANNEAL, X.STAGE_FINISH):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        D.decode_groups([g], 1, 2, flags=stage, ws=ws)
+        b.record()
+        torch.cuda.synchronize()
+        times[stage] = a.elapsed_time(b)
+    print(f"[routes] stages {times}", flush=True)
+    assert times[X.STAGE_FINISH] < 0.2 * times[X.STAGE_ANNEAL]
+    short = [t.clone() for t in (o.e_best, o.cls, o.recovery)]
+    D.decode_groups([g], 1, 2, ws=full)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(short, (o.e_best, o.cls, o.recovery)))
