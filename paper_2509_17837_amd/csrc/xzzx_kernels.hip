@@ -54,7 +54,10 @@ namespace xzzx {
 // of a row, so a wavefront's LDS accesses fall in distinct banks (the row
 // pitch is odd) and its global ones in 64-byte runs.
 // ---------------------------------------------------------------------------
-constexpr int kSynThreads = 256;
+// A workgroup has 256 threads, or 1024 where a few workgroups have large
+// lattices to take and their latency counts (planar d = 31, 1 to 1000
+// configurations: 10.3 us with 256 threads, 6.8 so).
+constexpr int kSynThreads = 256, kSynThreadsMost = 1024;
 
 // bytes (v0.j, v1.j, v2.j, v3.j) of four dwords into dword j
 __device__ __forceinline__ void transpose4x4(uint32_t (&v)[4])
@@ -71,7 +74,8 @@ __device__ __forceinline__ void transpose4x4(uint32_t (&v)[4])
 // padded to whole dwords of a configuration
 static int syndrome_rows(int nq) { return (nq + 4) / 4 * 4; }
 
-__global__ __launch_bounds__(kSynThreads) void k_syndrome(const PlanDev *__restrict__ pl,
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_syndrome(const PlanDev *__restrict__ pl,
                                                           const uint8_t *__restrict__ cfg, int64_t n, int lg4,
                                                           uint8_t *__restrict__ syn)
 {
@@ -80,7 +84,7 @@ __global__ __launch_bounds__(kSynThreads) void k_syndrome(const PlanDev *__restr
     const int n4 = 1 << lg4, pitch = n4 + 1;
     const int64_t s0 = (int64_t)blockIdx.x << (lg4 + 2);
     const int nc = (nq + 4) / 4;
-    for (int idx = threadIdx.x; idx < nc << lg4; idx += kSynThreads) {
+    for (int idx = threadIdx.x; idx < nc << lg4; idx += THREADS) {
         const int hi = (idx >> 2) / nc, c = (idx >> 2) - hi * nc, s4 = 4 * hi + (idx & 3);
         uint32_t v[4];
 #pragma unroll
@@ -101,7 +105,7 @@ __global__ __launch_bounds__(kSynThreads) void k_syndrome(const PlanDev *__restr
     }
     __syncthreads();
     const int nf = nstab / 4;
-    for (int idx = threadIdx.x; idx < nf << lg4; idx += kSynThreads) {
+    for (int idx = threadIdx.x; idx < nf << lg4; idx += THREADS) {
         const int hi = (idx >> 2) / nf, f4 = (idx >> 2) - hi * nf, s4 = 4 * hi + (idx & 3);
         uint32_t v[4];
 #pragma unroll
@@ -1863,8 +1867,10 @@ int xzzx_syndrome(const xzzx_plan *plan, const uint8_t *d_cfg, int64_t n, uint8_
     const int rows = syndrome_rows(plan->P.lat.nq);
     const int lg4 = rows * 17 * 4 <= 40960 && n >= 64 * 1024 ? 4 : 2;
     const int64_t per = (int64_t)4 << lg4, blocks = (n + per - 1) / per;
-    hipLaunchKernelGGL(k_syndrome, dim3((unsigned)blocks), dim3(kSynThreads), rows * ((1 << lg4) + 1) * 4,
-                       (hipStream_t)stream, plan->P.ddev, d_cfg, n, lg4, d_syn);
+    const bool wide = blocks <= device_cus() && (rows / 4 << lg4) > kSynThreadsMost;
+    hipLaunchKernelGGL(wide ? k_syndrome<kSynThreadsMost> : k_syndrome<kSynThreads>, dim3((unsigned)blocks),
+                       dim3(wide ? kSynThreadsMost : kSynThreads), rows * ((1 << lg4) + 1) * 4, (hipStream_t)stream,
+                       plan->P.ddev, d_cfg, n, lg4, d_syn);
     return check_hip(hipGetLastError(), "k_syndrome launch");
 }
 

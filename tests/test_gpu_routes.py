@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import oracle as O
 from paper_2509_17837_amd import _lib as X
 from paper_2509_17837_amd import decoder as D
 from tests._parity import Problem, compare_decode, gpu_plan, to_dev
@@ -178,3 +179,37 @@ def test_random_site_states_in_a_short_workspace():
     D.decode_groups([g], 1, 2, ws=full)
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(short, (o.e_best, o.cls, o.recovery)))
+
+
+@pytest.mark.parametrize("layout,d,n", [(1, 31, 1), (1, 31, 17), (1, 25, 100), (1, 31, 4100), (1, 23, 16)])
+def test_syndrome_large_lattices(layout, d, n):
+    """Syndromes of large lattices: a few workgroups with more threads, many with
+    fewer; a small batch costs about what one of a small lattice does."""
+    olat = O.Lattice(layout, d)
+    rng = np.random.default_rng(d + n)
+    cfg = rng.integers(0, 4, (n, olat.nq), dtype=np.uint8)
+    plan = gpu_plan(Problem(layout, d, 0.1, 10.0, 0, 1, 0))
+    got = D.syndrome(plan, to_dev(cfg)).cpu().numpy()
+    for i in {0, n // 2, n - 1}:
+        assert np.array_equal(got[i], olat.syndrome(cfg[i]))
+    if n > 1000:
+        return
+
+    def us(plan, nq):
+        x = torch.zeros((n, nq), dtype=torch.uint8, device="cuda")
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            for _ in range(50):
+                D.syndrome(plan, x)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, 20.0 * a.elapsed_time(b))
+        return best
+
+    small = us(gpu_plan(Problem(1, 3, 0.1, 10.0, 0, 1, 0)), 13)
+    large = us(plan, olat.nq)
+    print(f"[routes] syndrome d={d} n={n}: {large:.1f} us, d=3 {small:.1f}", flush=True)
+    assert large < 1.3 * small
