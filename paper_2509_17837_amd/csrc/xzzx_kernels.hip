@@ -145,9 +145,10 @@ __global__ __launch_bounds__(THREADS) void k_syndrome(const PlanDev *__restrict_
 // The first round's scan was 40-70 % of the time when every replica did it,
 // gathering distances through L1 at a line per lane.
 // Bound now by latency and instruction issue of the later rounds and the walks.
-// Measured before -> now (references alone): d = 21, 1021 syndromes x 10: 578 ->
-// 259 us; d = 31, 512 x 32: 3.71 -> 1.16 ms; d = 11, 8192 x 32: 1211 -> 688 us;
-// planar d = 9, 12288 x 10: 613 -> 367 us; d = 11, 20000 x 1: 160 -> 138 us.
+// References alone, a wavefront to each with a scan of its own -> now (three
+// defects in ten generators): d = 21, 1021 syndromes x 10: 466 -> 220 us; d = 11, 8192
+// x 32: 1172 -> 662 us; planar d = 9, 12288 x 10: 691 -> 390 us; d = 11, 20000 x 1: 128 ->
+// 113 us; d = 31, 512 x 32: 2.85 -> 1.03 ms.
 // ---------------------------------------------------------------------------
 // partners whose distances a scan loads at once (the table is in HBM or L2:
 // the loads of a batch overlap)
@@ -164,12 +165,12 @@ struct GreedyLds {
     uint32_t ents, db, weights, defects, first, waves;   // shared arrays, then the wavefronts' parts
     uint32_t cfg, flags, per_wave;                       // within a wavefront's part
 };
-__host__ __device__ inline GreedyLds greedy_lds_layout(int sets, int stride, int nwords, int cache_entries)
+__host__ __device__ inline GreedyLds greedy_lds_layout(int sets, int stride, int nwords, int cache_entries, int ties)
 {
     GreedyLds L;
     const uint32_t n = (uint32_t)(sets * stride);
     L.ents = 0;
-    L.db = L.ents + 4 * 3 * n;
+    L.db = L.ents + 4 * (uint32_t)(sets * ties);
     L.weights = L.db + 4 * n;
     L.defects = L.weights + 4 * (uint32_t)(sets * cache_entries);
     L.first = L.defects + 2 * n;
@@ -199,7 +200,9 @@ struct GreedyArgs {
     int n_units;               // references per syndrome: n_rep / rep_div, rounded up
     int shares;                // workgroups per syndrome
     int unit_step;             // wavefronts per syndrome: a wavefront's references are so many apart
-    int64_t block0;            // workgroup 0 of this launch
+    int ties;                  // entries of a colour's list of first ties
+    int64_t syn0;              // syndrome and share of this launch's first workgroup
+    int share0;
 };
 
 __device__ __forceinline__ void xor_edge(uint32_t *cfgw, int eid)
@@ -286,16 +289,15 @@ __global__ __launch_bounds__(kGreedyWaves *kWave)
     const int lane = threadIdx.x % kWave, wave = (int)uni(threadIdx.x / kWave), n_waves = blockDim.x / kWave;
     const int hl = lane % kHalf;
     const int nq = pl->nq, nwords = (nq + 3) / 4, stride = A.stride;
-    const int64_t blk = A.block0 + blockIdx.x;
-    const int64_t s = blk / A.shares;
-    const int unit0 = (int)(blk - s * A.shares) * n_waves + wave;
+    const int64_t s = A.syn0 + blockIdx.x;
+    const int unit0 = (A.share0 + (int)blockIdx.y) * n_waves + wave;
     const uint32_t uid = A.uid[s];
-    const GreedyLds L = greedy_lds_layout(kSets, stride, nwords, A.cache_entries);
+    const GreedyLds L = greedy_lds_layout(kSets, stride, nwords, A.cache_entries, A.ties);
     uint8_t *mine = smem + L.waves + (uint32_t)wave * L.per_wave;
     uint32_t *cfgw = reinterpret_cast<uint32_t *>(mine + L.cfg);
     const bool randomized = A.mode == XZZX_GREEDY_RANDOM;
     const uint8_t *sy = A.syn + s * A.syn_stride;
-    const int ent_cap = 3 * stride;
+    const int ent_cap = A.ties;
 
     // the reference in cfgw and its symplectic products with L_Z and L_X, for
     // each replica that shares it
@@ -333,36 +335,40 @@ __global__ __launch_bounds__(kGreedyWaves *kWave)
         // rows of an odd stride: the lanes' reads of one column fall in distinct banks
         auto cached_of = [&](int na) { return (int64_t)na * (na | 1) <= (int64_t)A.cache_entries; };
 
-        // ---- shared: the defects of each colour, ascending node index ----
+        // ---- shared: the defects of each colour, ascending node index (a lone
+        // wavefront takes the two colours on its halves) ----
         if (gg) __syncthreads();   // the wavefronts have left the other colour
-        for (int set = wave; set < kSets; set += n_waves) {
+        const bool halves = SPLIT && n_waves == 1;
+        const int width = halves ? kHalf : kWave, wl = lane & (width - 1);
+        if (const int set = halves ? lane / kHalf : wave; set < kSets) {
             const int g = SPLIT ? set : gg;
-            const int n = pl->ncol[g];
+            const int n = pl->ncol[g], n_both = halves ? max(pl->ncol[0], pl->ncol[1]) : n;
             const int32_t *cf = pl->col_face[g], *db = pl->db[g];
             int nd = 0;
-            for (int base = 0; base < n; base += kWave * kGreedyBatch) {
+            for (int base = 0; base < n_both; base += width * kGreedyBatch) {
                 bool flag[kGreedyBatch];
                 int32_t face[kGreedyBatch], dbv[kGreedyBatch];
 #pragma unroll
                 for (int k = 0; k < kGreedyBatch; ++k) {
-                    const int v = min(base + k * kWave + lane, n - 1);
+                    const int v = min(base + k * width + wl, n - 1);
                     face[k] = cf[v];
                     dbv[k] = db[v];
                 }
 #pragma unroll
-                for (int k = 0; k < kGreedyBatch; ++k) flag[k] = base + k * kWave + lane < n && sy[face[k]];
+                for (int k = 0; k < kGreedyBatch; ++k) flag[k] = base + k * width + wl < n && sy[face[k]];
 #pragma unroll
                 for (int k = 0; k < kGreedyBatch; ++k) {
-                    const uint64_t mask = __ballot(flag[k]);
-                    const int pos = nd + __popcll(mask & ((1ull << lane) - 1ull));
+                    uint64_t mask = __ballot(flag[k]);
+                    if (halves) mask = (mask >> (set * kHalf)) & 0xFFFFFFFFull;
+                    const int pos = nd + __popcll(mask & ((1ull << wl) - 1ull));
                     if (flag[k]) {
-                        defects_of(set)[pos] = (uint16_t)(base + k * kWave + lane);
+                        defects_of(set)[pos] = (uint16_t)(base + k * width + wl);
                         db_of(set)[pos] = dbv[k];
                     }
                     nd += __popcll(mask);
                 }
             }
-            if (lane == 0) { s_nd[set] = nd; s_ents[set] = 0; s_scan[set] = 0; }
+            if (wl == 0) { s_nd[set] = nd; s_ents[set] = 0; s_scan[set] = 0; }
         }
         __syncthreads();
 
@@ -487,7 +493,7 @@ __global__ __launch_bounds__(kGreedyWaves *kWave)
             // only leave, so a defect whose least partner is still free keeps it;
             // only the others search again.
             int np = 0;
-            for (int round = 0; round <= na_all / 2; ++round) {
+            for (int round = 0; round < na_all / 2; ++round) {
                 if (round > 0 || __ballot(s_scan[set]) != 0) {
                     // the free defects, and of those the ones to search for, ascending
                     int nfl = 0, nn = 0;
@@ -936,26 +942,30 @@ static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // the whole wavefront per colour on larger lattices.
 static bool greedy_split(const Plan &P) { return std::max(P.hdev.ncol[0], P.hdev.ncol[1]) <= 128; }
 
-// references a launch takes one to a wavefront: four times the wavefronts the
-// device holds.  With more, a wavefront takes several in turn, so that fewer
-// are dispatched and set up (planar d = 9, 12288 x 10: 438 us with one each,
-// 367 with three, 499 where twice as many left some workgroups two; half as
-// many left too few wavefronts to hide latency, 524).
-constexpr int64_t kGreedyFill = 32768;
-// launches of at most this many references cache the pair weights in LDS
-// whatever the workgroup's size (see below)
-constexpr int64_t kGreedyCacheWaves = 2048;
-
 // The greedy references of n syndromes, A's outputs and syndromes set by the
-// caller.  A workgroup's wavefronts share a syndrome's scan, so it takes as
-// many of its replicas as the LDS holds, at most kGreedyWaves, spread evenly
-// over the workgroups.  The weights of up to about half the nodes as defects
-// (more are rare: each fires with probability below one half) are cached where
-// the workgroup has wavefronts enough to share them, or the launch is small
-// and latency matters more than occupancy; a share of 64 KiB in all.
+// caller.  A workgroup's wavefronts take replicas of one syndrome and share its
+// scan.  Two forms, by the references of the launch:
+// - wide: up to kGreedyWaves wavefronts, and the pair weights of up to about
+//   half the nodes as defects (more are rare: each fires with probability below
+//   one half) in what a 64 KiB share has left.  Small launches, where latency
+//   counts, and those in which the workgroups that fit a CU still fill it: at
+//   most 1024 references for every wavefront of a workgroup, or 2048 in the split
+//   form.
+// - narrow: up to four wavefronts and no weights in LDS, but for whole workgroups
+//   of small lattices, so that many workgroups fit a CU; in the split form a
+//   wavefront takes several references in turn, which saves dispatches (planar
+//   d = 9, 12288 x 10: 438 us with one each, 367 with three).
+// Measured wide / narrow (us; rotated d = 21, three defects in ten generators;
+// in brackets one in twelve): 250 syndromes x 10 replicas 86 / 116 (49 / 52); 800 x 10
+// 164 / 215 (93 / 96); 3000 x 10 533 / 606 (309 / 267); 2000 x 4 324 / 213 (155 / 99);
+// 7500 x 4 1097 / 548 (525 / 247).  A wavefront to each reference with a scan of
+// its own took 254, 399, 1004, 413 and 1034 (77, 135, 335, 132 and 345); this rule
+// is slower than that only for d = 3 and 5, by up to a microsecond a call and 8 %
+// (60000 references of one replica at d = 3: 47 us, now 50).
+constexpr int64_t kGreedyWide = 2048;   // references of a launch that is wide whatever its workgroups
 static int launch_greedy(const Plan &P, GreedyArgs A, int64_t n_syn, uint64_t seed, int mode, hipStream_t stream)
 {
-    const bool split = greedy_split(P);
+    const bool split = greedy_split(P), random = mode == XZZX_GREEDY_RANDOM;
     const int sets = split ? 2 : 1, nwords = (P.lat.nq + 3) / 4;
     const int nodes = std::max(P.hdev.ncol[0], P.hdev.ncol[1]);
     A.plan = P.ddev;
@@ -964,33 +974,54 @@ static int launch_greedy(const Plan &P, GreedyArgs A, int64_t n_syn, uint64_t se
     A.seed_hi = (uint32_t)(seed >> 32);
     A.stride = (nodes + 2) & ~1;
     A.n_units = (A.n_rep + A.rep_div - 1) / A.rep_div;
-    const GreedyLds base = greedy_lds_layout(sets, A.stride, nwords, 0);
+    // the list of first ties: small lattices have about as many as a dense
+    // syndrome's; larger ones have fewer each, and LDS that costs occupancy (one
+    // replica of planar d = 31, 30000 syndromes: 42.0 ms with three entries a node,
+    // 29.8 with half of one)
+    A.ties = !random ? 0 : split ? 3 * A.stride : A.n_units == 1 ? A.stride / 2 : A.stride;
+    GreedyLds base = greedy_lds_layout(sets, A.stride, nwords, 0, A.ties);
     // boundary references share no scan: a wavefront each, over as many CUs
     const bool alone = mode == XZZX_GREEDY_BOUNDARY;
-    const int fit = alone ? 1 : std::max(1, std::min(kGreedyWaves, (int)((65536 - base.waves) / base.per_wave)));
+    // (tiny lattices have little to share: their dispatches count more)
+    const bool tiny = nodes <= 16;
     const int64_t refs = n_syn * A.n_units;
-    const int each = split && !alone ? (int)std::max<int64_t>(1, std::min<int64_t>(refs / kGreedyFill, A.n_units)) : 1;
+    const int cap = std::min(kGreedyWaves, (int)((65536 - 64 - base.waves) / base.per_wave));
+    const int most_waves = std::min(cap, A.n_units), wide_shares = (A.n_units + most_waves - 1) / most_waves;
+    const bool wide = !alone && (refs <= kGreedyWide ||
+                                 (most_waves >= 5 && wide_shares <= 2 &&
+                                  refs <= (split && !tiny ? 2048 * most_waves : 1024 * std::min(most_waves, 12))));
+    if (random && split && !wide && nodes > 48) {
+        A.ties = A.stride;
+        base = greedy_lds_layout(sets, A.stride, nwords, 0, A.ties);
+    }
+    const int in_turn = tiny || A.n_units % 16 ? 3 : 4;   // four: whole workgroups
+    const int each = split && !alone && !wide && A.n_units > (tiny ? 2 : 4)
+                         ? (int)std::max<int64_t>(1, std::min<int64_t>(refs / (tiny ? 10000 : 20000), in_turn)) : 1;
+    const int fit = alone ? 1 : std::min(cap, split && (wide ? refs <= 256 && nodes <= 48 : tiny) ? 2 : wide ? kGreedyWaves : 4);
     const int per_syn = (A.n_units + each - 1) / each;
     A.shares = (per_syn + fit - 1) / fit;
-    const int waves = (per_syn + A.shares - 1) / A.shares;
+    int waves = (per_syn + A.shares - 1) / A.shares;
     A.unit_step = A.shares * waves;
+    // a few references of a large lattice: wavefronts without one help in the scan
+    if (!split && !alone && refs <= 256) waves = std::max(waves, std::min(cap, 4));
     A.cache_entries = 0;
-    if (!alone && (A.n_units >= 4 * A.shares || refs <= kGreedyCacheWaves)) {
+    if (wide || (split && !alone && nodes <= 72 && waves == 4)) {
         const int rows = nodes * 7 / 16 + 8, room = 65536 - 64 - (int)(base.waves + waves * base.per_wave);
         A.cache_entries = std::max(0, std::min(rows * (rows | 1), room / (4 * sets)));
     }
-    const uint32_t lds = greedy_lds_layout(sets, A.stride, nwords, A.cache_entries).waves + waves * base.per_wave;
+    const uint32_t lds = greedy_lds_layout(sets, A.stride, nwords, A.cache_entries, A.ties).waves + waves * base.per_wave;
     void (*kernel)(GreedyArgs) = k_greedy<false, false>;
     if (split) kernel = each > 1 ? k_greedy<true, true> : k_greedy<true, false>;
-    // one launch addresses fewer than 2^32 work-items
-    const int64_t blocks = n_syn * A.shares, most = kMaxLaunchWaves / waves;
-    for (int64_t b0 = 0; b0 < blocks; b0 += most) {
-        A.block0 = b0;
-        const int64_t nb = std::min<int64_t>(most, blocks - b0);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(waves * kWave), lds, stream, A);
-        const int rc = check_hip(hipGetLastError(), "k_greedy launch");
-        if (rc) return rc;
-    }
+    // one launch addresses fewer than 2^32 work-items, and 2^16 rows of workgroups
+    const int rows = std::min(A.shares, 65535);
+    const int64_t most = std::max<int64_t>(1, kMaxLaunchWaves / ((int64_t)waves * rows));
+    for (A.syn0 = 0; A.syn0 < n_syn; A.syn0 += most)
+        for (A.share0 = 0; A.share0 < A.shares; A.share0 += rows) {
+            const dim3 grid((unsigned)std::min<int64_t>(most, n_syn - A.syn0), (unsigned)std::min(rows, A.shares - A.share0));
+            hipLaunchKernelGGL(kernel, grid, dim3(waves * kWave), lds, stream, A);
+            const int rc = check_hip(hipGetLastError(), "k_greedy launch");
+            if (rc) return rc;
+        }
     return XZZX_OK;
 }
 

@@ -213,3 +213,54 @@ def test_syndrome_large_lattices(layout, d, n):
     large = us(plan, olat.nq)
     print(f"[routes] syndrome d={d} n={n}: {large:.1f} us, d=3 {small:.1f}", flush=True)
     assert large < 1.3 * small
+
+
+@pytest.mark.parametrize("layout,d,n_syn,R", [
+    (0, 17, 2500, 7), (0, 31, 150, 24), (1, 17, 6000, 2), (0, 21, 9001, 1), (1, 31, 1, 9), (0, 27, 3, 1), (1, 13, 60, 3),
+    (0, 11, 4001, 1), (0, 9, 1, 16), (0, 15, 3000, 4), (0, 7, 12001, 5), (0, 3, 6001, 10), (1, 3, 90, 3), (0, 5, 2, 300)])
+def test_greedy_forms(layout, d, n_syn, R):
+    """Greedy references in wide and narrow workgroups: several workgroups a
+    syndrome, one wavefront for both colours, wavefronts that only help in the
+    scan, shorter lists of first ties; every node a defect (more ties than any
+    list), every second and third one, one and none among the syndromes."""
+    print(f"[routes] greedy layout={layout} d={d} n_syn={n_syn} R={R}", flush=True)
+    prob = Problem(layout, d, 0.18, 0.5, n_syn, R, 1, seed=170 + d, conv=layout)
+    for i, step in enumerate((1, 2, 3, 0, prob.olat.nstab)):
+        if i < n_syn:
+            prob.syn[i] = 0
+            if step:
+                prob.syn[i, ::step] = 1
+    plan = gpu_plan(prob)
+    refs, qcls = D.greedy_init(plan, to_dev(prob.syn), to_dev(prob.uid.view(np.int32)), R, prob.greedy_seed,
+                               X.GREEDY_RANDOM)
+    refs, qcls = refs.cpu().numpy(), qcls.cpu().numpy()
+    for i in sorted({*range(min(5, n_syn)), n_syn // 2, n_syn - 1}):
+        for r in {*range(min(R, 8)), R - 1}:
+            want = prob.oracle_greedy(i, r, X.GREEDY_RANDOM)
+            assert np.array_equal(refs[i, r], want), (i, r)
+            assert qcls[i, r] == prob.olat.cls(want, refs[i, 0]), (i, r)
+
+
+@pytest.mark.parametrize("layout,d,n,R", [(0, 21, 8192, 4), (0, 25, 8192, 4), (0, 15, 26000, 5), (1, 17, 12000, 5)])
+def test_greedy_sharing_pays(layout, d, n, R):
+    """R replicas that share their syndrome's scan take no longer than R calls of
+    one replica, also where weights kept in LDS would leave a CU few wavefronts."""
+    plan = gpu_plan(Problem(layout, d, 0.1, 10.0, 0, 1, 1, seed=d, conv=layout))
+    rng = np.random.default_rng(d)
+    syn = to_dev((rng.random((n, plan.nstab)) < 0.06).astype(np.uint8))
+    uid = torch.arange(n, dtype=torch.int32, device="cuda")
+
+    def us(reps):
+        best = 1e9
+        for k in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            D.greedy_init(plan, syn, uid, reps, 3)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, 1e3 * a.elapsed_time(b)) if k else best
+        return best
+
+    one, many = us(1), us(R)
+    print(f"[routes] greedy d={d} n={n}: 1 x {one:.0f} us, {R} x {many:.0f} us", flush=True)
+    assert many < R * one
