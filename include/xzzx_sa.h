@@ -87,7 +87,9 @@ enum {
     XZZX_FLAG_PLAIN = 1,         /* one anneal launch per syndrome, no persistent queue */
     /* Stage selection (none set = all stages).  Stages communicate through the
      * workspace, so a split decode passes the same groups and workspace to
-     * each call, in this order. */
+     * each call, in this order.  The annealing and finish stages need the same
+     * workspace size too, where it is below xzzx_decode_workspace(): it decides
+     * what the one leaves for the other. */
     XZZX_FLAG_STAGE_GREEDY = 2,  /* greedy references and their classes */
     XZZX_FLAG_STAGE_ANNEAL = 4,  /* annealing of every chain */
     XZZX_FLAG_STAGE_FINISH = 8   /* per-syndrome reduction and recovery */
@@ -307,15 +309,23 @@ typedef struct {
     uint8_t *d_chain_final;      /* [n_syn][4 n_rep][n_qubits] final states (optional) */
 } xzzx_group;
 
-/* Device workspace needed by xzzx_decode / xzzx_anneal for these groups.  A
- * small call is accepted with less (what the packed-row kernels need) and then
- * runs one chain per lane. */
+/* Device workspace of xzzx_decode / xzzx_anneal for these groups: *bytes holds
+ * what every group's best form uses, as far as that is at most 18 GiB beyond
+ * the least size; _least gives the size a call is accepted with.  Between the
+ * two the groups whose best form takes fewest bytes have it.  The others (same
+ * results): calls that would run on the kernel of several lanes per chain run
+ * one chain per lane, or, on planar d > 15 and with chosen lanes, on byte
+ * states; groups with 4 n_rep no multiple of 64 keep no checkpoints (longer
+ * replays; ladders run on the generic kernel); schedules below 512 sweeps keep
+ * sparser ones; random-site chains take longer to keep a state. */
 int xzzx_decode_workspace(const xzzx_group *groups, int n_groups, size_t *bytes);
+int xzzx_decode_workspace_least(const xzzx_group *groups, int n_groups, size_t *bytes);
 
 /* Full decoder (Alg. 7) for every group: greedy init, annealing of all
  * chains of all groups in one persistent launch (uneven distances allowed),
  * per-syndrome reduction and recovery.  d_workspace: caller-owned device
- * memory of at least xzzx_decode_workspace() bytes.  ENOMEM if smaller. */
+ * memory of xzzx_decode_workspace() bytes.  ENOMEM below
+ * xzzx_decode_workspace_least(). */
 int xzzx_decode(const xzzx_group *groups, int n_groups, uint64_t greedy_seed,
                 uint64_t anneal_seed, int greedy_mode, int flags, void *d_workspace,
                 size_t workspace_bytes, void *stream);
@@ -342,7 +352,7 @@ int xzzx_anneal(const xzzx_group *groups, int n_groups, uint64_t anneal_seed, in
  * The call allocates nothing: no device memory, and no stream or event (its
  * launches run in order on `stream`, so groups do not overlap each other).
  * The caller still allocates every group's inputs and outputs.  ERANGE if
- * xzzx_decode_workspace() for these groups exceeds the limit.  Every call on
+ * xzzx_decode_workspace_least() for these groups exceeds the limit.  Every call on
  * one device shares that device's array, which keeps the last call's contents
  * (the decode clears what must start at zero itself): calls whose work
  * overlaps on one device -- on different streams or threads -- race and give

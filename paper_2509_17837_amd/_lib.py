@@ -150,6 +150,7 @@ def lib():
         "xzzx_syndrome": (I, [V, V, I64, V, V]),
         "xzzx_greedy_init": (I, [V, V, V, I64, I, U64, I, V, V, V]),
         "xzzx_decode_workspace": (I, [P(Group), I, P(C.c_size_t)]),
+        "xzzx_decode_workspace_least": (I, [P(Group), I, P(C.c_size_t)]),
         "xzzx_decode": (I, [P(Group), I, U64, U64, I, I, V, C.c_size_t, V]),
         "xzzx_anneal": (I, [P(Group), I, U64, I, V, C.c_size_t, V]),
         "xzzx_decode_noalloc": (I, [P(Group), I, U64, U64, I, I, V]),

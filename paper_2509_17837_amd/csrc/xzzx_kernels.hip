@@ -1055,7 +1055,7 @@ struct GroupWs {
     uint32_t *cp_rows;     // checkpoints of groups on the specialised packed-row kernel
     uint32_t *min_snap;    // random-site, planar specialised, ladder and grid groups: each chain's state at its first E_min
     int grid;              // lanes per chain on the grid core (0: another kernel)
-    bool lean;             // the call's workspace is short (see ws_bytes)
+    bool lean;             // short of workspace (see call_form)
 };
 
 // Replica exchange on the packed-row kernels specialised to d: the distance
@@ -1188,9 +1188,8 @@ static std::vector<int> grid_routes(const xzzx_group *groups, int n_groups)
     return lanes;
 }
 
-// Bytes of a group's buffers; grid: on the grid core (lanes per chain); lean:
-// without the checkpoints of groups whose tasks span syndromes.
-static size_t group_ws_bytes(const xzzx_group &g, bool decode, int grid, bool lean)
+// Bytes of the buffers a group has in every form.
+static size_t fixed_bytes(const xzzx_group &g, bool decode)
 {
     const Plan &P = g.plan->P;
     const size_t nq = P.lat.nq, ns = (size_t)g.n_syn, R = (size_t)g.n_rep, nc = 4 * R * ns;
@@ -1202,48 +1201,98 @@ static size_t group_ws_bytes(const xzzx_group &g, bool decode, int grid, bool le
     if (!g.d_chain_stop) b += align256(nc * 4);
     if (!g.d_chain_e) b += align256(nc * 4);
     if (!g.d_best_chain) b += align256(ns * 4);
-    if (grid) return b + align256((size_t)P.hdev.grid_words * nc * 4);
-    if (!lean || !spans(g)) b += align256((size_t)checkpoints_of(g, lean) * P.lat.d * P.static_words * nc * 4);
-    return b + align256((size_t)min_snap_words(g, lean) * nc * 4);
+    return b;
 }
 
-// Workspace of a call: what its kernels use at best (`full`), and what it is
-// accepted with (`least`): the grid core's states may take more than the
-// other kernels' checkpoints, and a call whose workspace is short of them
-// runs on those kernels instead; groups whose tasks span syndromes then keep
-// no checkpoints, and their recoveries are replayed from the references;
-// random-site groups keep their states in fewer words.
-static void ws_bytes(const xzzx_group *groups, int n_groups, bool decode, const std::vector<int> &grid, size_t *full,
-                     size_t *least)
+// Checkpoints and words per chain of the states kept at E_min, by the group's
+// form.  grid: on the grid core (lanes per chain); lean: short of workspace.
+static size_t form_checkpoints(const xzzx_group &g, int grid, bool lean)
 {
-    *full = *least = 256;
-    for (int i = 0; i < n_groups; ++i) {
-        const size_t other = group_ws_bytes(groups[i], decode, 0, false);
-        *least += group_ws_bytes(groups[i], decode, 0, true);
-        *full += grid[i] ? std::max(other, group_ws_bytes(groups[i], decode, grid[i], false)) : other;
-    }
+    return grid || (lean && spans(g)) ? 0 : (size_t)checkpoints_of(g, lean);
 }
-
-static GroupWs carve_group(const xzzx_group &g, bool decode, int grid, bool lean, uint8_t *&p)
+static size_t form_words(const xzzx_group &g, int grid, bool lean)
+{
+    return grid ? (size_t)g.plan->P.hdev.grid_words : (size_t)min_snap_words(g, lean);
+}
+static size_t form_bytes(const xzzx_group &g, int grid, bool lean)
 {
     const Plan &P = g.plan->P;
-    const size_t nq = P.lat.nq, ns = (size_t)g.n_syn, R = (size_t)g.n_rep, nc = 4 * R * ns;
-    GroupWs w{};
+    const size_t nc = 4 * (size_t)g.n_rep * (size_t)g.n_syn;
+    return align256(form_checkpoints(g, grid, lean) * P.lat.d * P.static_words * nc * 4) +
+           align256(form_words(g, grid, lean) * nc * 4);
+}
+
+// The forms of a call's groups with a workspace of so many bytes.  A call is
+// accepted with `least` bytes, in which no group runs on the grid core, groups
+// whose tasks span syndromes keep no checkpoints (their recoveries are replayed
+// from the references), short schedules keep sparser ones, random-site groups
+// keep their states in fewer words and spanning ladders run on the generic
+// kernel.  What is left goes to the groups' better forms, those that take fewest
+// bytes first: at most kMostForms bytes of a call (a sixteenth of the card's
+// memory), so that a large call does not ask for much more than it needs.
+constexpr size_t kMostForms = (size_t)18 << 30;
+
+struct CallForm {
+    std::vector<int> grid;     // lanes per chain on the grid core (0: another kernel)
+    std::vector<char> lean;    // short of workspace
+    size_t least = 256;
+    size_t bytes = 256;        // what the forms use
+};
+
+static CallForm call_form(const xzzx_group *groups, int n_groups, bool decode, size_t workspace_bytes)
+{
+    CallForm F;
+    F.grid = grid_routes(groups, n_groups);
+    F.lean.assign(n_groups, 0);
+    std::vector<std::pair<size_t, int>> more;   // bytes a better form takes beyond the least, group
+    for (int i = 0; i < n_groups; ++i) {
+        const size_t lean = form_bytes(groups[i], 0, true), best = form_bytes(groups[i], F.grid[i], false);
+        F.least += fixed_bytes(groups[i], decode) + lean;
+        more.push_back({best > lean ? best - lean : 0, i});
+    }
+    std::sort(more.begin(), more.end());
+    F.bytes = F.least;
+    size_t left = workspace_bytes > F.least ? std::min(workspace_bytes - F.least, kMostForms) : 0;
+    for (const auto &[bytes, i] : more) {
+        if (bytes > left) {
+            F.lean[i] = 1;
+            F.grid[i] = 0;
+            continue;
+        }
+        left -= bytes;
+        F.bytes += bytes;
+    }
+    return F;
+}
+
+// The buffers of every form come first, so that stages agree on them.
+static std::vector<GroupWs> carve(const xzzx_group *groups, int n_groups, bool decode, const CallForm &F, uint8_t *p)
+{
+    std::vector<GroupWs> ws(n_groups);
     auto take = [&](size_t bytes) { uint8_t *r = p; p += align256(bytes); return r; };
-    w.grid = grid;
-    w.lean = lean;
-    w.refs = g.d_refs ? g.d_refs : (decode ? take(ns * R * nq) : nullptr);
-    w.qraw = take(ns * R);
-    w.qcls = g.d_qcls ? g.d_qcls : take(ns * R);
-    w.emin = g.d_chain_emin ? g.d_chain_emin : reinterpret_cast<int32_t *>(take(nc * 4));
-    w.stop = g.d_chain_stop ? g.d_chain_stop : reinterpret_cast<int32_t *>(take(nc * 4));
-    w.efin = g.d_chain_e ? g.d_chain_e : reinterpret_cast<int32_t *>(take(nc * 4));
-    w.best_chain = g.d_best_chain ? g.d_best_chain : reinterpret_cast<int32_t *>(take(ns * 4));
-    const size_t ncp = grid || (lean && spans(g)) ? 0 : (size_t)checkpoints_of(g, lean);
-    const size_t snap = grid ? (size_t)P.hdev.grid_words : (size_t)min_snap_words(g, lean);
-    w.cp_rows = ncp ? reinterpret_cast<uint32_t *>(take(ncp * P.lat.d * P.static_words * nc * 4)) : nullptr;
-    w.min_snap = snap ? reinterpret_cast<uint32_t *>(take(snap * nc * 4)) : nullptr;
-    return w;
+    for (int i = 0; i < n_groups; ++i) {
+        const xzzx_group &g = groups[i];
+        const size_t nq = g.plan->P.lat.nq, ns = (size_t)g.n_syn, R = (size_t)g.n_rep, nc = 4 * R * ns;
+        GroupWs &w = ws[i];
+        w.grid = F.grid[i];
+        w.lean = F.lean[i];
+        w.refs = g.d_refs ? g.d_refs : (decode ? take(ns * R * nq) : nullptr);
+        w.qraw = take(ns * R);
+        w.qcls = g.d_qcls ? g.d_qcls : take(ns * R);
+        w.emin = g.d_chain_emin ? g.d_chain_emin : reinterpret_cast<int32_t *>(take(nc * 4));
+        w.stop = g.d_chain_stop ? g.d_chain_stop : reinterpret_cast<int32_t *>(take(nc * 4));
+        w.efin = g.d_chain_e ? g.d_chain_e : reinterpret_cast<int32_t *>(take(nc * 4));
+        w.best_chain = g.d_best_chain ? g.d_best_chain : reinterpret_cast<int32_t *>(take(ns * 4));
+    }
+    for (int i = 0; i < n_groups; ++i) {
+        const xzzx_group &g = groups[i];
+        const Plan &P = g.plan->P;
+        const size_t nc = 4 * (size_t)g.n_rep * (size_t)g.n_syn;
+        const size_t ncp = form_checkpoints(g, F.grid[i], F.lean[i]), words = form_words(g, F.grid[i], F.lean[i]);
+        ws[i].cp_rows = ncp ? reinterpret_cast<uint32_t *>(take(ncp * P.lat.d * P.static_words * nc * 4)) : nullptr;
+        ws[i].min_snap = words ? reinterpret_cast<uint32_t *>(take(words * nc * 4)) : nullptr;
+    }
+    return ws;
 }
 
 static int validate_groups(const xzzx_group *groups, int n_groups, bool decode)
@@ -1535,7 +1584,7 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
     std::vector<int> bytes_sel[7];
     std::vector<int> static_sel[2][kStaticMaxD + 1];   // [tasks span syndromes][d]
     std::vector<int> replay_cp;   // replays starting from checkpoints: one chain per wavefront
-    std::vector<int> site_sel[2]; // random-site plans, by site_wide: one chain per lane
+    std::vector<int> site_sel[2][2];   // random-site plans, by site_wide and form: one chain per lane
     std::vector<int> planar_sel[kPlanarStaticMaxD + 1];   // planar kernels specialised to d
     std::vector<int> grid_sel[5][4];   // grid core, by lanes per chain (4..64) and moves per lane (1, 2, 4, 8)
     std::vector<int> ladder_sel;  // replica exchange: one chain per lane
@@ -1554,7 +1603,7 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
             if (mode == AnnealMode::Replay) continue;   // these kept their states
             if (const int ld = ladder_rows_d(groups[i], ws[i].lean)) ladder_rows_sel[spans(groups[i])][ld].push_back(i);
             else if (ladder_planar_d(groups[i])) ladder_planar_sel[ladder_planar_d(groups[i])].push_back(i);
-            else (P.ladder_k ? ladder_sel : site_sel[P.site_wide]).push_back(i);
+            else (P.ladder_k ? ladder_sel : site_sel[P.site_wide][ws[i].lean]).push_back(i);
             continue;
         }
         total_syn += groups[i].n_syn;
@@ -1597,8 +1646,9 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
     };
     std::vector<Set> sets;
     if (!rows_sel.empty()) sets.push_back({&rows_sel, true, 1, 0, false, 0, false, 0});
-    for (auto &sel : site_sel)
-        if (!sel.empty()) sets.push_back({&sel, false, 1, 0, true, 0, false, 0});
+    for (auto &wide : site_sel)
+        for (auto &sel : wide)
+            if (!sel.empty()) sets.push_back({&sel, false, 1, 0, true, 0, false, 0});
     if (!ladder_sel.empty()) sets.push_back({&ladder_sel, false, 1, 0, false, 0, true, 0});
     for (int d = 3; d <= kPlanarStaticMaxD; d += 2)
         if (!planar_sel[d].empty()) sets.push_back({&planar_sel[d], true, 1, 0, false, d, false, 0});
@@ -1748,17 +1798,10 @@ static int run_decode(const xzzx_group *groups, int n_groups, uint64_t greedy_se
         set_error("unknown greedy mode");
         return XZZX_EINVAL;
     }
-    std::vector<int> grid = grid_routes(groups, n_groups);
-    size_t full = 0, least = 0;
-    ws_bytes(groups, n_groups, decode, grid, &full, &least);
-    if (!d_workspace || workspace_bytes < least) { set_error("workspace too small"); return XZZX_ENOMEM; }
-    const bool lean = workspace_bytes < full;
-    if (lean) std::fill(grid.begin(), grid.end(), 0);
-    uint8_t *p = static_cast<uint8_t *>(d_workspace);
-    uint32_t *counter = reinterpret_cast<uint32_t *>(p);
-    p += 256;
-    std::vector<GroupWs> ws(n_groups);
-    for (int i = 0; i < n_groups; ++i) ws[i] = carve_group(groups[i], decode, grid[i], lean, p);
+    const CallForm form = call_form(groups, n_groups, decode, workspace_bytes);
+    if (!d_workspace || workspace_bytes < form.least) { set_error("workspace too small"); return XZZX_ENOMEM; }
+    uint32_t *counter = static_cast<uint32_t *>(d_workspace);
+    const std::vector<GroupWs> ws = carve(groups, n_groups, decode, form, static_cast<uint8_t *>(d_workspace) + 256);
     const int stage_bits = XZZX_FLAG_STAGE_GREEDY | XZZX_FLAG_STAGE_ANNEAL | XZZX_FLAG_STAGE_FINISH;
     const int stages = (flags & stage_bits) ? (flags & stage_bits) : stage_bits;
     // the groups' greedy launches run concurrently (one group's launch alone
@@ -1921,25 +1964,33 @@ int xzzx_greedy_init(const xzzx_plan *plan, const uint8_t *d_syn, const uint32_t
     return launch_qcls(d_qcls, n_syn, n_rep, d_qcls, (hipStream_t)stream);
 }
 
-int xzzx_decode_workspace(const xzzx_group *groups, int n_groups, size_t *bytes)
+static int workspace_query(const xzzx_group *groups, int n_groups, size_t *bytes, bool least)
 {
     if (!groups || !bytes || n_groups < 1 || n_groups > kMaxGroups) { set_error("bad arguments"); return XZZX_EINVAL; }
     for (int i = 0; i < n_groups; ++i)
         if (!groups[i].plan) { set_error("group without plan"); return XZZX_EINVAL; }
-    size_t least = 0;
-    ws_bytes(groups, n_groups, true, grid_routes(groups, n_groups), bytes, &least);
+    const CallForm F = call_form(groups, n_groups, true, SIZE_MAX);
+    *bytes = least ? F.least : F.bytes;
     return XZZX_OK;
+}
+
+int xzzx_decode_workspace(const xzzx_group *groups, int n_groups, size_t *bytes)
+{
+    return workspace_query(groups, n_groups, bytes, false);
+}
+
+int xzzx_decode_workspace_least(const xzzx_group *groups, int n_groups, size_t *bytes)
+{
+    return workspace_query(groups, n_groups, bytes, true);
 }
 
 int xzzx_decode_routes(const xzzx_group *groups, int n_groups, size_t workspace_bytes, int32_t *kernel, int32_t *lanes)
 {
-    std::vector<int> grid = grid_routes(groups, n_groups);
-    size_t full = 0, least = 0;
-    ws_bytes(groups, n_groups, true, grid, &full, &least);
-    if (workspace_bytes < least) { set_error("workspace too small"); return XZZX_ENOMEM; }
+    const CallForm form = call_form(groups, n_groups, true, workspace_bytes);
+    if (workspace_bytes < form.least) { set_error("workspace too small"); return XZZX_ENOMEM; }
     for (int i = 0; i < n_groups; ++i) {
         const Plan &P = groups[i].plan->P;
-        const int on_grid = workspace_bytes < full ? 0 : grid[i];
+        const int on_grid = form.grid[i];
         lanes[i] = 1;
         if (P.order == XZZX_ORDER_RANDOM_SITE) kernel[i] = XZZX_KERNEL_SITE;
         else if (P.ladder_k) kernel[i] = XZZX_KERNEL_LADDER;
@@ -1999,10 +2050,9 @@ extern "C" {
 int xzzx_decode_noalloc(const xzzx_group *groups, int n_groups, uint64_t greedy_seed, uint64_t anneal_seed,
                         int greedy_mode, int flags, void *stream)
 {
-    size_t full = 0, need = 0;
-    int rc = xzzx_decode_workspace(groups, n_groups, &full);
+    size_t need = 0;
+    int rc = xzzx_decode_workspace_least(groups, n_groups, &need);
     if (rc) return rc;
-    ws_bytes(groups, n_groups, true, std::vector<int>(n_groups, 0), &full, &need);
     if (need > (size_t)XZZX_NOALLOC_SCRATCH_BYTES) {
         set_error("workspace of these groups exceeds XZZX_NOALLOC_SCRATCH_BYTES");
         return XZZX_ERANGE;

@@ -286,7 +286,12 @@ def workspace(groups, device="cuda", stream=None):
     nb = C.c_size_t()
     call("xzzx_decode_workspace", arr, len(groups), C.byref(nb))
     with _on(stream):
-        return torch.empty(nb.value, dtype=torch.uint8, device=device)
+        try:
+            return torch.empty(nb.value, dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            # the call is accepted with less (same results, slower kernels)
+            call("xzzx_decode_workspace_least", arr, len(groups), C.byref(nb))
+            return torch.empty(nb.value, dtype=torch.uint8, device=device)
 
 
 def decode_groups(groups, greedy_seed, anneal_seed, greedy_mode=X.GREEDY_RANDOM, flags=0, ws=None, stream=None):

@@ -264,3 +264,89 @@ def test_greedy_sharing_pays(layout, d, n, R):
     one, many = us(1), us(R)
     print(f"[routes] greedy d={d} n={n}: 1 x {one:.0f} us, {R} x {many:.0f} us", flush=True)
     assert many < R * one
+
+
+def least_bytes(groups):
+    n = C.c_size_t()
+    X.check("xzzx_decode_workspace_least", X.lib().xzzx_decode_workspace_least(
+        (X.Group * len(groups))(*groups), len(groups), C.byref(n)))
+    return n.value
+
+
+def made(probs, plans, **kw):
+    out = [D.make_group(plan, p.n_rep, to_dev(p.uid.view(np.int32)), syn=to_dev(p.syn), want_chains=True, **kw)
+           for p, plan in zip(probs, plans)]
+    return [g for g, _ in out], [o for _, o in out]
+
+
+def test_workspace_is_shared_out_by_group():
+    """A workspace short by a byte costs only the group whose better form takes
+    most its form: the small group stays on the grid core."""
+    probs = [Problem(0, 11, 0.15, 10.0, 2, 8, 40, seed=5), Problem(0, 21, 0.15, 10.0, 9, 5, 40, seed=5),
+             Problem(1, 7, 0.15, 5.0, 3, 6, 40, seed=5, conv=1)]
+    plans = [gpu_plan(p) for p in probs]
+    plans[1].set_kernel(X.KERNEL_ROWS)
+    plans[2].set_order(X.ORDER_RANDOM_SITE)
+    groups, outs = made(probs, plans)
+    full, least = D.workspace(groups).numel(), least_bytes(groups)
+    assert least < full
+    refs = [probs[0].oracle_decode(), probs[1].oracle_decode(), probs[2].oracle_decode(order=O.ORDER_RANDOM_SITE)]
+    for size, first in ((full, GRID), (full - 1, GRID), (least, X.KERNEL_ROWS)):
+        assert routes(groups, size)[0][0] == first
+        D.decode_groups(groups, probs[0].greedy_seed, probs[0].anneal_seed,
+                        ws=torch.empty(size, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        for prob, o, ref in zip(probs, outs, refs):
+            compare_decode(prob, o, ref)
+    with pytest.raises(X.XzzxError) as e:
+        D.decode_groups(groups, 1, 2, ws=torch.empty(least - 1, dtype=torch.uint8, device="cuda"))
+    assert e.value.rc == X.XZZX_ENOMEM
+
+
+def test_stages_agree_on_the_references():
+    """A greedy stage with one workspace size and the other stages with another
+    find the references in the same place."""
+    probs = [Problem(0, 11, 0.15, 10.0, 2, 8, 30, seed=6), Problem(0, 13, 0.15, 10.0, 3, 5, 30, seed=6)]
+    plans = [gpu_plan(p) for p in probs]
+    for p in plans:
+        p.set_kernel(X.KERNEL_ROWS)
+    groups, outs = made(probs, plans, want_extra=False)
+    ws = torch.empty(D.workspace(groups).numel(), dtype=torch.uint8, device="cuda")
+    seeds = probs[0].greedy_seed, probs[0].anneal_seed
+    D.decode_groups(groups, *seeds, flags=X.STAGE_GREEDY, ws=ws)
+    D.decode_groups(groups, *seeds, flags=X.STAGE_ANNEAL | X.STAGE_FINISH, ws=ws[:least_bytes(groups)])
+    torch.cuda.synchronize()
+    for prob, o in zip(probs, outs):
+        compare_decode(prob, o, prob.oracle_decode())
+
+
+@pytest.mark.parametrize("layout,d,R,n", [(1, 31, 16, 1 << 20), (0, 31, 5, 1 << 22), (1, 17, 16, 1 << 22)])
+def test_workspace_stays_near_the_least(layout, d, R, n):
+    """What a call asks for beyond the least is bounded."""
+    plan = gpu_plan(Problem(layout, d, 0.15, 10.0, 0, 1, 2000, seed=d, conv=layout))
+    plan.set_kernel(X.KERNEL_ROWS if layout == 0 else X.KERNEL_AUTO)
+    g = X.Group()
+    g.plan, g.n_syn, g.n_rep = plan.h, n, R
+    full = C.c_size_t()
+    X.check("xzzx_decode_workspace", X.lib().xzzx_decode_workspace((X.Group * 1)(g), 1, C.byref(full)))
+    assert least_bytes([g]) <= full.value <= least_bytes([g]) + (18 << 30)
+
+
+def test_workspace_falls_back_when_memory_is_short(monkeypatch):
+    """Where the whole size cannot be allocated, the Python face takes the least."""
+    prob = Problem(0, 11, 0.15, 10.0, 2, 8, 30, seed=7)
+    groups, outs = made([prob], [gpu_plan(prob)])
+    full, empty = D.workspace(groups).numel(), torch.empty
+
+    def short(size, *a, **kw):
+        if size == full:
+            raise torch.OutOfMemoryError("no room")
+        return empty(size, *a, **kw)
+
+    monkeypatch.setattr(torch, "empty", short)
+    ws = D.workspace(groups)
+    monkeypatch.undo()
+    assert ws.numel() == least_bytes(groups) < full
+    D.decode_groups(groups, prob.greedy_seed, prob.anneal_seed, ws=ws)
+    torch.cuda.synchronize()
+    compare_decode(prob, outs[0], prob.oracle_decode())
