@@ -350,3 +350,25 @@ def test_workspace_falls_back_when_memory_is_short(monkeypatch):
     D.decode_groups(groups, prob.greedy_seed, prob.anneal_seed, ws=ws)
     torch.cuda.synchronize()
     compare_decode(prob, outs[0], prob.oracle_decode())
+
+
+def test_recoveries_past_four_gigabytes():
+    """A call with more than 2^32 bytes of recoveries on a lattice without a
+    packed-row kernel is accepted, and the ends of the batch are right."""
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 100 GB of device memory")
+    prob = Problem(1, 17, 0.15, 5.0, 2, 1, 1, seed=8, conv=1)
+    plan = gpu_plan(prob)
+    n = (1 << 32) // plan.nq + 1000
+    syn = torch.zeros((n, plan.nstab), dtype=torch.uint8, device="cuda")
+    uid = torch.zeros(n, dtype=torch.int32, device="cuda")
+    ends = [0, n - 1]
+    for k, i in enumerate(ends):
+        syn[i] = to_dev(prob.syn[k])
+        uid[i] = int(prob.uid[k])
+    g, o = D.make_group(plan, 1, uid, syn=syn, want_extra=False)
+    D.decode_groups([g], prob.greedy_seed, prob.anneal_seed, ws=D.workspace([g]))
+    torch.cuda.synchronize()
+    for (i, ref) in zip(ends, prob.oracle_decode()):
+        assert o.e_best[i].item() == ref["e_best"] and o.cls[i].item() == ref["cls"]
+        assert np.array_equal(o.recovery[i].cpu().numpy(), ref["recovery"])
