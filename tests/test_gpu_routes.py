@@ -372,3 +372,84 @@ def test_recoveries_past_four_gigabytes():
     for (i, ref) in zip(ends, prob.oracle_decode()):
         assert o.e_best[i].item() == ref["e_best"] and o.cls[i].item() == ref["cls"]
         assert np.array_equal(o.recovery[i].cpu().numpy(), ref["recovery"])
+
+
+def check_decodes(prob, plan, want, ref, sizes=("full",), flags=(0,), final=True):
+    """Decodes of a problem whose only group must run on the kernel `want`."""
+    for size in sizes:
+        for flag in flags:
+            g, o = D.make_group(plan, prob.n_rep, to_dev(prob.uid.view(np.int32)), syn=to_dev(prob.syn),
+                                want_chains=True, want_final=final)
+            ws = D.workspace([g])
+            if size == "least":
+                ws = ws[:least_bytes([g])]
+            assert routes([g], ws.numel())[0] == want
+            D.decode_groups([g], prob.greedy_seed, prob.anneal_seed, flags=flag, ws=ws)
+            torch.cuda.synchronize()
+            compare_decode(prob, o, ref)
+
+
+@pytest.mark.parametrize("d", range(3, 32, 2))
+def test_rows_of_one_syndrome(d):
+    """The packed-row kernel specialised to d with tasks inside one syndrome, which
+    the default leaves to calls larger than these: both forms."""
+    prob = Problem(0, d, 0.2, 10.0, 3 if d <= 21 else 2, 32 if d <= 9 else 16, 24 if d <= 21 else 12, seed=900 + d)
+    plan = gpu_plan(prob)
+    plan.set_kernel(X.KERNEL_ROWS)
+    check_decodes(prob, plan, (X.KERNEL_ROWS, 1), prob.oracle_decode(), flags=(0, X.FLAG_PLAIN))
+
+
+@pytest.mark.parametrize("d,R,sweeps", [(7, 16, 64), (7, 16, 65), (7, 16, 300), (7, 5, 300), (7, 16, 2100), (15, 16, 300),
+                                        (19, 16, 300), (31, 16, 300), (31, 5, 600)])
+def test_rows_replayed_from_checkpoints(d, R, sweeps):
+    """Recoveries of the packed-row kernels, replayed from dense and sparse
+    checkpoints (one and two words a row) and, spanning with the least
+    workspace, from the references."""
+    prob = Problem(0, d, 0.2, 10.0, 4 if d < 15 else 2, R, sweeps, seed=950 + sweeps + d)
+    plan = gpu_plan(prob)
+    plan.set_kernel(X.KERNEL_ROWS)
+    check_decodes(prob, plan, (X.KERNEL_ROWS, 1), prob.oracle_decode(), sizes=("full", "least"), final=False)
+
+
+@pytest.mark.parametrize("layout,d", [(0, 5), (0, 11), (0, 17), (1, 7), (1, 17)])
+def test_byte_states_on_every_lane_count(layout, d):
+    """The byte-state kernels with 1 to 64 lanes: chosen lanes from four up run
+    there only with the least workspace."""
+    prob = Problem(layout, d, 0.15, 8.0, 3, 5, 20, seed=970 + d, conv=layout)
+    ref = prob.oracle_decode()
+    for lanes in (1, 2, 4, 8, 16, 32, 64):
+        plan = gpu_plan(prob)
+        try:
+            plan.set_lanes(lanes)
+        except X.XzzxError as e:   # 64 / lanes chains of a large lattice pass the LDS of a workgroup
+            assert e.rc == X.XZZX_ERANGE and lanes < 4
+            continue
+        check_decodes(prob, plan, (X.KERNEL_BYTES, lanes), ref, sizes=("least",), flags=(0, X.FLAG_PLAIN))
+
+
+@pytest.mark.parametrize("d", [17, 25, 31])
+def test_large_planar_default_without_room(d):
+    """Planar lattices beyond d = 15: the grid core, or byte states with the least workspace."""
+    prob = Problem(1, d, 0.15, 8.0, 2, 3, 8, seed=980 + d, conv=1)
+    plan, ref = gpu_plan(prob), prob.oracle_decode()
+    check_decodes(prob, plan, (GRID, 64), ref)
+    check_decodes(prob, plan, (X.KERNEL_BYTES, plan.info()["lanes_per_chain"]), ref, sizes=("least",))
+
+
+@pytest.mark.parametrize("R", [4, 16])
+def test_mixed_distances_on_packed_rows(R):
+    """Uneven distances in one call on the packed-row kernels, tasks inside and
+    across syndromes."""
+    probs = [Problem(0, d, 0.18, 10.0, n, R, 30, seed=990 + d) for d, n in [(5, 7), (9, 5), (13, 3), (17, 2), (21, 2)]]
+    plans = [gpu_plan(p) for p in probs]
+    for p in plans:
+        p.set_kernel(X.KERNEL_ROWS)
+    for p in probs:
+        p.greedy_seed, p.anneal_seed = probs[0].greedy_seed, probs[0].anneal_seed
+    groups, outs = made(probs, plans, want_final=True)
+    ws = D.workspace(groups)
+    assert set(routes(groups, ws.numel())) == {(X.KERNEL_ROWS, 1)}
+    D.decode_groups(groups, probs[0].greedy_seed, probs[0].anneal_seed, ws=ws)
+    torch.cuda.synchronize()
+    for prob, o in zip(probs, outs):
+        compare_decode(prob, o, prob.oracle_decode())
