@@ -184,6 +184,7 @@ struct AnnealArgs {
     uint32_t n_tasks, grid;    // tasks, workgroups (at most as many)
     uint32_t *counter;         // tasks taken from the queue (NULL: one task per workgroup)
     uint32_t seed_lo, seed_hi;
+    int priority;              // of its wavefronts among those on a SIMD (specialised packed rows)
 };
 
 // The tasks of a wavefront: the one of its workgroup's number, then the next
@@ -1362,6 +1363,14 @@ __device__ __forceinline__ void batch_kernel_body(const AnnealArgs &A)
     }
 }
 
+// Issue priority 0 (the default) to 3 of a wavefront among those on its SIMD.
+__device__ __forceinline__ void wave_priority(int p)
+{
+    if (p == 1) __builtin_amdgcn_s_setprio(1);
+    if (p == 2) __builtin_amdgcn_s_setprio(2);
+    if (p == 3) __builtin_amdgcn_s_setprio(3);
+}
+
 // Batch body of the specialised packed-row kernel.  Every group of the launch
 // has distance SD; tasks of 64 chains (SPAN: see rows_static_core).
 template <int SD, bool SPAN>
@@ -1369,6 +1378,7 @@ __device__ __forceinline__ void static_rows_body(const AnnealArgs &A)
 {
     __shared__ uint16_t lut_s[256 * 6];
     __shared__ uint2 et_s[kStaticRanks];
+    wave_priority(A.priority);
     const PlanDev *loaded = nullptr;
     for (uint32_t task = blockIdx.x; task < A.n_tasks; task = later_task(A)) {
         int gi = 0;

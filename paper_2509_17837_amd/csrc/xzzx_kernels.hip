@@ -1344,10 +1344,11 @@ enum class AnnealMode { Persistent, Replay, Plain };
 static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::vector<int> &sel, bool rows, int lanes,
                       AnnealMode mode, uint64_t seed, int64_t unit_offset, int64_t units_override,
                       uint32_t *d_counter, hipStream_t stream, int static_d = 0, bool site = false,
-                      int planar_d = 0, bool ladder = false, int grid_mv = 0)
+                      int planar_d = 0, bool ladder = false, int grid_mv = 0, int priority = 0)
 {
     const bool replay = mode == AnnealMode::Replay;
     AnnealArgs A{};
+    A.priority = priority;
     A.seed_lo = (uint32_t)seed;
     A.seed_hi = (uint32_t)(seed >> 32);
     A.counter = d_counter;
@@ -1450,8 +1451,8 @@ static int launch_set(const xzzx_group *groups, const GroupWs *ws, const std::ve
     // hardware ids of four launches of 1024: 20 to 80 SIMDs hold two of a
     // launch, most seven wavefronts in all; after this clear all hold one of
     // each).  Chains last long and a SIMD with one more ends last: five
-    // distances d = 5..21 of 256 syndromes and 256 chains took 214 ms, now 150;
-    // ladders at d = 11, four wavefronts a SIMD, 16.6 ms, now 16.0.
+    // distances d = 5..21 of 256 syndromes and 256 chains took 201 ms, now 152;
+    // ladders at d = 11, four wavefronts a SIMD, 18.9 ms, now 16.4.
     hipLaunchKernelGGL(k_zero_u32, dim3(4 * (unsigned)device_cus()), dim3(kWave), 0, stream, d_counter, 1);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kWave * site_waves), lds, stream, A);
     return check_hip(hipGetLastError(), "anneal launch");
@@ -1668,20 +1669,25 @@ static int launch_anneal(const xzzx_group *groups, const GroupWs *ws, int n_grou
     // the sets whose tasks take longest first: with more sets than queues the
     // last ones start when earlier ones have ended, and the longest tasks
     // must not be among them (256 syndromes of 256 chains each at d = 5..21, 1000
-    // sweeps: 42.1 ms in ascending order, 31.4 so; d = 19, 25, 31: 29.2 and 27.5.
-    // Wavefronts of large lattices at a higher priority on top took 2 % longer.)
+    // sweeps: 42.1 ms in ascending order, 31.4 so; d = 19, 25, 31: 29.2 and 27.5)
     auto task_work = [&](const Set &S) {
         double w = 0;
         for (int i : *S.sel) w = std::max(w, (double)groups[i].plan->P.n_sweeps * groups[i].plan->P.lat.nstab / S.lanes);
         return w;
     };
     std::stable_sort(sets.begin(), sets.end(), [&](const Set &a, const Set &b) { return task_work(a) > task_work(b); });
+    // Wavefronts of the sets whose tasks take longer go first on their SIMDs (see
+    // wave_priority).  Which sets share a SIMD with which is the dispatcher's, and
+    // without this one call in three had some of the longest chains wait for
+    // others' (d = 5..21, 5000 sweeps: 150 to 165 ms a call, so 150 to 152).  A call of
+    // one set, and serving, leave the priority alone: others share the device.
+    const int most_priority = std::min<int>((int)sets.size() - 1, 3);
     // each set holds at least one group, so at most kMaxGroups of them
     static_assert(kMaxGroups <= kReplayCounters, "queue counters of the sets");
     auto one = [&](int i, hipStream_t s) {
         const Set &S = sets[i];
         return launch_set(groups, ws, *S.sel, S.rows, S.lanes, mode, seed, unit_offset, units_override, d_counters + i,
-                          s, S.static_d, S.site, S.planar_d, S.ladder, S.grid_mv);
+                          s, S.static_d, S.site, S.planar_d, S.ladder, S.grid_mv, std::max(0, most_priority - i));
     };
     if (sets.size() <= 1 || mode == AnnealMode::Plain) {
         int rc = XZZX_OK;
