@@ -994,9 +994,9 @@ static int launch_greedy(const Plan &P, GreedyArgs A, int64_t n_syn, uint64_t se
         A.ties = A.stride;
         base = greedy_lds_layout(sets, A.stride, nwords, 0, A.ties);
     }
-    const int in_turn = tiny || A.n_units % 16 ? 3 : 4;   // four: whole workgroups
-    const int each = split && !alone && !wide && A.n_units > (tiny ? 2 : 4)
-                         ? (int)std::max<int64_t>(1, std::min<int64_t>(refs / (tiny ? 10000 : 20000), in_turn)) : 1;
+    // a wavefront's references in turn: three, or four where that fills workgroups
+    const int in_turn = tiny ? (int)std::min<int64_t>(refs / 10000, 3) : refs < 40000 ? 1 : A.n_units % 16 ? 3 : 4;
+    const int each = split && !alone && !wide && A.n_units > (tiny ? 2 : 4) ? std::max(1, in_turn) : 1;
     const int fit = alone ? 1 : std::min(cap, split && (wide ? refs <= 256 && nodes <= 48 : tiny) ? 2 : wide ? kGreedyWaves : 4);
     const int per_syn = (A.n_units + each - 1) / each;
     A.shares = (per_syn + fit - 1) / fit;
@@ -1005,7 +1005,7 @@ static int launch_greedy(const Plan &P, GreedyArgs A, int64_t n_syn, uint64_t se
     // a few references of a large lattice: wavefronts without one help in the scan
     if (!split && !alone && refs <= 256) waves = std::max(waves, std::min(cap, 4));
     A.cache_entries = 0;
-    if (wide || (split && !alone && nodes <= 72 && waves == 4)) {
+    if (wide || (split && !alone && nodes <= 84 && waves == 4)) {
         const int rows = nodes * 7 / 16 + 8, room = 65536 - 64 - (int)(base.waves + waves * base.per_wave);
         A.cache_entries = std::max(0, std::min(rows * (rows | 1), room / (4 * sets)));
     }
