@@ -415,13 +415,15 @@ int xzzx_probe_lds(int bytes_per_read, int waves_per_simd, int iters, void *stre
  *
  * Lanes per chain: each slice picks the largest power of two up to
  * max_lanes_per_chain for which the slice's wavefronts stay within max_waves
- * and its LDS within the budget; a request then runs on the byte-state kernel
- * with that many lanes per chain, or fewer where fewer already give each lane
- * one generator of a colour class (or, when the class has more generators
- * than that many lanes, at most one block of four), which cuts its latency
- * when the device is lightly loaded.  When even two lanes do not fit, every
- * request runs on its plan's own kernel choice.  Results do not depend on
- * this choice. */
+ * and its LDS within the budget; a request then spreads each of its chains over
+ * that many lanes, or over fewer where fewer already give a lane as few
+ * generators of a colour class, which cuts its latency when the device is
+ * lightly loaded.  When even two lanes do not fit, every request runs on its
+ * plan's own kernel choice.  With max_waves and lds_budget_bytes both 0, requests
+ * whose plan has a packed-row kernel specialised to its distance (rotated
+ * lattices) change to one chain per lane as soon as their work fills the device
+ * in that form, and planar ones with d > 15 keep all the lanes.  Results do not
+ * depend on this choice. */
 typedef struct xzzx_server xzzx_server;
 
 typedef struct {

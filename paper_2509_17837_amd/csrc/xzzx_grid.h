@@ -2,9 +2,10 @@
 // few chains to give every lane one of its own (one syndrome awaited, a few
 // requests being served).  Same chains as the other cores, bit for bit.
 //
-// What bounds it: with few wavefronts per SIMD a sweep is a serial chain of
-// LDS round trips, four per sweep and class (read the qubits, look the move
-// up, store), with the ten Philox rounds beside it.  So the form is chosen for
+// What bounds it: a wavefront alone on its SIMD issues an instruction in about
+// eight cycles, whatever the others wait for, so a sweep takes as long as its
+// instructions are many; then a serial chain of LDS round trips, four per sweep
+// and class (read the qubits, look the move up, store).  So the form is chosen for
 // the shortest chain rather than the least work:
 // - the lattice is a grid of bytes in LDS, code << 3 per qubit, every absent
 //   cell 0; a generator is a 2 x 2 block of it, so a move reads two adjacent
@@ -23,7 +24,8 @@
 // Measured (rotated d = 11, 64 chains): 0.61 us a sweep on 32 or 64 lanes, where
 // one chain per lane takes 7.3 us; with the device full, 4 x 10^5 chains and
 // more, 1.1 x 10^12 attempts/s on 32 lanes, half the packed-row kernel's rate.
-// 145 VALU and 34 LDS instructions a wavefront and sweep.
+// 145 VALU and 34 LDS instructions a wavefront and sweep: 179 x 8 cycles are the
+// 0.61 us.
 #pragma once
 
 #include "xzzx_device.h"

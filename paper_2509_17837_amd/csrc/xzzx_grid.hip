@@ -1,5 +1,4 @@
-// Annealing kernels of the grid core (one chain over several lanes) and the
-// recovery gather from the states it keeps.
+// Annealing and serving kernels of the grid core (one chain over several lanes).
 #include "xzzx_grid.h"
 
 namespace xzzx {

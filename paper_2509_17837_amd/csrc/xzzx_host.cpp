@@ -485,7 +485,8 @@ static bool build_site(const Lattice &L, GridTables &T, const std::vector<int> &
 // right; absent cells 0).  A shape without all four cells uses a few of the
 // 256 patterns, so each shape's table starts at the first slot where its
 // patterns fall between the others' -- 256 entries and a few, not 256 a
-// shape.  Returns false where a table does not fit the core's registers.
+// shape.  Returns false if a table does not fit the core's registers: no lattice's
+// does not (at most half of a shape's patterns raise the energy).
 static bool build_grid(const Lattice &L, const std::vector<int32_t> &dE, const std::vector<uint8_t> &lut,
                        const std::vector<int> &shape_of_face, const std::vector<int> &shapes, int kneg, GridTables &T)
 {
@@ -814,8 +815,7 @@ int build_plan(const Lattice &L, const int32_t w[4], const int32_t wg[2], const 
         for (int m = 0; m < L.per_class; ++m) desc[k * L.per_class + m] = fdesc[L.by_class[k * L.per_class + m]];
 
     GridTables grid;
-    P.grid_ok = build_grid(L, all, lut, shape_of_face, shapes, P.kneg, grid) ? 1 : 0;
-    if (!P.grid_ok) { set_error("inconsistent grid tables"); return XZZX_EINVAL; }   // holds for both layouts
+    if (!build_grid(L, all, lut, shape_of_face, shapes, P.kneg, grid)) { set_error("inconsistent grid tables"); return XZZX_EINVAL; }   // holds for both layouts
     P.site_wide = grid.site_wide;
 
     Graph G[2];

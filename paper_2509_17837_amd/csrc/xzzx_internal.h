@@ -270,7 +270,6 @@ struct Plan {
     int order = 0;                 // XZZX_ORDER_COLOUR or XZZX_ORDER_RANDOM_SITE
     int planar_ok = 0;             // the planar kernel specialised to d applies
     int planar_d = 0;              // d while that kernel is in use, else 0
-    int grid_ok = 0;               // the grid core applies (its tables are in place)
     int site_wide = 0;             // random-site core: some row takes several words
     int grid_auto = 1;             // no kernel or lane count was asked for: small launches may use the grid core
     int ladder_k = 0;              // replica exchange: levels per ladder (0 = off)

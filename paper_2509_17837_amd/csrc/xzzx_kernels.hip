@@ -1100,8 +1100,9 @@ static int64_t min_snap_words(const xzzx_group &g, bool lean)
 // A group runs on the packed-row kernel specialised to its distance when the
 // plan allows it: in the form whose tasks of 64 chains may span syndromes
 // where they do not all lie inside one.  (That form takes two more products
-// per Philox block: 2.17 against 2.31 x 10^12 attempts/s at d = 11, 1.80
-// against 1.93 at d = 31; before, such groups ran on the generic packed-row
+// per Philox block: 2.16 against 2.28 x 10^12 attempts/s at d = 11, 2.37 against
+// 2.40 at d = 17, 1.95 against 2.03 at d = 31, 200 sweeps of 524288 chains, half as
+// many from d = 21; before, such groups ran on the generic packed-row
 // kernel, rows in LDS (a decode of 4099 syndromes of 40 chains at d = 13, 100
 // sweeps: 4.03 -> 2.29 ms), or, d = 31, on byte states.)
 static bool uses_static(const xzzx_group &g)
@@ -1170,7 +1171,7 @@ static std::vector<int> grid_routes(const xzzx_group *groups, int n_groups)
     for (int i = 0; i < n_groups; ++i) {
         const xzzx_group &g = groups[i];
         const Plan &P = g.plan->P;
-        if (!P.grid_ok || P.order != XZZX_ORDER_COLOUR || P.ladder_k || g.n_syn <= 0 || g.n_rep <= 0) continue;
+        if (P.order != XZZX_ORDER_COLOUR || P.ladder_k || g.n_syn <= 0 || g.n_rep <= 0) continue;
         if (!P.use_rows) {
             const int l = P.grid_auto ? grid_lanes(P) : P.lanes;
             if (l >= 4 && P.grid_moves(l)) lanes[i] = l;

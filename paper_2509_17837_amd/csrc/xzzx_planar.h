@@ -88,7 +88,10 @@ __device__ __forceinline__ void planar_applies(uint32_t (&r)[PlanarRows<D>::N], 
 // before and after block B's flips, and its entries are looked up before
 // those flips.  Its LDS round trips then overlap block B's acceptance
 // instead of waiting for it (the register dependence through the rows would
-// otherwise serialise the blocks; d = 9: 3 % faster).
+// otherwise serialise the blocks; d = 9: 3 % faster).  With entries of twelve bytes
+// d = 5, 11 and 15, and ladders at d = 7, were faster without; with eight every
+// distance runs it (whole decodes of 262144 chains, against then: 0.80, 0.83 and 0.73
+// of the time; ladders of four levels 0.56, 0.73 and 0.60, at d = 7 0.66).
 template <int D, int K, int B, int NB>
 __device__ __forceinline__ void planar_pipe(uint32_t (&r)[PlanarRows<D>::N], const LaneKey &lk,
                                             const LaneHead &h, uint32_t k0, uint32_t k1, const uint16_t *lut_s,

@@ -140,9 +140,9 @@ int class_blocks(const Plan &P)
 
 // lanes per chain for a request when the slice offers g: on the grid core the
 // least power of two on which a lane has no more generators of a class than
-// on g; else (lattices without it, or g < 4) the byte-state kernel's: one
+// on g; else (g < 4, or more than eight generators a lane) the byte-state kernel's: one
 // generator per lane where g lanes can take a class, else at most one block
-bool on_grid(const Plan &P, int g) { return g >= 4 && P.grid_ok && P.grid_moves(g) > 0; }
+bool on_grid(const Plan &P, int g) { return g >= 4 && P.grid_moves(g) > 0; }
 
 int lanes_for(const Plan &P, int g)
 {
