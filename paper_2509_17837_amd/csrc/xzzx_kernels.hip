@@ -146,9 +146,9 @@ __global__ __launch_bounds__(THREADS) void k_syndrome(const PlanDev *__restrict_
 // gathering distances through L1 at a line per lane.
 // Bound now by latency and instruction issue of the later rounds and the walks.
 // References alone, a wavefront to each with a scan of its own -> now (three
-// defects in ten generators): d = 21, 1021 syndromes x 10: 466 -> 220 us; d = 11, 8192
-// x 32: 1172 -> 662 us; planar d = 9, 12288 x 10: 691 -> 390 us; d = 11, 20000 x 1: 128 ->
-// 113 us; d = 31, 512 x 32: 2.85 -> 1.03 ms.
+// defects in ten generators): d = 21, 1021 syndromes x 10: 466 -> 219 us; d = 11, 8192
+// x 32: 1172 -> 671 us; planar d = 9, 12288 x 10: 691 -> 393 us; d = 11, 20000 x 1: 128 ->
+// 112 us; d = 31, 512 x 32: 2.85 -> 0.81 ms.
 // ---------------------------------------------------------------------------
 // partners whose distances a scan loads at once (the table is in HBM or L2:
 // the loads of a batch overlap)
@@ -156,6 +156,7 @@ constexpr int kGreedyBatch = 4;
 // lanes per defect in the shared scan, wavefronts (replicas) per workgroup
 constexpr int kGreedyRow = 8;
 constexpr int kGreedyWaves = 16;
+constexpr int kGreedyCuLds = 163840;   // LDS of a CU
 
 // LDS of a greedy workgroup, byte offsets.  Shared, per colour set: the tied
 // pairs of the first round, boundary distances, the weight cache, the defects
@@ -936,32 +937,64 @@ static int check_hip(hipError_t e, const char *what)
 }
 
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+static int device_cus();
 
 // One colour per half wavefront where a colour has at most 128 nodes (rotated
 // d <= 15: few enough defects that 32 lanes take them in one or two turns);
 // the whole wavefront per colour on larger lattices.
 static bool greedy_split(const Plan &P) { return std::max(P.hdev.ncol[0], P.hdev.ncol[1]) <= 128; }
 
+// A workgroup of the greedy references: `fit` wavefronts at most, `least` at
+// least, for `units` tasks of a syndrome, shared evenly by its workgroups.
+struct GreedyForm {
+    int shares, waves, cache_entries;
+    uint32_t lds;
+    int per_cu;                // workgroups that a CU holds at once
+};
+static GreedyForm greedy_form(int sets, int nodes, int stride, int nwords, int ties, int units, int fit, int least, bool weights)
+{
+    const GreedyLds base = greedy_lds_layout(sets, stride, nwords, 0, ties);
+    GreedyForm f{};
+    f.shares = (units + fit - 1) / fit;
+    f.waves = std::max(least, (units + f.shares - 1) / f.shares);
+    if (weights) {
+        const int rows = nodes * 7 / 16 + 8, room = 65536 - 64 - (int)(base.waves + f.waves * base.per_wave);
+        f.cache_entries = std::max(0, std::min(rows * (rows | 1), room / (4 * sets)));
+    }
+    f.lds = greedy_lds_layout(sets, stride, nwords, f.cache_entries, ties).waves + f.waves * base.per_wave;
+    f.per_cu = std::max(1, std::min(kGreedyCuLds / (int)f.lds, 32 / f.waves));
+    return f;
+}
+
 // The greedy references of n syndromes, A's outputs and syndromes set by the
 // caller.  A workgroup's wavefronts take replicas of one syndrome and share its
-// scan.  Two forms, by the references of the launch:
+// scan.  Two forms:
 // - wide: up to kGreedyWaves wavefronts, and the pair weights of up to about
 //   half the nodes as defects (more are rare: each fires with probability below
-//   one half) in what a 64 KiB share has left.  Small launches, where latency
-//   counts, and those in which the workgroups that fit a CU still fill it: at
-//   most 1024 references for every wavefront of a workgroup, or 2048 in the split
-//   form.
+//   one half) in what a 64 KiB share has left;
 // - narrow: up to four wavefronts and no weights in LDS, but for whole workgroups
-//   of small lattices, so that many workgroups fit a CU; in the split form a
-//   wavefront takes several references in turn, which saves dispatches (planar
-//   d = 9, 12288 x 10: 438 us with one each, 367 with three).
-// Measured wide / narrow (us; rotated d = 21, three defects in ten generators;
-// in brackets one in twelve): 250 syndromes x 10 replicas 86 / 116 (49 / 52); 800 x 10
-// 164 / 215 (93 / 96); 3000 x 10 533 / 606 (309 / 267); 2000 x 4 324 / 213 (155 / 99);
-// 7500 x 4 1097 / 548 (525 / 247).  A wavefront to each reference with a scan of
-// its own took 254, 399, 1004, 413 and 1034 (77, 135, 335, 132 and 345); this rule
-// is slower than that only for d = 3 and 5, by up to a microsecond a call and 8 %
-// (60000 references of one replica at d = 3: 47 us, now 50).
+//   of small lattices, so that many workgroups fit a CU and go through their
+//   phases at different times; in the split form a wavefront takes several
+//   references in turn, which saves dispatches.
+// Small launches go wide, for latency.  Beyond them the lines stand where the
+// two forms cross in dense syndromes, three or four defects in ten generators;
+// sparse ones cross earlier, as they need few weights.  Wide / narrow, us, at
+// three in ten (in brackets one in twelve):
+// - d >= 17, by the wavefronts of a wide workgroup: 11 or 12 (two workgroups a CU,
+//   with room for weights) wide at any size (4017 syndromes x 12 at d = 21 637 / 827,
+//   1774 x 12 at d = 19 261 / 329); 8 to 10 up to 2048 references for each (1021 x 10 at
+//   d = 21 220 us, 800 x 10 164 / 215 (93 / 96)); others in one turn of workgroups over the
+//   device that leaves no CU far fuller than narrow ones would (250 x 32 at d = 21
+//   182 / 223 (100 / 102), but 156 x 32 158 / 144 (93 / 65), 1250 x 32 730 / 722 (409 /
+//   327)).  13 to 15 wavefronts leave the weights no room (625 x 64 at d = 27 1577 / 1267
+//   (630 / 456)), fewer than eight share too little (2000 x 4 at d = 21 324 / 213 (155 /
+//   99)).  Where LDS keeps the narrow form below 32 wavefronts a CU: also where the
+//   wide one takes no more turns (4000 x 10 at d = 31 2.02 / 2.46 ms, planar d = 25 1250 x
+//   32 2.79 / 3.43 ms (0.80 / 0.85), but 4000 x 10 there 4.82 / 4.01 (1.09 / 0.99));
+// - split form: beyond 64 nodes, where weights from L1 cost most, up to 5120
+//   references for each wavefront (1250 x 32 at d = 15 232 / 284 (132 / 151), 4096 x 32
+//   683 / 690 (376 / 355)); else up to 2048 and only with one or two workgroups a
+//   syndrome (625 x 32 at d = 11 80 / 81 (62 / 56), 2048 x 32 214 / 212 (155 / 146)).
 constexpr int64_t kGreedyWide = 2048;   // references of a launch that is wide whatever its workgroups
 static int launch_greedy(const Plan &P, GreedyArgs A, int64_t n_syn, uint64_t seed, int mode, hipStream_t stream)
 {
@@ -979,37 +1012,51 @@ static int launch_greedy(const Plan &P, GreedyArgs A, int64_t n_syn, uint64_t se
     // replica of planar d = 31, 30000 syndromes: 42.0 ms with three entries a node,
     // 29.8 with half of one)
     A.ties = !random ? 0 : split ? 3 * A.stride : A.n_units == 1 ? A.stride / 2 : A.stride;
-    GreedyLds base = greedy_lds_layout(sets, A.stride, nwords, 0, A.ties);
+    const GreedyLds base = greedy_lds_layout(sets, A.stride, nwords, 0, A.ties);
     // boundary references share no scan: a wavefront each, over as many CUs
     const bool alone = mode == XZZX_GREEDY_BOUNDARY;
     // (tiny lattices have little to share: their dispatches count more)
     const bool tiny = nodes <= 16;
     const int64_t refs = n_syn * A.n_units;
     const int cap = std::min(kGreedyWaves, (int)((65536 - 64 - base.waves) / base.per_wave));
-    const int most_waves = std::min(cap, A.n_units), wide_shares = (A.n_units + most_waves - 1) / most_waves;
-    const bool wide = !alone && (refs <= kGreedyWide ||
-                                 (most_waves >= 5 && wide_shares <= 2 &&
-                                  refs <= (split && !tiny ? 2048 * most_waves : 1024 * std::min(most_waves, 12))));
-    if (random && split && !wide && nodes > 48) {
-        A.ties = A.stride;
-        base = greedy_lds_layout(sets, A.stride, nwords, 0, A.ties);
+    const int most_waves = std::min(cap, A.n_units);
+    auto form = [&](int units, int fit, int least, bool weights) {
+        return greedy_form(sets, nodes, A.stride, nwords, A.ties, units, std::min(cap, fit), least, weights);
+    };
+    bool wide = !alone && refs <= kGreedyWide;
+    if (!alone && !wide && most_waves >= 5) {
+        const GreedyForm w = form(A.n_units, kGreedyWaves, 1, true), n = form(A.n_units, 4, 1, false);
+        if (split) {
+            wide = nodes > 64 ? refs <= 5120 * most_waves
+                              : w.shares <= 2 && refs <= (tiny ? 1024 * std::min(most_waves, 12) : 2048 * std::max(most_waves, 10));
+        } else {
+            // turns of workgroups over the device, and the references of the fullest CU by those of a syndrome
+            const int64_t cus = device_cus();
+            auto turns = [&](const GreedyForm &g) { return (n_syn * g.shares + g.per_cu * cus - 1) / (g.per_cu * cus); };
+            auto load = [&](const GreedyForm &g) { return (double)((n_syn * g.shares + cus - 1) / cus) / g.shares; };
+            const bool lds_bound = n.per_cu < 32 / n.waves;
+            wide = (turns(w) == 1 && load(w) <= 1.4 * load(n)) || w.waves == 11 || w.waves == 12 ||
+                   (w.waves >= 8 && w.waves <= 10 && refs <= 2048 * w.waves) ||
+                   (lds_bound && w.waves <= 12 && turns(w) <= turns(n));
+        }
     }
-    // a wavefront's references in turn: three, or four where that fills workgroups
-    const int in_turn = tiny ? (int)std::min<int64_t>(refs / 10000, 3) : refs < 40000 ? 1 : A.n_units % 16 ? 3 : 4;
-    const int each = split && !alone && !wide && A.n_units > (tiny ? 2 : 4) ? std::max(1, in_turn) : 1;
-    const int fit = alone ? 1 : std::min(cap, split && (wide ? refs <= 256 && nodes <= 48 : tiny) ? 2 : wide ? kGreedyWaves : 4);
+    if (random && split && !wide && nodes > 48) A.ties = A.stride;
+    // a wavefront's references in turn: three, or four where that fills workgroups;
+    // more of small lattices where a launch has very many (d = 7, 30000 x 10: 514 us
+    // with three, 476 with nine)
+    int64_t in_turn = tiny ? std::min<int64_t>(refs / 10000, 3) : A.n_units % 16 ? (refs < 40000 ? 1 : 3) : refs < 49152 ? 1 : 4;
+    if (nodes <= 48) in_turn = std::max(in_turn, std::min<int64_t>(refs / 32768, A.n_units));
+    const int each = split && !alone && !wide && A.n_units > (tiny ? 2 : 4) ? (int)std::max<int64_t>(1, in_turn) : 1;
+    const int fit = alone ? 1 : split && (wide ? refs <= 256 && nodes <= 48 : tiny) ? 2 : wide ? kGreedyWaves : 4;
     const int per_syn = (A.n_units + each - 1) / each;
-    A.shares = (per_syn + fit - 1) / fit;
-    int waves = (per_syn + A.shares - 1) / A.shares;
-    A.unit_step = A.shares * waves;
+    GreedyForm f = form(per_syn, fit, 1, wide);
+    A.shares = f.shares;
+    A.unit_step = f.shares * f.waves;
     // a few references of a large lattice: wavefronts without one help in the scan
-    if (!split && !alone && refs <= 256) waves = std::max(waves, std::min(cap, 4));
-    A.cache_entries = 0;
-    if (wide || (split && !alone && nodes <= 84 && waves == 4)) {
-        const int rows = nodes * 7 / 16 + 8, room = 65536 - 64 - (int)(base.waves + waves * base.per_wave);
-        A.cache_entries = std::max(0, std::min(rows * (rows | 1), room / (4 * sets)));
-    }
-    const uint32_t lds = greedy_lds_layout(sets, A.stride, nwords, A.cache_entries, A.ties).waves + waves * base.per_wave;
+    if (!split && !alone && refs <= 256) f = form(per_syn, fit, std::min(cap, 4), wide);
+    else if (split && !alone && !wide && nodes <= 84 && f.waves == 4) f = form(per_syn, fit, 1, true);
+    A.cache_entries = f.cache_entries;
+    const int waves = f.waves;
     void (*kernel)(GreedyArgs) = k_greedy<false, false>;
     if (split) kernel = each > 1 ? k_greedy<true, true> : k_greedy<true, false>;
     // one launch addresses fewer than 2^32 work-items, and 2^16 rows of workgroups
@@ -1018,7 +1065,7 @@ static int launch_greedy(const Plan &P, GreedyArgs A, int64_t n_syn, uint64_t se
     for (A.syn0 = 0; A.syn0 < n_syn; A.syn0 += most)
         for (A.share0 = 0; A.share0 < A.shares; A.share0 += rows) {
             const dim3 grid((unsigned)std::min<int64_t>(most, n_syn - A.syn0), (unsigned)std::min(rows, A.shares - A.share0));
-            hipLaunchKernelGGL(kernel, grid, dim3(waves * kWave), lds, stream, A);
+            hipLaunchKernelGGL(kernel, grid, dim3(waves * kWave), f.lds, stream, A);
             const int rc = check_hip(hipGetLastError(), "k_greedy launch");
             if (rc) return rc;
         }

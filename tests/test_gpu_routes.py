@@ -241,6 +241,15 @@ def test_greedy_forms(layout, d, n_syn, R):
             assert qcls[i, r] == prob.olat.cls(want, refs[i, 0]), (i, r)
 
 
+@pytest.mark.parametrize("layout,d,n_syn,R", [
+    (0, 21, 1500, 12), (0, 21, 250, 32), (0, 31, 1000, 10), (1, 25, 300, 16), (0, 15, 1250, 32), (0, 7, 30000, 10)])
+def test_greedy_forms_by_size(layout, d, n_syn, R):
+    """Launches past the smallest that take wide workgroups: by their wavefronts,
+    by turns over the device, where LDS bounds the narrow ones, in the split form;
+    and references nine in turn."""
+    test_greedy_forms(layout, d, n_syn, R)
+
+
 @pytest.mark.parametrize("layout,d,n,R", [(0, 21, 8192, 4), (0, 25, 8192, 4), (0, 15, 26000, 5), (1, 17, 12000, 5)])
 def test_greedy_sharing_pays(layout, d, n, R):
     """R replicas that share their syndrome's scan take no longer than R calls of
