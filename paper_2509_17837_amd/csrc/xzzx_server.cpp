@@ -204,16 +204,20 @@ struct SliceForm {
         while (wider && o < kWave && !on_grid(P, o)) o *= 2;
         return o;
     }
-    bool rows(const Plan &P) const { return offer(P) == 1 && P.use_rows; }
-    int lanes(const Plan &P) const
+    // the kernel of a request: lanes per chain, moves a lane on the grid core (0:
+    // not there), packed rows, LDS of a workgroup.  Once a request and slice (asked
+    // for one by one they took 30 us of the 1.04 ms slices of 28 requests)
+    struct Kernel {
+        int lanes, moves;
+        bool rows;
+        size_t lds;
+    };
+    Kernel kernel(const Plan &P) const
     {
         const int o = offer(P);
-        return o > 1 ? lanes_for(P, o) : P.use_rows ? 1 : P.lanes;
-    }
-    int moves(const Plan &P) const { return offer(P) > 1 && on_grid(P, offer(P)) ? P.grid_moves(lanes(P)) : 0; }   // 0: not on the grid core
-    size_t lds(const Plan &P) const
-    {
-        return rows(P) ? P.lds_bytes_rows() : moves(P) ? P.lds_bytes_grid(lanes(P)) : P.lds_bytes_anneal(lanes(P));
+        if (o == 1 && P.use_rows) return {1, 0, true, P.lds_bytes_rows()};
+        const int l = o > 1 ? lanes_for(P, o) : P.lanes, mv = o > 1 && on_grid(P, o) ? P.grid_moves(l) : 0;
+        return {l, mv, false, mv ? P.lds_bytes_grid(l) : P.lds_bytes_anneal(l)};
     }
 };
 
@@ -246,8 +250,9 @@ bool fits(const SliceForm &F, const std::vector<Resident> &resident, int64_t wav
     for (const Resident &r : resident) {
         const Plan &P = *r.plan;
         if (!P.use_rows && P.grid_auto && on_grid(P, F.always)) continue;
-        waves += (4 * r.n_rep * F.lanes(P) + kWave - 1) / kWave;
-        if (!F.rows(P)) lds_max = std::max(lds_max, F.lds(P));
+        const SliceForm::Kernel k = F.kernel(P);
+        waves += (4 * r.n_rep * k.lanes + kWave - 1) / kWave;
+        if (!k.rows) lds_max = std::max(lds_max, k.lds);
     }
     return waves <= wave_budget && (size_t)waves * lds_max <= lds_budget;
 }
@@ -268,7 +273,7 @@ SliceForm slice_form(const std::vector<Resident> &resident, const xzzx_server_cf
     }
     F.g = cfg.max_lanes_per_chain;
     while (F.g > 1 && !fits(F, resident, wave_budget, lds_budget)) F.g >>= 1;
-    if (cfg.max_lanes_per_chain == kWave && F.g > 1) {
+    if (cfg.max_lanes_per_chain == kWave && F.g > 1 && F.g < kWave) {
         SliceForm W = F;
         W.wider = true;
         for (int k = 0; k < 2 && W.g > 1; ++k, W.g >>= 1)
@@ -404,11 +409,11 @@ int xzzx_server::slice()
         // and the stored state even for an empty schedule)
         if (t1 > t0 || !sl.started) {
             sl.started = true;
-            const bool rows = form.rows(P);
-            const int gr = form.lanes(P);
+            const SliceForm::Kernel kernel = form.kernel(P);
+            const bool rows = kernel.rows;
+            const int gr = kernel.lanes, mv = kernel.moves;
             const int C = kWave / gr;
-            const int mv = form.moves(P);
-            const size_t lds = form.lds(P);
+            const size_t lds = kernel.lds;
             const int nc = 4 * sl.n_rep;
             uint8_t *base = slot_ptr(s);
             for (int c0 = 0; c0 < nc; c0 += C) {
@@ -694,9 +699,10 @@ extern "C" int xzzx_server_routes(const xzzx_server *srv, const xzzx_request *re
     const SliceForm form = slice_form(in_slice, srv->cfg, srv->wave_budget, srv->lds_budget);
     for (int i = 0; i < n; ++i) {
         const Plan &P = reqs[i].plan->P;
-        kernel[i] = form.moves(P) ? (int)kRouteGrid : !form.rows(P) ? (int)XZZX_KERNEL_BYTES
+        const SliceForm::Kernel k = form.kernel(P);
+        kernel[i] = k.moves ? (int)kRouteGrid : !k.rows ? (int)XZZX_KERNEL_BYTES
                     : P.static_d ? (int)XZZX_KERNEL_ROWS : (int)XZZX_KERNEL_ROWS_GENERIC;
-        lanes[i] = form.lanes(P);
+        lanes[i] = k.lanes;
     }
     return XZZX_OK;
 }
